@@ -92,6 +92,14 @@ dbp_status run_nsd(const float *delta, int64_t rows, int64_t cols, float step, u
     if (ex) {
         a.act = ex->act; a.step_dev = ex->step_dev; a.bias_sums = ex->bias_sums; a.bias_grad = ex->bias_grad;
         a.bias_mode = ex->bias_mode; a.bias_len = ex->bias_len;
+        // A layer's own call (the sums stay inside) over a convolution's planes needs no atomics: small planes are added up from
+        // their codes (64 KiB a channel is what a workgroup reads in the shadow of the next launch; above it the sums by tile,
+        // which need whole rows of tiles and the room of the entries that this pass does not write)
+        if (bias_zeroed && a.bias_sums && a.bias_mode == DBP_BIAS_PER_ROW_GROUP && fmt_base && !fmt) {
+            if (rows / a.bias_len * cols <= (64 << 10)) a.bias_from_codes = true;
+            else a.tile_sums = (int32_t *)(fmt_base + L->entries_offset);
+            a.bias_sums = nullptr;
+        }
     }
     const DitherKeys k = make_dither_keys(seed);
     a.k0 = k.k0; a.k1 = k.k1; a.idx_base = idx_base;

@@ -73,14 +73,17 @@ __device__ __forceinline__ void cdx_stage_map(uint8_t (&lm)[64], const CdxTapMap
 }
 
 // The quantiser's pending statistics sum and bias gradient, taken along by the weight preparation (the first kernel after
-// the quantiser on the stream): the launch has one workgroup more, and that one does nothing else.  All of its loads are
-// in flight at once (the sum is of integers: any order gives the same result).  `workers` = workgroups that prepare weights.
+// the quantiser on the stream): the launch has StatsJob::workgroups() more, and those do nothing else -- one the statistics (all
+// of its loads in flight at once; the sum is of integers: any order gives the same result) and, where the quantiser kept
+// no bias sums, one per channel the bias gradient.  `workers` = workgroups that prepare weights.
 __device__ __forceinline__ bool cdx_side_jobs(const StatsJob &job, int &workers)
 {
-    workers = (int)gridDim.x;
-    if (job.n <= 0 && job.bias_len <= 0) return false;
-    workers = (int)gridDim.x - 1;
-    if ((int)blockIdx.x != workers) return false;
+    workers = (int)gridDim.x - (int)job.workgroups();
+    if ((int)blockIdx.x < workers) return false;
+    if (job.per_channel() && (int)gridDim.x - (int)blockIdx.x <= (int)job.bias_len) {
+        bias_of_channel(job, (int)gridDim.x - 1 - (int)blockIdx.x);
+        return true;
+    }
     if (job.n > 0) {
         __shared__ uint64_t s_sum[3][4];
         __shared__ uint32_t s_max[4];
@@ -112,7 +115,7 @@ __device__ __forceinline__ bool cdx_side_jobs(const StatsJob &job, int &workers)
             write_density_flags(job, s_sum[0][0] + s_sum[0][1] + s_sum[0][2] + s_sum[0][3]);
         }
     }
-    if (job.bias_len > 0) {
+    if (job.bias_len > 0 && !job.per_channel()) {
         const double d = job.step_dev ? (double)job.step_dev[0] : (double)job.step;
         for (int64_t i = threadIdx.x; i < job.bias_len; i += 256) job.bias_grad[i] = (float)(d * (double)job.bias_sums[i]);
     }

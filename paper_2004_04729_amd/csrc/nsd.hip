@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256) void nsd_kernel(NsdArgs a)
     int in_run = 0;
     int64_t row = t / a.tiles_per_row;
     int64_t seg = t - row * a.tiles_per_row;
-    int bias_acc[4] = {0, 0, 0, 0};                                   // COLWALK: code sums of this lane's four columns in the run
+    int bias_acc[4] = {0, 0, 0, 0};                                   // COLWALK: code sums of this lane's four columns in the run; row groups: [0]
     // COLWALK: unit u = t / run is (row block u / tiles_per_row, segment u % tiles_per_row); the run walks the block's rows
     auto colwalk_place = [&](int64_t tt, int64_t &r, int64_t &sg) {
         const int64_t u = tt / a.run, rb = u / a.tiles_per_row;
@@ -163,9 +163,13 @@ __global__ __launch_bounds__(256) void nsd_kernel(NsdArgs a)
         x[0] = x[1] = x[2] = x[3] = 0.f;
         const float *src = tensor + base;
         if (VEC) {
-            if (c_in < valid) {
+            if (c_in + 4 <= valid) {
                 const f32x4 v = __builtin_nontemporal_load((const f32x4 *)(src + c_in));
                 x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+            } else if (!FORMAT && c_in < valid) {                     // the last elements of a tensor taken as one row
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    if (c_in + j < valid) x[j] = src[c_in + j];
             }
         } else {
 #pragma unroll
@@ -288,7 +292,12 @@ __global__ __launch_bounds__(256) void nsd_kernel(NsdArgs a)
         // ---- codes
         int8_t *dst = a.codes + base;
         if (VEC) {
-            if (c_in < valid) __builtin_nontemporal_store(pack_low_bytes(k[0], k[1], k[2], k[3]), (uint32_t *)(dst + c_in));
+            if (c_in + 4 <= valid) __builtin_nontemporal_store(pack_low_bytes(k[0], k[1], k[2], k[3]), (uint32_t *)(dst + c_in));
+            else if (!FORMAT && c_in < valid) {
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    if (c_in + j < valid) dst[c_in + j] = (int8_t)k[j];
+            }
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -296,7 +305,7 @@ __global__ __launch_bounds__(256) void nsd_kernel(NsdArgs a)
         }
 
         // ---- bias gradient: integer sums of the codes (exact, order-free: atomics are deterministic here)
-        if (EX && a.bias_sums) {
+        if (EX && (a.bias_sums || a.tile_sums)) {
             if (a.bias_mode == 0) {
                 // per column; columns past the row's end hold x = 0 -> code 0 and add nothing
                 int64_t *col = a.bias_sums + seg * DBP_TILE + c_in;
@@ -317,11 +326,21 @@ __global__ __launch_bounds__(256) void nsd_kernel(NsdArgs a)
                         if (k[j] != 0) atomicAdd((unsigned long long *)(col + j), (unsigned long long)(long long)k[j]);
                 }
             } else {
-                int sum = (k[0] + k[1]) + (k[2] + k[3]);
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-                if (lane == 0 && sum != 0)
-                    atomicAdd((unsigned long long *)(a.bias_sums + row % a.bias_len), (unsigned long long)(long long)sum);
+                // per row group (a convolution's planes): a lane keeps its sum over the consecutive tiles of one row that the
+                // wavefront meets (at most kMaxRun).  One device atomic per such stretch lands on a few cache lines (bias_len
+                // sums of 8 bytes) and those serialise at about 12 ns each: N=128, 64 planes of 32x32 with one per tile 94 us, the
+                // quantiser without sums 12 us.  Hence tile_sums where the caller gives room: a plain store at the stretch's
+                // last tile, added up per channel by a later kernel (bias_of_channel).
+                bias_acc[0] += (k[0] + k[1]) + (k[2] + k[3]);
+                if (last_of_run || row_next != row) {
+                    const int sum = wave_sum(bias_acc[0]);
+                    bias_acc[0] = 0;
+                    if (a.tile_sums) {
+                        if (lane == 0) a.tile_sums[t] = sum;
+                    } else if (lane == 0 && sum != 0) {
+                        atomicAdd((unsigned long long *)(a.bias_sums + row % a.bias_len), (unsigned long long)(long long)sum);
+                    }
+                }
             }
         }
 
@@ -448,6 +467,8 @@ __global__ void bias_grad_kernel(const int64_t *sums, int64_t n, float step, con
         grad[i] = (float)(d * (double)sums[i]);
 }
 
+__global__ __launch_bounds__(256) void bias_channels_kernel(StatsJob j) { bias_of_channel(j, (int)blockIdx.x); }
+
 // ---- step size of Algorithm 1: sigma = std(delta_z), Delta = s * sigma --------------------------------------
 // Population standard deviation from S1 = sum x and S2 = sum x*x in fp64 (x*x is exact there).  Delta decides
 // integer codes, so the ORDER of the sums is fixed: a radix-16 tree -- groups of 16 consecutive values are
@@ -461,24 +482,44 @@ __global__ __launch_bounds__(256) void std_tree_kernel(const float *delta, const
     const int tid = threadIdx.x, lane = tid & 63;
     // by the way: clear the bias code sums that the quantiser (the next kernel of the stream) adds into
     for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < zero_len; i += (int64_t)gridDim.x * 256) zero[i] = 0;
-    const int64_t first = ((int64_t)blockIdx.x * 256 + tid) * 16;     // this thread's 16 consecutive elements
+    const int64_t block0 = (int64_t)blockIdx.x * 4096;
+    const int64_t first = block0 + tid * 16;                           // this thread's 16 consecutive elements
     const int have = (int)max((int64_t)0, min((int64_t)16, n - first));
-    float v[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) v[j] = 0.f;
-    if (have == 16 && (((uintptr_t)(delta + first)) & 15) == 0) {
+    // The definition gives a thread 16 CONSECUTIVE elements; loaded that way a wavefront's instruction touches 64 cache lines
+    // (and the activations went element by element).  So the workgroup's 4096 values come in whole lines, 16 bytes a lane, are
+    // masked, and go through LDS; the groups of four of a thread's run are rotated so that the reads spread over the banks.
+    // Bound by the two streams: N=128, 64 planes of 32x32 with activations (67 MB) 31 us before.
+    __shared__ __align__(16) float s_v[4096];
+    const bool whole = block0 + 4096 <= n && ((uintptr_t)(delta + block0) & 15) == 0 && (!act || ((uintptr_t)(act + block0) & 15) == 0);
+    if (whole) {
+        f32x4 d[4], m[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const f32x4 t = *(const f32x4 *)(delta + first + 4 * q);
-            v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
+            d[q] = *(const f32x4 *)(delta + block0 + 1024 * q + 4 * tid);
+            m[q] = act ? *(const f32x4 *)(act + block0 + 1024 * q + 4 * tid) : f32x4{1.f, 1.f, 1.f, 1.f};
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[q][j] = m[q][j] > 0.0f ? d[q][j] : 0.0f;   // delta_z = delta_a where the activation is positive
+            const int c = 256 * q + tid;                               // four values: number c & 3 of thread c >> 2
+            *(f32x4 *)(s_v + 4 * ((c & ~3) | ((c + (c >> 3)) & 3))) = d[q];
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) if (j < have) v[j] = delta[first + j];
+        for (int q = 0; q < 16; ++q) {
+            const int e = 256 * q + tid, c = e >> 2;
+            float x = 0.f;
+            if (block0 + e < n) { x = delta[block0 + e]; if (act) x = act[block0 + e] > 0.0f ? x : 0.0f; }
+            s_v[4 * ((c & ~3) | ((c + (c >> 3)) & 3)) + (e & 3)] = x;
+        }
     }
-    if (act) {                                                         // delta_z = delta_a where the activation is positive
+    __syncthreads();
+    float v[16];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) if (j < have) v[j] = act[first + j] > 0.0f ? v[j] : 0.0f;
+    for (int q = 0; q < 4; ++q) {
+        const f32x4 t = *(const f32x4 *)(s_v + 4 * (4 * tid + ((q + (tid >> 1)) & 3)));
+        v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
     }
     // level 0 (elements past the end do not exist; adding their +0.0 squares or values changes nothing)
     double s1 = (double)v[0], s2 = (double)v[0] * (double)v[0];
@@ -719,7 +760,9 @@ DitherKeys make_dither_keys(uint64_t seed)
 hipError_t launch_stats_job(const StatsJob &j, hipStream_t s)
 {
     if (j.n > 0) hipLaunchKernelGGL(finalize_stats_kernel, dim3(1), dim3(1024), 0, s, j.partials, j.n, j.out, j);
-    if (j.bias_len > 0) {
+    if (j.per_channel()) {
+        hipLaunchKernelGGL(bias_channels_kernel, dim3((unsigned)j.bias_len), dim3(256), 0, s, j);
+    } else if (j.bias_len > 0) {
         const int64_t zb = (j.bias_len + 255) / 256;
         hipLaunchKernelGGL(bias_grad_kernel, dim3((unsigned)(zb < 1024 ? zb : 1024)), dim3(256), 0, s, j.bias_sums, j.bias_len,
                            j.step, j.step_dev, j.bias_grad);
@@ -734,10 +777,28 @@ hipError_t launch_nsd(const NsdArgs &a_in, hipStream_t s, StatsJob *defer)
     if (!a.stats) a.partials = nullptr;
     const bool use_atomics = a.stats && !a.partials;
     if (use_atomics) hipLaunchKernelGGL(zero_stats_kernel, dim3(1), dim3(64), 0, s, a.stats);
+    StatsJob later{nullptr, 0, nullptr, nullptr, 0, nullptr, 0.0f, nullptr};
+    if ((a.bias_sums || a.tile_sums || a.bias_from_codes) && a.bias_grad) {
+        later.bias_len = a.bias_len; later.bias_grad = a.bias_grad;
+        later.step = a.step; later.step_dev = a.step_dev;
+        later.images = a.rows / a.bias_len; later.plane = a.cols; later.tiles_per_row = a.tiles_per_row;
+        if (a.bias_from_codes) later.bias_codes = a.codes;
+        else if (a.tile_sums) later.tile_sums = a.tile_sums;
+        else later.bias_sums = a.bias_sums;
+    }
+    if (a.bias_from_codes) a.bias_sums = nullptr;
+    // Without the format and without sums by row or column the shape means nothing: one row, whole tiles but for the last, aligned
+    // loads whatever the row length (7x7 planes had 49 of a tile's 256 lanes' columns in use and loads of one element).
+    if (!a.bitmap && !a.topk_thr && !a.bias_sums && !a.tile_sums) {
+        a.cols *= a.rows; a.rows = 1;
+        a.tiles_per_row = a.n_tiles = (a.cols + DBP_TILE - 1) / DBP_TILE;
+    }
     // per-wave element counts are 32-bit: one wave sees at most n_tiles/(4*blocks) tiles of 256 elements
     // One run of consecutive tiles per wavefront: as long as it takes to keep 8192 wavefronts (full
     // occupancy of 256 CUs) busy, at most kMaxRun; beyond kNsdMaxBlocks workgroups the runs are grid-strided.
-    int64_t run = a.n_tiles / 8192;
+    // (rounded up: with the quotient rounded down 43 workgroups of 2091 ran alone after the 2048 resident ones, 28 -> 33 us
+    // on 25.7M elements, and the sum of the statistics needed a second round of loads)
+    int64_t run = (a.n_tiles + 8191) / 8192;
     run = run < 1 ? 1 : run > kMaxRun ? kMaxRun : run;
     // Per-column bias sums without the format: runs go down the rows of one 256-column segment (sums in registers, see
     // nsd_kernel), as many rows as leave 16384 runs for the chip, at most 64; a.n_tiles then counts the row blocks' tiles,
@@ -757,13 +818,13 @@ hipError_t launch_nsd(const NsdArgs &a_in, hipStream_t s, StatsJob *defer)
     const int64_t max_blocks = use_atomics ? 256 : kNsdMaxBlocks;
     if (blocks > max_blocks) blocks = max_blocks;
     if (blocks < 1) blocks = 1;
-    const bool vec_d = (a.cols % 4 == 0) && ((uintptr_t)a.delta % 16 == 0) && ((uintptr_t)a.codes % 4 == 0);
+    const bool vec_d = (a.cols % 4 == 0 || (a.rows == 1 && !a.bitmap)) && ((uintptr_t)a.delta % 16 == 0) && ((uintptr_t)a.codes % 4 == 0);
     const int64_t jump = (blocks * 4 - 1) * run + 1;        // tiles from the last tile of a run to the next run
     a.wave_stride_rows = jump / a.tiles_per_row;
     a.wave_stride_segs = jump % a.tiles_per_row;
     const dim3 grid((unsigned)blocks), block(256);
-    const bool ex = a.act || a.step_dev || a.bias_sums;
-    if (a.bias_sums && !a.bias_zeroed) {
+    const bool ex = a.act || a.step_dev || a.bias_sums || a.tile_sums;
+    if (a.bias_sums && !a.bias_zeroed && !a.tile_sums && !a.bias_from_codes) {
         const int64_t zb = (a.bias_len + 255) / 256;
         hipLaunchKernelGGL(zero_i64_kernel, dim3((unsigned)(zb < 1024 ? zb : 1024)), dim3(256), 0, s, a.bias_sums, a.bias_len);
     }
@@ -787,11 +848,7 @@ hipError_t launch_nsd(const NsdArgs &a_in, hipStream_t s, StatsJob *defer)
         else if (a.bitmap)         hipLaunchKernelGGL((nsd_kernel<false, true, true>), grid, block, 0, s, a);
         else                       hipLaunchKernelGGL((nsd_kernel<false, false, true>), grid, block, 0, s, a);
     }
-    StatsJob later{nullptr, 0, nullptr, nullptr, 0, nullptr, 0.0f, nullptr};
-    if (a.bias_sums && a.bias_grad) {
-        later.bias_sums = a.bias_sums; later.bias_len = a.bias_len; later.bias_grad = a.bias_grad;
-        later.step = a.step; later.step_dev = a.step_dev;
-    }
+    later.run = (int)run;
     if (a.partials) { later.partials = (const u32x4 *)a.partials; later.n = (int)blocks; later.out = a.stats; }
     if (defer) *defer = later;
     else return launch_stats_job(later, s);

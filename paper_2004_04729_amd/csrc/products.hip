@@ -997,9 +997,9 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
             const int64_t cells = (int64_t)taps * KG * Cp;
             int pb = (int)((cells + 255) / 256 < 4096 ? (cells + 255) / 256 : 4096);
             const int rs = (int)(a.R * a.S);
-            // the quantiser's pending statistics sum / bias gradient ride along in one more workgroup
+            // the quantiser's pending statistics sum / bias gradient ride along in workgroups of their own
             StatsJob job{nullptr, 0, nullptr, nullptr, 0, nullptr, 0.0f, nullptr};
-            if (a.pending && (a.pending->n > 0 || a.pending->bias_len > 0)) { job = *a.pending; a.pending->n = 0; a.pending->bias_len = 0; ++pb; }
+            if (a.pending && (a.pending->n > 0 || a.pending->bias_len > 0)) { job = *a.pending; *a.pending = StatsJob{}; pb += (int)job.workgroups(); }
             if constexpr (I8) {
                 if (map) hipLaunchKernelGGL(conv_dx_weight_prep_i8_kernel<true>, dim3(pb), dim3(256), 0, s, a.W8, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, *map, job);
                 else     hipLaunchKernelGGL(conv_dx_weight_prep_i8_kernel<false>, dim3(pb), dim3(256), 0, s, a.W8, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, CdxTapMap{}, job);

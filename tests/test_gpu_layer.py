@@ -260,6 +260,30 @@ def test_conv_layer_backward_through_the_dw_gate(s, flags):
     assert got == flags
 
 
+# planes below one 16-byte piece, of odd sizes, of whole pieces; more than 64 KiB of codes a channel in planes of one tile, of
+# several with a remainder, and of whole runs of tiles (3 to a run: stretches that end inside a row and with it)
+@pytest.mark.parametrize("N,K,P,Q", [(5, 3, 1, 1), (4, 6, 3, 5), (3, 7, 7, 7), (70, 5, 14, 14), (2, 3, 181, 181), (400, 2, 13, 13), (300, 3, 15, 18), (96, 65, 32, 33)])
+def test_conv_bias_gradient_alone(N, K, P, Q):
+    import torch
+    import paper_2004_04729_amd as dbp
+    from gpu_util import stream
+    from oracle import oracle as O
+    rng = np.random.default_rng(N + K + P)
+    da = rng.laplace(0, 5e-4, size=(N, K, P, Q)).astype(np.float32)
+    a = np.maximum(rng.standard_normal((N, K, P, Q)), 0).astype(np.float32)
+    db = torch.full((K,), float("nan"), dtype=torch.float32, device="cuda:0")
+    codes = torch.empty((N, K, P, Q), dtype=torch.int8, device="cuda:0")
+    ws = torch.empty(dbp.conv2d_layer_workspace_bytes(N, 1, P, Q, K, 1, 1, 1, 0, dbp.F32), dtype=torch.uint8, device="cuda:0")
+    dbp.dithered_conv2d_layer_backward(_dev(da), _dev(a), _dev(np.zeros((K, 1, 1, 1), np.float32)), None, dbp.F32, N, 1, P, Q, K, 1, 1, 1, 0, 4.0, 1, 0,
+                                       codes, None, None, db, None, ws, None, dbp.PATH_AUTO, stream())
+    torch.cuda.synchronize()
+    dz = O.relu_backward(da, a)
+    step, _ = O.step_size(dz, 4.0)
+    k_ref, _ = O.nsd(dz, step, 1)
+    assert np.array_equal(codes.cpu().numpy(), k_ref)
+    assert np.array_equal(db.cpu().numpy(), O.bias_grad(k_ref, N * K, P * Q, False, K, step)[1])
+
+
 def _conv_layer_case(case, i8, path, s_mult, want_flags=False):
     import torch
     import paper_2004_04729_amd as dbp
