@@ -11,7 +11,9 @@ typedef float    f32x16 __attribute__((ext_vector_type(16)));
 typedef int32_t  i32x4  __attribute__((ext_vector_type(4)));
 typedef int32_t  i32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4  __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4_unaligned __attribute__((ext_vector_type(4), aligned(1)));   // 16 bytes at any address (one load)
+// 16 bytes at any address, and at a multiple of 4: one load or store either way
+typedef uint32_t u32x4_unaligned __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u32x4_dw4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef __bf16   bf16x8 __attribute__((ext_vector_type(8)));
 
 // A product's output scale: a host value, or (Algorithm 1 on the device) the Delta an earlier kernel of the
@@ -106,60 +108,6 @@ __device__ __forceinline__ int wave_sum(int v)
     return __builtin_amdgcn_readlane(v, 63);
 }
 
-// Bias gradient of channel `ch` by a workgroup of 256 threads: Delta * (sum of the channel's codes over all images), one fp64
-// product rounded to fp32; the sum is of integers, so its order does not matter.
-__device__ __forceinline__ void bias_of_channel(const StatsJob &j, int ch)
-{
-    const double d = j.step_dev ? (double)j.step_dev[0] : (double)j.step;
-    long long sum = 0;
-    if (j.tile_sums) {
-        // a stretch's sum sits at its last tile: the last of a row, of a wavefront's run, or of the tensor (which ends a row)
-        const int64_t total = j.images * j.tiles_per_row;
-        for (int64_t i = threadIdx.x; i < total; i += 256) {
-            const int64_t img = i / j.tiles_per_row, seg = i - img * j.tiles_per_row;
-            const int64_t t = (img * j.bias_len + ch) * j.tiles_per_row + seg;
-            if (seg == j.tiles_per_row - 1 || (t + 1) % j.run == 0) sum += j.tile_sums[t];
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-    } else {
-        // 16-byte pieces of all the channel's planes in turn, four loads in flight: the codes come from memory, about 2 us a round
-        // (a plane's last piece ends at its last code and gives up what it repeats; tiny planes go byte by byte)
-        const int plane = (int)j.plane, bytes = plane < 16 ? 1 : 16;
-        const int pieces = (plane + bytes - 1) / bytes, step_i = 256 / pieces, step_w = 256 % pieces;
-        const int64_t img_bytes = j.bias_len * j.plane;
-        const int8_t *base = j.bias_codes + ch * j.plane;
-        int img = (int)threadIdx.x / pieces, w = (int)threadIdx.x - img * pieces, acc = 0;
-        while (img < (int)j.images) {
-            u32x4 v[4];
-            int drop[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const bool in = img < (int)j.images;
-                const int8_t *p = base + (in ? img : 0) * img_bytes;
-                const int at = min(bytes * w, plane - bytes);
-                drop[u] = in ? bytes * w - at : 16;
-                if (bytes == 16) v[u] = *(const u32x4_unaligned *)(p + at);
-                else v[u] = u32x4{(uint32_t)(uint8_t)p[at], 0u, 0u, 0u};
-                img += step_i; w += step_w;
-                if (w >= pieces) { w -= pieces; ++img; }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    const int gone = min(max(drop[u] - 4 * d, 0), 4);
-                    const int x = gone == 4 ? 0 : (int)(v[u][d] >> (8 * gone));
-                    acc += (x << 24 >> 24) + (x << 16 >> 24) + (x << 8 >> 24) + (x >> 24);
-                }
-        }
-        sum = wave_sum(acc);                                           // (the caller keeps such channels below 2^31 / 127 codes)
-    }
-    __shared__ long long s_bias[4];
-    if ((threadIdx.x & 63) == 0) s_bias[threadIdx.x >> 6] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) j.bias_grad[ch] = (float)(d * (double)(s_bias[0] + s_bias[1] + s_bias[2] + s_bias[3]));
-}
 // Launches the quantiser.  With `defer` non-null and statistics kept in records, the final sum is not
 // launched: *defer describes it, and the caller either folds it into a later kernel of the same stream
 // or calls launch_stats_job.

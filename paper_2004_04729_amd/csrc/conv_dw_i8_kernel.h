@@ -113,13 +113,13 @@ __global__ __launch_bounds__(512, 1) void conv_dw_i8_kernel(ConvDwI8Args a)
 #pragma unroll
             for (int j = 0; j < CI; ++j) {
                 if (j >= c_passes) break;
-                cr[j] = *(const u32x4_dw *)(cb + min(co, ccap));
+                cr[j] = *(const u32x4_dw4 *)(cb + min(co, ccap));
                 co += cs;
             }
 #pragma unroll
             for (int j = 0; j < XI; ++j) {
                 if (j >= x_passes) break;
-                xr[j] = *(const u32x4_dw *)(xb + min(xo, xcap));
+                xr[j] = *(const u32x4_dw4 *)(xb + min(xo, xcap));
                 xo += xs;
             }
         };

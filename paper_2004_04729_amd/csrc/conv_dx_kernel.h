@@ -28,6 +28,7 @@
 #pragma once
 #include <type_traits>
 #include "gemm_core.h"
+#include "side_jobs.h"
 
 namespace dbp {
 
@@ -72,53 +73,13 @@ __device__ __forceinline__ void cdx_stage_map(uint8_t (&lm)[64], const CdxTapMap
     }
 }
 
-// The quantiser's pending statistics sum and bias gradient, taken along by the weight preparation (the first kernel after
-// the quantiser on the stream): the launch has StatsJob::workgroups() more, and those do nothing else -- one the statistics (all
-// of its loads in flight at once; the sum is of integers: any order gives the same result) and, where the quantiser kept
-// no bias sums, one per channel the bias gradient.  `workers` = workgroups that prepare weights.
+// The quantiser's pending sums ride along in the weight preparation (the first kernel after the quantiser on the stream), in
+// workgroups of their own at the end of the grid.  `workers` = workgroups that prepare weights.
 __device__ __forceinline__ bool cdx_side_jobs(const StatsJob &job, int &workers)
 {
     workers = (int)gridDim.x - (int)job.workgroups();
     if ((int)blockIdx.x < workers) return false;
-    if (job.per_channel() && (int)gridDim.x - (int)blockIdx.x <= (int)job.bias_len) {
-        bias_of_channel(job, (int)gridDim.x - 1 - (int)blockIdx.x);
-        return true;
-    }
-    if (job.n > 0) {
-        __shared__ uint64_t s_sum[3][4];
-        __shared__ uint32_t s_max[4];
-        uint64_t nnz = 0, sat = 0, nf = 0; uint32_t mx = 0;
-        for (int base = 0; base < job.n; base += 256 * 8) {
-            u32x4 q[8];
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const int i = base + (int)threadIdx.x + 256 * r;
-                q[r] = i < job.n ? job.partials[i] : u32x4{0u, 0u, 0u, 0u};
-            }
-#pragma unroll
-            for (int r = 0; r < 8; ++r) { nnz += q[r].x; sat += q[r].y; nf += q[r].z; mx = max(mx, q[r].w); }
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            nnz += __shfl_xor((unsigned long long)nnz, off); sat += __shfl_xor((unsigned long long)sat, off);
-            nf += __shfl_xor((unsigned long long)nf, off); mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
-        }
-        const int w = threadIdx.x >> 6;
-        if ((threadIdx.x & 63) == 0) { s_sum[0][w] = nnz; s_sum[1][w] = sat; s_sum[2][w] = nf; s_max[w] = mx; }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            job.out->nnz = s_sum[0][0] + s_sum[0][1] + s_sum[0][2] + s_sum[0][3];
-            job.out->n_saturated = s_sum[1][0] + s_sum[1][1] + s_sum[1][2] + s_sum[1][3];
-            job.out->n_nonfinite = s_sum[2][0] + s_sum[2][1] + s_sum[2][2] + s_sum[2][3];
-            job.out->max_abs_code = (int32_t)max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
-            job.out->reserved = 0;
-            write_density_flags(job, s_sum[0][0] + s_sum[0][1] + s_sum[0][2] + s_sum[0][3]);
-        }
-    }
-    if (job.bias_len > 0 && !job.per_channel()) {
-        const double d = job.step_dev ? (double)job.step_dev[0] : (double)job.step;
-        for (int64_t i = threadIdx.x; i < job.bias_len; i += 256) job.bias_grad[i] = (float)(d * (double)job.bias_sums[i]);
-    }
+    side_job(job, (int)blockIdx.x - workers, 256);
     return true;
 }
 

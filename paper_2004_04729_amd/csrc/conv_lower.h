@@ -5,7 +5,7 @@
 // which is the dX form of a fully connected layer (rows k, reduction (n,p,q), columns (c,r,s)) once
 //   * the codes [N][K][P*Q] are re-laid reduction-contiguous per channel, [K][N*P*Q]   (conv_codes_kmajor_kernel), and
 //   * the activations are expanded into the column matrix, row-major                  (conv_im2col_kernel).
-// Both passes are plain copies at memory speed; the product then runs on the kernels of fc2_kernel.h / fc2_i8_kernel.h.
+// Both passes are plain copies at memory speed; the product then runs on the fully connected kernels.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>

@@ -14,6 +14,7 @@
 namespace dbp {
 
 constexpr int FC2I_KT = 64;
+typedef uint64_t u64_any __attribute__((aligned(1)));
 
 struct Fc2IStage {
     uint4 a[NCHUNK][FC2_TM];          // [chunk of 16 reduction indices][row position]      16 KiB
@@ -34,6 +35,14 @@ __device__ __forceinline__ void fc2i_transpose(uint32_t r0, uint32_t r1, uint32_
     const uint32_t y0 = __builtin_amdgcn_perm(r1, r0, 0x07030602u), y1 = __builtin_amdgcn_perm(r3, r2, 0x07030602u);
     out[0] = __builtin_amdgcn_perm(x1, x0, 0x05040100u); out[1] = __builtin_amdgcn_perm(x1, x0, 0x07060302u);
     out[2] = __builtin_amdgcn_perm(y1, y0, 0x05040100u); out[3] = __builtin_amdgcn_perm(y1, y0, 0x07060302u);
+}
+
+// First of the four output columns of multiplier lane `lcol`, or -1: a ragged row's last columns start early, in groups of the
+// eight (NT: four) columns that the staging loads together; columns that two lanes share get the same values.
+__device__ __forceinline__ int fc2i_col(bool nt, int tile_n, int lcol, int N)
+{
+    const int g = nt ? 4 : 8, first = tile_n + 4 * lcol / g * g;
+    return first < N ? min(first, N - g) + 4 * lcol % g : -1;
 }
 
 // NT: the batched form with both operands reduction-contiguous, as in fc2_kernel.h (weight gradient of a 1x1
@@ -73,6 +82,8 @@ __global__ __launch_bounds__(512, 1) void fc2_i8_pair_kernel(FcPairArgs a)
         int64_t nt_a_img = 0, nt_b_img = 0;
         const int8_t *nt_a = nullptr;
         const char *nt_b = nullptr;
+        // NT: column 64*j + tid/4 of the tile; a ragged row's last four columns start early (the stores do the same)
+        auto nt_col = [&](int j) { const int q = 64 * j + (tid >> 2); return min(c.tile_n + (q & ~3), c.N - 4) + (q & 3); };
         auto open_item = [&](int i) {
             if (!fc2_open(a, table, mine, i, c)) return false;
             if constexpr (NT) {
@@ -85,7 +96,7 @@ __global__ __launch_bounds__(512, 1) void fc2_i8_pair_kernel(FcPairArgs a)
                 // dense operand: columns tid/4 and 64 + tid/4 of the tile, reduction indices 16*(tid%4) .. +15 of the window
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
-                    boff[j] = (uint32_t)min(c.tile_n + 64 * j + (tid >> 2), c.N - 1) * (uint32_t)c.ldb + 16u * (uint32_t)(tid & 3);
+                    boff[j] = (uint32_t)nt_col(j) * (uint32_t)c.ldb + 16u * (uint32_t)(tid & 3);
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     aoff[j] = (uint32_t)min(c.tile_m + 64 * j + (tid >> 2), c.M - 1) * (uint32_t)c.lda + 16u * (uint32_t)(tid & 3);
@@ -107,12 +118,12 @@ __global__ __launch_bounds__(512, 1) void fc2_i8_pair_kernel(FcPairArgs a)
                 for (int j = 0; j < 4; ++j)
                     aoff[j] = (uint32_t)min(c.tile_m + 64 * j + (tid >> 2), c.M - 1) * lda + 16u * (uint32_t)(tid & 3);
             } else {
-                // reduction indices 4*k4 .. +3 and 16 consecutive rows of the matrix each (M >= 16, M % 4 == 0); a run
+                // reduction indices 4*k4 .. +3 and 16 consecutive rows of the matrix each (M >= 16); a run
                 // that would pass the last row starts earlier and is moved back when the step is committed
                 a_unit = c.lda;
                 a_step = c.A + (int64_t)c.k0 * c.lda;
                 const int m = c.tile_m + 16 * (tid & 15);
-                a_shift = max(0, m + 16 - c.M) >> 2;
+                a_shift = min(max(0, m + 16 - c.M), 16);
                 const uint32_t a0 = 4u * (uint32_t)k4 * lda + (uint32_t)max(0, min(m, c.M - 16));
 #pragma unroll
                 for (int j = 0; j < 4; ++j) aoff[j] = a0 + (uint32_t)j * lda;
@@ -146,16 +157,16 @@ __global__ __launch_bounds__(512, 1) void fc2_i8_pair_kernel(FcPairArgs a)
             if constexpr (NT) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    const u32x4 v = *(const u32x4_dw *)(b_cur + (size_t)boff[i]);
+                    const u32x4 v = *(const u32x4_unaligned *)(b_cur + (size_t)boff[i]);
                     r.b[2 * i] = uint2{v.x, v.y}; r.b[2 * i + 1] = uint2{v.z, v.w};
                 }
             } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) r.b[i] = *(const uint2 *)(b_cur + (size_t)boff[i]);
+                for (int i = 0; i < 4; ++i) { const uint64_t v = *(const u64_any *)(b_cur + (size_t)boff[i]); r.b[i] = uint2{(uint32_t)v, (uint32_t)(v >> 32)}; }
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const u32x4 v = *(const u32x4_dw *)(a_cur + (size_t)aoff[i]);
+                const u32x4 v = *(const u32x4_unaligned *)(a_cur + (size_t)aoff[i]);
                 r.a[4 * i] = v.x; r.a[4 * i + 1] = v.y; r.a[4 * i + 2] = v.z; r.a[4 * i + 3] = v.w;
             }
             if (open) {
@@ -169,26 +180,17 @@ __global__ __launch_bounds__(512, 1) void fc2_i8_pair_kernel(FcPairArgs a)
             }
         };
 
-        auto unshift = [](uint32_t (&w)[4], int sh) {
-            const uint32_t t0 = w[0], t1 = w[1], t2 = w[2], t3 = w[3];
-            w[0] = sh == 0 ? t0 : sh == 1 ? t1 : sh == 2 ? t2 : sh == 3 ? t3 : 0u;
-            w[1] = sh == 0 ? t1 : sh == 1 ? t2 : sh == 2 ? t3 : 0u;
-            w[2] = sh == 0 ? t2 : sh == 1 ? t3 : 0u;
-            w[3] = sh == 0 ? t3 : 0u;
-        };
-
         auto commit = [&](const Fc2IRaw &r, Fc2IStage &sm) {
             // window indices below `dup` repeat the step before (only in an item's last, shorter step)
             const int dup = FC2I_KT - r.k_valid;
             if (r.kfast) {
-                // set i = the cell of chunk tid%4 of row position tid/4 + 64*i (the item's ends are multiples of 4:
-                // whole dwords are in or out)
+                // set i = the cell of chunk tid%4 of row position tid/4 + 64*i
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     uint32_t w[4] = {r.a[4 * i], r.a[4 * i + 1], r.a[4 * i + 2], r.a[4 * i + 3]};
                     if (dup > 0) {
 #pragma unroll
-                        for (int d = 0; d < 4; ++d) w[d] = 16 * (tid & 3) + 4 * d >= dup ? w[d] : 0u;
+                        for (int d = 0; d < 4; ++d) w[d] = fc2_drop(w[d], dup - 16 * (tid & 3) - 4 * d);
                     }
                     sm.a[tid & 3][64 * i + (tid >> 2)] = uint4{w[0], w[1], w[2], w[3]};
                 }
@@ -201,7 +203,7 @@ __global__ __launch_bounds__(512, 1) void fc2_i8_pair_kernel(FcPairArgs a)
                 for (int i = 0; i < 4; ++i) {
 #pragma unroll
                     for (int d = 0; d < 4; ++d) w[i][d] = r.a[4 * i + d];
-                    if (r.a_shift) unshift(w[i], r.a_shift);
+                    if (r.a_shift) fc2_unshift(w[i], r.a_shift);
                     if (dup > 0 && 4 * k4 + i < dup) { w[i][0] = w[i][1] = w[i][2] = w[i][3] = 0u; }
                 }
                 uint32_t *cell = (uint32_t *)&sm.a[k4 >> 2][m16] + (k4 & 3);
@@ -220,7 +222,7 @@ __global__ __launch_bounds__(512, 1) void fc2_i8_pair_kernel(FcPairArgs a)
                     uint32_t w[4] = {r.b[2 * i].x, r.b[2 * i].y, r.b[2 * i + 1].x, r.b[2 * i + 1].y};
                     if (dup > 0) {
 #pragma unroll
-                        for (int d = 0; d < 4; ++d) w[d] = 16 * (tid & 3) + 4 * d >= dup ? w[d] : 0u;
+                        for (int d = 0; d < 4; ++d) w[d] = fc2_drop(w[d], dup - 16 * (tid & 3) - 4 * d);
                     }
                     const int n = 64 * i + (tid >> 2);
                     sm.b[tid & 3][32 * (n & 3) + (n >> 2)] = uint4{w[0], w[1], w[2], w[3]};
@@ -300,6 +302,7 @@ __global__ __launch_bounds__(512, 1) void fc2_i8_pair_kernel(FcPairArgs a)
         if (c.k0 >= c.k_end) {
             const Fc2Cursor p = c;
             typedef int32_t i32v4 __attribute__((ext_vector_type(4)));
+            typedef int32_t i32v4_dw __attribute__((ext_vector_type(4), aligned(4)));
             if (p.n_split > 1) {
                 i32v4 *mine_p = (i32v4 *)((int32_t *)p.partial + ((int64_t)c.tile * p.n_split + c.z) * (FC2_TM * FC2_TN));
 #pragma unroll
@@ -308,8 +311,8 @@ __global__ __launch_bounds__(512, 1) void fc2_i8_pair_kernel(FcPairArgs a)
                     for (int v = 0; v < 16; ++v)
                         mine_p[(i * 16 + v) * 256 + tid] = i32v4{acc[i][0][v], acc[i][1][v], acc[i][2][v], acc[i][3][v]};
             } else {
-                const int col = c.tile_n + 4 * lcol;
-                if (col < p.N) {
+                const int col = fc2i_col(NT, c.tile_n, lcol, p.N);
+                if (col >= 0) {
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -318,7 +321,7 @@ __global__ __launch_bounds__(512, 1) void fc2_i8_pair_kernel(FcPairArgs a)
                             const int row = fc2_row(p.a_kfast, c.tile_m, wave, i, ii);
                             if (row < p.M)
                                 __builtin_nontemporal_store(i32v4{acc[i][0][v], acc[i][1][v], acc[i][2][v], acc[i][3][v]},
-                                                            (i32v4 *)((int32_t *)p.out + (int64_t)row * p.ldc + col));
+                                                            (i32v4_dw *)((int32_t *)p.out + (int64_t)row * p.ldc + col));
                         }
                 }
             }
@@ -339,6 +342,7 @@ __global__ __launch_bounds__(256) void fc2_i8_reduce_kernel(FcPairArgs a, int ti
 {
     if (a.gate.closed()) return;
     typedef int32_t i32v4 __attribute__((ext_vector_type(4)));
+    typedef int32_t i32v4_dw __attribute__((ext_vector_type(4), aligned(4)));
     const int which = (int)(blockIdx.x >> 5) < tiles0 ? 0 : 1;
     const FcProblem &p = a.prob[which];
     const int tile = (int)(blockIdx.x >> 5) - (which ? tiles0 : 0), slot = blockIdx.x & 31;
@@ -346,7 +350,7 @@ __global__ __launch_bounds__(256) void fc2_i8_reduce_kernel(FcPairArgs a, int ti
     const int tile_m = (tile % p.tiles_m) * FC2_TM;
     const int tile_n = (tile / p.tiles_m) * FC2_TN;
     const i32v4 *all = (const i32v4 *)((const int32_t *)p.partial + (int64_t)tile * p.n_split * (FC2_TM * FC2_TN)) + slot * 256 + tid;
-    const int col = tile_n + 4 * (lane & 31);
+    const int col = fc2i_col(p.nt_pq != 0, tile_n, lane & 31, p.N);
     i32v4 sum = i32v4{0, 0, 0, 0};
     const int n_split = p.n_split;
     for (int q = 0; q < n_split; q += 8) {
@@ -360,7 +364,7 @@ __global__ __launch_bounds__(256) void fc2_i8_reduce_kernel(FcPairArgs a, int ti
     const int i = slot >> 4, v = slot & 15;
     const int ii = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
     const int row = fc2_row(p.a_kfast, tile_m, wave, i, ii);
-    if (col < p.N && row < p.M) *(i32v4 *)((int32_t *)p.out + (int64_t)row * p.ldc + col) = sum;
+    if (col >= 0 && row < p.M) *(i32v4_dw *)((int32_t *)p.out + (int64_t)row * p.ldc + col) = sum;
 }
 
 }  // namespace dbp

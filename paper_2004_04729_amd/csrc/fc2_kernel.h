@@ -1,5 +1,6 @@
 // Fully connected products, Eqs. (qda)/(qdw), with separate staging and multiplying wavefronts
-// (internal header; arithmetic, LDS cell layout and operand conventions are those of fc_kernel.h).
+// (internal header; operand conventions and problem description in fc_kernel.h, arithmetic and LDS cells in gemm_core.h).
+// Rows and columns of any length: only the codes' loads meet odd addresses, and wide loads and stores take them.
 //
 // A workgroup has eight wavefronts and a CU to itself.  Wavefronts 0-3 (64 rows x 128 columns each) do
 // nothing but read matrix-core fragments from LDS and multiply; wavefronts 4-7 do nothing but move data:
@@ -129,11 +130,30 @@ struct Fc2Raw {                       // one K step of one stager thread, as loa
     f32x4 b[4];
     uint32_t a[8];
     int kfast, k_valid;               // operand layout of the item; reduction indices of the step that exist
-    int a_shift;                      // !kfast: dwords by which the loaded run of rows was moved back to stay inside the matrix
+    int a_shift;                      // !kfast: rows by which the loaded run of rows starts early to stay inside the matrix
 };
 
-// 16 bytes from an address that is only known to be a multiple of 4 (one global_load_dwordx4)
-typedef uint32_t u32x4_dw __attribute__((ext_vector_type(4), aligned(4)));
+// 16 bytes of floats from an address that is only known to be a multiple of 4 (one global_load_dwordx4; codes: any address)
+typedef float f32x4_dw __attribute__((ext_vector_type(4), aligned(4)));
+
+// A run of 16 consecutive rows that was loaded `sh` rows early to stay inside the matrix, moved back (what lies past the
+// last row is zero).
+__device__ __forceinline__ void fc2_unshift(uint32_t (&w)[4], int sh)
+{
+    const uint32_t t0 = w[0], t1 = w[1], t2 = w[2], t3 = w[3];
+    const int dw = sh >> 2, b = 8 * (sh & 3);
+    w[0] = dw == 0 ? t0 : dw == 1 ? t1 : dw == 2 ? t2 : dw == 3 ? t3 : 0u;
+    w[1] = dw == 0 ? t1 : dw == 1 ? t2 : dw == 2 ? t3 : 0u;
+    w[2] = dw == 0 ? t2 : dw == 1 ? t3 : 0u;
+    w[3] = dw == 0 ? t3 : 0u;
+    if (b) {
+        w[0] = __builtin_amdgcn_alignbit(w[1], w[0], b); w[1] = __builtin_amdgcn_alignbit(w[2], w[1], b);
+        w[2] = __builtin_amdgcn_alignbit(w[3], w[2], b); w[3] >>= b;
+    }
+}
+
+// Dword `w` of consecutive codes with the first `gone` bytes cleared (gone <= 0: none, >= 4: all).
+__device__ __forceinline__ uint32_t fc2_drop(uint32_t w, int gone) { return gone >= 4 ? 0u : gone > 0 ? w >> (8 * gone) << (8 * gone) : w; }
 
 // Sum of the quantiser's statistics records by one wavefront (integers: any order gives the same result); four
 // loads in flight per lane.
@@ -242,7 +262,7 @@ __global__ __launch_bounds__(512, 1) void fc2_pair_kernel(FcPairArgs a)
                 // dense operand: columns 4*nq .. +3 of the tile (one per load), reduction indices 4*kq .. +3 of the window
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    boff[j] = (uint32_t)min(c.tile_n + 4 * nq + j, c.N - 1) * (uint32_t)c.ldb * 4u + 16u * (uint32_t)kq;
+                    boff[j] = (uint32_t)(min(c.tile_n + 4 * nq, c.N - 4) + j) * (uint32_t)c.ldb * 4u + 16u * (uint32_t)kq;
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
                     aoff[j] = (uint32_t)min(c.tile_m + 128 * j + (tid >> 1), c.M - 1) * (uint32_t)c.lda + 16u * (uint32_t)(tid & 1);
@@ -265,12 +285,12 @@ __global__ __launch_bounds__(512, 1) void fc2_pair_kernel(FcPairArgs a)
                 for (int j = 0; j < 2; ++j)
                     aoff[j] = (uint32_t)min(c.tile_m + 128 * j + (tid >> 1), c.M - 1) * lda + 16u * (uint32_t)(tid & 1);
             } else {
-                // reduction indices 2*(tid/16), +1 and 16 consecutive rows of the matrix each (M >= 16, M % 4 == 0);
+                // reduction indices 2*(tid/16), +1 and 16 consecutive rows of the matrix each (M >= 16);
                 // a run that would pass the last row starts earlier and is moved back when the step is committed
                 a_unit = c.lda;
                 a_step = c.A + (int64_t)c.k0 * c.lda;
                 const int m = c.tile_m + 16 * (tid & 15);
-                a_shift = max(0, m + 16 - c.M) >> 2;
+                a_shift = min(max(0, m + 16 - c.M), 16);
                 aoff[0] = 2u * (uint32_t)(tid >> 4) * lda + (uint32_t)max(0, min(m, c.M - 16));
                 aoff[1] = aoff[0] + lda;
             }
@@ -303,10 +323,10 @@ __global__ __launch_bounds__(512, 1) void fc2_pair_kernel(FcPairArgs a)
             r.k_valid = kv_cur;
             r.a_shift = a_shift;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) r.b[i] = *(const f32x4 *)(b_cur + (size_t)boff[i]);
+            for (int i = 0; i < 4; ++i) r.b[i] = *(const f32x4_dw *)(b_cur + (size_t)boff[i]);
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                const u32x4 v = *(const u32x4_dw *)(a_cur + (size_t)aoff[i]);
+                const u32x4 v = *(const u32x4_unaligned *)(a_cur + (size_t)aoff[i]);
                 r.a[4 * i] = v.x; r.a[4 * i + 1] = v.y; r.a[4 * i + 2] = v.z; r.a[4 * i + 3] = v.w;
             }
             if (open) {
@@ -320,15 +340,6 @@ __global__ __launch_bounds__(512, 1) void fc2_pair_kernel(FcPairArgs a)
             }
         };
 
-        // dwords of a 16-byte run moved back by `sh` dwords (what lies past the last row is zero)
-        auto unshift = [](uint32_t (&w)[4], int sh) {
-            const uint32_t t0 = w[0], t1 = w[1], t2 = w[2], t3 = w[3];
-            w[0] = sh == 0 ? t0 : sh == 1 ? t1 : sh == 2 ? t2 : sh == 3 ? t3 : 0u;
-            w[1] = sh == 0 ? t1 : sh == 1 ? t2 : sh == 2 ? t3 : 0u;
-            w[2] = sh == 0 ? t2 : sh == 1 ? t3 : 0u;
-            w[3] = sh == 0 ? t3 : 0u;
-        };
-
         auto commit = [&](const Fc2Raw &r, Fc2Stage &sm) {
             // window indices below `dup` repeat the step before (only in an item's last, shorter step)
             const int dup = FC2_KT - r.k_valid;
@@ -338,9 +349,8 @@ __global__ __launch_bounds__(512, 1) void fc2_pair_kernel(FcPairArgs a)
                 for (int i = 0; i < 2; ++i) {
                     uint32_t w[4] = {r.a[4 * i], r.a[4 * i + 1], r.a[4 * i + 2], r.a[4 * i + 3]};
                     if (dup > 0) {
-                        // the item's ends are multiples of 4, so whole dwords are in or out
 #pragma unroll
-                        for (int d = 0; d < 4; ++d) w[d] = 16 * (tid & 1) + 4 * d >= dup ? w[d] : 0u;
+                        for (int d = 0; d < 4; ++d) w[d] = fc2_drop(w[d], dup - 16 * (tid & 1) - 4 * d);
                     }
                     const int pos = 128 * i + (tid >> 1);
 #pragma unroll
@@ -356,7 +366,7 @@ __global__ __launch_bounds__(512, 1) void fc2_pair_kernel(FcPairArgs a)
                 // of the tile -> position 16*(4*d + j) + tid%16, dword k2%4 of the cell of chunk k2/4
                 const int k2 = tid >> 4, m16 = tid & 15;
                 uint32_t w0[4] = {r.a[0], r.a[1], r.a[2], r.a[3]}, w1[4] = {r.a[4], r.a[5], r.a[6], r.a[7]};
-                if (r.a_shift) { unshift(w0, r.a_shift); unshift(w1, r.a_shift); }
+                if (r.a_shift) { fc2_unshift(w0, r.a_shift); fc2_unshift(w1, r.a_shift); }
                 if (dup > 0) {
 #pragma unroll
                     for (int d = 0; d < 4; ++d) { w0[d] = 2 * k2 >= dup ? w0[d] : 0u; w1[d] = 2 * k2 + 1 >= dup ? w1[d] : 0u; }
@@ -474,9 +484,10 @@ __global__ __launch_bounds__(512, 1) void fc2_pair_kernel(FcPairArgs a)
             } else {
                 // block (i,j) covers row positions 64*wave + 32*i.. and column positions 32*j.. (column 4*lcol + j);
                 // D[ii][jj] of a block sits in lane (jj, ii%8/4), register 4*(ii/8)+ii%4.
-                const int col = c.tile_n + 4 * lcol;
+                // (a ragged row's last four columns start early, as their loads did; the columns two lanes share get the same values)
+                const int col = min(c.tile_n + 4 * lcol, p.N - 4);
                 const float sc = c.which ? scale1 : scale0;
-                if (col < p.N) {
+                if (c.tile_n + 4 * lcol < p.N) {
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -487,7 +498,7 @@ __global__ __launch_bounds__(512, 1) void fc2_pair_kernel(FcPairArgs a)
                                 // written once and read by nobody in this launch: streaming stores (the MLP step 124 -> 120 us; the partial tiles
                                 // above, which the reduction reads right away, lose 4 us with them)
                                 __builtin_nontemporal_store(f32x4{sc * acc[i][0][v], sc * acc[i][1][v], sc * acc[i][2][v], sc * acc[i][3][v]},
-                                                            (f32x4 *)(p.out + (int64_t)row * p.ldc + col));
+                                                            (f32x4_dw *)(p.out + (int64_t)row * p.ldc + col));
                         }
                 }
             }
@@ -515,7 +526,7 @@ __global__ __launch_bounds__(256) void fc2_reduce_kernel(FcPairArgs a, int tiles
     const int tile_m = (tile % p.tiles_m) * FC2_TM;
     const int tile_n = (tile / p.tiles_m) * FC2_TN;
     const float4 *all = (const float4 *)(p.partial + (int64_t)tile * p.n_split * (FC2_TM * FC2_TN)) + slot * 256 + tid;
-    const int col = tile_n + 4 * (lane & 31);
+    const int col = min(tile_n + 4 * (lane & 31), p.N - 4);
     float4 sum = float4{0.f, 0.f, 0.f, 0.f};
     // eight loads in flight at a time (the loop is bound by their latency); the additions stay in split order
     const int n_split = p.n_split;
@@ -531,8 +542,8 @@ __global__ __launch_bounds__(256) void fc2_reduce_kernel(FcPairArgs a, int tiles
     const int ii = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
     const int row = fc2_row(p.a_kfast, tile_m, wave, i, ii);
     const float sc = p.scale.get();
-    if (col < p.N && row < p.M)
-        *(float4 *)(p.out + (int64_t)row * p.ldc + col) = float4{sc * sum.x, sc * sum.y, sc * sum.z, sc * sum.w};
+    if (tile_n + 4 * (lane & 31) < p.N && row < p.M)
+        *(f32x4_dw *)(p.out + (int64_t)row * p.ldc + col) = f32x4_dw{sc * sum.x, sc * sum.y, sc * sum.z, sc * sum.w};
 }
 
 }  // namespace dbp

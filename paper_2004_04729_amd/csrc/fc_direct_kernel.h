@@ -1,0 +1,352 @@
+// Fully connected products, Eqs. (qda)/(qdw), for layers of any shape, straight from global memory (internal header).
+//
+//   dX[b,i] = Delta * sum_o code[b,o] W[o,i]      A = codes, reduction index contiguous  (KFAST)
+//   dW[o,i] = Delta * sum_b code[b,o] X[b,i]      A = codes^T, reduction index strided
+//
+// The kernels of fc_kernel.h and fc2_kernel.h stage tiles through LDS, which pays for large products and wants aligned, whole
+// vectors.  What is left -- layers of a few workgroups, widths that no vector divides -- is bound by the latency of a chain of
+// (load, stage, barrier, multiply) steps with an idle chip around it.  Here a WAVEFRONT is the unit:
+//   * it owns 32*MF rows x 32*NF columns and loads its matrix-core fragments directly.  The dense operand is stored
+//     [reduction][column]: a lane loads NF adjacent columns of 8 (16 in the int8 form) reduction indices, 256 (128) contiguous
+//     bytes per half wavefront and row, and they become the lane's elements of NF fragments -- fragment j covers columns
+//     NF*lane + j -- so nothing is exchanged between lanes and a result row leaves in whole lines.  The strided codes of
+//     dW work the same way (MF adjacent rows per load).  Wide loads of floats need 4-byte alignment only, loads of codes none.
+//     fp32 operands: NF = 2, MF = 1 or 2; int8: NF = 4 (a dword), MF = 1 -- what leaves room for two steps of loads in half of a
+//     SIMD's registers (64 x 128 and 128 x 64 spilled).
+//   * no LDS and no barrier in the loop: the loads of the next step are in flight during the multiplications of this one.
+//   * KW wavefronts of a workgroup share a tile's reduction and add up through LDS at the end (fixed order), so that a small layer is
+//     a few steps deep instead of dozens; the others of the workgroup's eight take neighbouring tiles.  Reductions that still
+//     leave the chip idle are split over workgroups as well (partials in row-major order, summed by fcd_reduce_kernel).
+//   * a window of reduction indices never leaves the matrix: the last one ends at the matrix's end and the codes it repeats are
+//     zeroed; matrices shorter than a window clamp the rows; tiles past an edge repeat its last rows or columns.
+// Bound: the dense operand is cut into its three bf16 planes by every wavefront that reads it (about 180 vector instructions per step
+// beside 12*MF matrix instructions), so large products go to the staged kernels.
+// Measured (whole call): 64x784x300 23 -> 12.3 us, 300x521x1030 (on the generic kernel before) 103 -> 18.8 us.
+#pragma once
+#include "fc_kernel.h"
+#include "side_jobs.h"
+
+namespace dbp {
+
+constexpr int FCD_WAVES = 8;           // wavefronts of a workgroup
+__host__ __device__ constexpr int fcd_tn(bool i8) { return i8 ? 128 : 64; }
+
+struct FcdProblem {
+    const int8_t *A; int64_t lda;        // KFAST: A[m*lda + k]   else: A[k*lda + m]
+    const void   *B; int64_t ldb;        // B[k*ldb + n], fp32 or int8
+    void *out, *partial;                 // out[m*N + n], fp32 or int32; partial[split][m*N + n] (n_split > 1)
+    int M, N, K;
+    int tiles_m, tiles, kw, n_split, steps_per_split;
+    int groups;                          // workgroups per reduction split
+    int form;                            // fcd_form(int8, kfast, MF)
+    Scale scale;
+};
+// Workgroups [0, first1) take problem 0, the others problem 1, the last job.workgroups() the quantiser's pending sums.
+struct FcdArgs { FcdProblem prob[2]; int first1; StatsJob stats; Gate gate; };
+
+__host__ __device__ constexpr int fcd_form(bool i8, bool kfast, int mf) { return (i8 ? 16 : 0) | (kfast ? 8 : 0) | mf; }
+
+typedef float    f32x2_dw4 __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32x2_dw4 __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32_u   __attribute__((aligned(1)));
+typedef uint64_t u64_u   __attribute__((aligned(1)));
+typedef uint16_t u16_u   __attribute__((aligned(1)));
+
+// Rows of 4 bytes each -> column e of the four rows, reduction index lowest first.
+__device__ __forceinline__ void fcd_transpose4(const uint32_t *r, uint32_t (&t)[4])
+{
+    const uint32_t x0 = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u), x1 = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u);
+    const uint32_t y0 = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u), y1 = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
+    t[0] = __builtin_amdgcn_perm(x1, x0, 0x05040100u); t[1] = __builtin_amdgcn_perm(x1, x0, 0x07060302u);
+    t[2] = __builtin_amdgcn_perm(y1, y0, 0x05040100u); t[3] = __builtin_amdgcn_perm(y1, y0, 0x07060302u);
+}
+
+template <bool I8, bool KFAST, int MF> struct FcdRaw {
+    static constexpr int KH = I8 ? 16 : 8;                  // reduction indices of a half wavefront
+    f32x2_t  bf[I8 ? 1 : 8];
+    uint32_t bi[I8 ? 16 : 1];
+    uint32_t a[KFAST ? MF * (KH / 4) : KH];
+};
+
+template <bool I8, bool KFAST, int MF>
+__device__ __forceinline__ void fcd_tile(const FcdProblem &p, int local, uint4 *lds)
+{
+    using Acc = typename std::conditional<I8, i32x16, f32x16>::type;
+    using E = typename std::conditional<I8, int32_t, float>::type;
+    using V = typename std::conditional<I8, u32x4, u32x2_dw4>::type;
+    using VOut = typename std::conditional<I8, u32x4_dw4, u32x2_dw4>::type;
+    using Raw = FcdRaw<I8, KFAST, MF>;
+    constexpr int MODE = I8 ? MODE_I8 : MODE_BF16;
+    constexpr int KH = Raw::KH, KT = 2 * KH, AD = KH / 4;   // AD: dwords of a fragment's codes
+    constexpr int NF = I8 ? 4 : 2, TN = 32 * NF;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lrow = lane & 31, half = lane >> 5;
+    const int KW = p.kw, kw = wave % KW, per_wg = FCD_WAVES / KW;
+    const int z = local / p.groups, tile_raw = (local - z * p.groups) * per_wg + wave / KW;
+    const bool live = tile_raw < p.tiles;
+    const int tile = live ? tile_raw : p.tiles - 1;
+    const int tile_m = tile % p.tiles_m * (32 * MF), tile_n = tile / p.tiles_m * TN;
+
+    // this wavefront's steps: a KW-th of the workgroup's
+    const int all = (p.K + KT - 1) / KT;
+    const int z0 = z * p.steps_per_split, z1 = min(all, z0 + p.steps_per_split);
+    const int s0 = z0 + (z1 - z0) * kw / KW, s1 = live ? z0 + (z1 - z0) * (kw + 1) / KW : s0;
+
+    // lane offsets, fixed for the tile (a window's rows are close together: 32 bits)
+    const int col = min(tile_n + NF * lrow, p.N - NF);
+    const bool short_k = p.K < KT;
+    uint32_t boff[KH], aoff[KFAST ? MF : KH];
+#pragma unroll
+    for (int i = 0; i < KH; ++i) boff[i] = ((uint32_t)min(KH * half + i, p.K - 1) * (uint32_t)p.ldb + (uint32_t)col) * (I8 ? 1u : 4u);
+    if constexpr (KFAST) {
+#pragma unroll
+        for (int i = 0; i < MF; ++i) aoff[i] = (uint32_t)min(tile_m + 32 * i + lrow, p.M - 1) * (uint32_t)p.lda + (uint32_t)(KH * half);
+    } else {
+        const int arow = min(tile_m + MF * lrow, p.M - MF);
+#pragma unroll
+        for (int i = 0; i < KH; ++i) aoff[i] = (uint32_t)min(KH * half + i, p.K - 1) * (uint32_t)p.lda + (uint32_t)arow;
+    }
+
+    auto load = [&](Raw &r, int step) {
+        const int k = max(min(step * KT, p.K - KT), 0);
+        const char *b = (const char *)p.B + (int64_t)k * p.ldb * (I8 ? 1 : 4);
+        const int8_t *a = p.A + (KFAST ? (int64_t)k : (int64_t)k * p.lda);
+#pragma unroll
+        for (int i = 0; i < KH; ++i) {
+            if constexpr (I8) r.bi[i] = *(const u32_u *)(b + boff[i]);
+            else r.bf[i] = *(const f32x2_dw4 *)(b + boff[i]);
+        }
+        if constexpr (KFAST) {
+            if (!short_k) {
+#pragma unroll
+                for (int i = 0; i < MF; ++i) {
+                    if constexpr (I8) {
+                        const u32x4 v = *(const u32x4_unaligned *)(a + aoff[i]);
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) r.a[4 * i + d] = v[d];
+                    } else {
+                        const uint64_t v = *(const u64_u *)(a + aoff[i]);
+                        r.a[2 * i] = (uint32_t)v; r.a[2 * i + 1] = (uint32_t)(v >> 32);
+                    }
+                }
+            } else {
+                // one window in all, wider than a row: code by code, zero past the row's end
+#pragma unroll
+                for (int i = 0; i < MF; ++i)
+#pragma unroll
+                    for (int d = 0; d < AD; ++d) {
+                        uint32_t w = 0;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int kk = KH * half + 4 * d + e;
+                            const uint32_t v = (uint8_t)a[aoff[i] - KH * half + min(kk, p.K - 1)];
+                            w |= (kk < p.K ? v : 0u) << (8 * e);
+                        }
+                        r.a[AD * i + d] = w;
+                    }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < KH; ++i) {
+                if constexpr (MF == 2) r.a[i] = *(const u16_u *)(a + aoff[i]);
+                else r.a[i] = (uint8_t)a[aoff[i]];
+            }
+        }
+    };
+
+    Acc acc[MF][NF];
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NF; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+
+    auto multiply = [&](Raw &r, int step) {
+        // window indices below `dup` belong to the step before (the last window), those from K on do not exist (a short matrix)
+        const int dup = short_k ? 0 : max(step * KT + KT - p.K, 0);
+        if (dup > 0 || short_k) {
+            const int lo = dup - KH * half;                  // indices of this half below lo are void
+            if constexpr (KFAST) {
+#pragma unroll
+                for (int i = 0; i < MF; ++i)
+#pragma unroll
+                    for (int d = 0; d < AD; ++d) {
+                        const int gone = min(max(lo - 4 * d, 0), 4);
+                        r.a[AD * i + d] = gone == 4 ? 0u : r.a[AD * i + d] >> (8 * gone) << (8 * gone);
+                    }
+            } else {
+#pragma unroll
+                for (int i = 0; i < KH; ++i) r.a[i] = i >= lo && KH * half + i < p.K ? r.a[i] : 0u;
+            }
+        }
+        u32x4 af[MF];
+#pragma unroll
+        for (int i = 0; i < MF; ++i) {
+            if constexpr (I8 && KFAST) {
+                af[i] = u32x4{r.a[4 * i], r.a[4 * i + 1], r.a[4 * i + 2], r.a[4 * i + 3]};
+            } else if constexpr (I8) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {                // byte i of four rows
+                    const uint32_t lo2 = __builtin_amdgcn_perm(r.a[4 * g + 1], r.a[4 * g], i ? 0x0c0c0501u : 0x0c0c0400u);
+                    const uint32_t hi2 = __builtin_amdgcn_perm(r.a[4 * g + 3], r.a[4 * g + 2], i ? 0x05010c0cu : 0x04000c0cu);
+                    af[i][g] = lo2 | hi2;
+                }
+            } else if constexpr (KFAST) {
+#pragma unroll
+                for (int d = 0; d < 2; ++d) {
+                    const uint32_t w = r.a[2 * i + d];
+                    af[i][2 * d] = bf16x2_from_codes((int8_t)w, (int8_t)(w >> 8));
+                    af[i][2 * d + 1] = bf16x2_from_codes((int8_t)(w >> 16), (int8_t)(w >> 24));
+                }
+            } else {
+#pragma unroll
+                for (int d = 0; d < 4; ++d) af[i][d] = bf16x2_from_codes((int8_t)(r.a[2 * d] >> (8 * i)), (int8_t)(r.a[2 * d + 1] >> (8 * i)));
+            }
+        }
+        if constexpr (I8) {
+            u32x4 bf[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                uint32_t t[4];
+                fcd_transpose4(&r.bi[4 * g], t);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) bf[j][g] = t[j];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < MF; ++i) Mma<MODE>::run(af[i], bf[j], acc[i][j]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NF; ++j) {
+                uint32_t h[8], m[8], l[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) split3_upper(r.bf[i][j], h[i], m[i], l[i]);
+                const u32x4 lo = {upper_halves(l[1], l[0]), upper_halves(l[3], l[2]), upper_halves(l[5], l[4]), upper_halves(l[7], l[6])};
+                const u32x4 md = {upper_halves(m[1], m[0]), upper_halves(m[3], m[2]), upper_halves(m[5], m[4]), upper_halves(m[7], m[6])};
+                const u32x4 hi = {upper_halves(h[1], h[0]), upper_halves(h[3], h[2]), upper_halves(h[5], h[4]), upper_halves(h[7], h[6])};
+#pragma unroll
+                for (int i = 0; i < MF; ++i) Mma<MODE>::run(af[i], lo, acc[i][j]);
+#pragma unroll
+                for (int i = 0; i < MF; ++i) Mma<MODE>::run(af[i], md, acc[i][j]);
+#pragma unroll
+                for (int i = 0; i < MF; ++i) Mma<MODE>::run(af[i], hi, acc[i][j]);
+            }
+        }
+    };
+
+    if (s0 < s1) {
+        Raw r0, r1;
+        load(r0, s0);
+        for (int s = s0; s < s1; s += 2) {                   // every path issues the same loads (the last window once more at the end)
+            load(r1, min(s + 1, s1 - 1));
+            multiply(r0, s);
+            if (s + 1 < s1) {
+                load(r0, min(s + 2, s1 - 1));
+                multiply(r1, s + 1);
+            }
+        }
+    }
+
+    // ---- the wavefronts of a tile add up in halves: 2 steps to go with four, and so on (a fixed order)
+    for (int h = KW >> 1; h > 0; h >>= 1) {
+        uint32_t *slot = (uint32_t *)lds + (size_t)((wave / KW) * h + kw % h) * (MF * NF * 16 * 64) + NF * lane;
+        if (kw >= h && kw < 2 * h) {
+#pragma unroll
+            for (int i = 0; i < MF; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    V t;
+#pragma unroll
+                    for (int j = 0; j < NF; ++j) t[j] = __builtin_bit_cast(uint32_t, (E)acc[i][j][v]);
+                    *(V *)(slot + (i * 16 + v) * 64 * NF) = t;
+                }
+        }
+        __syncthreads();
+        if (kw < h) {
+#pragma unroll
+            for (int i = 0; i < MF; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const V t = *(const V *)(slot + (i * 16 + v) * 64 * NF);
+#pragma unroll
+                    for (int j = 0; j < NF; ++j) acc[i][j][v] += __builtin_bit_cast(E, (uint32_t)t[j]);
+                }
+        }
+        __syncthreads();
+    }
+    if (!live || kw != 0 || tile_n + NF * lrow >= p.N) return;
+
+    // ---- D[ii][lrow] of fragment (i, j): row ii of block i, column NF*lrow + j (the last NF of a ragged row start earlier)
+    const bool split = p.n_split > 1;
+    const float sc = I8 || split ? 1.0f : p.scale.get();
+    uint32_t *out = (uint32_t *)(split ? p.partial : p.out) + (split ? (int64_t)z * p.M * p.N : 0) + col;
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int ii = 8 * (v >> 2) + 4 * half + (v & 3);
+            const int row = KFAST ? tile_m + 32 * i + ii : min(tile_m + MF * ii, p.M - MF) + i;
+            if (KFAST ? row < p.M : tile_m + MF * ii < p.M) {
+                VOut t;
+#pragma unroll
+                for (int j = 0; j < NF; ++j)
+                    if constexpr (I8) t[j] = (uint32_t)acc[i][j][v]; else t[j] = __float_as_uint(sc * acc[i][j][v]);
+                *(VOut *)(out + (int64_t)row * p.N) = t;
+            }
+        }
+}
+
+__global__ __launch_bounds__(64 * FCD_WAVES, 1) void fc_direct_kernel(FcdArgs a)
+{
+    if (a.gate.closed()) return;
+    extern __shared__ uint4 fcd_lds[];
+    const int work = (int)gridDim.x - (int)a.stats.workgroups();
+    if ((int)blockIdx.x >= work) { side_job(a.stats, (int)blockIdx.x - work, 64 * FCD_WAVES); return; }
+    const bool second = (int)blockIdx.x >= a.first1;
+    const FcdProblem &p = a.prob[second ? 1 : 0];
+    const int local = (int)blockIdx.x - (second ? a.first1 : 0);
+    switch (p.form) {
+    case fcd_form(false, true, 1):  fcd_tile<false, true, 1>(p, local, fcd_lds); break;
+    case fcd_form(false, true, 2):  fcd_tile<false, true, 2>(p, local, fcd_lds); break;
+    case fcd_form(false, false, 1): fcd_tile<false, false, 1>(p, local, fcd_lds); break;
+    case fcd_form(false, false, 2): fcd_tile<false, false, 2>(p, local, fcd_lds); break;
+    case fcd_form(true, true, 1):   fcd_tile<true, true, 1>(p, local, fcd_lds); break;
+    default:                        fcd_tile<true, false, 1>(p, local, fcd_lds); break;
+    }
+}
+
+// Sum of the reduction splits, in split order, four neighbouring outputs a thread.
+__global__ __launch_bounds__(256) void fcd_reduce_kernel(FcdArgs a, int blocks0)
+{
+    if (a.gate.closed()) return;
+    const bool second = (int)blockIdx.x >= blocks0;
+    const FcdProblem &p = a.prob[second ? 1 : 0];
+    const int64_t total = (int64_t)p.M * p.N;
+    const int64_t i = 4 * ((int64_t)((int)blockIdx.x - (second ? blocks0 : 0)) * 256 + threadIdx.x);
+    if (i >= total) return;
+    const int64_t at = min(i, total - 4);                    // the last four overlap their neighbours: the same sums twice
+    const bool i8 = (p.form & 16) != 0;
+    const uint32_t *src = (const uint32_t *)p.partial + at;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    int32_t n[4] = {0, 0, 0, 0};
+    for (int q = 0; q < p.n_split; q += 8) {
+        u32x4 t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = *(const u32x4_dw4 *)(src + (int64_t)min(q + u, p.n_split - 1) * total);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q + u < p.n_split) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { s[j] += __uint_as_float(t[u][j]); n[j] += (int32_t)t[u][j]; }
+            }
+    }
+    const float sc = i8 ? 1.0f : p.scale.get();
+    u32x4 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = i8 ? (uint32_t)n[j] : __float_as_uint(sc * s[j]);
+    *(u32x4_dw4 *)((uint32_t *)p.out + at) = r;
+}
+
+}  // namespace dbp

@@ -10,7 +10,7 @@
 // wave ballots (free by-products of the compares); their popcounts give the tile count and, via
 // mbcnt, each lane's exclusive prefix, so compaction needs neither LDS nor atomics.  The four
 // ballots ARE the bitmap words of the tile (word j = sub-column j), so the bitmap costs nothing.
-#include "common.h"
+#include "side_jobs.h"
 
 namespace dbp {
 
@@ -467,7 +467,7 @@ __global__ void bias_grad_kernel(const int64_t *sums, int64_t n, float step, con
         grad[i] = (float)(d * (double)sums[i]);
 }
 
-__global__ __launch_bounds__(256) void bias_channels_kernel(StatsJob j) { bias_of_channel(j, (int)blockIdx.x); }
+__global__ __launch_bounds__(256) void bias_channels_kernel(StatsJob j) { bias_of_channel(j, (int)blockIdx.x, 256); }
 
 // ---- step size of Algorithm 1: sigma = std(delta_z), Delta = s * sigma --------------------------------------
 // Population standard deviation from S1 = sum x and S2 = sum x*x in fp64 (x*x is exact there).  Delta decides

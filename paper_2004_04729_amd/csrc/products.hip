@@ -4,6 +4,7 @@
 #include "conv_loaders.h"
 #include "fc_kernel.h"
 #include "fc2_kernel.h"
+#include "fc_direct_kernel.h"
 #include "fc2_i8_kernel.h"
 #include "conv_dx_kernel.h"
 #include "conv_dw_kernel.h"
@@ -402,29 +403,8 @@ hipError_t launch_conv_dw_fast(const ConvDwPlan &pl, hipStream_t s)
                                           : launch_conv_dw_fast_as<MODE, R, S, PAD, MB, 0>(pl, s);
 }
 
-// ---- fast fully connected path (fc_kernel.h) -------------------------------------------------------
+// ---- fully connected products with staging and multiplying wavefronts (fc2_kernel.h, fc2_i8_kernel.h) -----------
 struct FcPlan { int tiles_m, tiles_n, n_split, k_per_split; int64_t tiles; size_t partial_bytes; };
-
-// Split the reduction of a product with few tiles into about two items per CU, never below 8 K steps per
-// item (the length of a dW item at batch 256, so the persistent workgroups stay balanced).  Every split
-// costs a partial write + read.
-FcPlan fc_plan(int64_t M, int64_t N, int64_t K, int tm = FC_TM, int tn = FC_TN)
-{
-    FcPlan pl;
-    pl.tiles_m = (int)((M + tm - 1) / tm);
-    pl.tiles_n = (int)((N + tn - 1) / tn);
-    pl.tiles = (int64_t)pl.tiles_m * pl.tiles_n;
-    const int64_t steps = (K + FC_KT - 1) / FC_KT;
-    int64_t want = (512 + pl.tiles - 1) / pl.tiles;
-    const int64_t max_n = steps / 8 > 0 ? steps / 8 : 1;
-    if (want > max_n) want = max_n;
-    if (want < 1) want = 1;
-    const int64_t per = (steps + want - 1) / want;
-    pl.k_per_split = (int)(per * FC_KT);
-    pl.n_split = (int)((steps + per - 1) / per);
-    pl.partial_bytes = pl.n_split > 1 ? (size_t)pl.tiles * pl.n_split * tm * tn * sizeof(float) : 0;
-    return pl;
-}
 
 // Plans of the two products for the kernel with staging and multiplying wavefronts: reductions are split
 // into items of about half a workgroup's share of all K steps (one workgroup per CU), at least 8 steps.
@@ -499,12 +479,86 @@ int fc2_group_plan(int64_t B, int64_t in, int64_t out, FcPlan &dx, FcPlan &dw, i
     return gx;
 }
 
-bool fc_fast_ok(bool a_kfast, const int8_t *A, int64_t lda, const float *B, int64_t ldb, int64_t M, int64_t N, const float *out)
+// ---- fully connected layers straight from global memory (fc_direct_kernel.h) ----------------------------------
+struct FcdPlan { int mf, kw, n_split, steps_per_split, tiles_m, tiles, groups; size_t partial_bytes; float us; };
+
+// Shape of one product on fc_direct_kernel, by modelled time: 32 or 64 rows a wavefront, the wavefronts that share a tile's
+// reduction, and (where that leaves most of `room` CUs idle and the partials fit `cap` bytes) splits over workgroups.
+// Calibrated on layers from 16x64x64 to 512x2048x2048: a step of a wavefront takes about 0.45 us (0.55 with 64 rows), twice that
+// where the dense operand comes from HBM; adding up through LDS about 0.5 us a halving; a second launch 5 us.
+FcdPlan fcd_plan(int64_t M, int64_t N, int64_t K, bool i8, int room, size_t cap)
 {
-    if (N < 4 || N % 4 || ldb % 4 || ((uintptr_t)B % 16) || ((uintptr_t)out % 8)) return false;
-    if (lda % 4 || ((uintptr_t)A % 4)) return false;
-    if (!a_kfast && (M < 4 || M % 4)) return false;
-    return true;
+    FcdPlan best{};
+    best.us = -1.0f;
+    const int steps = (int)((K + (i8 ? 31 : 15)) / (i8 ? 32 : 16));
+    const int64_t tn = (N + fcd_tn(i8) - 1) / fcd_tn(i8);
+    const float cold = (float)K * N * (i8 ? 1.0f : 4.0f) > 32.0e6f ? 2.0f : 1.0f;
+    for (int mf = 1; mf <= (i8 ? 1 : 2); ++mf) {
+        const int64_t tm = (M + 32 * mf - 1) / (32 * mf), tiles = tm * tn;
+        const float step = cold * (mf == 2 ? 0.55f : 0.45f);
+        for (int kw = 1, halvings = 0; kw <= FCD_WAVES && kw <= steps; kw *= 2, ++halvings) {
+            const int64_t groups = (tiles * kw + FCD_WAVES - 1) / FCD_WAVES;
+            int most = steps / (4 * kw);
+            if (most > room / groups) most = (int)(room / groups);
+            if (most > 1 && (size_t)most * M * N * 4 > cap) most = (int)(cap / ((size_t)M * N * 4));
+            for (int n = 1;; n = most) {
+                const int per = (steps + n - 1) / n, ns = (steps + per - 1) / per;
+                const float rounds = groups * ns <= room ? 1.0f : (float)(groups * ns) / room;
+                float us = rounds * (1.5f + (float)((per + kw - 1) / kw) * step + 0.5f * halvings);
+                if (ns > 1) us += 5.0f + (float)ns * M * N * 8.0f / 4.0e6f;
+                if (best.us < 0.0f || us < best.us)
+                    best = FcdPlan{mf, kw, ns, per, (int)tm, (int)tiles, (int)groups, ns > 1 ? (size_t)ns * M * N * 4 : 0, us};
+                if (n >= most) break;
+            }
+        }
+    }
+    return best;
+}
+
+// What the kernel takes: rows of at least NF (MF) elements, 32-bit offsets.
+bool fcd_ok(bool kfast, int64_t M, int64_t N, int64_t K, int64_t lda, bool i8)
+{
+    return N >= (i8 ? 4 : 2) && (kfast || M >= 2) && M * N >= 4 && lda < (1 << 24) && N < (1 << 24) && (!kfast || M * lda < ((int64_t)1 << 31)) && K >= 1 &&
+           M < ((int64_t)1 << 24) && K < ((int64_t)1 << 24);
+}
+
+// The products of `a` that are asked for, on the direct kernel, with the quantiser's pending sums beside them.
+hipError_t launch_fc_direct(const LinearArgs &a, bool want_dx, bool want_dw, const StatsJob &job, hipStream_t s)
+{
+    static bool raised = false;                                      // with its static LDS above 64 KiB: allowed per kernel, once
+    if (!raised) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&fc_direct_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 64 << 10);
+        if (e != hipSuccess) return e;
+        raised = true;
+    }
+    FcdArgs fa{};
+    char *scratch = (char *)a.scratch;
+    // the chip in proportion to the products' multiply-adds, which are the same: half each
+    const int room = want_dx && want_dw ? 128 : 256;
+    size_t left = a.scratch_bytes & ~(size_t)255, lds = 0;
+    int blocks = 0, reduce[2] = {0, 0};
+    auto fill = [&](int which, bool kfast, bool i8, const void *Bop, int64_t M, int64_t K, void *out) {
+        const FcdPlan pl = fcd_plan(M, a.in, K, i8, room, left);
+        FcdProblem &p = fa.prob[which];
+        p.A = a.codes; p.lda = a.out; p.B = Bop; p.ldb = a.in; p.out = out; p.partial = scratch;
+        p.M = (int)M; p.N = (int)a.in; p.K = (int)K;
+        p.tiles_m = pl.tiles_m; p.tiles = pl.tiles; p.kw = pl.kw; p.n_split = pl.n_split; p.steps_per_split = pl.steps_per_split;
+        p.groups = pl.groups; p.form = fcd_form(i8, kfast, pl.mf); p.scale = i8 ? Scale{1.0f, nullptr} : Scale{a.step, a.step_dev};
+        const size_t used = align_up(pl.partial_bytes, 256);
+        scratch += used; left = left > used ? left - used : 0;
+        blocks += pl.groups * pl.n_split;
+        if (pl.n_split > 1) reduce[which] = (int)((M * a.in + 1023) / 1024);
+        const size_t slots = pl.kw > 1 ? (size_t)(FCD_WAVES / 2) * pl.mf * fcd_tn(i8) * 32 * 4 : 0;
+        if (slots > lds) lds = slots;
+    };
+    if (want_dx) fill(0, true, a.W8 != nullptr, a.W8 ? (const void *)a.W8 : (const void *)a.W, a.B, a.out, a.dX);
+    fa.first1 = blocks;
+    if (want_dw) fill(1, false, a.x_dtype == DBP_I8, a.X, a.out, a.B, a.dW);
+    fa.stats = job; fa.gate = a.gate;
+    hipLaunchKernelGGL(fc_direct_kernel, dim3((unsigned)(blocks + job.workgroups())), dim3(64 * FCD_WAVES), lds, s, fa);
+    if (reduce[0] + reduce[1] > 0)
+        hipLaunchKernelGGL(fcd_reduce_kernel, dim3((unsigned)(reduce[0] + reduce[1])), dim3(256), 0, s, fa, reduce[0]);
+    return hipGetLastError();
 }
 
 FcProblem fc_problem(bool a_kfast, const int8_t *A, int64_t lda, const float *B, int64_t ldb, int M, int N, int K,
@@ -533,9 +587,8 @@ size_t linear_scratch_bytes(int64_t B, int64_t in, int64_t out)
     };
     size_t a = part(B, in, out), b = part(out, in, B);
     const size_t generic = align_up(a > b ? a : b, 256);
-    // fast path: both products in one launch, each with its own partials
-    const FcPlan dx = fc_plan(B, in, out), dw = fc_plan(out, in, B);
-    size_t fast = align_up(dx.partial_bytes, 256) + align_up(dw.partial_bytes, 256);
+    // staged kernels: both products in one launch, each with its own partials (the direct kernel makes do with what there is)
+    size_t fast = 0;
     for (int m = 1; m < 4; ++m) {                               // every combination of products a call can ask for
         FcPlan dx2, dw2;
         for (int kt = FC2_KT; kt <= FC2I_KT; kt *= 2) {              // the bf16 kernel's K step and the int8 kernel's
@@ -562,7 +615,7 @@ Conv1x1Plan conv1x1_dw_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t
     const int64_t PQ = H * Wd;
     if (!(R == 1 && S == 1 && pad == 0 && stride == 1)) return pl;
     pl.kt = kt;
-    if (K < FC2_TM / 4 || C < 4 || C % 4 || PQ % 4 || PQ < kt) return pl;           // row tiles at least a quarter full (lowering costs more than the idle rows); 16-byte loads and stores
+    if (K < FC2_TM / 4 || C < 4 || PQ < kt) return pl;              // row tiles at least a quarter full (lowering costs more than the idle rows); whole windows
     if (C * PQ >= ((int64_t)1 << 29) || K * PQ >= ((int64_t)1 << 31) || K * C >= ((int64_t)1 << 30)) return pl;   // 32-bit lane offsets
     pl.spi = (int)((PQ + kt - 1) / kt);
     if (N * pl.spi >= ((int64_t)1 << 25)) return pl;                              // the reduction axis counts windows of kt
@@ -633,9 +686,8 @@ ConvLowerPlan conv_dw_lower_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, in
     lp.ok = false; lp.bytes = 0;
     const int64_t P = (H + 2 * pad - R) / stride + 1, Q = (Wd + 2 * pad - S) / stride + 1;
     lp.NPQ = N * P * Q; lp.CRS = C * R * S;
-    // the product kernels want: reduction rows of the codes a multiple of 4 bytes, columns a multiple of 4 (fp32) or 8
-    // (int8) elements; below that, or when the products are tiny, the generic kernel serves
-    if (lp.NPQ % 4 || lp.NPQ < 64 || lp.CRS % (esz == 4 ? 4 : 8) || K < 16) return lp;
+    // tiny products: the generic kernel serves
+    if (lp.NPQ < 64 || lp.CRS < 8 || K < 16) return lp;
     if (lp.NPQ * lp.CRS >= ((int64_t)1 << 30) || K * lp.NPQ >= ((int64_t)1 << 30) || K * lp.CRS >= ((int64_t)1 << 30)) return lp;
     if ((double)lp.NPQ * lp.CRS * K < 2e8) return lp;              // launch-bound sizes: three more launches do not pay (measured)
     lp.col_bytes = align_up((size_t)(lp.NPQ * lp.CRS) * esz, 256);
@@ -724,184 +776,101 @@ hipError_t launch_linear_mfma(const LinearArgs &a, hipStream_t s)
     RowMajorOut om{a.in};
     StatsJob pending = a.stats_job;
     if (a.plan_only && (!a.codes || a.W8)) { *a.plan_only = 1; return hipSuccess; }
-    if (a.codes && a.W8) {
-        // full 8-bit mode: both products on int8 matrix cores, exact int32 results
-        auto i8_ok = [&](bool a_kfast, const void *Bop, const void *outp, int64_t M) {
-            if (in < 8 || in % 8 || ((uintptr_t)Bop % 8) || ((uintptr_t)outp % 16)) return false;     // 8-byte loads, 16-byte stores
-            if (out % 4 || ((uintptr_t)a.codes % 4)) return false;
-            if (!a_kfast && (M < 16 || M % 4)) return false;
-            return true;
-        };
-        bool dx_fast = a.dX && i8_ok(true, a.W8, a.dX, B) && out >= FC2I_KT && B > FC2_TM / 2;
-        bool dw_fast = a.dW && i8_ok(false, a.X, a.dW, out) && B >= FC2I_KT && out > FC2_TM / 2;
-        if ((int64_t)B * in >= (1ll << 30) || (int64_t)out * in >= (1ll << 30) || (int64_t)B * out >= (1ll << 30)) dx_fast = dw_fast = false;
-        FcPlan pdx, pdw;
-        if (dx_fast || dw_fast) {
-            fc2_plans(B, in, out, dx_fast, dw_fast, pdx, pdw, FC2I_KT);
-            const int64_t items = (dx_fast ? pdx.tiles * pdx.n_split : 0) + (dw_fast ? pdw.tiles * pdw.n_split : 0);
-            if (items > (int64_t)FC2_MAX_ITEMS * 256) dx_fast = dw_fast = false;
-        }
-        int gx = 0;
-        if (dx_fast && dw_fast) gx = fc2_group_plan(B, in, out, pdx, pdw, FC2I_KT);
-        if (dx_fast || dw_fast) {
-            static bool raised = false;
-            if (!raised) {
-                e = hipFuncSetAttribute(reinterpret_cast<const void *>(&fc2_i8_pair_kernel<false>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, FC2I_LDS_BYTES);
-                if (e != hipSuccess) return e;
-                raised = true;
-            }
-            char *scratch = (char *)a.scratch;
-            FcPairArgs pa;
-            if (!dx_fast) { pdx.n_split = 1; pdx.partial_bytes = 0; }
-            if (!dw_fast) { pdw.n_split = 1; pdw.partial_bytes = 0; }
-            pa.prob[0] = fc_problem(true, a.codes, a.out, (const float *)a.W8, a.in, B, in, out, Scale{1.0f, nullptr}, a.dX, pdx, scratch);
-            pa.prob[1] = fc_problem(false, a.codes, a.out, (const float *)a.X, a.in, out, in, B, Scale{1.0f, nullptr}, (float *)a.dW, pdw, scratch);
-            if (!dx_fast) pa.prob[0].n_items = 0;
-            if (!dw_fast) pa.prob[1].n_items = 0;
-            if ((size_t)(scratch - (char *)a.scratch) > a.scratch_bytes) return hipErrorInvalidValue;
-            pa.stats = pending;
-            pending.n = 0; pending.bias_len = 0;
-            pa.gx = gx; pa.gate = a.gate;
-            const int total = pa.prob[0].n_items + pa.prob[1].n_items;
-            const int grid = total < 256 ? total : 256;
-            hipLaunchKernelGGL(fc2_i8_pair_kernel<false>, dim3(grid), dim3(512), FC2I_LDS_BYTES, s, pa);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            const bool r0 = dx_fast && pdx.n_split > 1, r1 = dw_fast && pdw.n_split > 1;
-            if (r0 || r1) {
-                const int tiles0 = r0 ? (int)pdx.tiles : 0, tiles1 = r1 ? (int)pdw.tiles : 0;
-                hipLaunchKernelGGL(fc2_i8_reduce_kernel, dim3(32 * (tiles0 + tiles1)), dim3(256), 0, s, pa, tiles0);
-                e = hipGetLastError();
-                if (e != hipSuccess) return e;
-            }
-        }
-        if (pending.n || pending.bias_len) { e = launch_stats_job(pending, s); if (e != hipSuccess) return e; }
-        if (a.dX && !dx_fast) {
-            MatrixLoader<MODE_I8, true, true>   al{a.codes, a.out, B, out};
-            MatrixLoader<MODE_I8, false, false> bl{a.W8, a.in, in, out};
-            e = run_gemm<MODE_I8>(al, bl, om, B, in, out, k_step<MODE_I8>(), Scale{1.0f, nullptr}, (int32_t *)a.dX, a.scratch, a.scratch_bytes, s);
-            if (e != hipSuccess) return e;
-        }
-        if (a.dW && !dw_fast) {
-            MatrixLoader<MODE_I8, true, false>  al{a.codes, a.out, out, B};
-            MatrixLoader<MODE_I8, false, false> bl{(const int8_t *)a.X, a.in, in, B};
-            e = run_gemm<MODE_I8>(al, bl, om, out, in, B, k_step<MODE_I8>(), Scale{1.0f, nullptr}, (int32_t *)a.dW, a.scratch, a.scratch_bytes, s);
-        }
-        return e;
-    }
     if (a.codes) {
-        // fast path: one launch for every product whose layout allows it
-        const bool dx_fast = a.dX && fc_fast_ok(true, a.codes, a.out, a.W, a.in, B, in, a.dX);
-        const bool dw_fast = a.dW && a.x_dtype == DBP_F32 &&
-                             fc_fast_ok(false, a.codes, a.out, (const float *)a.X, a.in, out, in, (const float *)a.dW);
-        // Large products: the kernel with separate staging and multiplying wavefronts (256x128 tiles, one
-        // workgroup per CU); small ones (less than half such a tile of rows): the 128x128 kernel.
-        const bool big = (!dx_fast || B > FC2_TM / 2) && (!dw_fast || out > FC2_TM / 2) &&
-                         (!dx_fast || out >= 32) && (!dw_fast || (B >= 32 && out >= 16)) &&         // a full window of 32 reduction indices; 16-row runs
-                         (int64_t)B * in < (1ll << 30) && (int64_t)out * in < (1ll << 30) && (int64_t)B * out < (1ll << 30);                // 32-bit lane offsets
-        FcPlan pdx, pdw;
-        bool use_fc2 = (dx_fast || dw_fast) && big;
-        if (use_fc2) {
-            fc2_plans(B, in, out, dx_fast, dw_fast, pdx, pdw);
-            const int64_t items = (dx_fast ? pdx.tiles * pdx.n_split : 0) + (dw_fast ? pdw.tiles * pdw.n_split : 0);
-            if (items > (int64_t)FC2_MAX_ITEMS * 256) use_fc2 = false;     // the per-workgroup item table is fixed
-        }
-        int gx = 0;
-        if (use_fc2 && dx_fast && dw_fast) gx = fc2_group_plan(B, in, out, pdx, pdw);
+        const bool dx_i8 = a.W8 != nullptr, dw_i8 = a.x_dtype == DBP_I8;
+        const bool small_index = (int64_t)B * in < (1ll << 30) && (int64_t)out * in < (1ll << 30) && (int64_t)B * out < (1ll << 30);   // 32-bit lane offsets
+        // What the staged kernels take: more than half a tile of rows and a full window of reduction indices ...
+        auto staged_ok = [&](bool i8, int64_t M, int64_t K) { return M > FC2_TM / 2 && K >= (i8 ? FC2I_KT : FC2_KT) && in >= (i8 ? 8 : 4) && small_index; };
+        bool dx_staged = a.dX && staged_ok(dx_i8, B, out), dw_staged = a.dW && staged_ok(dw_i8, out, B);
+        // ... and what they are the faster ones for.  Whole calls, direct against staged (us): 256x1024x1024 19 / 24, 128x2048x2048 32 / 39,
+        // 512x512x1024 equal, 400x304x3000 43 / 29, 256x1024x4096 40 / 31: the line lies near 3e8 multiply-adds a product, and a layer
+        // with one product too short for a tile goes to the direct kernel whole.  Two planes exist on the staged kernel only.
+        const bool large = (double)B * in * out > 3.0e8 || (a.two_planes && !dx_i8);
+        if (!large || (a.dX && !dx_staged && !(dw_i8 && !dx_i8)) || (a.dW && !dw_staged && !(dw_i8 && !dx_i8))) dx_staged = dw_staged = false;
         if (a.plan_only) {
-            // gated: both requested products on one of the pair kernels (the generic kernel takes no gate)
-            const bool int8_dw = a.dW && a.x_dtype != DBP_F32;
-            if ((a.dX && !dx_fast) || (a.dW && !dw_fast) || int8_dw) *a.plan_only = 1;
+            // gated: both requested products on kernels that take a gate, fp32 operands
+            if ((a.dX && !dx_staged && !fcd_ok(true, B, in, out, out, false)) || (a.dW && (dw_i8 || (!dw_staged && !fcd_ok(false, out, in, B, out, false))))) *a.plan_only = 1;
             return hipSuccess;
         }
-        if (use_fc2) {
+        // staged products of one kind share a launch
+        for (int i8 = 0; i8 < 2; ++i8) {
+            const bool dx_here = dx_staged && dx_i8 == (i8 != 0), dw_here = dw_staged && dw_i8 == (i8 != 0);
+            if (!dx_here && !dw_here) continue;
+            const int kt = i8 ? FC2I_KT : FC2_KT;
+            FcPlan pdx, pdw;
+            fc2_plans(B, in, out, dx_here, dw_here, pdx, pdw, kt);
+            if ((dx_here ? pdx.tiles * pdx.n_split : 0) + (dw_here ? pdw.tiles * pdw.n_split : 0) > (int64_t)FC2_MAX_ITEMS * 256) {
+                if (dx_here) dx_staged = false;                    // the per-workgroup item table is fixed
+                if (dw_here) dw_staged = false;
+                continue;
+            }
+            const int gx = dx_here && dw_here ? fc2_group_plan(B, in, out, pdx, pdw, kt) : 0;
             static bool raised = false;
             if (!raised) {
-                e = hipFuncSetAttribute(reinterpret_cast<const void *>(&fc2_pair_kernel<false, 3>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, FC2_LDS_BYTES);
-                if (e != hipSuccess) return e;
-                e = hipFuncSetAttribute(reinterpret_cast<const void *>(&fc2_pair_kernel<false, 2>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, FC2_LDS_BYTES);
-                if (e != hipSuccess) return e;
+                const void *fns[3] = {reinterpret_cast<const void *>(&fc2_pair_kernel<false, 3>), reinterpret_cast<const void *>(&fc2_pair_kernel<false, 2>),
+                                      reinterpret_cast<const void *>(&fc2_i8_pair_kernel<false>)};
+                for (int f = 0; f < 3; ++f) {
+                    e = hipFuncSetAttribute(fns[f], hipFuncAttributeMaxDynamicSharedMemorySize, f == 2 ? FC2I_LDS_BYTES : FC2_LDS_BYTES);
+                    if (e != hipSuccess) return e;
+                }
                 raised = true;
             }
             char *scratch = (char *)a.scratch;
+            const Scale scale = i8 ? Scale{1.0f, nullptr} : Scale{a.step, a.step_dev};
             FcPairArgs pa;
-            if (!dx_fast) { pdx.n_split = 1; pdx.partial_bytes = 0; }
-            if (!dw_fast) { pdw.n_split = 1; pdw.partial_bytes = 0; }
-            pa.prob[0] = fc_problem(true, a.codes, a.out, a.W, a.in, B, in, out, Scale{a.step, a.step_dev}, a.dX, pdx, scratch);
-            pa.prob[1] = fc_problem(false, a.codes, a.out, (const float *)a.X, a.in, out, in, B, Scale{a.step, a.step_dev}, (float *)a.dW, pdw, scratch);
-            if (!dx_fast) pa.prob[0].n_items = 0;
-            if (!dw_fast) pa.prob[1].n_items = 0;
+            if (!dx_here) { pdx.n_split = 1; pdx.partial_bytes = 0; }
+            if (!dw_here) { pdw.n_split = 1; pdw.partial_bytes = 0; }
+            pa.prob[0] = fc_problem(true, a.codes, a.out, dx_i8 ? (const float *)a.W8 : a.W, a.in, B, in, out, scale, a.dX, pdx, scratch);
+            pa.prob[1] = fc_problem(false, a.codes, a.out, (const float *)a.X, a.in, out, in, B, scale, (float *)a.dW, pdw, scratch);
+            if (!dx_here) pa.prob[0].n_items = 0;
+            if (!dw_here) pa.prob[1].n_items = 0;
             if ((size_t)(scratch - (char *)a.scratch) > a.scratch_bytes) return hipErrorInvalidValue;
-            pa.stats = pending;                            // finished by a stager wavefront of the last workgroup
-            pending.n = 0; pending.bias_len = 0;
+            pa.stats = pending;                                // finished by a stager wavefront of the last workgroup
+            pending = StatsJob{};
             pa.gx = gx; pa.gate = a.gate;
             const int total = pa.prob[0].n_items + pa.prob[1].n_items;
-            const int grid = total < 256 ? total : 256;    // persistent: one workgroup per CU (256 whenever gx > 0)
-            if (a.two_planes) hipLaunchKernelGGL((fc2_pair_kernel<false, 2>), dim3(grid), dim3(512), FC2_LDS_BYTES, s, pa);
-            else              hipLaunchKernelGGL((fc2_pair_kernel<false, 3>), dim3(grid), dim3(512), FC2_LDS_BYTES, s, pa);
+            const int grid = total < 256 ? total : 256;        // persistent: one workgroup per CU (256 whenever gx > 0)
+            if (i8)                hipLaunchKernelGGL(fc2_i8_pair_kernel<false>, dim3(grid), dim3(512), FC2I_LDS_BYTES, s, pa);
+            else if (a.two_planes) hipLaunchKernelGGL((fc2_pair_kernel<false, 2>), dim3(grid), dim3(512), FC2_LDS_BYTES, s, pa);
+            else                   hipLaunchKernelGGL((fc2_pair_kernel<false, 3>), dim3(grid), dim3(512), FC2_LDS_BYTES, s, pa);
+            const int tiles0 = dx_here && pdx.n_split > 1 ? (int)pdx.tiles : 0, tiles1 = dw_here && pdw.n_split > 1 ? (int)pdw.tiles : 0;
+            if (tiles0 + tiles1 > 0) {
+                if (i8) hipLaunchKernelGGL(fc2_i8_reduce_kernel, dim3(32 * (tiles0 + tiles1)), dim3(256), 0, s, pa, tiles0);
+                else    hipLaunchKernelGGL(fc2_reduce_kernel, dim3(32 * (tiles0 + tiles1)), dim3(256), 0, s, pa, tiles0);
+            }
             e = hipGetLastError();
             if (e != hipSuccess) return e;
-            const bool r0 = dx_fast && pdx.n_split > 1, r1 = dw_fast && pdw.n_split > 1;
-            if (r0 || r1) {
-                const int tiles0 = r0 ? (int)pdx.tiles : 0, tiles1 = r1 ? (int)pdw.tiles : 0;
-                hipLaunchKernelGGL(fc2_reduce_kernel, dim3(32 * (tiles0 + tiles1)), dim3(256), 0, s, pa, tiles0);
-                e = hipGetLastError();
-                if (e != hipSuccess) return e;
-            }
-        } else if (dx_fast || dw_fast) {
-            char *scratch = (char *)a.scratch;
-            FcPairArgs pa;
-            const FcPlan none = {0, 0, 1, FC_KT, 0, 0};
-            const FcPlan pdx = dx_fast ? fc_plan(B, in, out) : none, pdw = dw_fast ? fc_plan(out, in, B) : none;
-            pa.prob[0] = fc_problem(true, a.codes, a.out, a.W, a.in, B, in, out, Scale{a.step, a.step_dev}, a.dX, pdx, scratch);
-            pa.prob[1] = fc_problem(false, a.codes, a.out, (const float *)a.X, a.in, out, in, B, Scale{a.step, a.step_dev}, (float *)a.dW, pdw, scratch);
-            if (!dx_fast) pa.prob[0].n_items = 0;
-            if (!dw_fast) pa.prob[1].n_items = 0;
-            if (pending.bias_len) {                        // this kernel folds the statistics only
-                StatsJob bias = pending;
-                bias.n = 0;
-                e = launch_stats_job(bias, s);
-                if (e != hipSuccess) return e;
-                pending.bias_len = 0;
-            }
-            pa.stats = pending;                            // summed by the last workgroup of the launch
-            pending.n = 0;
-            pa.gate = a.gate;
-            if ((size_t)(scratch - (char *)a.scratch) > a.scratch_bytes) return hipErrorInvalidValue;
-            const int total = pa.prob[0].n_items + pa.prob[1].n_items;
-            // odd grid: a persistent workgroup then alternates between the two products
-            int grid = total < 767 ? total : 767;          // 3 resident workgroups on each of 256 CUs
-            hipLaunchKernelGGL(fc_pair_kernel, dim3(grid), dim3(256), 0, s, pa);
-            e = hipGetLastError();
+        }
+        // the rest in one launch of the direct kernel, or (rows shorter than its vectors) product by product on the generic one
+        const bool dx_direct = a.dX && !dx_staged && fcd_ok(true, B, in, out, out, dx_i8), dw_direct = a.dW && !dw_staged && fcd_ok(false, out, in, B, out, dw_i8);
+        if (dx_direct || dw_direct) {
+            e = launch_fc_direct(a, dx_direct, dw_direct, pending, s);
             if (e != hipSuccess) return e;
-            // split-K: one reduction launch for both products (a problem without splits gets no workgroups)
-            const bool r0 = dx_fast && pdx.n_split > 1, r1 = dw_fast && pdw.n_split > 1;
-            if (r0 || r1) {
-                FcPairArgs ra = pa;
-                int tiles0 = r0 ? (int)pdx.tiles : 0, tiles1 = r1 ? (int)pdw.tiles : 0;
-                hipLaunchKernelGGL(fc_reduce_kernel, dim3(32 * (tiles0 + tiles1)), dim3(256), 0, s, ra, tiles0);
-                e = hipGetLastError();
-                if (e != hipSuccess) return e;
-            }
+            pending = StatsJob{};
         }
         if (pending.n || pending.bias_len) { e = launch_stats_job(pending, s); if (e != hipSuccess) return e; }
-        if (a.dX && !dx_fast) {
-            MatrixLoader<MODE_BF16, true, true>   al{a.codes, a.out, B, out};
-            MatrixLoader<MODE_BF16, false, false> bl{a.W, a.in, in, out};
-            e = run_gemm<MODE_BF16>(al, bl, om, B, in, out, k_step<MODE_BF16>(), Scale{a.step, a.step_dev}, a.dX, a.scratch, a.scratch_bytes, s);
+        if (a.dX && !dx_staged && !dx_direct) {
+            if (dx_i8) {
+                MatrixLoader<MODE_I8, true, true>   al{a.codes, a.out, B, out};
+                MatrixLoader<MODE_I8, false, false> bl{a.W8, a.in, in, out};
+                e = run_gemm<MODE_I8>(al, bl, om, B, in, out, k_step<MODE_I8>(), Scale{1.0f, nullptr}, (int32_t *)a.dX, a.scratch, a.scratch_bytes, s);
+            } else {
+                MatrixLoader<MODE_BF16, true, true>   al{a.codes, a.out, B, out};
+                MatrixLoader<MODE_BF16, false, false> bl{a.W, a.in, in, out};
+                e = run_gemm<MODE_BF16>(al, bl, om, B, in, out, k_step<MODE_BF16>(), Scale{a.step, a.step_dev}, a.dX, a.scratch, a.scratch_bytes, s);
+            }
             if (e != hipSuccess) return e;
         }
-        if (a.dW && a.x_dtype == DBP_F32 && !dw_fast) {
-            MatrixLoader<MODE_BF16, true, false>  al{a.codes, a.out, out, B};
-            MatrixLoader<MODE_BF16, false, false> bl{(const float *)a.X, a.in, in, B};
-            e = run_gemm<MODE_BF16>(al, bl, om, out, in, B, k_step<MODE_BF16>(), Scale{a.step, a.step_dev}, (float *)a.dW, a.scratch, a.scratch_bytes, s);
-        } else if (a.dW && a.x_dtype != DBP_F32) {
-            MatrixLoader<MODE_I8, true, false>  al{a.codes, a.out, out, B};
-            MatrixLoader<MODE_I8, false, false> bl{(const int8_t *)a.X, a.in, in, B};
-            e = run_gemm<MODE_I8>(al, bl, om, out, in, B, k_step<MODE_I8>(), Scale{1.0f, nullptr}, (int32_t *)a.dW, a.scratch, a.scratch_bytes, s);
+        if (a.dW && !dw_staged && !dw_direct) {
+            if (dw_i8) {
+                MatrixLoader<MODE_I8, true, false>  al{a.codes, a.out, out, B};
+                MatrixLoader<MODE_I8, false, false> bl{(const int8_t *)a.X, a.in, in, B};
+                e = run_gemm<MODE_I8>(al, bl, om, out, in, B, k_step<MODE_I8>(), Scale{1.0f, nullptr}, (int32_t *)a.dW, a.scratch, a.scratch_bytes, s);
+            } else {
+                MatrixLoader<MODE_BF16, true, false>  al{a.codes, a.out, out, B};
+                MatrixLoader<MODE_BF16, false, false> bl{(const float *)a.X, a.in, in, B};
+                e = run_gemm<MODE_BF16>(al, bl, om, out, in, B, k_step<MODE_BF16>(), Scale{a.step, a.step_dev}, (float *)a.dW, a.scratch, a.scratch_bytes, s);
+            }
         }
         return e;
     }
@@ -1136,8 +1105,7 @@ static hipError_t conv_dw(const ConvArgs &a, const void *grad, Scale scale, hipS
     if constexpr (MODE != MODE_F32) {
         constexpr bool I8 = MODE == MODE_I8;
         const Conv1x1Plan p1 = conv1x1_dw_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, a.stride, I8 ? FC2I_KT : FC2_KT);
-        if (p1.ok && rb + p1.partial_bytes <= a.scratch_bytes && (uintptr_t)grad % 4 == 0 && (uintptr_t)a.X % (I8 ? 4 : 16) == 0 &&
-            (uintptr_t)a.dW % 16 == 0)
+        if (p1.ok && rb + p1.partial_bytes <= a.scratch_bytes)
             return a.plan_only ? hipSuccess : launch_conv1x1_dw<I8>(a, p1, (const int8_t *)grad, scale, (char *)a.scratch + rb, s);
     }
     if (a.plan_only) { *a.plan_only = 1; return hipSuccess; }         // the lowered and the generic forms are not gated
@@ -1147,7 +1115,7 @@ static hipError_t conv_dw(const ConvArgs &a, const void *grad, Scale scale, hipS
         constexpr int ESZ = MODE == MODE_I8 ? 1 : 4;
         const ConvLowerPlan lp = conv_dw_lower_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, a.stride, ESZ);
         if (lp.ok && (MODE == MODE_BF16 || lp.vec4) &&      // int8 entries written one byte at a time: measured slower than generic
-            rb + lp.bytes <= a.scratch_bytes && (uintptr_t)grad % 4 == 0 && (uintptr_t)a.X % 4 == 0 && (uintptr_t)a.dW % 16 == 0) {
+            rb + lp.bytes <= a.scratch_bytes && (uintptr_t)grad % 4 == 0 && (uintptr_t)a.X % 4 == 0) {
             int8_t *ck = (int8_t *)a.scratch + rb;
             char *col = (char *)ck + lp.codes_bytes;
             const int PQ = lp.im.P * lp.im.Q;

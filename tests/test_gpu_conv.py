@@ -167,6 +167,12 @@ ONE_BY_ONE = [  # N, C, H, Wd, K: 1x1, stride 1, no padding, more than 128 outpu
 ]
 
 
+ONE_BY_ONE += [             # pixel and channel counts that no vector divides
+    (4, 37, 7, 9, 70),
+    (3, 70, 13, 13, 129),
+]
+
+
 @pytest.mark.parametrize("case", ONE_BY_ONE)
 def test_conv_1x1_dw_batched_fc_kernel(case):
     from gpu_util import run_conv
@@ -185,6 +191,9 @@ ONE_BY_ONE_I8 = [  # the same with int8 activations: windows of 64 pixels
     (6, 96, 12, 12, 64),        # 64 output channels: a quarter of the row tile
     (4, 200, 8, 16, 100),       # 100 output channels
 ]
+
+
+ONE_BY_ONE_I8 += [(4, 37, 9, 9, 70), (3, 70, 13, 13, 129)]
 
 
 @pytest.mark.parametrize("case", ONE_BY_ONE_I8)

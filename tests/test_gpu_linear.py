@@ -96,6 +96,36 @@ def test_fc_int8_mode_is_bit_exact(B, in_, out, path):
     check_products(res["dX"], rX, aX, "int8-mode dX")
 
 
+# the direct kernel at its edges: reductions around one window of 16 (fp32) or 32 (int8) and around multiples of what the
+# wavefronts of a tile share, rows and columns around a fragment (32), a tile (64) and the smallest its loads take
+@pytest.mark.parametrize("B,in_,out", [(2, 2, 7), (3, 5, 8), (31, 33, 15), (33, 63, 16), (32, 64, 17), (65, 65, 31), (1, 130, 33), (127, 66, 2), (40, 3, 300),
+                                       (2, 1000, 130), (130, 7, 1027), (16, 129, 5), (64, 4100, 70), (20, 131, 3001)])
+def test_fc_direct_kernel_edges(B, in_, out):
+    import paper_2004_04729_amd as dbp
+    from gpu_util import run_linear
+    from oracle import oracle as O
+    p = _problem(B, in_, out)
+    _check_fp32(p, run_linear(p, path=dbp.PATH_MFMA))
+    _check_fp32(p, run_linear(p, path=dbp.PATH_MFMA, want_dw=False))
+    X8 = workloads.int8_relu_uniform(np.random.default_rng(B), (B, in_))
+    res = run_linear(p, path=dbp.PATH_MFMA, x_i8=X8)
+    assert np.array_equal(res["dW"], O.linear_dw_i8(O.nsd(p.delta, p.step, p.seed)[0], X8))
+
+
+# large layers with rows, columns and reductions that no vector divides (above 3e8 multiply-adds: the staged kernels)
+@pytest.mark.parametrize("B,in_,out", [(259, 1101, 1235), (1033, 598, 517), (131, 4099, 641)])
+def test_fc_staged_kernels_take_ragged_layers(B, in_, out):
+    import paper_2004_04729_amd as dbp
+    from gpu_util import run_linear
+    from oracle import oracle as O
+    p = _problem(B, in_, out)
+    _check_fp32(p, run_linear(p, path=dbp.PATH_MFMA))
+    _check_fp32(p, run_linear(p, path=dbp.PATH_MFMA, want_dx=False))
+    X8 = workloads.int8_relu_uniform(np.random.default_rng(B), (B, in_))
+    res = run_linear(p, path=dbp.PATH_MFMA, x_i8=X8)
+    assert np.array_equal(res["dW"], O.linear_dw_i8(O.nsd(p.delta, p.step, p.seed)[0], X8))
+
+
 def test_fc_results_are_deterministic_and_paths_agree_on_codes():
     import paper_2004_04729_amd as dbp
     from gpu_util import run_linear

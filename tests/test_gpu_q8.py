@@ -94,6 +94,13 @@ def test_fc_q8_large_layer_kernel(B, in_, out):
     _fc(B, in_, out, seed=B + in_ + out, c=8.0, want_dx=False)
 
 
+# ragged layers: the direct kernel around one window of 32, the staged one (above 3e8 multiply-adds) with odd rows and columns
+@pytest.mark.parametrize("B,in_,out", [(3, 4, 31), (33, 5, 32), (65, 127, 33), (130, 131, 7), (259, 1101, 1235), (1033, 598, 517)])
+def test_fc_q8_ragged_layers(B, in_, out):
+    _fc(B, in_, out, seed=B + in_ + out)
+    _fc(B, in_, out, seed=B + in_ + out, want_dx=False)
+
+
 def test_fc_q8_single_products_and_dense_codes():
     _fc(70, 130, 90, seed=3, want_dw=False)
     _fc(70, 130, 90, seed=3, want_dx=False)
