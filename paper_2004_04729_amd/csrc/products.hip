@@ -9,7 +9,7 @@
 #include "conv_dx_kernel.h"
 #include "conv_dw_kernel.h"
 #include "conv_dw_i8_kernel.h"
-#include "conv_lower.h"
+#include "conv_dwt_kernel.h"
 
 namespace dbp {
 
@@ -374,6 +374,152 @@ hipError_t launch_conv_dw_i8(const ConvDwI8Plan &pl, hipStream_t s)
     return hipGetLastError();
 }
 
+// Geometry of the general dW kernel (conv_dwt_kernel.h), or ok == false when it does not apply (planes below one run of codes,
+// more than 62 taps, frames that do not fit).
+struct ConvDwtPlan { bool ok; int G, waves, grid, reduce_grid, tch, tap_chunks, zg; ConvDwtArgs args; size_t lds_bytes, partial_bytes, reduce_lds; float us; };
+
+ConvDwtPlan conv_dwt_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t pad, int64_t stride, bool i8, int planes)
+{
+    ConvDwtPlan pl;
+    pl.ok = false; pl.partial_bytes = 0;
+    const int64_t P = (H + 2 * pad - R) / stride + 1, Q = (Wd + 2 * pad - S) / stride + 1, T = R * S;
+    const int RUN = DWT_RUN(i8), pitch = (i8 ? 32 : 64 * planes) + 8;
+    if (T > 4096 || C * H * Wd >= ((int64_t)1 << 29) || K * P * Q >= ((int64_t)1 << 29) || K * C * T >= ((int64_t)1 << 30)) return pl;
+    ConvDwtArgs &k = pl.args;
+    k.N = (int)N; k.C = (int)C; k.H = (int)H; k.Wd = (int)Wd; k.K = (int)K; k.S = (int)S; k.T = (int)T; k.st = (int)stride; k.pad = (int)pad;
+    k.P = (int)P; k.Q = (int)Q; k.Ct = k.C; k.Kt = k.K; k.tiny = P * Q < RUN ? 1 : 0;
+    // One tap: a wavefront takes several blocks of input channels.  Else taps per wavefront: 3 (up to 12 wavefronts) or 4 (8), whichever
+    // keeps more of the matrix instructions on real taps and the wavefronts even over the four SIMDs.
+    double best = -1.0;
+    int m = 8;
+    const bool one = T == 1;
+    if (one) { pl.G = C > 64 ? 4 : 2; k.tap_blocks = 1; k.tg = 1; }
+    for (int G = 3; G <= 4 && !one; ++G) {
+        const int most = G == 3 ? 12 : 8, groups = (int)((T + G - 1) / G), blocks = (groups + most - 1) / most, tg = (groups + blocks - 1) / blocks;
+        int mm = 1;
+        while (2 * mm * tg <= most) mm *= 2;
+        const int waves = mm * tg;
+        const double eff = (double)T / ((double)G * tg * blocks) * waves / ((waves + 3) / 4 * 4);
+        if (eff > best) { best = eff; pl.G = G; k.tap_blocks = blocks; k.tg = tg; m = mm; }
+    }
+    const int MF = pl.G == 2 ? 4 : 2, gc = one ? pl.G : 1;                   // gc: blocks of input channels of a wavefront
+    const int items = one ? 6 : 4, citems = (one ? 16 : pl.G == 3 ? 8 : 12) / (RUN / 4);
+    pl.waves = m * k.tg;
+    // The rest of the wavefronts along output channels (an activation is then staged for more of them), input channels, or steps
+    // (fewer partial sums); units: whole images (several small ones), bands of rows, or bands of rows and columns.  By modelled
+    // time: a step keeps the four SIMDs busy for its matrix instructions, a chunk of staged pixels (halos included) costs about
+    // 600 cycles, a unit 1500 more; partial sums are written and read at about 4.5 TB/s.
+    best = -1.0;
+    int64_t best_units = 0;
+    const double t_step = (double)pl.waves / 4.0 * MF * pl.G * 32.0 * (i8 ? 1 : planes);
+    const int widths[8] = {(int)Q, 4, 8, 16, 32, 48, 64, 96};
+    for (int kg = 1; kg <= m; kg *= 2)
+        for (int cb = 1; kg * cb <= m; cb *= 2) {
+            const int kt = 32 * MF * kg, ps = m / (kg * cb);
+            const int blocks = cb * gc;
+            if ((kg > 1 && kt / 2 >= K) || (cb > 1 && 16 * blocks >= C)) continue;         // half of the tile would be empty
+            int max_chunks = items * pl.waves / (8 * blocks);
+            const int fit = (int)((DWT_MAX_LDS - 4096) / ((size_t)64 * (2 * pitch * blocks)));
+            if (max_chunks > fit) max_chunks = fit;
+            const int max_px = 64 * max_chunks;
+            const int64_t tk = (K + kt - 1) / kt, tc = (C + 32 * blocks - 1) / (32 * blocks), tiles = tk * tc * k.tap_blocks;
+            for (int wi = 0; wi < 8; ++wi) {
+                const int qb = widths[wi];
+                if (wi > 0 && (qb >= Q || k.tiny)) break;
+                const int fw = (int)((qb - 1) * stride + S);
+                if ((int)R * fw > max_px) continue;
+                const int cbands = (int)((Q + qb - 1) / qb);
+                const bool flat = wi == 0;
+                int pb = (int)((max_px / fw - R) / stride + 1), bands = 0, ni = 1, frame = 0, runs_row = 0, runs_img = 0, steps = 0, chunks = 0;
+                size_t lds = 0;
+                if (pb > P) pb = (int)P;
+                bool fits = false;
+                for (; pb >= 1 && !fits; --pb) {                             // the tallest band (then the most images) whose codes fit beside it
+                    bands = (int)((P + pb - 1) / pb);
+                    pb = (int)((P + bands - 1) / bands);
+                    frame = (int)((pb - 1) * stride + R) * fw;
+                    ni = 1;
+                    if (flat && bands == 1) {
+                        ni = max_px / frame;
+                        const int64_t keep = N * tiles / 256;             // no more images a unit than leave every CU a unit
+                        if (ni > keep) ni = keep < 1 ? 1 : (int)keep;
+                        if (ni > 127) ni = 127;
+                    }
+                    runs_row = flat ? (pb * qb + RUN - 1) / RUN : (qb + RUN - 1) / RUN; runs_img = flat ? runs_row : runs_row * pb;
+                    for (; ni >= 1 && !fits; --ni) {
+                        steps = (runs_img * ni + 1) / 2; chunks = (frame * ni + 63) / 64;
+                        lds = 2 * ((size_t)chunks * 64 * pitch * blocks + (size_t)kt * (2 * steps + 1) * RUN) + (size_t)steps * RUN * 8;
+                        fits = lds <= (size_t)DWT_MAX_LDS && chunks <= pl.waves && pl.waves / chunks * items >= 8 * blocks && 2 * steps <= 64 * pl.waves && kt <= citems * (64 * pl.waves / (2 * steps));
+                        if (fits) break;
+                    }
+                    if (fits) break;
+                }
+                if (!fits) continue;
+                const int64_t units = (N + ni - 1) / ni * bands * cbands;
+                int64_t want = tiles >= 256 ? 1 : 256 / tiles;             // one workgroup per CU
+                if (want > units) want = units;
+                const int64_t per = (units + want - 1) / want, ns = (units + per - 1) / per;
+                const double rounds = (double)((tiles * ns + 255) / 256);
+                double us = rounds * (double)per * ((double)((steps + ps - 1) / ps) * t_step + chunks * blocks * 600.0 + 1500.0) / 2000.0;
+                if (ns > 1) us += 4.0 + (double)tiles * ns * (pl.waves / ps) * MF * pl.G * 4096.0 * 2.0 / 4.5e6;
+                if (best >= 0.0 && us >= best) continue;
+                best = us; best_units = units;
+                k.kg = kg; k.cb = cb; k.ps = ps; k.tiles_k = (int)tk; k.tiles_c = (int)tc;
+                k.PB = pb; k.bands = bands; k.QB = qb; k.cbands = cbands; k.NI = ni; k.frame_w = fw; k.frame = frame; k.chunks = chunks;
+                k.runs_row = runs_row; k.runs_img = runs_img; k.steps = steps; k.flat = flat ? 1 : 0;
+                k.blocks = blocks; k.x_bytes = chunks * 64 * pitch * blocks; k.buf_bytes = k.x_bytes + kt * (2 * steps + 1) * RUN;
+                k.code_step = 64 * pl.waves / (2 * steps); pl.lds_bytes = lds;
+                k.units_per_split = (int)per; k.n_split = (int)ns;
+            }
+        }
+    if (best < 0.0) return pl;
+    pl.us = (float)best;
+    const int64_t tiles = (int64_t)k.tiles_k * k.tiles_c * k.tap_blocks;
+    if (best_units >= ((int64_t)1 << 30) || tiles > 65535 || (int64_t)k.NI * k.K * P * Q >= ((int64_t)1 << 30) || (int64_t)k.NI * C * H * Wd >= ((int64_t)1 << 29)) return pl;
+    k.units = (int)best_units;
+    const size_t wave_bytes = (size_t)MF * pl.G * 4096;
+    const int tile_waves = k.tg * k.cb * k.kg;
+    pl.partial_bytes = k.n_split > 1 ? (size_t)tiles * k.n_split * tile_waves * wave_bytes : 0;
+    const size_t fold = (size_t)(k.ps / 2) * tile_waves * wave_bytes;
+    if (fold > pl.lds_bytes) pl.lds_bytes = fold;
+    if (pl.lds_bytes > (size_t)DWT_MAX_LDS) return pl;
+    pl.grid = (int)(tiles * k.n_split);
+    // taps per workgroup of the reduction: all of them, fewer while the chip has room (never below 4 where there are as many)
+    const int red = k.tiles_k * k.tiles_c * k.kg * k.blocks * MF * 4;
+    pl.tch = (int)(T < 60 ? T : 60);                                        // (64 of them fill the default LDS of a workgroup)
+    while (pl.tch > 4 && red * ((T + pl.tch - 1) / pl.tch) < 256) pl.tch = (pl.tch + 1) / 2;
+    pl.tap_chunks = (int)((T + pl.tch - 1) / pl.tch);
+    pl.reduce_grid = red * pl.tap_chunks;
+    pl.zg = 16 / pl.tch < (k.n_split + 3) / 4 ? 16 / pl.tch : (k.n_split + 3) / 4;      // groups of threads: at least four splits each
+    if (pl.zg < 1) pl.zg = 1;
+    pl.reduce_lds = (size_t)pl.zg * 64 * pl.tch * 16;
+    pl.ok = true;
+    return pl;
+}
+
+template <bool I8, int PL, int G, bool ONE>
+hipError_t launch_conv_dwt_as(const ConvDwtPlan &pl, hipStream_t s)
+{
+    static bool raised = false;                                      // more than 64 KiB of dynamic LDS: allowed per kernel, once
+    if (!raised) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_dwt_kernel<I8, PL, G, ONE>), hipFuncAttributeMaxDynamicSharedMemorySize, DWT_MAX_LDS);
+        if (e != hipSuccess) return e;
+        raised = true;
+    }
+    hipLaunchKernelGGL((conv_dwt_kernel<I8, PL, G, ONE>), dim3(pl.grid), dim3(64 * pl.waves), pl.lds_bytes, s, pl.args);
+    if (pl.args.n_split > 1)
+        hipLaunchKernelGGL((conv_dwt_reduce_kernel<G, ONE>), dim3(pl.reduce_grid), dim3(64 * pl.tch * pl.zg < 1024 ? 64 * pl.tch * pl.zg : 1024), pl.reduce_lds, s, pl.args, I8 ? 1 : 0,
+                           pl.tch, pl.tap_chunks, pl.zg);
+    return hipGetLastError();
+}
+
+template <bool I8, int PL>
+hipError_t launch_conv_dwt(const ConvDwtPlan &pl, hipStream_t s)
+{
+    if (pl.args.T == 1) return pl.G == 2 ? launch_conv_dwt_as<I8, PL, 2, true>(pl, s) : launch_conv_dwt_as<I8, PL, 4, true>(pl, s);
+    return pl.G == 3 ? launch_conv_dwt_as<I8, PL, 3, false>(pl, s) : launch_conv_dwt_as<I8, PL, 4, false>(pl, s);
+}
+
 template <int MODE, int R, int S, int PAD, int MB, int ROWS>
 hipError_t launch_conv_dw_fast_as(const ConvDwPlan &pl, hipStream_t s)
 {
@@ -605,7 +751,7 @@ size_t linear_scratch_bytes(int64_t B, int64_t in, int64_t out)
 // dW of a 1x1, stride-1, unpadded convolution: dW[k][c] = sum_n sum_p code[n][k][p] X[n][c][p] is the batched,
 // reduction-contiguous form of the FC kernels (fc2_kernel.h / fc2_i8_kernel.h, NT) straight on the NCHW tensors: no copy
 // pass.  kt = reduction indices per K step of the kernel (32 with fp32 activations, 64 with int8 activations).
-struct Conv1x1Plan { bool ok; int n_split, imgs_per_split, spi, tiles_m, tiles_n, kt; size_t partial_bytes; };
+struct Conv1x1Plan { bool ok; int n_split, imgs_per_split, spi, tiles_m, tiles_n, kt; size_t partial_bytes; float us; };
 
 Conv1x1Plan conv1x1_dw_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t pad, int64_t stride,
                             int kt = FC2_KT)
@@ -628,6 +774,9 @@ Conv1x1Plan conv1x1_dw_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t
     pl.n_split = (int)((N + pl.imgs_per_split - 1) / pl.imgs_per_split);
     if (tiles * pl.n_split > (int64_t)FC2_MAX_ITEMS * 256) return pl;
     pl.partial_bytes = pl.n_split > 1 ? (size_t)tiles * pl.n_split * FC2_TM * FC2_TN * sizeof(float) : 0;
+    // a step takes 0.8 us (int8: 0.5), more when all CUs stream from HBM; 12 to 14 us for the ends and the partial sums
+    const float wgs = tiles * pl.n_split < 256 ? (float)(tiles * pl.n_split) / 256.0f : 1.0f, rounds = (float)((tiles * pl.n_split + 255) / 256);
+    pl.us = (kt == FC2_KT ? 14.0f : 12.0f) + rounds * pl.imgs_per_split * pl.spi * (kt == FC2_KT ? 0.8f + 0.5f * wgs : 0.5f + 0.6f * wgs);
     pl.ok = true;
     return pl;
 }
@@ -676,59 +825,6 @@ hipError_t launch_conv1x1_dw(const ConvArgs &a, const Conv1x1Plan &pl, const int
     return e;
 }
 
-// dW lowered to the fully connected kernels (conv_lower.h): taken for shapes the convolution dW kernels decline when the
-// column matrix is small enough to sit in the workspace.  esz = bytes per activation (4, or 1 in the 8-bit modes).
-struct ConvLowerPlan { bool ok, vec4; int64_t NPQ, CRS; size_t codes_bytes, col_bytes, fc_bytes, bytes; Im2colArgs im; size_t lds_bytes; };
-
-ConvLowerPlan conv_dw_lower_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t pad, int64_t stride, int esz)
-{
-    ConvLowerPlan lp;
-    lp.ok = false; lp.bytes = 0;
-    const int64_t P = (H + 2 * pad - R) / stride + 1, Q = (Wd + 2 * pad - S) / stride + 1;
-    lp.NPQ = N * P * Q; lp.CRS = C * R * S;
-    // tiny products: the generic kernel serves
-    if (lp.NPQ < 64 || lp.CRS < 8 || K < 16) return lp;
-    if (lp.NPQ * lp.CRS >= ((int64_t)1 << 30) || K * lp.NPQ >= ((int64_t)1 << 30) || K * lp.CRS >= ((int64_t)1 << 30)) return lp;
-    if ((double)lp.NPQ * lp.CRS * K < 2e8) return lp;              // launch-bound sizes: three more launches do not pay (measured)
-    lp.col_bytes = align_up((size_t)(lp.NPQ * lp.CRS) * esz, 256);
-    if (lp.col_bytes > ((size_t)256 << 20)) return lp;              // keep the workspace modest
-    lp.codes_bytes = align_up((size_t)(K * lp.NPQ), 256);
-    lp.fc_bytes = linear_scratch_bytes(K, lp.CRS, lp.NPQ);
-    lp.bytes = lp.codes_bytes + lp.col_bytes + lp.fc_bytes;
-    Im2colArgs &m = lp.im;
-    m.N = (int)N; m.C = (int)C; m.H = (int)H; m.Wd = (int)Wd; m.R = (int)R; m.S = (int)S; m.pad = (int)pad; m.st = (int)stride;
-    m.P = (int)P; m.Q = (int)Q;
-    // channels per workgroup: enough for 256 consecutive entries per output pixel; output rows per workgroup: what fits
-    const int64_t RS = R * S;
-    int64_t ct = (256 + RS - 1) / RS;
-    if (ct < 32) ct = 32;
-    ct = (ct + 3) / 4 * 4;
-    if (ct > C) ct = C;
-    lp.vec4 = RS % 4 == 0 || (C % 4 == 0 && ct % 4 == 0);             // every tile's entries and every matrix row: multiples of 4
-    if (ct * RS >= (1 << 16) || R > 63 || S > 63) return lp;          // the entry table packs r and s into 6 bits each
-    const size_t budget = 40 * 1024;
-    int64_t pb = 0;
-    for (int64_t t = 1; t <= P; ++t) {
-        const int64_t hb = (t - 1) * stride + R < H ? (t - 1) * stride + R : H;
-        if ((size_t)(ct * (hb * Wd + 1)) * esz > budget) break;
-        pb = t;
-    }
-    if (pb == 0) return lp;
-    const int64_t ctiles = (C + ct - 1) / ct;
-    while (pb > 1 && N * ((P + pb - 1) / pb) * ctiles < 1024) --pb;   // enough workgroups to fill the chip
-    const int64_t hb = (pb - 1) * stride + R < H ? (pb - 1) * stride + R : H;
-    int64_t pitch = hb * Wd;
-    if (pitch % 2 == 0) ++pitch;                                      // odd: the channels of a pixel's entries spread over the banks
-    if (ct * pitch >= (1 << 20)) return lp;
-    m.CT = (int)ct; m.ctiles = (int)((C + ct - 1) / ct);
-    m.PB = (int)pb; m.bands = (int)((P + pb - 1) / pb);
-    m.pitch = (int)pitch;
-    lp.lds_bytes = (size_t)((ct * RS * 4 + 15) & ~15) + (size_t)(ct * pitch) * esz;
-    if (N * m.bands * m.ctiles > 0x7FFFFFFF) return lp;
-    lp.ok = true;
-    return lp;
-}
-
 size_t conv_scratch_bytes(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t pad, int64_t stride)
 {
     const int64_t P = (H + 2 * pad - R) / stride + 1, Q = (Wd + 2 * pad - S) / stride + 1;
@@ -741,28 +837,23 @@ size_t conv_scratch_bytes(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K
     const int64_t PQp16 = (P * Q + 15) / 16 * 16;
     size_t dw = part(K, C * R * S, N * PQp16, 16);
     size_t big = dx > dw ? dx : dw;
-    bool fast[2] = {false, false};                                   // a convolution dW kernel serves fp32 / int8 activations
     for (int i8 = 0; i8 < 2; ++i8) {
         const ConvDwPlan pl = conv_dw_plan(N, C, H, Wd, K, R, S, pad, i8 != 0);
-        if (pl.ok && stride == 1) fast[i8] = true;
         if (pl.ok && pl.partial_bytes > big) big = pl.partial_bytes;
     }
     const ConvDwI8Plan p8 = conv_dw_i8_plan(N, C, H, Wd, K, R, S, pad);
-    if (p8.ok && stride == 1) fast[1] = true;
     if (p8.ok && p8.partial_bytes > big) big = p8.partial_bytes;
     for (int i8 = 0; i8 < 2; ++i8) {
         const Conv1x1Plan p1 = conv1x1_dw_plan(N, C, H, Wd, K, R, S, pad, stride, i8 ? FC2I_KT : FC2_KT);
         if (p1.ok && p1.partial_bytes > big) big = p1.partial_bytes;
     }
+    for (int i8 = 0; i8 < 2; ++i8)
+        for (int planes = i8 ? 3 : 2; planes <= 3; ++planes) {
+            const ConvDwtPlan pd = conv_dwt_plan(N, C, H, Wd, K, R, S, pad, stride, i8 != 0, planes);
+            if (pd.ok && pd.partial_bytes > big) big = pd.partial_bytes;
+        }
     const size_t padded = (size_t)(N * K * ((P * Q + 3) / 4 * 4));    // dX: the codes in planes that start on 4-byte boundaries
     if (padded > big) big = padded;
-    // dW lowered to the FC kernels: room for the column matrix only where no convolution dW kernel serves the shape (a
-    // call whose pointers those kernels cannot take then runs on the generic kernel, which needs less)
-    for (int i8 = 0; i8 < 2; ++i8) {
-        if (fast[i8]) continue;
-        const ConvLowerPlan lp = conv_dw_lower_plan(N, C, H, Wd, K, R, S, pad, stride, i8 ? 1 : 4);
-        if (lp.ok && lp.bytes > big) big = lp.bytes;
-    }
     return relayout_bytes(K, C, R, S) + align_up(big, 256) + 256;
 }
 
@@ -1087,11 +1178,39 @@ static hipError_t conv_dw(const ConvArgs &a, const void *grad, Scale scale, hipS
         }
     }
     if constexpr (MODE != MODE_F32) {
-        ConvDwPlan pl = conv_dw_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, MODE == MODE_I8);
-        if (a.stride != 1) pl.ok = false;                            // the fast kernel is a stride-1 kernel
-        const size_t xal = MODE == MODE_I8 ? 4 : 16;                 // aligned 4-element loads of both operands
-        if (pl.ok && rb + pl.partial_bytes <= a.scratch_bytes && (uintptr_t)a.X % xal == 0 && (uintptr_t)grad % 4 == 0) {
-            if (a.plan_only) return hipSuccess;
+        constexpr bool I8 = MODE == MODE_I8;
+        ConvDwPlan pl = conv_dw_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, I8);
+        const size_t xal = I8 ? 4 : 16;                              // aligned 4-element loads of both operands
+        if (a.stride != 1 || rb + pl.partial_bytes > a.scratch_bytes || (uintptr_t)a.X % xal != 0 || (uintptr_t)grad % 4 != 0) pl.ok = false;
+        Conv1x1Plan p1 = conv1x1_dw_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, a.stride, I8 ? FC2I_KT : FC2_KT);
+        if (rb + p1.partial_bytes > a.scratch_bytes) p1.ok = false;
+        // The general kernel takes what the two specialised forms do not, and what they are the slower ones for:
+        //   * of the 3x3 kernel, rows that fill half (int8: a quarter) of its padded rows or less.  Whole products, 3x3 kernel / general (us): 64->64
+        //     32x32 50 / 53, 128->128 28x28 59 / 67, 256->256 14x14 64 / 67, 8x8 63 / 48, 512->512 4x4 72 / 49; int8 14x14 37 / 40, 4x4 49 / 37;
+        //   * of the batched 1x1 form, what its plan and the general kernel's say, by modelled time: 1024->256 14x14 38 / 53, 512->128 28x28
+        //     48 / 55, 64->256 56x56 92 / 39, 256->64 56x56 94 / 46.
+        ConvDwtPlan pd;
+        pd.ok = false;
+        if (a.codes && !(pl.ok && a.Wd * (I8 ? 4 : 2) > pl.args.PW)) {
+            pd = conv_dwt_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, a.stride, I8, a.two_planes && !I8 ? 2 : 3);
+            // (a group of a grouped layer: images further apart than its own planes say)
+            if (pd.ok && (rb + pd.partial_bytes > a.scratch_bytes || pd.args.NI * a.kt() * pd.args.P * pd.args.Q >= ((int64_t)1 << 30) ||
+                          pd.args.NI * a.ct() * a.H * a.Wd >= ((int64_t)1 << 29))) pd.ok = false;
+            if (pd.ok && p1.ok && p1.us <= pd.us + 7.0f) pd.ok = false;
+        }
+        if (a.plan_only) {
+            // a gate (another kernel may take the product over) is a launch more, 4.5 us: not for the layers that only the general kernel serves
+            if (!pl.ok && !p1.ok) *a.plan_only = 1;
+            return hipSuccess;
+        }
+        if (pd.ok) {
+            ConvDwtArgs &k = pd.args;
+            k.codes = (const int8_t *)grad; k.X = a.X; k.dW = a.dW; k.partial = (char *)a.scratch + rb; k.scale = scale; k.gate = a.gate;
+            k.Ct = (int)a.ct(); k.Kt = (int)a.kt();
+            if constexpr (I8) return launch_conv_dwt<true, 1>(pd, s);
+            else return a.two_planes ? launch_conv_dwt<false, 2>(pd, s) : launch_conv_dwt<false, 3>(pd, s);
+        }
+        if (pl.ok) {
             ConvDwArgs &k = pl.args;
             k.codes = (const int8_t *)grad; k.X = a.X; k.dW = a.dW; k.partial = (char *)a.scratch + rb; k.scale = scale; k.gate = a.gate;
             k.Ct = (int)a.ct(); k.Kt = (int)a.kt();
@@ -1101,48 +1220,9 @@ static hipError_t conv_dw(const ConvArgs &a, const void *grad, Scale scale, hipS
             }
             return a.pad == 1 ? launch_conv_dw_fast<MODE, 3, 3, 1, 1>(pl, s) : launch_conv_dw_fast<MODE, 3, 3, 0, 1>(pl, s);
         }
+        if (p1.ok) return launch_conv1x1_dw<I8>(a, p1, (const int8_t *)grad, scale, (char *)a.scratch + rb, s);
     }
-    if constexpr (MODE != MODE_F32) {
-        constexpr bool I8 = MODE == MODE_I8;
-        const Conv1x1Plan p1 = conv1x1_dw_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, a.stride, I8 ? FC2I_KT : FC2_KT);
-        if (p1.ok && rb + p1.partial_bytes <= a.scratch_bytes)
-            return a.plan_only ? hipSuccess : launch_conv1x1_dw<I8>(a, p1, (const int8_t *)grad, scale, (char *)a.scratch + rb, s);
-    }
-    if (a.plan_only) { *a.plan_only = 1; return hipSuccess; }         // the lowered and the generic forms are not gated
-    if constexpr (MODE != MODE_F32) {
-        // neither convolution kernel took it: expand the activations into the column matrix, re-lay the codes, and let the
-        // fully connected kernels do dW[k][(c,r,s)] = sum_(n,p,q) code[k][(n,p,q)] col[(n,p,q)][(c,r,s)]
-        constexpr int ESZ = MODE == MODE_I8 ? 1 : 4;
-        const ConvLowerPlan lp = conv_dw_lower_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, a.stride, ESZ);
-        if (lp.ok && (MODE == MODE_BF16 || lp.vec4) &&      // int8 entries written one byte at a time: measured slower than generic
-            rb + lp.bytes <= a.scratch_bytes && (uintptr_t)grad % 4 == 0 && (uintptr_t)a.X % 4 == 0) {
-            int8_t *ck = (int8_t *)a.scratch + rb;
-            char *col = (char *)ck + lp.codes_bytes;
-            const int PQ = lp.im.P * lp.im.Q;
-            const int64_t groups = (int64_t)a.K * lp.NPQ / (PQ % 4 == 0 ? 4 : 1);
-            const int cb = (int)((groups + 255) / 256 < 8192 ? (groups + 255) / 256 : 8192);
-            if (PQ % 4 == 0) hipLaunchKernelGGL(conv_codes_kmajor_kernel<4>, dim3(cb), dim3(256), 0, s, (const int8_t *)grad, ck, (int)a.N, (int)a.K, PQ, (int)a.kt());
-            else             hipLaunchKernelGGL(conv_codes_kmajor_kernel<1>, dim3(cb), dim3(256), 0, s, (const int8_t *)grad, ck, (int)a.N, (int)a.K, PQ, (int)a.kt());
-            Im2colArgs im = lp.im;
-            im.X = a.X; im.col = col; im.Ct = (int)a.ct();
-            const int grid = (int)(a.N * im.bands * im.ctiles);
-            using XT = typename std::conditional<MODE == MODE_I8, int8_t, float>::type;
-            if (lp.vec4) hipLaunchKernelGGL((conv_im2col_kernel<XT, 4>), dim3(grid), dim3(256), lp.lds_bytes, s, im);
-            else         hipLaunchKernelGGL((conv_im2col_kernel<XT, 1>), dim3(grid), dim3(256), lp.lds_bytes, s, im);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            LinearArgs la{};
-            la.codes = ck; la.dense = nullptr; la.step = scale.host; la.step_dev = scale.dev;
-            la.W = MODE == MODE_I8 ? nullptr : (const float *)col;
-            la.W8 = MODE == MODE_I8 ? (const int8_t *)col : nullptr;
-            la.X = nullptr; la.x_dtype = MODE == MODE_I8 ? DBP_I8 : DBP_F32;
-            la.B = a.K; la.in = lp.CRS; la.out = lp.NPQ;
-            la.dX = (float *)a.dW; la.dW = nullptr;
-            la.scratch = col + lp.col_bytes; la.scratch_bytes = lp.fc_bytes;
-            la.stats_job = StatsJob{}; la.two_planes = a.two_planes;
-            return launch_linear_mfma(la, s);
-        }
-    }
+    if (a.plan_only) { *a.plan_only = 1; return hipSuccess; }         // the generic kernel takes no gate
     ConvGeom g = make_geom(a, ModeTraits<MODE>::KCH, k_step<MODE>());
     const int CRS = g.C * g.R * g.S, Kred = g.N * g.PQp;
     ConvDwGradLoader<MODE> al{(const typename GradElem<MODE>::T *)grad, g};
@@ -1298,15 +1378,30 @@ static int check_conv_plans(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t
             if ((int64_t)p1.n_split * p1.imgs_per_split < N || (int64_t)(p1.n_split - 1) * p1.imgs_per_split >= N) return 40;
             if ((int64_t)p1.spi * p1.kt < H * Wd) return 41;
         }
-        const ConvLowerPlan lp = conv_dw_lower_plan(N, C, H, Wd, K, R, S, pad, stride, i8 ? 1 : 4);
-        const bool fast_dw = stride == 1 && (pw.ok || (i8 && conv_dw_i8_plan(N, C, H, Wd, K, R, S, pad).ok));
-        if (lp.ok && !fast_dw) {
-            if (rb + lp.bytes > total) return 42;
-            if (lp.lds_bytes > (size_t)64 * 1024) return 43;
-            if ((int64_t)lp.im.bands * lp.im.PB < lp.im.P || (int64_t)lp.im.ctiles * lp.im.CT < C) return 44;
-            // the product on the lowered operands is a fully connected dX: its own plan must be consistent too
-            const int e = check_fc2_pair(K, lp.CRS, lp.NPQ, true, false, i8 ? FC2I_KT : FC2_KT);
-            if (e) return 50 + e;
+        for (int planes = i8 ? 3 : 2; planes <= 3; ++planes) {
+            const ConvDwtPlan pd = conv_dwt_plan(N, C, H, Wd, K, R, S, pad, stride, i8 != 0, planes);
+            if (!pd.ok) continue;
+            const ConvDwtArgs &k = pd.args;
+            const int RUN = DWT_RUN(i8 != 0), G = pd.G, MF = G == 2 ? 4 : 2, per_chunk = pd.waves / k.chunks;
+            const bool one = k.T == 1;
+            if (pd.lds_bytes > (size_t)DWT_MAX_LDS || rb + pd.partial_bytes > total) return 42;
+            if ((int64_t)k.n_split * k.units_per_split < k.units || (int64_t)(k.n_split - 1) * k.units_per_split >= k.units) return 43;
+            // units cover the output, none is empty, and their frames what its taps reach
+            if ((int64_t)k.bands * k.PB < P || (int64_t)(k.bands - 1) * k.PB >= P || (int64_t)k.cbands * k.QB < Q || (int64_t)(k.cbands - 1) * k.QB >= Q) return 44;
+            if (k.units != (N + k.NI - 1) / k.NI * k.bands * k.cbands || (k.NI > 1 && (k.bands > 1 || k.cbands > 1)) || (k.flat && k.cbands > 1)) return 45;
+            if (k.frame_w < (k.QB - 1) * stride + S || (int64_t)k.frame < ((k.PB - 1) * stride + R) * k.frame_w || (int64_t)k.frame * k.NI > k.chunks * 64) return 46;
+            if ((int64_t)k.runs_row * RUN < (k.flat ? (int64_t)k.PB * k.QB : k.QB) || k.runs_img < k.runs_row * (k.flat ? 1 : k.PB) || k.runs_img * k.NI > 2 * k.steps) return 47;
+            // wavefronts, channels and taps; staging within a thread's items
+            if (k.tg * k.cb * k.kg * k.ps != pd.waves || pd.waves > (one || G == 4 ? 8 : 12) || (k.ps & (k.ps - 1)) || k.chunks > pd.waves) return 48;
+            if ((int64_t)k.tiles_k * k.kg * 32 * MF < K || (int64_t)k.tiles_c * k.blocks * 32 < C || k.blocks != k.cb * (one ? G : 1)) return 49;
+            if ((int64_t)k.tap_blocks * k.tg * (one ? 1 : G) < k.T || pd.grid != k.tiles_k * k.tiles_c * k.tap_blocks * k.n_split) return 50;
+            if (per_chunk * (one ? 6 : 4) < 8 * k.blocks || k.code_step < 1 || k.code_step * 2 * k.steps > 64 * pd.waves ||
+                k.code_step * ((one ? 16 : G == 3 ? 8 : 12) / (RUN / 4)) < 32 * MF * k.kg) return 51;
+            const int pitch = (i8 ? 32 : 64 * planes) + 8;
+            if (k.x_bytes != k.chunks * 64 * pitch * k.blocks || k.buf_bytes != k.x_bytes + 32 * MF * k.kg * (2 * k.steps + 1) * RUN) return 52;
+            if (pd.lds_bytes < (size_t)2 * k.buf_bytes + (size_t)8 * k.steps * RUN || pd.lds_bytes < (size_t)(k.ps / 2) * k.tg * k.cb * k.kg * MF * G * 4096) return 53;
+            if ((int64_t)(k.NI + 1) * K * P * Q >= ((int64_t)1 << 31) || (int64_t)k.NI * C * H * Wd >= ((int64_t)1 << 29)) return 54;
+            if (pd.tch * pd.tap_chunks < k.T || pd.reduce_lds > (size_t)64 * 1024 || pd.reduce_lds < (size_t)pd.zg * 64 * pd.tch * 16) return 55;
         }
     }
     return 0;

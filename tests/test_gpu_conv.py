@@ -204,6 +204,31 @@ def test_conv_1x1_dw_batched_fc_kernel_int8_bit_exact(case):
     _check(p, run_conv(p))
 
 
+GENERAL_DW = [  # N, C, H, Wd, K, R, S, pad, stride: dW where no kernel for one shape serves (runs of 8 codes, of 16 with int8 activations)
+    (3, 5, 1, 7, 6, 1, 1, 0, 1),            # planes one code short of a run (fp32)
+    (7, 40, 2, 4, 70, 1, 1, 0, 1),          # exactly a run; a last unit with fewer images
+    (9, 33, 3, 3, 65, 3, 3, 1, 1),          # a run and one code; one channel past a block on both sides
+    (2, 16, 3, 5, 24, 3, 3, 1, 1),          # planes one code short of a run (int8)
+    (130, 8, 4, 4, 16, 3, 3, 1, 1),         # many small images a unit, with a remainder
+    (2, 20, 40, 150, 30, 3, 3, 1, 1),       # bands of rows and of columns, both with remainders
+    (2, 12, 13, 11, 20, 5, 5, 2, 2),        # 25 taps: wavefronts of four taps, the last with one
+    (1, 3, 50, 46, 20, 7, 7, 3, 2),         # 49 taps in two blocks
+    (1, 3, 51, 47, 17, 11, 11, 2, 4),       # 121 taps: narrow column bands, the reduction over taps in parts
+    (2, 70, 12, 12, 130, 2, 3, 1, 3),       # six taps, stride 3
+    (20, 96, 9, 9, 96, 1, 1, 0, 2),         # one tap with a stride, more than 64 input channels
+    (3, 64, 17, 9, 129, 1, 1, 0, 1),        # one tap, up to 64 input channels
+]
+
+
+@pytest.mark.parametrize("case", GENERAL_DW)
+def test_conv_dw_general_kernel_edges(case):
+    from gpu_util import run_conv
+    p = _problem(*case[:8], stride=case[8])
+    _check(p, run_conv(p))
+    p8 = _problem(*case[:8], c=1.0, i8=True, stride=case[8])
+    _check(p8, run_conv(p8))
+
+
 STRIDED = [  # N, C, H, Wd, K, R, S, pad, stride  (the strided layers of a ResNet: 3x3/2, 1x1/2 shortcuts, 7x7/2 stem)
     (2, 5, 9, 7, 6, 3, 3, 1, 2),
     (3, 16, 14, 14, 24, 3, 3, 1, 2),
