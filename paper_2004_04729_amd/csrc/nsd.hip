@@ -550,17 +550,34 @@ __global__ __launch_bounds__(256) void std_tree_kernel(const float *delta, const
     }
 }
 
-__global__ __launch_bounds__(256) void std_finish_kernel(double *a1, double *a2, double *b1, double *b2, int64_t count,
-                                                         int64_t n, float s, float *step_out)
+// One workgroup adds the remaining levels.  It is a chain of memory latencies and nothing else, so a thread asks for all the
+// values of its group before it adds the first (in a loop of unknown length the loads came one at a time, a latency per addition),
+// and from 1024 groups on the levels stay in LDS; only trees of more than 2^26 elements go through the scratch halves.
+constexpr int kFinishThreads = 1024;
+
+__device__ __forceinline__ void std_group_sum(const double *v1, const double *v2, int64_t g, int64_t count, double &t1, double &t2)
 {
-    // remaining levels of the tree, ping-pong between the two scratch halves
+    const int64_t lo = g * 16;
+    double x1[16], x2[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { const int64_t at = min(lo + i, count - 1); x1[i] = v1[at]; x2[i] = v2[at]; }
+    t1 = x1[0]; t2 = x2[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i)
+        if (lo + i < count) { t1 += x1[i]; t2 += x2[i]; }
+}
+
+__global__ __launch_bounds__(kFinishThreads) void std_finish_kernel(double *a1, double *a2, double *b1, double *b2, int64_t count,
+                                                                    int64_t n, float s, float *step_out)
+{
+    __shared__ double l1[kFinishThreads], l2[kFinishThreads];
+    const int tid = threadIdx.x;
     double *src1 = a1, *src2 = a2, *dst1 = b1, *dst2 = b2;
-    while (count > 1) {
+    while (count > 16 * kFinishThreads) {
         const int64_t groups = (count + 15) / 16;
-        for (int64_t g = threadIdx.x; g < groups; g += 256) {
-            const int64_t lo = g * 16, hi = min(count, lo + 16);
-            double t1 = src1[lo], t2 = src2[lo];
-            for (int64_t i = lo + 1; i < hi; ++i) { t1 += src1[i]; t2 += src2[i]; }
+        for (int64_t g = tid; g < groups; g += kFinishThreads) {
+            double t1, t2;
+            std_group_sum(src1, src2, g, count, t1, t2);
             dst1[g] = t1; dst2[g] = t2;
         }
         __syncthreads();
@@ -569,9 +586,20 @@ __global__ __launch_bounds__(256) void std_finish_kernel(double *a1, double *a2,
         t = src2; src2 = dst2; dst2 = t;
         count = groups;
     }
-    if (threadIdx.x == 0) {
+    int groups = (int)((count + 15) / 16);                             // at most one a thread (a single value is its own sum)
+    double t1 = 0.0, t2 = 0.0;
+    if (tid < groups) std_group_sum(src1, src2, tid, count, t1, t2);
+    while (groups > 1) {
+        if (tid < groups) { l1[tid] = t1; l2[tid] = t2; }
+        __syncthreads();
+        const int have = groups;
+        groups = (groups + 15) / 16;
+        if (tid < groups) std_group_sum(l1, l2, tid, have, t1, t2);
+        __syncthreads();                                               // every read is over before the next level is written
+    }
+    if (tid == 0) {
         float step, inv;
-        step_pair_from_sums(n > 0 ? src1[0] : 0.0, n > 0 ? src2[0] : 0.0, n, s, step, inv);
+        step_pair_from_sums(n > 0 ? t1 : 0.0, n > 0 ? t2 : 0.0, n, s, step, inv);
         step_out[0] = step;
         step_out[1] = inv;
     }
@@ -673,7 +701,7 @@ hipError_t launch_step_size(const float *delta, const float *act, int64_t n, flo
         *defer = StepTree{a1, a2, (int)wgs, n, s, step_out};
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(std_finish_kernel, dim3(1), dim3(256), 0, st, a1, a2, b1, b2, wgs, n, s, step_out);
+    hipLaunchKernelGGL(std_finish_kernel, dim3(1), dim3(kFinishThreads), 0, st, a1, a2, b1, b2, wgs, n, s, step_out);
     return hipGetLastError();
 }
 

@@ -51,6 +51,16 @@ def test_step_size_matches_oracle_bit_for_bit(size):
         assert out.cpu().numpy()[0] == np.float32(step)
 
 
+@pytest.mark.parametrize("size", [256 * 4096 + 1, 2048 * 4096, 1024 * 16 * 4096 - 4095, 1024 * 16 * 4096 + 1])
+def test_step_size_of_large_trees_bit_for_bit(size):
+    """One level left above the workgroups' nodes, levels in LDS, the most groups LDS takes (1024), a level through the scratch first."""
+    from oracle import oracle as O
+    rng = np.random.default_rng(size)
+    d = rng.standard_normal(size, dtype=np.float32)
+    step, _ = O.step_size(d, 8.0)
+    assert _gpu_step(d, None, 8.0)[0] == np.float32(step)
+
+
 def test_step_size_laws_mask_and_degenerate_layers():
     from oracle import oracle as O
     rng = np.random.default_rng(11)
