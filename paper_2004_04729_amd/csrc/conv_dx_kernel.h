@@ -73,23 +73,47 @@ __device__ __forceinline__ void cdx_stage_map(uint8_t (&lm)[64], const CdxTapMap
     }
 }
 
-// The quantiser's pending sums ride along in the weight preparation (the first kernel after the quantiser on the stream), in
-// workgroups of their own at the end of the grid.  `workers` = workgroups that prepare weights.
-__device__ __forceinline__ bool cdx_side_jobs(const StatsJob &job, int &workers)
+// Code planes of P*Q bytes -> planes of `plane` bytes (a multiple of 4, zero filled): the patch fill reads aligned dwords.
+// Plane pl = (n, k) of the copy is plane n*Kt + k of the source tensor (Kt = K unless the K planes are one group's block).
+struct CdxPad { const int8_t *src; uint32_t *dst; int64_t planes; int pq, plane, K, Kt; int workgroups; };   // workgroups = 0: no copy
+
+__device__ __forceinline__ void cdx_pad_codes(const CdxPad &p, int block)
 {
-    workers = (int)gridDim.x - (int)job.workgroups();
-    if ((int)blockIdx.x < workers) return false;
-    side_job(job, (int)blockIdx.x - workers, 256);
+    const int dpp = p.plane >> 2;                                // dwords per padded plane
+    const int64_t total = p.planes * dpp;
+    for (int64_t i = (int64_t)block * 256 + threadIdx.x; i < total; i += (int64_t)p.workgroups * 256) {
+        const int64_t pl = i / dpp;
+        const int j0 = 4 * (int)(i - pl * dpp);
+        const int8_t *s = p.src + (pl / p.K * p.Kt + pl % p.K) * p.pq + j0;
+        uint32_t v = 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (j0 + e < p.pq) v |= (uint32_t)(uint8_t)s[e] << (8 * e);
+        p.dst[i] = v;
+    }
+}
+
+// The copy of the codes and the quantiser's pending sums ride along in the weight preparation (the first kernel after the
+// quantiser on the stream), in workgroups of their own behind those that prepare weights (`workers`): each of them is bound by
+// its launch and a memory latency, so one launch costs what the longest of them did (3x3 512->512 7x7 N=64, the call: the copy in a
+// launch of its own 157.9 us, here 156.6).
+__device__ __forceinline__ bool cdx_side_jobs(const StatsJob &job, const CdxPad &pad, int &workers)
+{
+    workers = (int)gridDim.x - (int)job.workgroups() - pad.workgroups;
+    const int b = (int)blockIdx.x - workers;
+    if (b < 0) return false;
+    if (b < pad.workgroups) cdx_pad_codes(pad, b);
+    else side_job(job, b - pad.workgroups, 256);
     return true;
 }
 
 template <bool MAPPED, int PL>
 __global__ __launch_bounds__(256) void conv_dx_weight_prep_kernel(const float *W, uint4 *wp, int K, int C, int RS, int KG, int Cp, int RS_real, CdxTapMap map,
-                                                                  StatsJob job)
+                                                                  StatsJob job, CdxPad pad)
 {
     __shared__ uint8_t lm[64];
     int workers;
-    if (cdx_side_jobs(job, workers)) return;
+    if (cdx_side_jobs(job, pad, workers)) return;
     cdx_stage_map<MAPPED>(lm, map);
     const int64_t total = (int64_t)RS * KG * Cp;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)workers * 256) {
@@ -124,11 +148,11 @@ __global__ __launch_bounds__(256) void conv_dx_weight_prep_kernel(const float *W
 // int8 weights [K][C][R][S] -> cells of 16 reduction channels in fragment order [tap][k-group][c], zero padded.
 template <bool MAPPED>
 __global__ __launch_bounds__(256) void conv_dx_weight_prep_i8_kernel(const int8_t *W, uint4 *wp, int K, int C, int RS, int KG, int Cp, int RS_real, CdxTapMap map,
-                                                                     StatsJob job)
+                                                                     StatsJob job, CdxPad pad)
 {
     __shared__ uint8_t lm[64];
     int workers;
-    if (cdx_side_jobs(job, workers)) return;
+    if (cdx_side_jobs(job, pad, workers)) return;
     cdx_stage_map<MAPPED>(lm, map);
     const int64_t total = (int64_t)RS * KG * Cp;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)workers * 256) {
@@ -144,24 +168,6 @@ __global__ __launch_bounds__(256) void conv_dx_weight_prep_i8_kernel(const int8_
             d[j >> 2] |= w << (8 * (j & 3));
         }
         wp[i] = uint4{d[0], d[1], d[2], d[3]};
-    }
-}
-
-// Code planes of P*Q bytes -> planes of `plane` bytes (a multiple of 4, zero filled): the patch fill reads aligned dwords.
-// Plane pl = (n, k) of the copy is plane n*Kt + k of the source tensor (Kt = K unless the K planes are one group's block).
-__global__ __launch_bounds__(256) void conv_dx_pad_codes_kernel(const int8_t *src, uint32_t *dst, int64_t planes, int pq, int plane, int K, int Kt)
-{
-    const int dpp = plane >> 2;                                  // dwords per padded plane
-    const int64_t total = planes * dpp;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        const int64_t pl = i / dpp;
-        const int j0 = 4 * (int)(i - pl * dpp);
-        const int8_t *s = src + (pl / K * Kt + pl % K) * pq + j0;
-        uint32_t v = 0u;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (j0 + e < pq) v |= (uint32_t)(uint8_t)s[e] << (8 * e);
-        dst[i] = v;
     }
 }
 

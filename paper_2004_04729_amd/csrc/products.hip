@@ -1053,21 +1053,6 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
     if constexpr (MODE_G != MODE_F32) {
         constexpr bool I8 = MODE_G == MODE_I8;
         constexpr int PL = CdxTraits<MODE_K>::PL;
-        auto prepare = [&](int taps, int KG, int Cp, const CdxTapMap *map) {
-            const int64_t cells = (int64_t)taps * KG * Cp;
-            int pb = (int)((cells + 255) / 256 < 4096 ? (cells + 255) / 256 : 4096);
-            const int rs = (int)(a.R * a.S);
-            // the quantiser's pending statistics sum / bias gradient ride along in workgroups of their own
-            StatsJob job{nullptr, 0, nullptr, nullptr, 0, nullptr, 0.0f, nullptr};
-            if (a.pending && (a.pending->n > 0 || a.pending->bias_len > 0)) { job = *a.pending; *a.pending = StatsJob{}; pb += (int)job.workgroups(); }
-            if constexpr (I8) {
-                if (map) hipLaunchKernelGGL(conv_dx_weight_prep_i8_kernel<true>, dim3(pb), dim3(256), 0, s, a.W8, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, *map, job);
-                else     hipLaunchKernelGGL(conv_dx_weight_prep_i8_kernel<false>, dim3(pb), dim3(256), 0, s, a.W8, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, CdxTapMap{}, job);
-            } else {
-                if (map) hipLaunchKernelGGL((conv_dx_weight_prep_kernel<true, PL>), dim3(pb), dim3(256), 0, s, a.W, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, *map, job);
-                else     hipLaunchKernelGGL((conv_dx_weight_prep_kernel<false, PL>), dim3(pb), dim3(256), 0, s, a.W, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, CdxTapMap{}, job);
-            }
-        };
         // The codes as the kernel wants them: planes that start on 4-byte boundaries.  Planes of a size that is not a
         // multiple of 4 (7x7 outputs ...) or a misaligned tensor are copied into padded planes behind the prepared weights.
         const size_t rbw = relayout_bytes(a.K, a.C, a.R, a.S);
@@ -1075,14 +1060,27 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
         const int64_t plane = (PQ + 3) / 4 * 4;
         const bool pad_codes = PQ % 4 != 0 || (uintptr_t)grad % 4 != 0;
         const bool codes_ok = !pad_codes || (rbw + (size_t)(a.N * a.K * plane) <= a.scratch_bytes && plane < (1 << 24));
-        auto kernel_codes = [&]() -> const int8_t * {
-            if (!pad_codes) return (const int8_t *)grad;
-            uint32_t *dst = (uint32_t *)((char *)a.scratch + rbw);
-            const int64_t dwords = a.N * a.K * (plane / 4);
-            const int pbk = (int)((dwords + 255) / 256 < 4096 ? (dwords + 255) / 256 : 4096);
-            hipLaunchKernelGGL(conv_dx_pad_codes_kernel, dim3(pbk), dim3(256), 0, s, (const int8_t *)grad, dst, a.N * a.K, (int)PQ, (int)plane,
-                               (int)a.K, (int)a.kt());
-            return (const int8_t *)dst;
+        const int8_t *kernel_codes = pad_codes ? (const int8_t *)a.scratch + rbw : (const int8_t *)grad;
+        auto prepare = [&](int taps, int KG, int Cp, const CdxTapMap *map) {
+            const int64_t cells = (int64_t)taps * KG * Cp;
+            int pb = (int)((cells + 255) / 256 < 4096 ? (cells + 255) / 256 : 4096);
+            const int rs = (int)(a.R * a.S);
+            // the quantiser's pending statistics sum / bias gradient and the padded copy of the codes ride along in workgroups of their own
+            StatsJob job{nullptr, 0, nullptr, nullptr, 0, nullptr, 0.0f, nullptr};
+            if (a.pending && (a.pending->n > 0 || a.pending->bias_len > 0)) { job = *a.pending; *a.pending = StatsJob{}; pb += (int)job.workgroups(); }
+            CdxPad pad{};
+            if (pad_codes) {
+                const int64_t wgs = (a.N * a.K * (plane / 4) + 255) / 256;
+                pad = CdxPad{(const int8_t *)grad, (uint32_t *)((char *)a.scratch + rbw), a.N * a.K, (int)PQ, (int)plane, (int)a.K, (int)a.kt(), (int)(wgs < 4096 ? wgs : 4096)};
+                pb += pad.workgroups;
+            }
+            if constexpr (I8) {
+                if (map) hipLaunchKernelGGL(conv_dx_weight_prep_i8_kernel<true>, dim3(pb), dim3(256), 0, s, a.W8, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, *map, job, pad);
+                else     hipLaunchKernelGGL(conv_dx_weight_prep_i8_kernel<false>, dim3(pb), dim3(256), 0, s, a.W8, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, CdxTapMap{}, job, pad);
+            } else {
+                if (map) hipLaunchKernelGGL((conv_dx_weight_prep_kernel<true, PL>), dim3(pb), dim3(256), 0, s, a.W, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, *map, job, pad);
+                else     hipLaunchKernelGGL((conv_dx_weight_prep_kernel<false, PL>), dim3(pb), dim3(256), 0, s, a.W, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, CdxTapMap{}, job, pad);
+            }
         };
         if (a.stride != 1 && codes_ok) {
             ConvDxStridedPlan sp = conv_dx_strided_plan(a, I8);
@@ -1097,10 +1095,9 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
                 if (sp.multi.n > 0) {
                     const int KG = sp.multi.cls[0].KG, Cp = sp.multi.cls[0].Cp;
                     prepare(sp.taps, KG, Cp, &sp.map);
-                    const int8_t *kc = kernel_codes();
                     for (int i = 0; i < sp.multi.n; ++i) {
                         ConvDxArgs &k = sp.multi.cls[i];
-                        k.codes = kc; k.dX = a.dX; k.scale = scale; k.gate = a.gate;
+                        k.codes = kernel_codes; k.dX = a.dX; k.scale = scale; k.gate = a.gate;
                         k.code_img = (pad_codes ? a.K : a.kt()) * k.PQ; k.dx_img = a.ct() * k.oPI;
                         k.wp = (const uint4 *)a.scratch + (int64_t)sp.tap_base[i] * KG * PL * Cp;
                     }
@@ -1115,7 +1112,7 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
         if (pl.ok && codes_ok && a.plan_only) return hipSuccess;
         if (pl.ok && codes_ok) {
             ConvDxArgs &k = pl.args;
-            k.codes = kernel_codes(); k.wp = (const uint4 *)a.scratch; k.dX = a.dX; k.scale = scale; k.gate = a.gate;
+            k.codes = kernel_codes; k.wp = (const uint4 *)a.scratch; k.dX = a.dX; k.scale = scale; k.gate = a.gate;
             k.code_img = (pad_codes ? a.K : a.kt()) * k.PQ; k.dx_img = a.ct() * k.PI;
             prepare(k.R * k.S, k.KG, k.Cp, nullptr);
             // tap counts that are a multiple of 3 (3x3 above all) take the form with three weight fragment sets in flight
