@@ -17,6 +17,8 @@
 //     added up through LDS at the end).
 //   * a unit is a band of output rows (or columns) of an image, or several small images; units go round the workgroups of a
 //     tile, LDS is double buffered: the next unit's operands are loaded before this unit's steps and written after them.
+//     Elements past a ragged band have zero codes and read the band's last pixels, not what lies behind them: a non-finite
+//     activation reaches the taps that pair with it and no other.
 // Partial sums of the workgroups that share a tile are added in a fixed order by conv_dwt_reduce_kernel.
 // What bounds it: about 20 us of ends (launch, first loads from HBM, folding and writing partial sums); beyond them 60 % of the bf16 rate that
 // matrix cores reach here.  Measured, kernel and reduction (us), against what served before: 128->256 28x28/2 N=64 50 / 67 (column matrix and
@@ -52,6 +54,8 @@ struct ConvDwtArgs {
     int frame_w, frame, chunks;                         // LDS pixels per row and per image of a unit; chunks of 64 of the unit's
     int runs_row, runs_img, steps;                      // runs per row (flat bands: per band), per image; steps of two runs per unit
     int flat;                                           // whole rows: runs go on across row ends
+    int last_rows, last_cols;                           // rows and columns of the last bands
+    int tables, table_row, table_col;                   // tables of pixels; where those of the last bands begin (0: as large as the others)
     int kg, cb, ps, tg;                                 // wavefronts along output channels, input channels, steps, taps
     int tiles_k, tiles_c, tap_blocks;
     int blocks;                                         // blocks of 32 input channels a workgroup stages
@@ -76,7 +80,9 @@ __device__ __forceinline__ uint2 dwt_read_tr(const unsigned char *p, bool i8)
     return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((p16)(p)));
 }
 
-template <bool I8, int PL, int G, bool ONE>
+// RAGGED: last bands smaller than the others, with a table of pixels of their own.  Choosing the table per unit costs 3 to 5 % in the loop (3x3/2
+// 128->256 28x28 N=64 50 / 52 us), so whole bands and int8 operands (no NaN) have a form without.
+template <bool I8, int PL, int G, bool ONE, bool RAGGED>
 __global__ __launch_bounds__((64 * DwtShape<G, ONE>::WAVES), 1) void conv_dwt_kernel(ConvDwtArgs a)
 {
     if (a.gate.closed()) return;
@@ -112,12 +118,16 @@ __global__ __launch_bounds__((64 * DwtShape<G, ONE>::WAVES), 1) void conv_dwt_ke
 
     // ---- a table, built once: run elements of a unit -> byte offset in LDS of the pixel that tap (0,0) reads
     uint32_t *t_pix = (uint32_t *)(lds + 2 * a.buf_bytes);
-    for (int i = tid; i < 2 * a.steps * RUN; i += threads) {
-        const int run = i / RUN, img = min(run / a.runs_img, a.NI - 1), f = run - run / a.runs_img * a.runs_img;
-        int row = f / a.runs_row, col = (f - row * a.runs_row) * RUN + (i - run * RUN);
-        if (a.flat) { row = col / a.Q; col -= row * a.Q; }
-        row = min(row, a.PB - 1); col = min(col, a.QB - 1);                // elements past the band: a staged pixel, their codes are zero
-        t_pix[i] = (uint32_t)((img * a.frame + row * a.st * a.frame_w + col * a.st) * PITCH);
+    // (and one each for the units of a ragged last row band, column band, and both)
+    for (int table = 0, n = 2 * a.steps * RUN; table < (RAGGED ? a.tables : 1); ++table) {
+        const int rows = a.table_row && (table & 1) ? a.last_rows : a.PB, cols = a.table_col && table * n >= a.table_col ? a.last_cols : a.QB;
+        for (int e = tid; e < n; e += threads) {
+            const int run = e / RUN, img = min(run / a.runs_img, a.NI - 1), f = run - run / a.runs_img * a.runs_img;
+            int row = f / a.runs_row, col = (f - row * a.runs_row) * RUN + (e - run * RUN);
+            if (a.flat) { row = col / a.Q; col -= row * a.Q; }
+            row = min(row, rows - 1); col = min(col, cols - 1);            // elements past the band: its last pixels, their codes are zero
+            t_pix[table * n + e] = (uint32_t)((img * a.frame + row * a.st * a.frame_w + col * a.st) * PITCH);
+        }
     }
     for (int i = tid; i < 2 * a.buf_bytes / 16; i += threads) dwt_lds[i] = uint4{0u, 0u, 0u, 0u};   // nothing unset is ever multiplied
     // ---- staging: a wavefront keeps to one chunk of 64 pixels, a lane to its pixel, and takes every per_chunk-th quad of channels
@@ -296,11 +306,12 @@ __global__ __launch_bounds__((64 * DwtShape<G, ONE>::WAVES), 1) void conv_dwt_ke
     const int e_lane = I8 ? (lane & 15) >> 1 : (lane & 15) >> 2;            // which pixel of a read's four (eight) the lane fetches
     const int c_lane = I8 ? 16 * ((lane >> 4) & 1) + 8 * (lane & 1) : 2 * (16 * ((lane >> 4) & 1) + 4 * (lane & 3));   // byte of its channels
     const int x_base = w_cb * (ONE ? G : 1) * (a.chunks * 64 * PITCH) + c_lane, k_base = a.x_bytes + (w_kg * 32 * MF + (lane & 31)) * CPITCH;
+    const int t_lane = half * RUN + e_lane;
     struct Head { uint32_t a[MF][AD], p0, p1; };                            // what a step starts from: its codes and its pixels
-    auto head = [&](const unsigned char *buf, int st) {
+    auto head = [&](const unsigned char *buf, int table, int st) {
         Head h;
-        const int run = 2 * min(st, a.steps - 1) + half;
-        const uint32_t *tp = t_pix + run * RUN + e_lane;
+        const int run = 2 * min(st, a.steps - 1) + half, first = 2 * min(st, a.steps - 1) * RUN;                   // uniform
+        const uint32_t *tp = t_pix + t_lane + (table + first);
         h.p0 = tp[0]; h.p1 = tp[RUN / 2];
 #pragma unroll
         for (int i = 0; i < MF; ++i) {
@@ -316,14 +327,14 @@ __global__ __launch_bounds__((64 * DwtShape<G, ONE>::WAVES), 1) void conv_dwt_ke
         }
         return h;
     };
-    auto multiply = [&](const unsigned char *buf) {
-        Head h = head(buf, w_ps);
+    auto multiply = [&](const unsigned char *buf, int table) {
+        Head h = head(buf, table, w_ps);
         for (int st = w_ps; st < a.steps; st += a.ps) {
             const unsigned char *px0 = buf + x_base + h.p0, *px1 = buf + x_base + h.p1;
             u32x4 af[MF];
 #pragma unroll
             for (int i = 0; i < MF; ++i) af[i] = code_fragment(h.a[i]);
-            h = head(buf, st + a.ps);
+            h = head(buf, table, st + a.ps);
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 u32x4 bf[PL];
@@ -342,6 +353,8 @@ __global__ __launch_bounds__((64 * DwtShape<G, ONE>::WAVES), 1) void conv_dwt_ke
 
     const int u_begin = split * a.units_per_split, u_end = min(a.units, u_begin + a.units_per_split);
     Unit cur = unit_of(u_begin), next = cur;
+    auto table_of = [&](const Unit &r) { return (r.p0 + a.PB >= a.P ? a.table_row : 0) + (r.q0 + a.QB >= a.Q ? a.table_col : 0); };
+    int table = RAGGED ? table_of(cur) : 0;
     if (u_begin + 1 < u_end) advance(next);
     fetch(cur); fetch_codes(cur);
     stage(lds); stage_codes(lds);
@@ -349,8 +362,9 @@ __global__ __launch_bounds__((64 * DwtShape<G, ONE>::WAVES), 1) void conv_dwt_ke
     __syncthreads();
     for (int u = u_begin; u < u_end; ++u) {
         const int ib = (u - u_begin) & 1;
-        multiply(lds + ib * a.buf_bytes);
+        multiply(lds + ib * a.buf_bytes, table);
         stage(lds + (1 - ib) * a.buf_bytes); stage_codes(lds + (1 - ib) * a.buf_bytes);
+        if constexpr (RAGGED) table = table_of(next);
         if (u + 2 < u_end) advance(next);
         fetch(next); fetch_codes(next);
         __syncthreads();

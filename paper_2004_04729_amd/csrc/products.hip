@@ -432,12 +432,16 @@ ConvDwtPlan conv_dwt_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K
                 const bool flat = wi == 0;
                 int pb = (int)((max_px / fw - R) / stride + 1), bands = 0, ni = 1, frame = 0, runs_row = 0, runs_img = 0, steps = 0, chunks = 0;
                 size_t lds = 0;
+                int tables = 1, last_rows = 0;
+                const int last_cols = (int)Q - (cbands - 1) * qb;
                 if (pb > P) pb = (int)P;
                 bool fits = false;
                 for (; pb >= 1 && !fits; --pb) {                             // the tallest band (then the most images) whose codes fit beside it
                     bands = (int)((P + pb - 1) / pb);
                     pb = (int)((P + bands - 1) / bands);
                     frame = (int)((pb - 1) * stride + R) * fw;
+                    last_rows = (int)P - (bands - 1) * pb;
+                    tables = i8 ? 1 : (last_rows < pb ? 2 : 1) * (last_cols < qb ? 2 : 1);     // (integers have no NaN)
                     ni = 1;
                     if (flat && bands == 1) {
                         ni = max_px / frame;
@@ -448,7 +452,7 @@ ConvDwtPlan conv_dwt_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K
                     runs_row = flat ? (pb * qb + RUN - 1) / RUN : (qb + RUN - 1) / RUN; runs_img = flat ? runs_row : runs_row * pb;
                     for (; ni >= 1 && !fits; --ni) {
                         steps = (runs_img * ni + 1) / 2; chunks = (frame * ni + 63) / 64;
-                        lds = 2 * ((size_t)chunks * 64 * pitch * blocks + (size_t)kt * (2 * steps + 1) * RUN) + (size_t)steps * RUN * 8;
+                        lds = 2 * ((size_t)chunks * 64 * pitch * blocks + (size_t)kt * (2 * steps + 1) * RUN) + (size_t)steps * RUN * 8 * tables;
                         fits = lds <= (size_t)DWT_MAX_LDS && chunks <= pl.waves && pl.waves / chunks * items >= 8 * blocks && 2 * steps <= 64 * pl.waves && kt <= citems * (64 * pl.waves / (2 * steps));
                         if (fits) break;
                     }
@@ -461,12 +465,15 @@ ConvDwtPlan conv_dwt_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K
                 const int64_t per = (units + want - 1) / want, ns = (units + per - 1) / per;
                 const double rounds = (double)((tiles * ns + 255) / 256);
                 double us = rounds * (double)per * ((double)((steps + ps - 1) / ps) * t_step + chunks * blocks * 600.0 + 1500.0) / 2000.0;
+                if (tables > 1) us *= 1.04;                                // (the pixel table chosen per unit)
                 if (ns > 1) us += 4.0 + (double)tiles * ns * (pl.waves / ps) * MF * pl.G * 4096.0 * 2.0 / 4.5e6;
                 if (best >= 0.0 && us >= best) continue;
                 best = us; best_units = units;
                 k.kg = kg; k.cb = cb; k.ps = ps; k.tiles_k = (int)tk; k.tiles_c = (int)tc;
                 k.PB = pb; k.bands = bands; k.QB = qb; k.cbands = cbands; k.NI = ni; k.frame_w = fw; k.frame = frame; k.chunks = chunks;
                 k.runs_row = runs_row; k.runs_img = runs_img; k.steps = steps; k.flat = flat ? 1 : 0;
+                k.last_rows = last_rows; k.last_cols = last_cols; k.tables = tables;
+                k.table_row = tables > 1 && last_rows < pb ? 2 * steps * RUN : 0; k.table_col = tables > 1 && last_cols < qb ? tables * steps * RUN : 0;
                 k.blocks = blocks; k.x_bytes = chunks * 64 * pitch * blocks; k.buf_bytes = k.x_bytes + kt * (2 * steps + 1) * RUN;
                 k.code_step = 64 * pl.waves / (2 * steps); pl.lds_bytes = lds;
                 k.units_per_split = (int)per; k.n_split = (int)ns;
@@ -497,27 +504,34 @@ ConvDwtPlan conv_dwt_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K
     return pl;
 }
 
-template <bool I8, int PL, int G, bool ONE>
+template <bool I8, int PL, int G, bool ONE, bool RAGGED>
 hipError_t launch_conv_dwt_as(const ConvDwtPlan &pl, hipStream_t s)
 {
     static bool raised = false;                                      // more than 64 KiB of dynamic LDS: allowed per kernel, once
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_dwt_kernel<I8, PL, G, ONE>), hipFuncAttributeMaxDynamicSharedMemorySize, DWT_MAX_LDS);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_dwt_kernel<I8, PL, G, ONE, RAGGED>), hipFuncAttributeMaxDynamicSharedMemorySize, DWT_MAX_LDS);
         if (e != hipSuccess) return e;
         raised = true;
     }
-    hipLaunchKernelGGL((conv_dwt_kernel<I8, PL, G, ONE>), dim3(pl.grid), dim3(64 * pl.waves), pl.lds_bytes, s, pl.args);
+    hipLaunchKernelGGL((conv_dwt_kernel<I8, PL, G, ONE, RAGGED>), dim3(pl.grid), dim3(64 * pl.waves), pl.lds_bytes, s, pl.args);
     if (pl.args.n_split > 1)
         hipLaunchKernelGGL((conv_dwt_reduce_kernel<G, ONE>), dim3(pl.reduce_grid), dim3(64 * pl.tch * pl.zg < 1024 ? 64 * pl.tch * pl.zg : 1024), pl.reduce_lds, s, pl.args, I8 ? 1 : 0,
                            pl.tch, pl.tap_chunks, pl.zg);
     return hipGetLastError();
 }
 
+template <bool I8, int PL, bool RAGGED>
+hipError_t launch_conv_dwt_of(const ConvDwtPlan &pl, hipStream_t s)
+{
+    if (pl.args.T == 1) return pl.G == 2 ? launch_conv_dwt_as<I8, PL, 2, true, RAGGED>(pl, s) : launch_conv_dwt_as<I8, PL, 4, true, RAGGED>(pl, s);
+    return pl.G == 3 ? launch_conv_dwt_as<I8, PL, 3, false, RAGGED>(pl, s) : launch_conv_dwt_as<I8, PL, 4, false, RAGGED>(pl, s);
+}
+
 template <bool I8, int PL>
 hipError_t launch_conv_dwt(const ConvDwtPlan &pl, hipStream_t s)
 {
-    if (pl.args.T == 1) return pl.G == 2 ? launch_conv_dwt_as<I8, PL, 2, true>(pl, s) : launch_conv_dwt_as<I8, PL, 4, true>(pl, s);
-    return pl.G == 3 ? launch_conv_dwt_as<I8, PL, 3, false>(pl, s) : launch_conv_dwt_as<I8, PL, 4, false>(pl, s);
+    if constexpr (!I8) { if (pl.args.tables > 1) return launch_conv_dwt_of<I8, PL, true>(pl, s); }
+    return launch_conv_dwt_of<I8, PL, false>(pl, s);
 }
 
 template <int MODE, int R, int S, int PAD, int MB, int ROWS>
@@ -1396,7 +1410,10 @@ static int check_conv_plans(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t
                 k.code_step * ((one ? 16 : G == 3 ? 8 : 12) / (RUN / 4)) < 32 * MF * k.kg) return 51;
             const int pitch = (i8 ? 32 : 64 * planes) + 8;
             if (k.x_bytes != k.chunks * 64 * pitch * k.blocks || k.buf_bytes != k.x_bytes + 32 * MF * k.kg * (2 * k.steps + 1) * RUN) return 52;
-            if (pd.lds_bytes < (size_t)2 * k.buf_bytes + (size_t)8 * k.steps * RUN || pd.lds_bytes < (size_t)(k.ps / 2) * k.tg * k.cb * k.kg * MF * G * 4096) return 53;
+            if (k.last_rows != P - (int64_t)(k.bands - 1) * k.PB || k.last_cols != Q - (int64_t)(k.cbands - 1) * k.QB) return 56;
+            if (!i8 && ((k.last_rows < k.PB) != (k.table_row > 0) || (k.last_cols < k.QB) != (k.table_col > 0))) return 57;
+            if (k.table_row + k.table_col + 2 * k.steps * RUN > k.tables * 2 * k.steps * RUN || k.table_col % (2 * k.steps * RUN)) return 58;
+            if (pd.lds_bytes < (size_t)2 * k.buf_bytes + (size_t)8 * k.steps * RUN * k.tables || pd.lds_bytes < (size_t)(k.ps / 2) * k.tg * k.cb * k.kg * MF * G * 4096) return 53;
             if ((int64_t)(k.NI + 1) * K * P * Q >= ((int64_t)1 << 31) || (int64_t)k.NI * C * H * Wd >= ((int64_t)1 << 29)) return 54;
             if (pd.tch * pd.tap_chunks < k.T || pd.reduce_lds > (size_t)64 * 1024 || pd.reduce_lds < (size_t)pd.zg * 64 * pd.tch * 16) return 55;
         }

@@ -229,6 +229,36 @@ def test_conv_dw_general_kernel_edges(case):
     _check(p8, run_conv(p8))
 
 
+# bands of rows, of rows and columns, whole images; strides that leave pixels without a tap
+@pytest.mark.parametrize("case", [(2, 20, 41, 151, 30, 5, 3, 2, 1), (2, 12, 13, 11, 20, 5, 5, 2, 2), (1, 3, 50, 46, 20, 7, 7, 3, 2), (1, 3, 51, 47, 17, 11, 11, 2, 4),
+                                  (2, 70, 60, 57, 130, 2, 3, 1, 3), (8, 33, 56, 56, 40, 5, 5, 2, 1), (2, 64, 58, 60, 70, 1, 1, 0, 2)])
+def test_conv_dw_non_finite_activations_stay_with_their_taps(case):
+    """A NaN in the last pixel reaches the taps that pair it with an output pixel and no other (5 * NaN and 0 * NaN are NaN;
+    a tap without such a pair has the oracle's value)."""
+    from gpu_util import check_products, run_conv
+    from oracle import oracle as O
+    p = _problem(*case[:8], stride=case[8])
+    N, C, H, Wd, K, R, S, pad, st = case
+    P, Q = (H + 2 * pad - R) // st + 1, (Wd + 2 * pad - S) // st + 1
+    hit = np.zeros((H, Wd), bool)
+    hit[-1, -1] = True
+    h = np.arange(P)[None, :] * st + np.arange(R)[:, None] - pad                    # [tap row][output row] -> input row
+    w = np.arange(Q)[None, :] * st + np.arange(S)[:, None] - pad
+    padded = np.zeros((H + 2 * pad, Wd + 2 * pad), bool)
+    padded[pad:pad + H, pad:pad + Wd] = hit
+    reached = np.array([[padded[np.ix_(h[r] + pad, w[s] + pad)].any() for s in range(S)] for r in range(R)])
+    assert not reached.all()
+    k_ref, _ = O.nsd(p.delta, p.step, p.seed)
+    zeroed = np.where(hit, np.float32(0), p.X)
+    ref = O.conv2d_backward(p.W, zeroed, codes=k_ref, step=p.step, stride=st, pad=pad)[1]
+    absref = O.conv2d_backward(np.abs(p.W), zeroed, codes=np.abs(k_ref), step=p.step, stride=st, pad=pad)[1]
+    p.X = np.where(hit, np.float32("nan"), p.X)
+    got = run_conv(p, want_dx=False)["dW"]
+    assert np.isnan(got[:, :, reached]).all()
+    apart = [a[:, :, ~reached].reshape(K, -1) for a in (got, ref, absref)]
+    check_products(*apart, p.name + " taps without a NaN")
+
+
 STRIDED = [  # N, C, H, Wd, K, R, S, pad, stride  (the strided layers of a ResNet: 3x3/2, 1x1/2 shortcuts, 7x7/2 stem)
     (2, 5, 9, 7, 6, 3, 3, 1, 2),
     (3, 16, 14, 14, 24, 3, 3, 1, 2),
