@@ -434,6 +434,13 @@ int dbp_plan_auto_conv2d(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K,
 int dbp_plan_auto_linear(int64_t B, int64_t in, int64_t out, int int8_x, int want_dx, int want_dw, int two_planes,
                          uint64_t *gather_below);
 
+/* Which kernel computes dW of a convolution on the matrix-core paths (aligned tensors, the workspace that
+ * dbp_conv2d_workspace_bytes reports; no GPU call): one of DBP_DW_*, -1 for invalid dimensions.  int8_x: X is DBP_I8; dense:
+ * dense_conv2d_backward instead of codes; two_planes: DBP_PATH_TWO_PLANES.  For tests and diagnostics. */
+enum { DBP_DW_GENERIC = 0, DBP_DW_3X3 = 1, DBP_DW_3X3_I8 = 2, DBP_DW_1X1 = 3, DBP_DW_GENERAL = 4 };
+int dbp_plan_conv2d_dw(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t stride, int64_t pad,
+                       int int8_x, int dense, int two_planes);
+
 #ifdef __cplusplus
 }
 #endif

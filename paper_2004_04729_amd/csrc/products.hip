@@ -1173,67 +1173,88 @@ static hipError_t conv_dx(const ConvArgs &a, const void *grad, Scale scale, hipS
     return conv_dx_run<MODE_G, MODE_G>(a, grad, scale, s);
 }
 
+// Which kernel computes a convolution's dW (the same for a launch and for dbp_plan_conv2d_dw), with its plan.
+struct ConvDwChoice { int kind; ConvDwPlan p3; ConvDwI8Plan p8; Conv1x1Plan p1; ConvDwtPlan pd; };
+
 template <int MODE>
-static hipError_t conv_dw(const ConvArgs &a, const void *grad, Scale scale, hipStream_t s)
+static ConvDwChoice conv_dw_choose(const ConvArgs &a, const void *grad)
 {
-    using Acc = typename ModeTraits<MODE>::Acc;
+    ConvDwChoice c{};
+    c.kind = DBP_DW_GENERIC;
     const size_t rb = relayout_bytes(a.K, a.C, a.R, a.S);
     if constexpr (MODE == MODE_I8) {
-        ConvDwI8Plan p8 = conv_dw_i8_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad);
-        if (p8.ok && a.stride == 1 && rb + p8.partial_bytes <= a.scratch_bytes && (uintptr_t)a.X % 4 == 0 && (uintptr_t)grad % 4 == 0) {
-            if (a.plan_only) return hipSuccess;
-            ConvDwI8Args &k = p8.args;
-            k.codes = (const int8_t *)grad; k.X = (const int8_t *)a.X; k.dW = (int32_t *)a.dW; k.partial = (int32_t *)((char *)a.scratch + rb);
-            k.gate = a.gate; k.Ct = (int)a.ct(); k.Kt = (int)a.kt();
-            return launch_conv_dw_i8(p8, s);
+        c.p8 = conv_dw_i8_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad);
+        if (c.p8.ok && a.stride == 1 && rb + c.p8.partial_bytes <= a.scratch_bytes && (uintptr_t)a.X % 4 == 0 && (uintptr_t)grad % 4 == 0) {
+            c.kind = DBP_DW_3X3_I8;
+            return c;
         }
     }
     if constexpr (MODE != MODE_F32) {
         constexpr bool I8 = MODE == MODE_I8;
-        ConvDwPlan pl = conv_dw_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, I8);
+        ConvDwPlan &pl = c.p3 = conv_dw_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, I8);
         const size_t xal = I8 ? 4 : 16;                              // aligned 4-element loads of both operands
         if (a.stride != 1 || rb + pl.partial_bytes > a.scratch_bytes || (uintptr_t)a.X % xal != 0 || (uintptr_t)grad % 4 != 0) pl.ok = false;
-        Conv1x1Plan p1 = conv1x1_dw_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, a.stride, I8 ? FC2I_KT : FC2_KT);
+        Conv1x1Plan &p1 = c.p1 = conv1x1_dw_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, a.stride, I8 ? FC2I_KT : FC2_KT);
         if (rb + p1.partial_bytes > a.scratch_bytes) p1.ok = false;
         // The general kernel takes what the two specialised forms do not, and what they are the slower ones for:
         //   * of the 3x3 kernel, rows that fill half (int8: a quarter) of its padded rows or less.  Whole products, 3x3 kernel / general (us): 64->64
         //     32x32 50 / 53, 128->128 28x28 59 / 67, 256->256 14x14 64 / 67, 8x8 63 / 48, 512->512 4x4 72 / 49; int8 14x14 37 / 40, 4x4 49 / 37;
         //   * of the batched 1x1 form, what its plan and the general kernel's say, by modelled time: 1024->256 14x14 38 / 53, 512->128 28x28
         //     48 / 55, 64->256 56x56 92 / 39, 256->64 56x56 94 / 46.
-        ConvDwtPlan pd;
-        pd.ok = false;
-        if (a.codes && !(pl.ok && a.Wd * (I8 ? 4 : 2) > pl.args.PW)) {
+        ConvDwtPlan &pd = c.pd;
+        if (!(pl.ok && a.Wd * (I8 ? 4 : 2) > pl.args.PW)) {
             pd = conv_dwt_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, a.stride, I8, a.two_planes && !I8 ? 2 : 3);
             // (a group of a grouped layer: images further apart than its own planes say)
             if (pd.ok && (rb + pd.partial_bytes > a.scratch_bytes || pd.args.NI * a.kt() * pd.args.P * pd.args.Q >= ((int64_t)1 << 30) ||
                           pd.args.NI * a.ct() * a.H * a.Wd >= ((int64_t)1 << 29))) pd.ok = false;
             if (pd.ok && p1.ok && p1.us <= pd.us + 7.0f) pd.ok = false;
         }
-        if (a.plan_only) {
-            // a gate (another kernel may take the product over) is a launch more, 4.5 us: not for the layers that only the general kernel serves
-            if (!pl.ok && !p1.ok) *a.plan_only = 1;
-            return hipSuccess;
+        c.kind = pd.ok ? DBP_DW_GENERAL : pl.ok ? DBP_DW_3X3 : p1.ok ? DBP_DW_1X1 : DBP_DW_GENERIC;
+    }
+    return c;
+}
+
+template <int MODE>
+static hipError_t conv_dw(const ConvArgs &a, const void *grad, Scale scale, hipStream_t s)
+{
+    using Acc = typename ModeTraits<MODE>::Acc;
+    const size_t rb = relayout_bytes(a.K, a.C, a.R, a.S);
+    ConvDwChoice c = conv_dw_choose<MODE>(a, grad);
+    if (a.plan_only) {
+        // the generic kernel takes no gate, and a gate (another kernel may take the product over) is a launch more, 4.5 us: not for the layers
+        // that only the general kernel serves
+        if (c.kind != DBP_DW_3X3_I8 && !c.p3.ok && !c.p1.ok) *a.plan_only = 1;
+        return hipSuccess;
+    }
+    if constexpr (MODE == MODE_I8) {
+        if (c.kind == DBP_DW_3X3_I8) {
+            ConvDwI8Args &k = c.p8.args;
+            k.codes = (const int8_t *)grad; k.X = (const int8_t *)a.X; k.dW = (int32_t *)a.dW; k.partial = (int32_t *)((char *)a.scratch + rb);
+            k.gate = a.gate; k.Ct = (int)a.ct(); k.Kt = (int)a.kt();
+            return launch_conv_dw_i8(c.p8, s);
         }
-        if (pd.ok) {
-            ConvDwtArgs &k = pd.args;
+    }
+    if constexpr (MODE != MODE_F32) {
+        constexpr bool I8 = MODE == MODE_I8;
+        if (c.kind == DBP_DW_GENERAL) {
+            ConvDwtArgs &k = c.pd.args;
             k.codes = (const int8_t *)grad; k.X = a.X; k.dW = a.dW; k.partial = (char *)a.scratch + rb; k.scale = scale; k.gate = a.gate;
             k.Ct = (int)a.ct(); k.Kt = (int)a.kt();
-            if constexpr (I8) return launch_conv_dwt<true, 1>(pd, s);
-            else return a.two_planes ? launch_conv_dwt<false, 2>(pd, s) : launch_conv_dwt<false, 3>(pd, s);
+            if constexpr (I8) return launch_conv_dwt<true, 1>(c.pd, s);
+            else return a.two_planes ? launch_conv_dwt<false, 2>(c.pd, s) : launch_conv_dwt<false, 3>(c.pd, s);
         }
-        if (pl.ok) {
-            ConvDwArgs &k = pl.args;
+        if (c.kind == DBP_DW_3X3) {
+            ConvDwArgs &k = c.p3.args;
             k.codes = (const int8_t *)grad; k.X = a.X; k.dW = a.dW; k.partial = (char *)a.scratch + rb; k.scale = scale; k.gate = a.gate;
             k.Ct = (int)a.ct(); k.Kt = (int)a.kt();
             if constexpr (MODE == MODE_BF16) {
                 if (a.two_planes)
-                    return a.pad == 1 ? launch_conv_dw_fast<MODE_BF16X2, 3, 3, 1, 1>(pl, s) : launch_conv_dw_fast<MODE_BF16X2, 3, 3, 0, 1>(pl, s);
+                    return a.pad == 1 ? launch_conv_dw_fast<MODE_BF16X2, 3, 3, 1, 1>(c.p3, s) : launch_conv_dw_fast<MODE_BF16X2, 3, 3, 0, 1>(c.p3, s);
             }
-            return a.pad == 1 ? launch_conv_dw_fast<MODE, 3, 3, 1, 1>(pl, s) : launch_conv_dw_fast<MODE, 3, 3, 0, 1>(pl, s);
+            return a.pad == 1 ? launch_conv_dw_fast<MODE, 3, 3, 1, 1>(c.p3, s) : launch_conv_dw_fast<MODE, 3, 3, 0, 1>(c.p3, s);
         }
-        if (p1.ok) return launch_conv1x1_dw<I8>(a, p1, (const int8_t *)grad, scale, (char *)a.scratch + rb, s);
+        if (c.kind == DBP_DW_1X1) return launch_conv1x1_dw<I8>(a, c.p1, (const int8_t *)grad, scale, (char *)a.scratch + rb, s);
     }
-    if (a.plan_only) { *a.plan_only = 1; return hipSuccess; }         // the generic kernel takes no gate
     ConvGeom g = make_geom(a, ModeTraits<MODE>::KCH, k_step<MODE>());
     const int CRS = g.C * g.R * g.S, Kred = g.N * g.PQp;
     ConvDwGradLoader<MODE> al{(const typename GradElem<MODE>::T *)grad, g};
@@ -1439,4 +1460,19 @@ extern "C" int dbp_plan_check_conv2d(int64_t N, int64_t C, int64_t H, int64_t Wd
     if (N <= 0 || C <= 0 || H <= 0 || Wd <= 0 || K <= 0 || R <= 0 || S <= 0 || stride <= 0 || pad < 0 || H + 2 * pad < R || Wd + 2 * pad < S) return -1;
     if (N > 65535 || C > 65535 || K > 65535 || H > 65535 || Wd > 65535 || R > 255 || S > 255 || pad > 255 || stride > 255) return -1;
     return dbp::check_conv_plans(N, C, H, Wd, K, R, S, stride, pad);
+}
+
+extern "C" int dbp_plan_conv2d_dw(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t stride, int64_t pad,
+                                  int int8_x, int dense, int two_planes)
+{
+    if (dbp_plan_check_conv2d(N, C, H, Wd, K, R, S, stride, pad) != 0) return -1;
+    // stand-ins for the tensors: the planners look at alignment only
+    char *fake = (char *)(uintptr_t)4096;
+    dbp::ConvArgs a{};
+    if (dense) a.dense = fake; else a.codes = (const int8_t *)fake;
+    a.X = fake; a.dW = fake; a.x_dtype = int8_x ? DBP_I8 : DBP_F32; a.two_planes = two_planes != 0;
+    a.N = N; a.C = C; a.H = H; a.Wd = Wd; a.K = K; a.R = R; a.S = S; a.pad = pad; a.stride = stride;
+    a.scratch = fake; a.scratch_bytes = dbp::conv_scratch_bytes(N, C, H, Wd, K, R, S, pad, stride);
+    if (int8_x) return dbp::conv_dw_choose<dbp::MODE_I8>(a, fake).kind;
+    return dense ? dbp::conv_dw_choose<dbp::MODE_F32>(a, fake).kind : dbp::conv_dw_choose<dbp::MODE_BF16>(a, fake).kind;
 }

@@ -229,6 +229,26 @@ def test_conv_dw_general_kernel_edges(case):
     _check(p8, run_conv(p8))
 
 
+# a dense int8 gradient over its whole range, on what serves codes: strides, odd planes, other kernel sizes, 1x1
+@pytest.mark.parametrize("case", [(2, 20, 40, 150, 30, 3, 3, 1, 1), (2, 12, 13, 11, 20, 5, 5, 2, 2), (9, 33, 3, 3, 65, 3, 3, 1, 1), (2, 70, 12, 12, 130, 2, 3, 1, 3),
+                                  (3, 70, 13, 13, 129, 1, 1, 0, 1), (20, 96, 9, 9, 96, 1, 1, 0, 2)])
+def test_dense_int8_conv_dw_bit_exact(case):
+    import torch
+    import paper_2004_04729_amd as dbp
+    from gpu_util import dev, stream
+    from oracle import oracle as O
+    N, C, H, Wd, K, R, S, pad, st = case
+    p = _problem(*case[:8], i8=True, stride=st)
+    rng = np.random.default_rng(N + C)
+    d8 = rng.integers(-128, 128, size=p.delta.shape, dtype=np.int8)
+    X8 = rng.integers(-128, 128, size=p.X.shape, dtype=np.int8)
+    dW = torch.full((K, C, R, S), -77, dtype=torch.int32, device="cuda:0")
+    ws = torch.empty(dbp.conv2d_workspace_bytes(N, C, H, Wd, K, R, S, st, pad, dbp.I8), dtype=torch.uint8, device="cuda:0")
+    dbp.dense_conv2d_backward(dev(d8), dev(p.W), dev(X8), dbp.I8, N, C, H, Wd, K, R, S, st, pad, None, dW, ws, stream())
+    torch.cuda.synchronize()
+    assert np.array_equal(dW.cpu().numpy(), O.conv2d_dw_i8(d8, X8, R, S, st, pad))
+
+
 # bands of rows, of rows and columns, whole images; strides that leave pixels without a tap
 @pytest.mark.parametrize("case", [(2, 20, 41, 151, 30, 5, 3, 2, 1), (2, 12, 13, 11, 20, 5, 5, 2, 2), (1, 3, 50, 46, 20, 7, 7, 3, 2), (1, 3, 51, 47, 17, 11, 11, 2, 4),
                                   (2, 70, 60, 57, 130, 2, 3, 1, 3), (8, 33, 56, 56, 40, 5, 5, 2, 1), (2, 64, 58, 60, 70, 1, 1, 0, 2)])

@@ -59,6 +59,25 @@ def test_conv_plans_stay_in_bounds():
     assert L.dbp_plan_check_conv2d(1, 1, 2, 2, 1, 5, 5, 1, 0) == -1
 
 
+GENERIC, THREE, THREE_I8, ONE, GENERAL = range(5)
+
+
+def _dw(N, C_, H, Wd, K, R, S, st, pad, i8=0, dense=0, two=0):
+    f = _lib().dbp_plan_conv2d_dw
+    f.argtypes, f.restype = [C.c_int64] * 9 + [C.c_int] * 3, C.c_int
+    return f(N, C_, H, Wd, K, R, S, st, pad, i8, dense, two)
+
+
+def test_conv_dw_of_dense_int8_runs_where_that_of_codes_does():
+    # an int8 gradient is an int8 gradient: strided layers, odd planes, odd kernels and 1x1 layers leave the generic kernel
+    for case in CONV:
+        assert _dw(*case, i8=1, dense=1) == _dw(*case, i8=1), case
+    for case in [(64, 128, 28, 28, 256, 3, 3, 2, 1), (64, 512, 7, 7, 512, 3, 3, 1, 1), (32, 96, 27, 27, 256, 5, 5, 1, 2), (64, 512, 14, 14, 1024, 1, 1, 2, 0)]:
+        assert _dw(*case, i8=1, dense=1) == GENERAL, case
+        assert _dw(*case, dense=1) == GENERIC, case                    # fp32 gradients have no other
+    assert _dw(1, 1, 2, 2, 1, 5, 5, 1, 0) == -1
+
+
 def test_conv_gather_plans_stay_in_bounds():
     # the gather kernels that scan the code planes: bands, tiles, LDS sizes, the reciprocals that replace divisions
     L = dbp.lib()
