@@ -15,6 +15,8 @@
 //   * a wavefront owns 32*MF output channels x 32 input channels x G taps in registers (one tap: x G blocks of input channels); the
 //     wavefronts of a workgroup divide output channels (kg), input channels (cb), taps (tg) and, where those are few, the steps (ps,
 //     added up through LDS at the end).
+//   * one tap with a stride reads every st-th pixel of every st-th row: only those are staged (1x1/2 512->1024 14x14 N=64: product 54 -> 43 us, with
+//     int8 activations 51 -> 34; the column matrix 43 and 36).
 //   * a unit is a band of output rows (or columns) of an image, or several small images; units go round the workgroups of a
 //     tile, LDS is double buffered: the next unit's operands are loaded before this unit's steps and written after them.
 //     Elements past a ragged band have zero codes and read the band's last pixels, not what lies behind them: a non-finite
@@ -49,6 +51,7 @@ struct ConvDwtArgs {
     const void   *X;              // [N][Ct][H][Wd]
     void *dW, *partial;           // [K][C][R][S]; partial: see conv_dwt_kernel's epilogue
     int N, C, H, Wd, K, S, T, st, pad, P, Q, Ct, Kt;    // T = R*S
+    int st_load, st_lds;                                // st as the step between LDS pixels in the image (one tap reads no others) or between outputs in LDS
     int PB, bands, QB, cbands, NI;                      // output rows / columns per unit, bands of them, images per unit
     int units, units_per_split, n_split;
     int frame_w, frame, chunks;                         // LDS pixels per row and per image of a unit; chunks of 64 of the unit's
@@ -126,7 +129,7 @@ __global__ __launch_bounds__((64 * DwtShape<G, ONE>::WAVES), 1) void conv_dwt_ke
             int row = f / a.runs_row, col = (f - row * a.runs_row) * RUN + (e - run * RUN);
             if (a.flat) { row = col / a.Q; col -= row * a.Q; }
             row = min(row, rows - 1); col = min(col, cols - 1);            // elements past the band: its last pixels, their codes are zero
-            t_pix[table * n + e] = (uint32_t)((img * a.frame + row * a.st * a.frame_w + col * a.st) * PITCH);
+            t_pix[table * n + e] = (uint32_t)((img * a.frame + row * a.st_lds * a.frame_w + col * a.st_lds) * PITCH);
         }
     }
     for (int i = tid; i < 2 * a.buf_bytes / 16; i += threads) dwt_lds[i] = uint4{0u, 0u, 0u, 0u};   // nothing unset is ever multiplied
@@ -139,6 +142,7 @@ __global__ __launch_bounds__((64 * DwtShape<G, ONE>::WAVES), 1) void conv_dwt_ke
         px_img = px / a.frame;
         const int f = px - px_img * a.frame;
         px_h = f / a.frame_w; px_w = f - px_h * a.frame_w;
+        px_h *= a.st_load; px_w *= a.st_load;
         px_off = px_img * a.Ct * HW + px_h * a.Wd + px_w;
         if (px_img >= a.NI) px_img = 1 << 24;                              // a pixel of no image
     }

@@ -393,6 +393,8 @@ ConvDwtPlan conv_dwt_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K
     double best = -1.0;
     int m = 8;
     const bool one = T == 1;
+    const int st_lds = one ? 1 : (int)stride;
+    k.st_load = one ? (int)stride : 1; k.st_lds = st_lds;
     if (one) { pl.G = C > 64 ? 4 : 2; k.tap_blocks = 1; k.tg = 1; }
     for (int G = 3; G <= 4 && !one; ++G) {
         const int most = G == 3 ? 12 : 8, groups = (int)((T + G - 1) / G), blocks = (groups + most - 1) / most, tg = (groups + blocks - 1) / blocks;
@@ -426,11 +428,11 @@ ConvDwtPlan conv_dwt_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K
             for (int wi = 0; wi < 8; ++wi) {
                 const int qb = widths[wi];
                 if (wi > 0 && (qb >= Q || k.tiny)) break;
-                const int fw = (int)((qb - 1) * stride + S);
+                const int fw = (int)((qb - 1) * st_lds + S);
                 if ((int)R * fw > max_px) continue;
                 const int cbands = (int)((Q + qb - 1) / qb);
                 const bool flat = wi == 0;
-                int pb = (int)((max_px / fw - R) / stride + 1), bands = 0, ni = 1, frame = 0, runs_row = 0, runs_img = 0, steps = 0, chunks = 0;
+                int pb = (int)((max_px / fw - R) / st_lds + 1), bands = 0, ni = 1, frame = 0, runs_row = 0, runs_img = 0, steps = 0, chunks = 0;
                 size_t lds = 0;
                 int tables = 1, last_rows = 0;
                 const int last_cols = (int)Q - (cbands - 1) * qb;
@@ -439,7 +441,7 @@ ConvDwtPlan conv_dwt_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K
                 for (; pb >= 1 && !fits; --pb) {                             // the tallest band (then the most images) whose codes fit beside it
                     bands = (int)((P + pb - 1) / pb);
                     pb = (int)((P + bands - 1) / bands);
-                    frame = (int)((pb - 1) * stride + R) * fw;
+                    frame = (int)((pb - 1) * st_lds + R) * fw;
                     last_rows = (int)P - (bands - 1) * pb;
                     tables = i8 ? 1 : (last_rows < pb ? 2 : 1) * (last_cols < qb ? 2 : 1);     // (integers have no NaN)
                     ni = 1;
@@ -1421,7 +1423,8 @@ static int check_conv_plans(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t
             // units cover the output, none is empty, and their frames what its taps reach
             if ((int64_t)k.bands * k.PB < P || (int64_t)(k.bands - 1) * k.PB >= P || (int64_t)k.cbands * k.QB < Q || (int64_t)(k.cbands - 1) * k.QB >= Q) return 44;
             if (k.units != (N + k.NI - 1) / k.NI * k.bands * k.cbands || (k.NI > 1 && (k.bands > 1 || k.cbands > 1)) || (k.flat && k.cbands > 1)) return 45;
-            if (k.frame_w < (k.QB - 1) * stride + S || (int64_t)k.frame < ((k.PB - 1) * stride + R) * k.frame_w || (int64_t)k.frame * k.NI > k.chunks * 64) return 46;
+            if (k.st_lds * k.st_load != stride || (k.st_load > 1 && k.T > 1) || (k.T == 1 && k.frame != k.PB * k.QB)) return 59;   // one tap: no pixel that it does not read
+            if (k.frame_w < (k.QB - 1) * k.st_lds + S || (int64_t)k.frame < ((k.PB - 1) * k.st_lds + R) * k.frame_w || (int64_t)k.frame * k.NI > k.chunks * 64) return 46;
             if ((int64_t)k.runs_row * RUN < (k.flat ? (int64_t)k.PB * k.QB : k.QB) || k.runs_img < k.runs_row * (k.flat ? 1 : k.PB) || k.runs_img * k.NI > 2 * k.steps) return 47;
             // wavefronts, channels and taps; staging within a thread's items
             if (k.tg * k.cb * k.kg * k.ps != pd.waves || pd.waves > (one || G == 4 ? 8 : 12) || (k.ps & (k.ps - 1)) || k.chunks > pd.waves) return 48;

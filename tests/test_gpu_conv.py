@@ -217,6 +217,8 @@ GENERAL_DW = [  # N, C, H, Wd, K, R, S, pad, stride: dW where no kernel for one 
     (2, 70, 12, 12, 130, 2, 3, 1, 3),       # six taps, stride 3
     (20, 96, 9, 9, 96, 1, 1, 0, 2),         # one tap with a stride, more than 64 input channels
     (3, 64, 17, 9, 129, 1, 1, 0, 1),        # one tap, up to 64 input channels
+    (3, 130, 57, 41, 70, 1, 1, 0, 2),       # one tap with a stride: bands of rows, the last image rows and columns without an output
+    (2, 20, 23, 19, 33, 1, 1, 1, 3),        # the same with padding
 ]
 
 
