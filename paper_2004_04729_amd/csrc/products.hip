@@ -506,6 +506,18 @@ ConvDwtPlan conv_dwt_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K
     return pl;
 }
 
+// Modelled time of dW on the generic kernel for layers of few input channels: a K step takes 4.4 us (int8, twice as deep, 9.4) with its loads and their checks, rounds of two
+// workgroups a CU, partial sums at 4.5 TB/s.  Within 17 % of 280 layers of up to 64 input channels.
+float conv_dw_generic_us(int64_t N, int64_t C, int64_t P, int64_t Q, int64_t K, int64_t taps, bool i8)
+{
+    const int step = i8 ? k_step<MODE_I8>() : k_step<MODE_BF16>(), cell = i8 ? 16 : 8;
+    const int64_t outputs = K * C * taps, tiles = ((K + TM - 1) / TM) * ((C * taps + TN - 1) / TN), Kred = N * ((P * Q + cell - 1) / cell * cell);
+    const Split sp = choose_split(tiles, Kred, step);
+    const float wgs = (float)tiles * sp.n / 256.0f, rounds = wgs > 2.0f ? wgs / 2.0f : 1.0f, steps = rounds * (float)(((sp.n > 1 ? sp.k_per : Kred) + step - 1) / step);
+    return (i8 ? 4.6f + 9.4f * steps : 3.3f + 4.4f * steps) + (i8 ? 11.3f : 8.4f) * (wgs < 2.0f ? wgs : 2.0f) +
+           (sp.n > 1 ? (i8 ? 4.2f : 2.0f) + (float)sp.n * outputs * 8.0f / 4.5e6f : 0.0f) + (i8 ? 0.0f : 2.9e-5f * outputs);
+}
+
 template <bool I8, int PL, int G, bool ONE, bool RAGGED>
 hipError_t launch_conv_dwt_as(const ConvDwtPlan &pl, hipStream_t s)
 {
@@ -1198,18 +1210,23 @@ static ConvDwChoice conv_dw_choose(const ConvArgs &a, const void *grad)
         if (a.stride != 1 || rb + pl.partial_bytes > a.scratch_bytes || (uintptr_t)a.X % xal != 0 || (uintptr_t)grad % 4 != 0) pl.ok = false;
         Conv1x1Plan &p1 = c.p1 = conv1x1_dw_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, a.stride, I8 ? FC2I_KT : FC2_KT);
         if (rb + p1.partial_bytes > a.scratch_bytes) p1.ok = false;
-        // The general kernel takes what the two specialised forms do not, and what they are the slower ones for:
-        //   * of the 3x3 kernel, rows that fill half (int8: a quarter) of its padded rows or less.  Whole products, 3x3 kernel / general (us): 64->64
-        //     32x32 50 / 53, 128->128 28x28 59 / 67, 256->256 14x14 64 / 67, 8x8 63 / 48, 512->512 4x4 72 / 49; int8 14x14 37 / 40, 4x4 49 / 37;
-        //   * of the batched 1x1 form, what its plan and the general kernel's say, by modelled time: 1024->256 14x14 38 / 53, 512->128 28x28
-        //     48 / 55, 64->256 56x56 92 / 39, 256->64 56x56 94 / 46.
+        // The general kernel takes what the two specialised forms do not, and what they are the slower ones for.  Products alone (us), fp32
+        // activations (int8 ones lie likewise):
+        //   * the 3x3 kernel where its padded rows are more than half (int8: a quarter) full, and small layers; 3x3 kernel / general: 64->64 32x32 52 / 58,
+        //     128->128 28x28 60 / 64, 256->256 14x14 64 / 67, narrow rows: 64->64 8x8 N=64 22 / 24, 512->512 4x4 109 / 56;
+        //   * the batched 1x1 form by modelled time: 1024->256 14x14 38 / 57, 512->128 28x28 51 / 58, 512->2048 7x7 40 / 55, 64->256 56x56 92 / 39;
+        //   * the generic kernel, by modelled time, where up to 16 input channels leave most of the general kernel's blocks of 32 empty: 1->20 5x5
+        //     28x28 N=64 34 / 43, 3->64 7x7/2 224x224 N=32 248 / 453, 16->32 3x3/2 32x32 N=128 55 / 34.
         ConvDwtPlan &pd = c.pd;
         if (!(pl.ok && a.Wd * (I8 ? 4 : 2) > pl.args.PW)) {
             pd = conv_dwt_plan(a.N, a.C, a.H, a.Wd, a.K, a.R, a.S, a.pad, a.stride, I8, a.two_planes && !I8 ? 2 : 3);
             // (a group of a grouped layer: images further apart than its own planes say)
             if (pd.ok && (rb + pd.partial_bytes > a.scratch_bytes || pd.args.NI * a.kt() * pd.args.P * pd.args.Q >= ((int64_t)1 << 30) ||
                           pd.args.NI * a.ct() * a.H * a.Wd >= ((int64_t)1 << 29))) pd.ok = false;
-            if (pd.ok && p1.ok && p1.us <= pd.us + 7.0f) pd.ok = false;
+            if (pd.ok && pl.ok && pd.us < 12.0f) pd.ok = false;
+            if (pd.ok && p1.ok && p1.us <= 15.0f + pd.us) pd.ok = false;
+            // (its own time is about 13 us of ends and 0.8 of the model's)
+            if (pd.ok && !pl.ok && !p1.ok && a.C <= 16 && conv_dw_generic_us(a.N, a.C, pd.args.P, pd.args.Q, a.K, a.R * a.S, I8) < 13.0f + 0.8f * pd.us) pd.ok = false;
         }
         c.kind = pd.ok ? DBP_DW_GENERAL : pl.ok ? DBP_DW_3X3 : p1.ok ? DBP_DW_1X1 : DBP_DW_GENERIC;
     }

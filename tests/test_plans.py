@@ -78,6 +78,29 @@ def test_conv_dw_of_dense_int8_runs_where_that_of_codes_does():
     assert _dw(1, 1, 2, 2, 1, 5, 5, 1, 0) == -1
 
 
+def test_conv_dw_kernels_are_the_faster_ones():
+    """The choice between the kernels for dW on layers where each was measured (the product alone, the next best kernel's time
+    in parentheses, us)."""
+    for want, cases in {
+        GENERIC: [(64, 1, 28, 28, 20, 5, 5, 1, 0),          # 34 (general 43): one input channel in a block of 32
+                  (32, 3, 224, 224, 64, 7, 7, 2, 3),        # 248 (453)
+                  (128, 1, 64, 64, 32, 5, 5, 2, 2),         # 59 (102)
+                  (1, 1, 12, 12, 64, 5, 5, 2, 0)],          # 10 (24)
+        GENERAL: [(64, 128, 28, 28, 256, 3, 3, 2, 1), (16, 64, 56, 56, 64, 5, 5, 1, 2), (32, 64, 56, 56, 256, 1, 1, 1, 0),
+                  (128, 16, 32, 32, 32, 3, 3, 2, 1), (128, 512, 4, 4, 512, 3, 3, 1, 1), (64, 512, 14, 14, 1024, 1, 1, 2, 0)],
+        ONE: [(64, 1024, 14, 14, 256, 1, 1, 1, 0), (64, 128, 28, 28, 512, 1, 1, 1, 0), (64, 512, 7, 7, 2048, 1, 1, 1, 0),      # 43 (52), 40 (55)
+              (61, 104, 8, 8, 232, 1, 1, 1, 0), (10, 128, 16, 16, 992, 1, 1, 1, 0)],                                   # 17 (22), 19 (27)
+        THREE: [(128, 64, 32, 32, 64, 3, 3, 1, 1), (64, 256, 14, 14, 256, 3, 3, 1, 1),
+                (20, 88, 8, 8, 32, 3, 3, 1, 1), (64, 64, 8, 8, 64, 3, 3, 1, 1)],                                       # 17 (20), 21 (24): small layers
+    }.items():
+        for case in cases:
+            assert _dw(*case) == want, (case, _dw(*case), want)
+    # int8 activations: 28 (40), 24 (40), 15 (20), 18 (20); 30 (41) the other way round
+    for case in [(64, 1024, 14, 14, 256, 1, 1, 1, 0), (64, 128, 28, 28, 512, 1, 1, 1, 0), (16, 216, 40, 40, 72, 1, 1, 1, 0), (28, 20, 20, 20, 146, 1, 1, 1, 0)]:
+        assert _dw(*case, i8=1) == ONE, case
+    assert _dw(1, 1, 12, 12, 64, 5, 5, 2, 0, i8=1) == GENERIC
+
+
 def test_conv_gather_plans_stay_in_bounds():
     # the gather kernels that scan the code planes: bands, tiles, LDS sizes, the reciprocals that replace divisions
     L = dbp.lib()
