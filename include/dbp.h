@@ -441,6 +441,11 @@ enum { DBP_DW_GENERIC = 0, DBP_DW_3X3 = 1, DBP_DW_3X3_I8 = 2, DBP_DW_1X1 = 3, DB
 int dbp_plan_conv2d_dw(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t stride, int64_t pad,
                        int int8_x, int dense, int two_planes);
 
+/* The same for the products of a fully connected layer: DBP_FC_* of dX, or'ed with that of dW << 4 (0: not asked for); -1 for
+ * invalid dimensions.  int8_w: dithered_linear_backward_q8. */
+enum { DBP_FC_GENERIC = 1, DBP_FC_DIRECT = 2, DBP_FC_STAGED = 3 };
+int dbp_plan_linear(int64_t B, int64_t in, int64_t out, int int8_x, int int8_w, int want_dx, int want_dw, int two_planes);
+
 #ifdef __cplusplus
 }
 #endif

@@ -659,7 +659,8 @@ struct FcdPlan { int mf, kw, n_split, steps_per_split, tiles_m, tiles, groups; s
 // Shape of one product on fc_direct_kernel, by modelled time: 32 or 64 rows a wavefront, the wavefronts that share a tile's
 // reduction, and (where that leaves most of `room` CUs idle and the partials fit `cap` bytes) splits over workgroups.
 // Calibrated on layers from 16x64x64 to 512x2048x2048: a step of a wavefront takes about 0.45 us (0.55 with 64 rows), twice that
-// where the dense operand comes from HBM; adding up through LDS about 0.5 us a halving; a second launch 5 us.
+// where the dense operand comes from HBM; adding up through LDS about 0.5 us a halving; a second launch 5 us, and from 32 splits on
+// 0.8 for every eight more that it adds (a latency each: dX of 32x64x8192 in 128 splits 24 us, in 16 splits of eight wavefronts 14); so one, as many as fit, or 16 in between.
 FcdPlan fcd_plan(int64_t M, int64_t N, int64_t K, bool i8, int room, size_t cap)
 {
     FcdPlan best{};
@@ -675,11 +676,11 @@ FcdPlan fcd_plan(int64_t M, int64_t N, int64_t K, bool i8, int room, size_t cap)
             int most = steps / (4 * kw);
             if (most > room / groups) most = (int)(room / groups);
             if (most > 1 && (size_t)most * M * N * 4 > cap) most = (int)(cap / ((size_t)M * N * 4));
-            for (int n = 1;; n = most) {
+            for (int n = 1;; n = n == 1 && most > 32 ? 16 : most) {
                 const int per = (steps + n - 1) / n, ns = (steps + per - 1) / per;
                 const float rounds = groups * ns <= room ? 1.0f : (float)(groups * ns) / room;
                 float us = rounds * (1.5f + (float)((per + kw - 1) / kw) * step + 0.5f * halvings);
-                if (ns > 1) us += 5.0f + (float)ns * M * N * 8.0f / 4.0e6f;
+                if (ns > 1) us += 5.0f + (ns > 32 ? 0.8f * (float)((ns - 25) / 8) : 0.0f) + (float)ns * M * N * 8.0f / 4.0e6f;
                 if (best.us < 0.0f || us < best.us)
                     best = FcdPlan{mf, kw, ns, per, (int)tm, (int)tiles, (int)groups, ns > 1 ? (size_t)ns * M * N * 4 : 0, us};
                 if (n >= most) break;
@@ -885,6 +886,53 @@ size_t conv_scratch_bytes(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K
     return relayout_bytes(K, C, R, S) + align_up(big, 256) + 256;
 }
 
+// Which kernel computes each product of a fully connected layer (the same for a launch and for dbp_plan_linear).
+struct FcChoice { bool dx_staged, dw_staged, dx_direct, dw_direct; };
+
+static FcChoice linear_choose(const LinearArgs &a)
+{
+    const int64_t B = a.B, in = a.in, out = a.out;
+    const bool dx_i8 = a.W8 != nullptr, dw_i8 = a.x_dtype == DBP_I8;
+    // What the staged kernels take: a full window of reduction indices, runs of 16 rows in dW, 32-bit lane offsets ...
+    const bool small_index = B * in < (1ll << 30) && out * in < (1ll << 30) && B * out < (1ll << 30);
+    const bool can_dx = a.dX && small_index && out >= (dx_i8 ? FC2I_KT : FC2_KT) && in >= (dx_i8 ? 8 : 4);
+    const bool can_dw = a.dW && small_index && B >= (dw_i8 ? FC2I_KT : FC2_KT) && out >= 16 && in >= (dw_i8 ? 8 : 4);
+    // ... and what they are the faster ones for, by multiply-adds of a product.  Two planes exist on the staged kernel only.
+    const double macs = (double)B * in * out;
+    const bool short_dx = B <= FC2_TM / 2, short_dw = out <= FC2_TM / 2, two = a.two_planes && !dx_i8;   // rows for half a tile at most
+    FcChoice c{};
+    if (a.dX && a.dW && dx_i8 == dw_i8) {
+        if (!short_dx && !short_dw) {
+            // one launch for both.  Direct / staged (us): 256x1024x1024 15 / 19, 160x2048x2048 29 / 24, 256x1024x4096 35 / 24
+            c.dx_staged = c.dw_staged = can_dx && can_dw && (macs > 3.0e8 || two);
+        } else if (macs > (dx_i8 ? 5.0e9 : 1.65e9)) {
+            // A product of few rows wastes most of its tiles, but the direct kernel cuts the dense operand again for every 32 or 64 rows.  Both
+            // direct / dX direct, dW staged / both staged (us): 32x8192x8192 146 / 105 / 141, 96x8192x8192 261 / 153 / 162, 128x8192x8192 281 / 160 / 160,
+            // 128x4096x4096 56 / 58 / 49, 64x4096x4096 43 / 44 / 56; with the rows in dX 4096x8192x100 116 / 113 / 82; int8 96x4096x16384 132 / 96 / 94, 128x8192x4096 49 / - / 54
+            c.dx_staged = can_dx && B > 96;
+            c.dw_staged = can_dw && out > 96;
+        }
+    } else {
+        // A product alone, or two kinds of product (a launch each).  Direct / staged (us): dX 160x1024x4096 22 / 25, 256x2048x2048 26 / 24. Alone: dX with few
+        // steps of reduction 512x8192x64 13 / 11; dW of many tiles 64x2048x2048 13 / 11, 59x2217x1811 14 / 11 (of few tiles 379x112x3790 16 / 26)
+        const bool alone = !a.dX || !a.dW;
+        c.dx_staged = can_dx && !short_dx && (macs > 3.0e8 || two || (alone && !dx_i8 && short_dw && macs > 2.0e8));
+        c.dw_staged = can_dw && !short_dw && (macs > 3.0e8 || two || (alone && !dw_i8 && (double)in * out > 1.5e6 && macs > 1.5e8));
+    }
+    for (int i8 = 0; i8 < 2; ++i8) {                                      // the per-workgroup item table is fixed
+        const bool dx_here = c.dx_staged && dx_i8 == (i8 != 0), dw_here = c.dw_staged && dw_i8 == (i8 != 0);
+        FcPlan pdx, pdw;
+        if (dx_here || dw_here) fc2_plans(B, in, out, dx_here, dw_here, pdx, pdw, i8 ? FC2I_KT : FC2_KT);
+        if ((dx_here ? pdx.tiles * pdx.n_split : 0) + (dw_here ? pdw.tiles * pdw.n_split : 0) > (int64_t)FC2_MAX_ITEMS * 256) {
+            if (dx_here) c.dx_staged = false;
+            if (dw_here) c.dw_staged = false;
+        }
+    }
+    c.dx_direct = a.dX && !c.dx_staged && fcd_ok(true, B, in, out, out, dx_i8);
+    c.dw_direct = a.dW && !c.dw_staged && fcd_ok(false, out, in, B, out, dw_i8);
+    return c;
+}
+
 // ------------------------------------------------------------------------------------------------
 // Fully connected layer.  dX = q.W : rows b, cols i, reduction o.   dW = q^T.X : rows o, cols i, reduction b.
 // ------------------------------------------------------------------------------------------------
@@ -897,32 +945,19 @@ hipError_t launch_linear_mfma(const LinearArgs &a, hipStream_t s)
     if (a.plan_only && (!a.codes || a.W8)) { *a.plan_only = 1; return hipSuccess; }
     if (a.codes) {
         const bool dx_i8 = a.W8 != nullptr, dw_i8 = a.x_dtype == DBP_I8;
-        const bool small_index = (int64_t)B * in < (1ll << 30) && (int64_t)out * in < (1ll << 30) && (int64_t)B * out < (1ll << 30);   // 32-bit lane offsets
-        // What the staged kernels take: more than half a tile of rows and a full window of reduction indices ...
-        auto staged_ok = [&](bool i8, int64_t M, int64_t K) { return M > FC2_TM / 2 && K >= (i8 ? FC2I_KT : FC2_KT) && in >= (i8 ? 8 : 4) && small_index; };
-        bool dx_staged = a.dX && staged_ok(dx_i8, B, out), dw_staged = a.dW && staged_ok(dw_i8, out, B);
-        // ... and what they are the faster ones for.  Whole calls, direct against staged (us): 256x1024x1024 19 / 24, 128x2048x2048 32 / 39,
-        // 512x512x1024 equal, 400x304x3000 43 / 29, 256x1024x4096 40 / 31: the line lies near 3e8 multiply-adds a product, and a layer
-        // with one product too short for a tile goes to the direct kernel whole.  Two planes exist on the staged kernel only.
-        const bool large = (double)B * in * out > 3.0e8 || (a.two_planes && !dx_i8);
-        if (!large || (a.dX && !dx_staged && !(dw_i8 && !dx_i8)) || (a.dW && !dw_staged && !(dw_i8 && !dx_i8))) dx_staged = dw_staged = false;
+        const FcChoice c = linear_choose(a);
         if (a.plan_only) {
             // gated: both requested products on kernels that take a gate, fp32 operands
-            if ((a.dX && !dx_staged && !fcd_ok(true, B, in, out, out, false)) || (a.dW && (dw_i8 || (!dw_staged && !fcd_ok(false, out, in, B, out, false))))) *a.plan_only = 1;
+            if ((a.dX && !c.dx_staged && !c.dx_direct) || (a.dW && (dw_i8 || (!c.dw_staged && !c.dw_direct)))) *a.plan_only = 1;
             return hipSuccess;
         }
         // staged products of one kind share a launch
         for (int i8 = 0; i8 < 2; ++i8) {
-            const bool dx_here = dx_staged && dx_i8 == (i8 != 0), dw_here = dw_staged && dw_i8 == (i8 != 0);
+            const bool dx_here = c.dx_staged && dx_i8 == (i8 != 0), dw_here = c.dw_staged && dw_i8 == (i8 != 0);
             if (!dx_here && !dw_here) continue;
             const int kt = i8 ? FC2I_KT : FC2_KT;
             FcPlan pdx, pdw;
             fc2_plans(B, in, out, dx_here, dw_here, pdx, pdw, kt);
-            if ((dx_here ? pdx.tiles * pdx.n_split : 0) + (dw_here ? pdw.tiles * pdw.n_split : 0) > (int64_t)FC2_MAX_ITEMS * 256) {
-                if (dx_here) dx_staged = false;                    // the per-workgroup item table is fixed
-                if (dw_here) dw_staged = false;
-                continue;
-            }
             const int gx = dx_here && dw_here ? fc2_group_plan(B, in, out, pdx, pdw, kt) : 0;
             static bool raised = false;
             if (!raised) {
@@ -961,14 +996,13 @@ hipError_t launch_linear_mfma(const LinearArgs &a, hipStream_t s)
             if (e != hipSuccess) return e;
         }
         // the rest in one launch of the direct kernel, or (rows shorter than its vectors) product by product on the generic one
-        const bool dx_direct = a.dX && !dx_staged && fcd_ok(true, B, in, out, out, dx_i8), dw_direct = a.dW && !dw_staged && fcd_ok(false, out, in, B, out, dw_i8);
-        if (dx_direct || dw_direct) {
-            e = launch_fc_direct(a, dx_direct, dw_direct, pending, s);
+        if (c.dx_direct || c.dw_direct) {
+            e = launch_fc_direct(a, c.dx_direct, c.dw_direct, pending, s);
             if (e != hipSuccess) return e;
             pending = StatsJob{};
         }
         if (pending.n || pending.bias_len) { e = launch_stats_job(pending, s); if (e != hipSuccess) return e; }
-        if (a.dX && !dx_staged && !dx_direct) {
+        if (a.dX && !c.dx_staged && !c.dx_direct) {
             if (dx_i8) {
                 MatrixLoader<MODE_I8, true, true>   al{a.codes, a.out, B, out};
                 MatrixLoader<MODE_I8, false, false> bl{a.W8, a.in, in, out};
@@ -980,7 +1014,7 @@ hipError_t launch_linear_mfma(const LinearArgs &a, hipStream_t s)
             }
             if (e != hipSuccess) return e;
         }
-        if (a.dW && !dw_staged && !dw_direct) {
+        if (a.dW && !c.dw_staged && !c.dw_direct) {
             if (dw_i8) {
                 MatrixLoader<MODE_I8, true, false>  al{a.codes, a.out, out, B};
                 MatrixLoader<MODE_I8, false, false> bl{(const int8_t *)a.X, a.in, in, B};
@@ -1495,4 +1529,16 @@ extern "C" int dbp_plan_conv2d_dw(int64_t N, int64_t C, int64_t H, int64_t Wd, i
     a.scratch = fake; a.scratch_bytes = dbp::conv_scratch_bytes(N, C, H, Wd, K, R, S, pad, stride);
     if (int8_x) return dbp::conv_dw_choose<dbp::MODE_I8>(a, fake).kind;
     return dense ? dbp::conv_dw_choose<dbp::MODE_F32>(a, fake).kind : dbp::conv_dw_choose<dbp::MODE_BF16>(a, fake).kind;
+}
+
+extern "C" int dbp_plan_linear(int64_t B, int64_t in, int64_t out, int int8_x, int int8_w, int want_dx, int want_dw, int two_planes)
+{
+    if (dbp_plan_check_linear(B, in, out) != 0 || (!want_dx && !want_dw)) return -1;
+    char *fake = (char *)(uintptr_t)4096;                            // stand-ins for the tensors
+    dbp::LinearArgs a{};
+    a.codes = (const int8_t *)fake; a.W8 = int8_w ? (const int8_t *)fake : nullptr; a.x_dtype = int8_x ? DBP_I8 : DBP_F32; a.two_planes = two_planes != 0;
+    a.B = B; a.in = in; a.out = out; a.dX = want_dx ? (float *)fake : nullptr; a.dW = want_dw ? fake : nullptr;
+    const dbp::FcChoice c = dbp::linear_choose(a);
+    auto kind = [](bool want, bool staged, bool direct) { return !want ? 0 : staged ? DBP_FC_STAGED : direct ? DBP_FC_DIRECT : DBP_FC_GENERIC; };
+    return kind(want_dx != 0, c.dx_staged, c.dx_direct) | kind(want_dw != 0, c.dw_staged, c.dw_direct) << 4;
 }

@@ -126,6 +126,27 @@ def test_fc_staged_kernels_take_ragged_layers(B, in_, out):
     assert np.array_equal(res["dW"], O.linear_dw_i8(O.nsd(p.delta, p.step, p.seed)[0], X8))
 
 
+# layers with a product too short for the staged kernel's tiles: above 1.65e9 multiply-adds the other product is staged, and
+# the short one from 97 rows on; ragged in every dimension
+@pytest.mark.parametrize("B,in_,out,kernels", [(97, 4103, 4205, (3, 3)), (33, 8191, 6211, (2, 3)), (4099, 6301, 67, (3, 2)), (4097, 4099, 100, (3, 3))])
+def test_fc_large_layers_with_a_short_product(B, in_, out, kernels):
+    from gpu_util import run_linear
+    from plan_util import fc_kernels
+    assert fc_kernels(B, in_, out) == kernels
+    p = _problem(B, in_, out, c=8.0)
+    _check_fp32(p, run_linear(p))
+
+
+# a product alone, staged from a lower line on: reductions of 33 (one window and one index) to 100, the narrowest rows (4; 3.06e8 multiply-adds)
+@pytest.mark.parametrize("B,in_,out,dx", [(33, 2301, 2003, 0), (64, 2049, 1301, 0), (8803, 4, 8701, 0), (530, 4001, 100, 1), (2100, 2003, 67, 1), (8701, 4, 8703, 1)])
+def test_fc_single_products_on_the_staged_kernel(B, in_, out, dx):
+    from gpu_util import run_linear
+    from plan_util import STAGED, fc_kernels
+    assert STAGED in fc_kernels(B, in_, out, dx=dx, dw=1 - dx)
+    p = _problem(B, in_, out, c=8.0)
+    _check_fp32(p, run_linear(p, want_dx=dx == 1, want_dw=dx == 0))
+
+
 def test_fc_results_are_deterministic_and_paths_agree_on_codes():
     import paper_2004_04729_amd as dbp
     from gpu_util import run_linear

@@ -101,6 +101,16 @@ def test_fc_q8_ragged_layers(B, in_, out):
     _fc(B, in_, out, seed=B + in_ + out, want_dx=False)
 
 
+# the staged kernel with a short product (above 5e9 multiply-adds), with a reduction of one window and one index, with the narrowest rows;
+# the direct kernel with its reduction split over workgroups
+@pytest.mark.parametrize("B,in_,out,dx,dw,kernels", [(65, 9001, 8603, 1, 1, (2, 3)), (97, 7307, 7109, 1, 1, (3, 3)), (65, 2203, 2201, 0, 1, (None, 3)),
+                                                     (6203, 8, 6201, 1, 1, (3, 3)), (9, 1001, 8203, 1, 1, (2, 2))])
+def test_fc_q8_staged_and_split_edges(B, in_, out, dx, dw, kernels):
+    from plan_util import fc_kernels
+    assert fc_kernels(B, in_, out, q8=1, dx=dx, dw=dw) == kernels
+    _fc(B, in_, out, seed=B, c=8.0, want_dx=dx == 1, want_dw=dw == 1)
+
+
 def test_fc_q8_single_products_and_dense_codes():
     _fc(70, 130, 90, seed=3, want_dw=False)
     _fc(70, 130, 90, seed=3, want_dx=False)

@@ -7,6 +7,7 @@ import itertools
 import pytest
 
 import paper_2004_04729_amd as dbp
+from plan_util import DIRECT, GENERAL, GENERIC, GENERIC_FC, ONE, STAGED, THREE, conv_dw_kernel as _dw, fc_kernels as _fc
 
 
 def _lib():
@@ -34,6 +35,27 @@ def test_fc_plans_cover_every_item_once_and_stay_in_bounds():
     assert L.dbp_plan_check_linear(0, 4, 4) == -1
 
 
+def test_fc_kernels_are_the_faster_ones():
+    """The choice between the direct and the staged kernel on layers where both were measured (us; dX direct and dW staged: mixed)."""
+    D, S = DIRECT, STAGED
+    for case, want in [((128, 8192, 8192), (S, S)),          # staged 160, direct 281
+                       ((96, 8192, 8192), (D, S)),           # mixed 153, staged 162, direct 261
+                       ((32, 8192, 8192), (D, S)),           # mixed 105, staged 141, direct 146
+                       ((128, 4096, 4096), (S, S)),          # 49, direct 56
+                       ((64, 4096, 4096), (D, D)),           # 43, mixed 44, staged 56
+                       ((4096, 8192, 100), (S, S)), ((4096, 8192, 64), (S, D)), ((2048, 4096, 16), (D, D)),      # 82 / 116, 66 / 81
+                       ((256, 4096, 4096), (S, S)), ((256, 1024, 4096), (S, S)), ((256, 1024, 1024), (D, D)), ((64, 784, 300), (D, D))]:
+        assert _fc(*case) == want, case
+    for case, want in [((128, 8192, 8192), (S, S)), ((96, 4096, 16384), (D, S)), ((128, 8192, 4096), (D, D)), ((128, 4096, 4096), (D, D)), ((256, 4096, 4096), (S, S))]:
+        assert _fc(*case, q8=1) == want, case
+    # a product alone
+    assert _fc(64, 2048, 2048, dx=0) == (None, S) and _fc(32, 1024, 1024, dx=0) == (None, D)                            # 11 / 13, 9 / 8
+    assert _fc(512, 8192, 64, dw=0) == (S, None) and _fc(64, 4096, 4096, dw=0) == (D, None)                              # 11 / 13, 37 / 25
+    assert _fc(4, 1, 4) == (GENERIC_FC, GENERIC_FC)
+    # two planes: the staged kernel wherever both products fill a tile
+    assert _fc(256, 300, 300, two=1) == (S, S) and _fc(64, 300, 300, two=1) == (D, D)
+
+
 CONV = [  # N, C, H, Wd, K, R, S, stride, pad
     (128, 64, 32, 32, 64, 3, 3, 1, 1), (64, 256, 14, 14, 256, 3, 3, 1, 1), (64, 1024, 14, 14, 256, 1, 1, 1, 0), (32, 256, 56, 56, 256, 3, 3, 1, 1),
     (64, 128, 28, 28, 256, 3, 3, 2, 1), (64, 256, 14, 14, 512, 3, 3, 2, 1), (64, 3, 224, 224, 64, 7, 7, 2, 3), (32, 64, 15, 15, 64, 3, 3, 1, 1),
@@ -57,15 +79,6 @@ def test_conv_plans_stay_in_bounds():
                 bad.append((N, C_, H, Wd, K, R, st, pad, e))
     assert not bad, bad[:10]
     assert L.dbp_plan_check_conv2d(1, 1, 2, 2, 1, 5, 5, 1, 0) == -1
-
-
-GENERIC, THREE, THREE_I8, ONE, GENERAL = range(5)
-
-
-def _dw(N, C_, H, Wd, K, R, S, st, pad, i8=0, dense=0, two=0):
-    f = _lib().dbp_plan_conv2d_dw
-    f.argtypes, f.restype = [C.c_int64] * 9 + [C.c_int] * 3, C.c_int
-    return f(N, C_, H, Wd, K, R, S, st, pad, i8, dense, two)
 
 
 def test_conv_dw_of_dense_int8_runs_where_that_of_codes_does():
