@@ -87,8 +87,10 @@ struct StatsJob {
     const int32_t *tile_sums = nullptr; const int8_t *bias_codes = nullptr;
     int64_t images = 0, plane = 0, tiles_per_row = 0; int run = 0;
     __host__ __device__ bool per_channel() const { return tile_sums || bias_codes; }
-    // workgroups a launch that takes this job along has to add
-    __host__ __device__ int64_t workgroups() const { return (n > 0 || (bias_len > 0 && !per_channel()) ? 1 : 0) + (per_channel() ? bias_len : 0); }
+    // workgroups for the bias gradient (a channel each, or kBiasPerGroup columns), and all that a launch that takes this job along has to add
+    static constexpr int kBiasPerGroup = 512;
+    __host__ __device__ int64_t bias_groups() const { return per_channel() ? bias_len : (bias_len + kBiasPerGroup - 1) / kBiasPerGroup; }
+    __host__ __device__ int64_t workgroups() const { return (n > 0 ? 1 : 0) + bias_groups(); }
 };
 __device__ __forceinline__ void write_density_flags(const StatsJob &j, uint64_t nnz)
 {

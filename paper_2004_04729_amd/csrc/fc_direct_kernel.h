@@ -41,7 +41,7 @@ struct FcdProblem {
     int form;                            // fcd_form(int8, kfast, MF)
     Scale scale;
 };
-// Workgroups [0, first1) take problem 0, the others problem 1, the last job.workgroups() the quantiser's pending sums.
+// The first stats.workgroups() take the quantiser's pending sums (short, so not behind a round of products), the next first1 problem 0, the others problem 1.
 struct FcdArgs { FcdProblem prob[2]; int first1; StatsJob stats; Gate gate; };
 
 __host__ __device__ constexpr int fcd_form(bool i8, bool kfast, int mf) { return (i8 ? 16 : 0) | (kfast ? 8 : 0) | mf; }
@@ -302,11 +302,11 @@ __global__ __launch_bounds__(64 * FCD_WAVES, 1) void fc_direct_kernel(FcdArgs a)
 {
     if (a.gate.closed()) return;
     extern __shared__ uint4 fcd_lds[];
-    const int work = (int)gridDim.x - (int)a.stats.workgroups();
-    if ((int)blockIdx.x >= work) { side_job(a.stats, (int)blockIdx.x - work, 64 * FCD_WAVES); return; }
-    const bool second = (int)blockIdx.x >= a.first1;
+    const int block = (int)blockIdx.x - (int)a.stats.workgroups();
+    if (block < 0) { side_job(a.stats, (int)blockIdx.x, 64 * FCD_WAVES); return; }
+    const bool second = block >= a.first1;
     const FcdProblem &p = a.prob[second ? 1 : 0];
-    const int local = (int)blockIdx.x - (second ? a.first1 : 0);
+    const int local = block - (second ? a.first1 : 0);
     switch (p.form) {
     case fcd_form(false, true, 1):  fcd_tile<false, true, 1>(p, local, fcd_lds); break;
     case fcd_form(false, true, 2):  fcd_tile<false, true, 2>(p, local, fcd_lds); break;

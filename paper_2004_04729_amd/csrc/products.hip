@@ -1506,6 +1506,11 @@ extern "C" int dbp_plan_check_linear(int64_t B, int64_t in, int64_t out)
             const int e = dbp::check_fc2_pair(B, in, out, (m & 1) != 0, (m & 2) != 0, kt);
             if (e) return e;
         }
+    // the bias gradient beside a product: 512 columns a workgroup
+    dbp::StatsJob job{};
+    job.n = 1; job.bias_len = out;
+    const int64_t columns = (job.workgroups() - 1) * dbp::StatsJob::kBiasPerGroup;
+    if (columns < out || columns - dbp::StatsJob::kBiasPerGroup >= out) return 11;
     return 0;
 }
 

@@ -64,9 +64,9 @@ __device__ __forceinline__ void bias_of_channel(const StatsJob &j, int ch, int N
     }
 }
 
-// The statistics and the bias gradient from int64 sums, by one workgroup of NT (at most 1024) threads.  All loads are in flight at once (the
-// sums are of integers: any order gives the same result).
-__device__ __forceinline__ void side_sums(const StatsJob &job, int NT)
+// The statistics, by one workgroup of NT (at most 1024) threads.  All loads are in flight at once (the sums are of integers: any order
+// gives the same result).
+__device__ __forceinline__ void side_stats(const StatsJob &job, int NT)
 {
     if (job.n > 0) {
         __shared__ uint64_t s_sum[3][16];
@@ -98,17 +98,17 @@ __device__ __forceinline__ void side_sums(const StatsJob &job, int NT)
             write_density_flags(job, nnz);
         }
     }
-    if (job.bias_len > 0 && !job.per_channel()) {
-        const double d = job.step_dev ? (double)job.step_dev[0] : (double)job.step;
-        for (int64_t i = threadIdx.x; i < job.bias_len; i += NT) job.bias_grad[i] = (float)(d * (double)job.bias_sums[i]);
-    }
 }
 
-// Workgroup `i` of job.workgroups(): the channels' bias gradients first, then the sums.
+// Workgroup `i` of job.workgroups(): the bias gradient first (from int64 sums a stretch of columns each: one workgroup for all of them is a chain of
+// memory latencies, the call of 16x64x65536 81 us instead of 44), then the statistics.
 __device__ __forceinline__ void side_job(const StatsJob &job, int i, int NT)
 {
-    if (job.per_channel() && i < (int)job.bias_len) bias_of_channel(job, i, NT);
-    else side_sums(job, NT);
+    if (i >= (int)job.bias_groups()) { side_stats(job, NT); return; }
+    if (job.per_channel()) { bias_of_channel(job, i, NT); return; }
+    const double d = job.step_dev ? (double)job.step_dev[0] : (double)job.step;
+    const int64_t first = (int64_t)i * StatsJob::kBiasPerGroup, end = min(job.bias_len, first + StatsJob::kBiasPerGroup);
+    for (int64_t c = first + threadIdx.x; c < end; c += NT) job.bias_grad[c] = (float)(d * (double)job.bias_sums[c]);
 }
 
 }  // namespace dbp

@@ -270,6 +270,33 @@ def test_conv_layer_backward_through_the_dw_gate(s, flags):
     assert got == flags
 
 
+# columns around what a workgroup takes (512), many workgroups with a remainder; beside the direct kernel's products and alone
+@pytest.mark.parametrize("out", [1, 511, 512, 513, 1025, 70001])
+@pytest.mark.parametrize("products", [True, False])
+def test_fc_bias_gradient_of_wide_layers(out, products):
+    import torch
+    import paper_2004_04729_amd as dbp
+    from gpu_util import stream
+    from oracle import oracle as O
+    B, in_ = 5, 6
+    rng = np.random.default_rng(out)
+    da = rng.laplace(0, 5e-4, size=(B, out)).astype(np.float32)
+    a = np.maximum(rng.standard_normal((B, out)), 0).astype(np.float32)
+    W, X = rng.standard_normal((out, in_)).astype(np.float32), rng.standard_normal((B, in_)).astype(np.float32)
+    db = torch.full((out,), float("nan"), dtype=torch.float32, device="cuda:0")
+    dX = torch.empty((B, in_), dtype=torch.float32, device="cuda:0") if products else None
+    dW = torch.empty((out, in_), dtype=torch.float32, device="cuda:0") if products else None
+    ws = torch.empty(dbp.linear_layer_workspace_bytes(B, in_, out, dbp.F32), dtype=torch.uint8, device="cuda:0")
+    st = torch.zeros(32, dtype=torch.uint8, device="cuda:0")
+    dbp.dithered_linear_layer_backward(_dev(da), _dev(a), _dev(W), _dev(X), dbp.F32, B, in_, out, 4.0, 1, 0, None, dX, dW, db, None, ws, st, dbp.PATH_AUTO, stream())
+    torch.cuda.synchronize()
+    dz = O.relu_backward(da, a)
+    step, _ = O.step_size(dz, 4.0)
+    k_ref, st_ref = O.nsd(dz, step, 1)
+    assert dbp.Stats.from_tensor(st).nnz == st_ref.nnz
+    assert np.array_equal(db.cpu().numpy(), O.bias_grad(k_ref, B, out, True, out, step)[1])
+
+
 # planes below one 16-byte piece, of odd sizes, of whole pieces; more than 64 KiB of codes a channel in planes of one tile, of
 # several with a remainder, and of whole runs of tiles (3 to a run: stretches that end inside a row and with it)
 @pytest.mark.parametrize("N,K,P,Q", [(5, 3, 1, 1), (4, 6, 3, 5), (3, 7, 7, 7), (70, 5, 14, 14), (2, 3, 181, 181), (400, 2, 13, 13), (300, 3, 15, 18), (96, 65, 32, 33)])
