@@ -506,12 +506,23 @@ __global__ __launch_bounds__(256) void std_tree_kernel(const float *delta, const
             *(f32x4 *)(s_v + 4 * ((c & ~3) | ((c + (c >> 3)) & 3))) = d[q];
         }
     } else {
+        // the last workgroup of a tensor that 4096 does not divide, or an address that 16 bytes do not: all its loads in flight too, past the end the
+        // last element again (behind a test for every element they came one at a time: 200x1000 with activations, the call 4 us longer)
+        const int last = (int)min(n - 1 - block0, (int64_t)4095);
+        float x[16], m[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) x[q] = delta[block0 + min(256 * q + tid, last)];
+        if (act) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) m[q] = act[block0 + min(256 * q + tid, last)];
+        } else {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) m[q] = 1.f;
+        }
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const int e = 256 * q + tid, c = e >> 2;
-            float x = 0.f;
-            if (block0 + e < n) { x = delta[block0 + e]; if (act) x = act[block0 + e] > 0.0f ? x : 0.0f; }
-            s_v[4 * ((c & ~3) | ((c + (c >> 3)) & 3)) + (e & 3)] = x;
+            s_v[4 * ((c & ~3) | ((c + (c >> 3)) & 3)) + (e & 3)] = e <= last && m[q] > 0.0f ? x[q] : 0.f;
         }
     }
     __syncthreads();
