@@ -3,9 +3,9 @@
 //   dX[b,i] = Delta * sum_o code[b,o] W[o,i]      A = codes, reduction index contiguous  (KFAST)
 //   dW[o,i] = Delta * sum_b code[b,o] X[b,i]      A = codes^T, reduction index strided
 //
-// The kernels of fc_kernel.h and fc2_kernel.h stage tiles through LDS, which pays for large products and wants aligned, whole
-// vectors.  What is left -- layers of a few workgroups, widths that no vector divides -- is bound by the latency of a chain of
-// (load, stage, barrier, multiply) steps with an idle chip around it.  Here a WAVEFRONT is the unit:
+// The kernels of fc2_kernel.h and fc2_i8_kernel.h stage tiles through LDS, which pays for large products (the choice: linear_choose).  What
+// is left -- layers of a few workgroups -- is bound by the latency of a chain of (load, stage, barrier, multiply) steps with an idle
+// chip around it.  Here a WAVEFRONT is the unit:
 //   * it owns 32*MF rows x 32*NF columns and loads its matrix-core fragments directly.  The dense operand is stored
 //     [reduction][column]: a lane loads NF adjacent columns of 8 (16 in the int8 form) reduction indices, 256 (128) contiguous
 //     bytes per half wavefront and row, and they become the lane's elements of NF fragments -- fragment j covers columns

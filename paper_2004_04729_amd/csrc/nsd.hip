@@ -825,7 +825,6 @@ hipError_t launch_nsd(const NsdArgs &a_in, hipStream_t s, StatsJob *defer)
         else if (a.tile_sums) later.tile_sums = a.tile_sums;
         else later.bias_sums = a.bias_sums;
     }
-    if (a.bias_from_codes) a.bias_sums = nullptr;
     // Without the format and without sums by row or column the shape means nothing: one row, whole tiles but for the last, aligned
     // loads whatever the row length (7x7 planes had 49 of a tile's 256 lanes' columns in use and loads of one element).
     if (!a.bitmap && !a.topk_thr && !a.bias_sums && !a.tile_sums) {
@@ -863,7 +862,7 @@ hipError_t launch_nsd(const NsdArgs &a_in, hipStream_t s, StatsJob *defer)
     a.wave_stride_segs = jump % a.tiles_per_row;
     const dim3 grid((unsigned)blocks), block(256);
     const bool ex = a.act || a.step_dev || a.bias_sums || a.tile_sums;
-    if (a.bias_sums && !a.bias_zeroed && !a.tile_sums && !a.bias_from_codes) {
+    if (a.bias_sums && !a.bias_zeroed) {
         const int64_t zb = (a.bias_len + 255) / 256;
         hipLaunchKernelGGL(zero_i64_kernel, dim3((unsigned)(zb < 1024 ? zb : 1024)), dim3(256), 0, s, a.bias_sums, a.bias_len);
     }

@@ -374,8 +374,8 @@ hipError_t launch_conv_dw_i8(const ConvDwI8Plan &pl, hipStream_t s)
     return hipGetLastError();
 }
 
-// Geometry of the general dW kernel (conv_dwt_kernel.h), or ok == false when it does not apply (planes below one run of codes,
-// more than 62 taps, frames that do not fit).
+// Geometry of the general dW kernel (conv_dwt_kernel.h), or ok == false when it does not apply (more than 4096 taps, frames that do not
+// fit, 32-bit offsets).
 struct ConvDwtPlan { bool ok; int G, waves, grid, reduce_grid, tch, tap_chunks, zg; ConvDwtArgs args; size_t lds_bytes, partial_bytes, reduce_lds; float us; };
 
 ConvDwtPlan conv_dwt_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t pad, int64_t stride, bool i8, int planes)
@@ -790,7 +790,7 @@ Conv1x1Plan conv1x1_dw_plan(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t
     const int64_t PQ = H * Wd;
     if (!(R == 1 && S == 1 && pad == 0 && stride == 1)) return pl;
     pl.kt = kt;
-    if (K < FC2_TM / 4 || C < 4 || PQ < kt) return pl;              // row tiles at least a quarter full (lowering costs more than the idle rows); whole windows
+    if (K < FC2_TM / 4 || C < 4 || PQ < kt) return pl;              // row tiles at least a quarter full; whole windows
     if (C * PQ >= ((int64_t)1 << 29) || K * PQ >= ((int64_t)1 << 31) || K * C >= ((int64_t)1 << 30)) return pl;   // 32-bit lane offsets
     pl.spi = (int)((PQ + kt - 1) / kt);
     if (N * pl.spi >= ((int64_t)1 << 25)) return pl;                              // the reduction axis counts windows of kt
@@ -1402,6 +1402,31 @@ static int check_fc2_pair(int64_t B, int64_t in, int64_t out, bool want_dx, bool
     return 0;
 }
 
+// The direct kernel's plans of a call, made as the launch makes them, with `scratch` bytes for the partial sums.
+static int check_fcd(int64_t B, int64_t in, int64_t out, bool want_dx, bool want_dw, bool dx_i8, bool dw_i8, size_t scratch)
+{
+    size_t left = scratch & ~(size_t)255, used = 0;
+    const int room = want_dx && want_dw ? 128 : 256;
+    for (int q = 0; q < 2; ++q) {
+        const bool kfast = q == 0, i8 = kfast ? dx_i8 : dw_i8;
+        const int64_t M = kfast ? B : out, K = kfast ? out : B, kt = i8 ? 32 : 16, tn = fcd_tn(i8), steps = (K + kt - 1) / kt;
+        if (!(kfast ? want_dx : want_dw) || !fcd_ok(kfast, M, in, K, out, i8)) continue;
+        const FcdPlan pl = fcd_plan(M, in, K, i8, room, left);
+        if (pl.us < 0.0f || pl.mf < 1 || pl.mf > (i8 ? 1 : 2) || pl.kw < 1 || pl.kw > FCD_WAVES || (pl.kw & (pl.kw - 1)) || pl.kw > steps) return 12;
+        // every tile has its wavefronts, no workgroup is empty, the reduction's parts cover it and none is empty
+        if (pl.tiles_m != (M + 32 * pl.mf - 1) / (32 * pl.mf) || pl.tiles != pl.tiles_m * ((in + tn - 1) / tn)) return 13;
+        if ((int64_t)pl.groups * FCD_WAVES < (int64_t)pl.tiles * pl.kw || (int64_t)(pl.groups - 1) * FCD_WAVES >= (int64_t)pl.tiles * pl.kw) return 14;
+        if ((int64_t)pl.n_split * pl.steps_per_split < steps || (int64_t)(pl.n_split - 1) * pl.steps_per_split >= steps) return 15;
+        if (pl.partial_bytes != (pl.n_split > 1 ? (size_t)pl.n_split * M * in * 4 : 0) || used + pl.partial_bytes > scratch) return 16;
+        if ((size_t)(FCD_WAVES / 2) * pl.mf * tn * 32 * 4 > (size_t)64 * 1024) return 17;
+        // 32-bit lane offsets: a window of rows of the dense operand, the codes
+        if (((K < kt ? K : kt) * in + in) * (i8 ? 1 : 4) >= ((int64_t)1 << 32) || (kfast ? M * out : (K < kt ? K : kt) * out + out) >= ((int64_t)1 << 32)) return 18;
+        const size_t take = align_up(pl.partial_bytes, 256);
+        used += take; left = left > take ? left - take : 0;
+    }
+    return 0;
+}
+
 static int check_conv_plans(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t stride, int64_t pad)
 {
     const int64_t P = (H + 2 * pad - R) / stride + 1, Q = (Wd + 2 * pad - S) / stride + 1;
@@ -1506,6 +1531,13 @@ extern "C" int dbp_plan_check_linear(int64_t B, int64_t in, int64_t out)
             const int e = dbp::check_fc2_pair(B, in, out, (m & 1) != 0, (m & 2) != 0, kt);
             if (e) return e;
         }
+    // the direct kernel: fp32, int8 activations, int8 both; the workspace there is, and next to none
+    for (int m = 1; m < 4; ++m)
+        for (int i8 = 0; i8 < 3; ++i8)
+            for (int small = 0; small < 2; ++small) {
+                const int e = dbp::check_fcd(B, in, out, (m & 1) != 0, (m & 2) != 0, i8 == 2, i8 > 0, small ? 1000 : dbp::linear_scratch_bytes(B, in, out));
+                if (e) return e;
+            }
     // the bias gradient beside a product: 512 columns a workgroup
     dbp::StatsJob job{};
     job.n = 1; job.bias_len = out;

@@ -138,17 +138,17 @@ def test_conv_int8_whole_cell_rows_bit_exact(case):
     _check(p, run_conv(p))
 
 
-LOWERED = [  # N, C, H, Wd, K, R, S, pad, stride: large enough that dW runs as column matrix x fully connected kernels
-    (32, 128, 14, 14, 256, 1, 1, 0, 1),     # 1x1: the column matrix is the transposed activations
+LARGER_DW = [  # N, C, H, Wd, K, R, S, pad, stride: more than 2e8 multiply-adds, off the 3x3 kernel
+    (32, 128, 14, 14, 256, 1, 1, 0, 1),     # 1x1: the batched form
     (16, 64, 28, 28, 128, 3, 3, 1, 2),      # 3x3 / 2
     (8, 32, 20, 20, 96, 5, 5, 2, 1),        # 5x5, several bands of rows per image
-    (16, 64, 15, 15, 128, 3, 3, 1, 1),      # rows of 15 pixels: codes re-laid a byte at a time
+    (16, 64, 15, 15, 128, 3, 3, 1, 1),      # rows of 15 pixels
     (64, 132, 24, 20, 264, 1, 1, 0, 2),     # 1x1 / 2, channel counts that are not tile multiples
 ]
 
 
-@pytest.mark.parametrize("case", LOWERED)
-def test_conv_dw_lowered_to_fc_kernels(case):
+@pytest.mark.parametrize("case", LARGER_DW)
+def test_conv_dw_of_larger_layers(case):
     from gpu_util import run_conv
     p = _problem(*case[:8], stride=case[8])
     _check(p, run_conv(p))
@@ -170,13 +170,19 @@ ONE_BY_ONE = [  # N, C, H, Wd, K: 1x1, stride 1, no padding, more than 128 outpu
 ONE_BY_ONE += [             # pixel and channel counts that no vector divides
     (4, 37, 7, 9, 70),
     (3, 70, 13, 13, 129),
+    (9, 130, 7, 9, 190),
+    (6, 517, 7, 7, 261),
+    (12, 261, 9, 9, 517),
 ]
+ON_GENERAL = [(4, 36, 14, 14, 130), (5, 16, 6, 6, 140), (6, 96, 12, 12, 64), (3, 70, 13, 13, 129)]      # by modelled time, with fp32 activations
 
 
 @pytest.mark.parametrize("case", ONE_BY_ONE)
 def test_conv_1x1_dw_batched_fc_kernel(case):
     from gpu_util import run_conv
+    from plan_util import GENERAL, ONE, conv_dw_kernel
     N, C, H, Wd, K = case
+    assert conv_dw_kernel(*case, 1, 1, 1, 0) == (GENERAL if case in ON_GENERAL else ONE)
     p = _problem(N, C, H, Wd, K, 1, 1, 0)
     _check(p, run_conv(p))
 
@@ -193,13 +199,15 @@ ONE_BY_ONE_I8 = [  # the same with int8 activations: windows of 64 pixels
 ]
 
 
-ONE_BY_ONE_I8 += [(4, 37, 9, 9, 70), (3, 70, 13, 13, 129)]
+ONE_BY_ONE_I8 += [(4, 37, 9, 9, 70), (3, 70, 13, 13, 129), (12, 261, 9, 9, 517)]
 
 
 @pytest.mark.parametrize("case", ONE_BY_ONE_I8)
 def test_conv_1x1_dw_batched_fc_kernel_int8_bit_exact(case):
     from gpu_util import run_conv
+    from plan_util import GENERAL, ONE, conv_dw_kernel
     N, C, H, Wd, K = case
+    assert conv_dw_kernel(*case, 1, 1, 1, 0, i8=1) == (GENERAL if H * Wd < 64 else ONE)
     p = _problem(N, C, H, Wd, K, 1, 1, 0, c=1.0, i8=True)
     _check(p, run_conv(p))
 
@@ -219,12 +227,17 @@ GENERAL_DW = [  # N, C, H, Wd, K, R, S, pad, stride: dW where no kernel for one 
     (3, 64, 17, 9, 129, 1, 1, 0, 1),        # one tap, up to 64 input channels
     (3, 130, 57, 41, 70, 1, 1, 0, 2),       # one tap with a stride: bands of rows, the last image rows and columns without an output
     (2, 20, 23, 19, 33, 1, 1, 1, 3),        # the same with padding
+    # above 16 input channels what the generic kernel takes below: planes one code short of a run (fp32, int8), many images a unit, 25 and 121 taps
+    (3, 20, 1, 7, 6, 1, 1, 0, 1), (2, 18, 3, 5, 24, 3, 3, 1, 1), (300, 64, 4, 4, 130, 3, 3, 1, 1), (2, 20, 13, 11, 20, 5, 5, 2, 2), (1, 20, 51, 47, 17, 11, 11, 2, 4),
 ]
 
 
 @pytest.mark.parametrize("case", GENERAL_DW)
 def test_conv_dw_general_kernel_edges(case):
     from gpu_util import run_conv
+    from plan_util import GENERAL, conv_dw_kernel
+    if case[1] > 16:
+        assert conv_dw_kernel(*case[:7], case[8], case[7]) == GENERAL
     p = _problem(*case[:8], stride=case[8])
     _check(p, run_conv(p))
     p8 = _problem(*case[:8], c=1.0, i8=True, stride=case[8])
@@ -252,15 +265,17 @@ def test_dense_int8_conv_dw_bit_exact(case):
 
 
 # bands of rows, of rows and columns, whole images; strides that leave pixels without a tap
-@pytest.mark.parametrize("case", [(2, 20, 41, 151, 30, 5, 3, 2, 1), (2, 12, 13, 11, 20, 5, 5, 2, 2), (1, 3, 50, 46, 20, 7, 7, 3, 2), (1, 3, 51, 47, 17, 11, 11, 2, 4),
+@pytest.mark.parametrize("case", [(2, 20, 41, 151, 30, 5, 3, 2, 1), (2, 20, 13, 11, 20, 5, 5, 2, 2), (1, 20, 50, 46, 20, 7, 7, 3, 2), (1, 20, 51, 47, 17, 11, 11, 2, 4),
                                   (2, 70, 60, 57, 130, 2, 3, 1, 3), (8, 33, 56, 56, 40, 5, 5, 2, 1), (2, 64, 58, 60, 70, 1, 1, 0, 2)])
 def test_conv_dw_non_finite_activations_stay_with_their_taps(case):
     """A NaN in the last pixel reaches the taps that pair it with an output pixel and no other (5 * NaN and 0 * NaN are NaN;
     a tap without such a pair has the oracle's value)."""
     from gpu_util import check_products, run_conv
     from oracle import oracle as O
+    from plan_util import GENERAL, conv_dw_kernel
     p = _problem(*case[:8], stride=case[8])
     N, C, H, Wd, K, R, S, pad, st = case
+    assert conv_dw_kernel(*case[:7], st, pad) == GENERAL
     P, Q = (H + 2 * pad - R) // st + 1, (Wd + 2 * pad - S) // st + 1
     hit = np.zeros((H, Wd), bool)
     hit[-1, -1] = True

@@ -1,6 +1,6 @@
 """GPU parity of the grouped convolution's backward products against the CPU oracle's grouped convolution: every element,
 on every kernel family a group's problem can land on (the fast stride-1 dX kernel, its strided form, the generic
-implicit-im2col kernel, the 3x3 dW kernel, the 1x1 dW form, the lowered dW, the int8 dW kernels, the gather kernels)."""
+implicit-im2col kernel, the 3x3 dW kernel, the 1x1 dW form, the general dW kernel, the int8 dW kernels, the gather kernels)."""
 import numpy as np
 import pytest
 import torch
@@ -51,8 +51,8 @@ CASES = [  # N, C, H, Wd, K, R, S, stride, pad, groups
     (2, 8, 9, 7, 6, 3, 3, 1, 1, 2),             # tiny: generic / fast kernels on ragged tiles
     (3, 64, 14, 14, 96, 3, 3, 1, 1, 2),         # the two-tower AlexNet pattern: fast dX and 3x3 dW kernels per group
     (2, 128, 28, 28, 128, 3, 3, 1, 1, 4),       # ResNeXt-like block, 32 channels per group
-    (2, 96, 12, 12, 192, 1, 1, 1, 0, 3),        # 1x1 layer: dW on the fully connected form, images strided by the whole tensor
-    (2, 32, 13, 13, 64, 3, 3, 2, 1, 2),         # strided: dX as stride-1 problems per pixel class, dW lowered or generic
+    (2, 96, 12, 12, 192, 1, 1, 1, 0, 3),        # 1x1 layer, images strided by the whole tensor
+    (2, 32, 13, 13, 64, 3, 3, 2, 1, 2),         # strided: dX as stride-1 problems per pixel class, dW on the general kernel
     (2, 16, 12, 12, 16, 1, 1, 2, 0, 4),         # 1x1 with stride 2: three of four pixel classes get no tap (dX cleared once)
     (4, 24, 7, 7, 48, 3, 3, 1, 1, 3),           # 7x7 planes: codes copied into padded planes for the dX kernel
     (2, 12, 10, 10, 12, 3, 3, 1, 1, 12),        # depthwise
@@ -61,8 +61,9 @@ CASES = [  # N, C, H, Wd, K, R, S, stride, pad, groups
     # 64 and more channels per group: the groups run one after the other on channel blocks of the tensors (fewer: one
     # ungrouped layer with block-diagonal weights)
     (3, 128, 14, 14, 192, 3, 3, 1, 1, 2),       # fast dX kernel and 3x3 dW kernel per group
-    (2, 192, 12, 12, 384, 1, 1, 1, 0, 3),       # 1x1: dW on the fully connected form, images strided by the whole tensor
-    (2, 128, 13, 13, 128, 3, 3, 2, 1, 2),       # strided: dX per pixel class, dW lowered or generic
+    (2, 192, 12, 12, 384, 1, 1, 1, 0, 3),       # 1x1, images strided by the whole tensor
+    (3, 128, 8, 8, 400, 1, 1, 1, 0, 2),         # 1x1: dW on the batched fully connected form
+    (2, 128, 13, 13, 128, 3, 3, 2, 1, 2),       # strided: dX per pixel class, dW on the general kernel
     (2, 128, 12, 12, 256, 1, 1, 2, 0, 2),       # 1x1 with stride 2: pixel classes without taps, dX cleared once
     (4, 128, 7, 7, 256, 3, 3, 1, 1, 2),         # 7x7 planes: codes copied into padded planes, planes strided by the whole tensor
     (2, 130, 9, 11, 70, 5, 3, 1, 2, 2),         # odd sizes: generic kernels

@@ -176,9 +176,8 @@ def test_dense_baseline_matches_oracle(B, in_, out):
     check_products(dW.cpu().numpy(), rW, aW, "dense dW")
 
 
-# Shapes that drive the role-specialised kernel (batch and out above 128) through its edges: a batch that is not a
-# multiple of 4 (the dW reduction ends inside a window of 32 and inside a dword), ragged row and column tiles, a
-# reduction shorter than two windows, many column tiles, out just above the kernel's lower limit.
+# Middle-sized layers (13 to 103 million multiply-adds, the direct kernel's): a batch that is not a multiple of 4, ragged row and column
+# tiles, many column tiles.  The staged kernel's edges: test_fc_staged_kernels_take_ragged_layers and the two tests after it.
 @pytest.mark.parametrize("B,in_,out", [(258, 260, 200), (1000, 136, 260), (130, 4100, 140), (133, 128, 129), (513, 516, 388)])
 def test_fc_large_layer_kernel_edges(B, in_, out):
     from gpu_util import run_linear

@@ -83,8 +83,8 @@ def test_fc_q8_is_bit_exact(B, in_, out):
     _fc(B, in_, out, seed=B + out)
 
 
-# shapes the role-specialised int8 kernel takes (batch and out above 128, in a multiple of 8), through its edges:
-# ragged tiles, reductions that end inside a window of 64, a batch that is not a multiple of 4
+# larger layers: ragged tiles, reductions that end inside a window of 64, a batch that is not a multiple of 4 (up to 3e8 multiply-adds
+# the direct kernel, above it the staged one; its own edges further down)
 @pytest.mark.parametrize("B,in_,out", [(258, 264, 200), (130, 4104, 140), (1000, 136, 260), (512, 512, 392),
                                        (256, 1024, 4096), (256, 4096, 1000),
                                        (256, 4096, 4096)])     # the two products on two groups of workgroups
@@ -124,7 +124,7 @@ CONV_CASES = [  # N, C, H, Wd, K, R, S, pad (, stride)
     (2, 16, 16, 16, 24, 1, 1, 0, 2),    # 1x1 / 2: three classes without taps (cleared), one with the single tap
     (2, 8, 15, 17, 8, 3, 3, 1, 2),      # odd image sizes: the classes have different extents
     (2, 6, 11, 13, 9, 3, 3, 0, 3),      # stride 3: nine classes of one tap each
-    (16, 64, 28, 28, 128, 3, 3, 1, 2),  # large enough that dW runs as column matrix x int8 fully connected kernel
+    (16, 64, 28, 28, 128, 3, 3, 1, 2),  # larger: dW on the general kernel
     (32, 128, 14, 14, 256, 1, 1, 0),    # 1x1, more than 128 output channels: dW by the int8 fully connected kernel on the NCHW tensors
     (4, 36, 14, 14, 130, 1, 1, 0),      # the same with partial tiles
     (1, 1, 1, 1, 1, 1, 1, 0),

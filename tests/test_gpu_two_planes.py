@@ -71,7 +71,8 @@ CONV = [  # N, C, H, Wd, K, R, S, pad, stride
     (1, 130, 6, 6, 260, 3, 3, 1, 1),
     (2, 64, 30, 30, 40, 3, 3, 1, 1),            # several pixel tiles per image
     (2, 33, 14, 14, 20, 1, 1, 0, 1),            # 1x1: the two-set weight ring; dW on the fully connected kernels
-    (3, 140, 14, 14, 260, 1, 1, 0, 1),          # 1x1 with more than 128 output channels: dW straight on the NCHW tensors
+    (3, 140, 14, 14, 260, 1, 1, 0, 1),          # 1x1 with more than 128 output channels
+    (2, 260, 10, 10, 300, 1, 1, 0, 1),          # the same: dW on the batched fully connected form
     (2, 16, 12, 12, 40, 2, 3, 1, 1),            # six taps
     (2, 8, 10, 10, 9, 3, 3, 0, 1),              # no padding (the other dW instantiation)
     (4, 64, 28, 28, 40, 3, 3, 1, 2),            # stride 2: the classes in one launch
