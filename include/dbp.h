@@ -220,8 +220,8 @@ dbp_status dithered_linear_backward(const float *delta, const float *W, const vo
  * otherwise).  3x3 and 1x1 layers whose planes are a multiple of 4 bytes run on kernels that scan the code planes (dX: stride
  * 1 only; they keep prepared weights and partial sums in the workspace), every other shape on kernels that walk the format's
  * entries.  On the matrix-core paths stride 1 runs on the specialised kernels; with another stride dX runs on them as stride*stride
- * stride-1 problems (one per class of output pixels modulo the stride) when stride <= 3, dW as a column-matrix
- * product on the fully connected kernels when the layer is large enough, the rest on the generic implicit-im2col kernel.
+ * stride-1 problems (one per class of output pixels modulo the stride) when stride <= 3, dW on the general kernel that takes
+ * any kernel size and stride, the rest on the generic implicit-im2col kernel (dbp_plan_conv2d_dw names dW's kernel).
  */
 dbp_status dithered_conv2d_backward(const float *delta, const float *W, const void *X,
                                     dbp_dtype x_dtype, int64_t N, int64_t C, int64_t H,
