@@ -1247,7 +1247,8 @@ static ConvDwChoice conv_dw_choose(const ConvArgs &a, const void *grad)
         // The general kernel takes what the two specialised forms do not, and what they are the slower ones for.  Products alone (us), fp32
         // activations (int8 ones lie likewise):
         //   * the 3x3 kernel where its padded rows are more than half (int8: a quarter) full, and small layers; 3x3 kernel / general: 64->64 32x32 52 / 58,
-        //     128->128 28x28 60 / 64, 256->256 14x14 64 / 67, narrow rows: 64->64 8x8 N=64 22 / 24, 512->512 4x4 109 / 56;
+        //     128->128 28x28 60 / 64, 256->256 14x14 64 / 67, narrow rows: 64->64 8x8 N=64 22 / 24, 512->512 4x4 109 / 56,
+        //     int8 64->64 4x4 N=128 18 / 29, 512->512 77 / 46;
         //   * the batched 1x1 form by modelled time: 1024->256 14x14 38 / 57, 512->128 28x28 51 / 58, 512->2048 7x7 40 / 55, 64->256 56x56 92 / 39;
         //   * the generic kernel, by modelled time, where up to 16 input channels leave most of the general kernel's blocks of 32 empty: 1->20 5x5
         //     28x28 N=64 34 / 43, 3->64 7x7/2 224x224 N=32 248 / 453, 16->32 3x3/2 32x32 N=128 55 / 34.
@@ -1257,7 +1258,7 @@ static ConvDwChoice conv_dw_choose(const ConvArgs &a, const void *grad)
             // (a group of a grouped layer: images further apart than its own planes say)
             if (pd.ok && (rb + pd.partial_bytes > a.scratch_bytes || pd.args.NI * a.kt() * pd.args.P * pd.args.Q >= ((int64_t)1 << 30) ||
                           pd.args.NI * a.ct() * a.H * a.Wd >= ((int64_t)1 << 29))) pd.ok = false;
-            if (pd.ok && pl.ok && pd.us < 12.0f) pd.ok = false;
+            if (pd.ok && pl.ok && pd.us < (I8 ? 17.0f : 12.0f)) pd.ok = false;
             if (pd.ok && p1.ok && p1.us <= 15.0f + pd.us) pd.ok = false;
             // (its own time is about 13 us of ends and 0.8 of the model's)
             if (pd.ok && !pl.ok && !p1.ok && a.C <= 16 && conv_dw_generic_us(a.N, a.C, pd.args.P, pd.args.Q, a.K, a.R * a.S, I8) < 13.0f + 0.8f * pd.us) pd.ok = false;

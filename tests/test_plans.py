@@ -112,6 +112,7 @@ def test_conv_dw_kernels_are_the_faster_ones():
     for case in [(64, 1024, 14, 14, 256, 1, 1, 1, 0), (64, 128, 28, 28, 512, 1, 1, 1, 0), (16, 216, 40, 40, 72, 1, 1, 1, 0), (28, 20, 20, 20, 146, 1, 1, 1, 0)]:
         assert _dw(*case, i8=1) == ONE, case
     assert _dw(1, 1, 12, 12, 64, 5, 5, 2, 0, i8=1) == GENERIC
+    assert _dw(128, 64, 4, 4, 64, 3, 3, 1, 1, i8=1) == THREE and _dw(128, 512, 4, 4, 512, 3, 3, 1, 1, i8=1) == GENERAL      # 18 (29); 46 (77)
 
 
 def test_conv_gather_plans_stay_in_bounds():
