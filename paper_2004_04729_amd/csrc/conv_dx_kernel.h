@@ -50,6 +50,7 @@ struct ConvDxArgs {
     int cgroups;              // ceil(C / (32*wc))
     int tiles;                // pixel tiles per image
     int prow, pw, patch_cells;// patch rows (maximum over tiles), patch width Wd+S-1 ... cells per k-group
+    int NI, img_cells, wave_cells, pairs;   // conv_dx_split_kernel: images per tile, patch cells of one; LDS cells of a wavefront; pairs of k-groups with weights
     Scale scale;
     Gate gate;
 };

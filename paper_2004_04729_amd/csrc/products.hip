@@ -7,6 +7,7 @@
 #include "fc_direct_kernel.h"
 #include "fc2_i8_kernel.h"
 #include "conv_dx_kernel.h"
+#include "conv_dx_split_kernel.h"
 #include "conv_dw_kernel.h"
 #include "conv_dw_i8_kernel.h"
 #include "conv_dwt_kernel.h"
@@ -104,7 +105,33 @@ size_t relayout_bytes(int64_t K, int64_t C, int64_t R, int64_t S)
 // Geometry of the fast dX kernel for one stride-1 problem (a whole layer, or one class of a strided layer), or
 // ok == false when the generic kernel has to serve.  `k` arrives with the problem (N, C, H, Wd, K, R, S, pad, pad_w, P, Q
 // and the output mapping) filled in; force_nb != 0 asks for that pixel-block count only.
-struct ConvDxPlan { bool ok; int nb; ConvDxArgs args; size_t lds_bytes; int grid; };
+struct ConvDxPlan { bool ok; int nb; ConvDxArgs args; size_t lds_bytes; int grid; int waves; float us; };   // waves: 0 conv_dx_kernel, else of conv_dx_split_kernel
+
+// Which of the two dX kernels, and with which tiles: by modelled time.  A workgroup costs its pairs (conv_dx_kernel: chunks) of k-groups,
+// each its taps' matrix instructions and the staging of `items` fill items a lane, and its end; workgroups go over the chip's places
+// in a row (two a CU, of eight wavefronts one), half a workgroup longer where they do not fit at once.  The constants (us) are a fit over 360 layers
+// (7 to 112 wide planes, 16 to 1024 channels, 1x1 to 5x5 taps, strides 1 and 2) with six forms of the new kernel each, 18 % rms.  What the rule
+// chooses takes 1.02 (int8 weights 1.01) of the best form's time over them, conv_dx_kernel alone 1.22 (1.12).  conv_dx_kernel keeps a layer
+// unless the other is modelled 12 % faster; a wavefront without a pair would be idle.
+static float conv_dx_workgroup_us(const ConvDxArgs &k, int nb, int waves, int items, bool i8)
+{
+    const float taps = (float)(k.R * k.S), mma = (float)(i8 ? nb : 3 * nb), staging = (float)(items * (i8 ? 16 : 8));
+    if (waves == 0)
+        return i8 ? 0.84f * nb + (float)k.n_chunks * (taps * 0.116f * mma + 0.094f * staging + 0.69f)
+                  : 1.21f * nb + (float)k.n_chunks * (taps * 0.0725f * mma + 0.05f * staging + 0.28f);
+    const float trips = (float)((k.pairs + waves - 1) / waves);
+    return i8 ? 0.76f * nb + trips * (taps * (0.095f + 0.0424f * mma) + 0.083f * staging + 1.17f)
+              : 0.93f * nb + trips * (taps * (0.0635f + 0.0255f * mma) + 0.051f * staging);
+}
+
+// `longest`: of one workgroup; `sum`: of all of them.
+static float conv_dx_launch_us(float longest, float sum, int64_t grid, int waves, size_t lds, bool i8)
+{
+    const float slots = waves == 8 || lds > CDS_MAX_LDS / 2 ? 256.0f : 512.0f, base = waves == 0 ? (i8 ? 11.1f : 7.5f) : i8 ? 10.4f : 9.1f;
+    const float spread = waves == 0 ? (i8 ? 1.6f : 1.19f) : i8 ? 0.93f : 1.2f;
+    const float all = sum / slots * spread + ((float)grid > slots ? 0.5f * longest : 0.0f);
+    return (base + (longest > all ? longest : all)) * (waves ? 1.12f : 1.0f);
+}
 
 static void conv_dx_plan_core(ConvDxPlan &pl, bool i8, int force_nb)
 {
@@ -147,7 +174,7 @@ static void conv_dx_plan_core(ConvDxPlan &pl, bool i8, int force_nb)
         const int64_t grid = (int64_t)k.N * tiles * k.cgroups;
         const double cost = (double)nb * (double)((grid + 511) / 512);
         if (best < 0.0 || cost < best) {
-            best = cost; pl.ok = true; pl.nb = nb; pl.lds_bytes = lds;
+            best = cost; pl.ok = true; pl.nb = nb; pl.waves = 0; pl.lds_bytes = lds; pl.us = conv_dx_workgroup_us(k, nb, 0, (n_dw * CDX_KGC + 255) / 256, i8);
             k.tiles = tiles; k.prow = prow; k.patch_cells = (int)cells;
         }
     }
@@ -157,6 +184,53 @@ static void conv_dx_plan_core(ConvDxPlan &pl, bool i8, int force_nb)
     pl.grid = (int)grid;
 }
 
+// Geometry of conv_dx_split_kernel for one stride-1 problem, likewise: 32*nb pixels and `waves` wavefronts a workgroup.
+static void conv_dx_split_plan_core(ConvDxPlan &pl, bool i8, int nb, int waves)
+{
+    ConvDxArgs &k = pl.args;
+    pl.ok = false;
+    k.PI = k.H * k.Wd; k.PQ = (k.P * k.Q + 3) / 4 * 4;
+    const int64_t img_out = k.dx_img + (int64_t)32 * k.oPI, img_codes = k.code_img;
+    if (img_out >= ((int64_t)1 << 31) || img_codes >= ((int64_t)1 << 31)) return;
+    const int G = i8 ? 16 : 8;
+    k.Cp = (k.C + 31) / 32 * 32;
+    k.KG = (k.K + CDX_KGC * G - 1) / (CDX_KGC * G) * CDX_KGC;
+    k.n_chunks = k.KG / CDX_KGC;
+    k.pairs = (k.K + 2 * G - 1) / (2 * G);
+    k.wc = k.wpx = 1;
+    k.cgroups = k.Cp / 32;
+    k.pw = k.Wd + k.S - 1;
+    const int tile_px = 32 * nb;
+    k.NI = tile_px / k.PI;
+    if (k.NI > k.N) k.NI = k.N;
+    if (k.NI < 1) k.NI = 1;
+    k.tiles = k.NI > 1 ? 1 : (k.PI + tile_px - 1) / tile_px;
+    int prow = 0, n_dw = 0;
+    for (int t = 0; t < k.tiles; ++t) {
+        const int j0 = t * tile_px, j_end = k.NI > 1 || j0 + tile_px > k.PI ? k.PI : j0 + tile_px;
+        const int h_first = j0 / k.Wd, h_last = (j_end - 1) / k.Wd, p_lo = h_first + k.pad - (k.R - 1);
+        const int p_a = p_lo > 0 ? p_lo : 0, p_b = h_last + k.pad < k.P - 1 ? h_last + k.pad : k.P - 1;
+        if (h_last - h_first + k.R > prow) prow = h_last - h_first + k.R;
+        if (p_b >= p_a) {
+            const int f_a = (p_a * k.Q) & ~3, d = ((p_b + 1) * k.Q - f_a + 3) >> 2;
+            if (d > n_dw) n_dw = d;
+        }
+    }
+    if (2 * n_dw > 64 * cds_items(nb)) return;
+    if (k.NI > 1 && 2 * k.NI * n_dw > 64 * cds_items(nb)) k.NI = 64 * cds_items(nb) / (2 * n_dw);
+    while (k.NI > 1 && (k.NI * img_codes >= ((int64_t)1 << 31) || k.NI * img_out >= ((int64_t)1 << 31))) --k.NI;
+    k.prow = prow; k.img_cells = prow * k.pw; k.patch_cells = k.NI * k.img_cells; k.wave_cells = 2 * k.patch_cells + 1;
+    const int64_t stage = (int64_t)waves * k.wave_cells * 16, fold = (int64_t)waves * nb * 8 * 64 * 4, lds = stage > fold ? stage : fold;
+    if (lds > CDS_MAX_LDS || k.wave_cells >= 0xFFFF || k.pairs < waves) return;
+    const int64_t grid = (int64_t)((k.N + k.NI - 1) / k.NI) * k.tiles * k.cgroups;
+    if (grid > 0x7FFFFFFF) return;
+    pl.ok = true; pl.nb = nb; pl.waves = waves; pl.lds_bytes = (size_t)lds; pl.grid = (int)grid;
+    pl.us = conv_dx_workgroup_us(k, nb, waves, (2 * k.NI * n_dw + 63) / 64, i8);
+}
+
+// The pixel blocks and wavefronts that conv_dx_split_kernel runs with.
+static const struct { int nb, waves; } kDxSplitForms[6] = {{7, 4}, {4, 4}, {2, 4}, {7, 8}, {4, 8}, {2, 8}};
+
 ConvDxPlan conv_dx_plan(const ConvArgs &a, bool i8 = false)
 {
     ConvDxPlan pl;
@@ -165,16 +239,24 @@ ConvDxPlan conv_dx_plan(const ConvArgs &a, bool i8 = false)
     if (a.stride != 1) return pl;                                // strided layers: conv_dx_strided_plan
     k.N = (int)a.N; k.C = (int)a.C; k.H = (int)a.H; k.Wd = (int)a.Wd; k.K = (int)a.K; k.R = (int)a.R; k.S = (int)a.S;
     k.pad = (int)a.pad; k.pad_w = (int)a.pad;
+    k.code_img = a.kt() * ((a.H + 2 * a.pad - a.R + 1) * (a.Wd + 2 * a.pad - a.S + 1) + 3); k.dx_img = a.ct() * a.H * a.Wd;   // upper bounds until the launch
     k.P = k.H + 2 * k.pad - k.R + 1; k.Q = k.Wd + 2 * k.pad - k.S + 1;
     k.oW = k.Wd; k.oPI = k.H * k.Wd; k.ost = 1; k.oh0 = 0; k.ow0 = 0;
     conv_dx_plan_core(pl, i8, 0);
+    float best = pl.ok ? conv_dx_launch_us(pl.us, pl.us * (float)pl.grid, pl.grid, 0, pl.lds_bytes, i8) : 3.0e38f;
+    for (const auto &f : kDxSplitForms) {
+        ConvDxPlan sp = pl;
+        conv_dx_split_plan_core(sp, i8, f.nb, f.waves);
+        const float us = sp.ok ? conv_dx_launch_us(sp.us, sp.us * (float)sp.grid, sp.grid, f.waves, sp.lds_bytes, i8) : 3.0e38f;
+        if (sp.ok && us < best) { best = us; pl = sp; }
+    }
     return pl;
 }
 
 // A strided layer as st*st stride-1 problems, one per class of output pixels (h mod st, w mod st): class (ph, pw) has
 // the taps r = r0 + st*t, r0 = (ph + pad) mod st, and reads code row i + (ph + pad - r0)/st - t for its output row i.
 // Classes without taps (a 1x1 kernel with stride 2 has three) are all zero: `zero_fill` asks for dX to be cleared first.
-struct ConvDxStridedPlan { bool ok, zero_fill; int nb; ConvDxMulti multi; CdxTapMap map; int taps, tap_base[CDX_MAX_CLASSES]; size_t lds_bytes; int grid; };
+struct ConvDxStridedPlan { bool ok, zero_fill; int nb; ConvDxMulti multi; CdxTapMap map; int taps, tap_base[CDX_MAX_CLASSES]; size_t lds_bytes; int grid, waves; };
 
 ConvDxStridedPlan conv_dx_strided_plan(const ConvArgs &a, bool i8)
 {
@@ -183,12 +265,17 @@ ConvDxStridedPlan conv_dx_strided_plan(const ConvArgs &a, bool i8)
     const int st = (int)a.stride, R = (int)a.R, S = (int)a.S, pad = (int)a.pad, H = (int)a.H, Wd = (int)a.Wd;
     if (st < 2 || st * st > CDX_MAX_CLASSES || R * S > 64) return sp;
     const int P = (H + 2 * pad - R) / st + 1, Q = (Wd + 2 * pad - S) / st + 1;
-    // one pixel-block count for all classes (one launch): the one with the least rounds x work per workgroup
+    // One pixel-block count for all classes (one launch): conv_dx_kernel's with the least rounds x work per workgroup, and then the faster
+    // kernel (conv_dx_workgroup_us).
     ConvDxStridedPlan best;
     double best_cost = -1.0;
+    float best_us = 3.0e38f;
     const int cand[3] = {7, 4, 2};
-    for (int attempt = 0; attempt < 3; ++attempt) {
-        const int nb = cand[attempt];
+    for (int attempt = 0; attempt < 9; ++attempt) {
+        const bool split = attempt >= 3;
+        const int nb = split ? kDxSplitForms[attempt - 3].nb : cand[attempt];
+        sp.waves = split ? kDxSplitForms[attempt - 3].waves : 0;
+        float longest = 0.0f, sum = 0.0f;
         sp.ok = false;
         bool all = true;
         sp.multi.n = 0; sp.taps = 0; sp.zero_fill = false; sp.lds_bytes = 0;
@@ -205,8 +292,9 @@ ConvDxStridedPlan conv_dx_strided_plan(const ConvArgs &a, bool i8)
                 k.N = (int)a.N; k.C = (int)a.C; k.H = Hv; k.Wd = Wv; k.K = (int)a.K; k.R = Rv; k.S = Sv;
                 k.pad = (ph + pad - r0) / st; k.pad_w = (pw + pad - s0) / st;
                 k.P = P; k.Q = Q;
+                k.code_img = a.kt() * ((int64_t)P * Q + 3); k.dx_img = a.ct() * H * Wd;          // upper bounds until the launch
                 k.oW = Wd; k.oPI = H * Wd; k.ost = st; k.oh0 = ph; k.ow0 = pw;
-                conv_dx_plan_core(pl, i8, nb);
+                if (split) conv_dx_split_plan_core(pl, i8, nb, sp.waves); else conv_dx_plan_core(pl, i8, nb);
                 if (!pl.ok) { all = false; break; }
                 // this class's prepared taps follow the earlier classes'
                 for (int t = 0; t < Rv; ++t)
@@ -217,6 +305,8 @@ ConvDxStridedPlan conv_dx_strided_plan(const ConvArgs &a, bool i8)
                 sp.tap_base[sp.multi.n] = sp.taps;
                 sp.taps += Rv * Sv;
                 grid += pl.grid;
+                sum += pl.us * (float)pl.grid;
+                if (pl.us > longest) longest = pl.us;
                 if (pl.lds_bytes > sp.lds_bytes) sp.lds_bytes = pl.lds_bytes;
                 ++sp.multi.n;
             }
@@ -225,9 +315,10 @@ ConvDxStridedPlan conv_dx_strided_plan(const ConvArgs &a, bool i8)
         sp.multi.first[sp.multi.n] = (int)grid;
         sp.ok = true; sp.nb = nb; sp.grid = (int)grid;
         const double cost = (double)nb * (double)((grid + 511) / 512);
-        if (best_cost < 0.0 || cost < best_cost) { best_cost = cost; best = sp; }
+        const float us = conv_dx_launch_us(longest, sum, grid, sp.waves, sp.lds_bytes, i8);
+        if (split ? us < best_us : best_cost < 0.0 || cost < best_cost) { best_cost = cost; best_us = us; best = sp; }
     }
-    if (best_cost < 0.0) { sp.ok = false; return sp; }
+    if (best_us > 2.0e38f) { sp.ok = false; return sp; }
     sp = best;
     for (int t = sp.taps; t < 64; ++t) sp.map.real[t] = 0;
     return sp;
@@ -1107,6 +1198,41 @@ hipError_t launch_zero_words(void *p, int64_t n_words, hipStream_t s)
 // ------------------------------------------------------------------------------------------------
 // Convolution (fast dX kernel: any stride; fast dW kernels: stride 1; the generic kernel serves the rest).
 // ------------------------------------------------------------------------------------------------
+template <class Args>
+static hipError_t launch_dx_split_as(void (*kernel)(Args), bool &raised, const Args &args, int grid, int waves, size_t lds, hipStream_t s)
+{
+    if (!raised) {                                                   // more than 64 KiB of dynamic LDS: allowed per kernel, once
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, CDS_MAX_LDS);
+        if (e != hipSuccess) return e;
+        raised = true;
+    }
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * waves), lds, s, args);
+    return hipGetLastError();
+}
+
+template <int NB, int MODE>
+static hipError_t launch_dx_split_nb(const ConvDxPlan &pl, hipStream_t s)
+{
+    static bool raised[2] = {false, false};
+    if constexpr (NB < 7 || MODE != MODE_I8) {                       // (unrolled, seven blocks and sixteen raw dwords an item do not fit the registers)
+        if (pl.args.R == 3 && pl.args.S == 3) return launch_dx_split_as(&conv_dx_split_kernel<NB, MODE, true>, raised[1], pl.args, pl.grid, pl.waves, pl.lds_bytes, s);
+    }
+    return launch_dx_split_as(&conv_dx_split_kernel<NB, MODE, false>, raised[0], pl.args, pl.grid, pl.waves, pl.lds_bytes, s);
+}
+
+template <int NB, int MODE>
+static hipError_t launch_dx_split_nb(const ConvDxStridedPlan &sp, hipStream_t s)
+{
+    static bool raised = false;
+    return launch_dx_split_as(&conv_dx_split_multi_kernel<NB, MODE>, raised, sp.multi, sp.grid, sp.waves, sp.lds_bytes, s);
+}
+
+template <int MODE, class Plan>
+static hipError_t launch_conv_dx_split(const Plan &pl, hipStream_t s)
+{
+    return pl.nb == 7 ? launch_dx_split_nb<7, MODE>(pl, s) : pl.nb == 4 ? launch_dx_split_nb<4, MODE>(pl, s) : launch_dx_split_nb<2, MODE>(pl, s);
+}
+
 template <int MODE_G, int MODE_K>
 static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, hipStream_t s)
 {
@@ -1163,6 +1289,7 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
                         k.code_img = (pad_codes ? a.K : a.kt()) * k.PQ; k.dx_img = a.ct() * k.oPI;
                         k.wp = (const uint4 *)a.scratch + (int64_t)sp.tap_base[i] * KG * PL * Cp;
                     }
+                    if (sp.waves) return launch_conv_dx_split<MODE_K>(sp, s);
                     if (sp.nb == 7)      hipLaunchKernelGGL((conv_dx_multi_kernel<7, MODE_K>), dim3(sp.grid), dim3(256), sp.lds_bytes, s, sp.multi);
                     else if (sp.nb == 4) hipLaunchKernelGGL((conv_dx_multi_kernel<4, MODE_K>), dim3(sp.grid), dim3(256), sp.lds_bytes, s, sp.multi);
                     else                 hipLaunchKernelGGL((conv_dx_multi_kernel<2, MODE_K>), dim3(sp.grid), dim3(256), sp.lds_bytes, s, sp.multi);
@@ -1177,6 +1304,7 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
             k.codes = kernel_codes; k.wp = (const uint4 *)a.scratch; k.dX = a.dX; k.scale = scale; k.gate = a.gate;
             k.code_img = (pad_codes ? a.K : a.kt()) * k.PQ; k.dx_img = a.ct() * k.PI;
             prepare(k.R * k.S, k.KG, k.Cp, nullptr);
+            if (pl.waves) return launch_conv_dx_split<MODE_K>(pl, s);
             // tap counts that are a multiple of 3 (3x3 above all) take the form with three weight fragment sets in flight
             const bool ring3 = (k.R * k.S) % 3 == 0;
             const dim3 grid(pl.grid), block(256);
@@ -1447,15 +1575,37 @@ static int check_conv_plans(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t
             if ((int64_t)k.prow * k.pw != k.patch_cells || CDX_KGC * (int64_t)k.patch_cells >= 0xFFFF) return 26;
             return 0;
         };
+        // ... or, for both, the kernel whose wavefronts divide the reduction
+        auto check_split = [&](const ConvDxArgs &k, int nb, int waves, size_t lds, int64_t grid) {
+            if ((waves != 4 && waves != 8) || k.pairs < waves || lds > (size_t)CDS_MAX_LDS) return 60;
+            if (lds < (size_t)waves * k.wave_cells * 16 || lds < (size_t)waves * nb * 2048 || k.wave_cells != 2 * k.patch_cells + 1 || k.wave_cells >= 0xFFFF) return 61;
+            if (k.NI < 1 || (k.NI > 1 && (k.tiles != 1 || k.NI * k.PI > 32 * nb)) || k.NI * k.img_cells != k.patch_cells || k.img_cells != k.prow * k.pw) return 62;
+            if ((int64_t)k.tiles * 32 * nb < k.PI || (int64_t)(k.tiles - 1) * 32 * nb >= k.PI) return 63;
+            if (grid != (int64_t)((k.N + k.NI - 1) / k.NI) * k.tiles * k.cgroups || k.cgroups * 32 != k.Cp || k.Cp < k.C) return 64;
+            const int G = i8 ? 16 : 8;
+            if ((int64_t)k.pairs * 2 * G < k.K || (int64_t)(k.pairs - 1) * 2 * G >= k.K || 2 * k.pairs > k.KG) return 65;
+            for (int t = 0; t < k.tiles; ++t) {                               // the rows a tile reads: within its patch and its lanes' items
+                const int h0 = k.NI > 1 ? 0 : t * 32 * nb / k.Wd, px = k.NI > 1 || (t + 1) * 32 * nb > k.PI ? k.PI : (t + 1) * 32 * nb, h1 = (px - 1) / k.Wd;
+                const int lo = h0 + k.pad - (k.R - 1) > 0 ? h0 + k.pad - (k.R - 1) : 0, hi = h1 + k.pad < k.P - 1 ? h1 + k.pad : k.P - 1;
+                if (h1 - h0 + k.R > k.prow) return 66;
+                if (hi >= lo && 2 * k.NI * (((hi + 1) * k.Q - (lo * k.Q & ~3) + 3) >> 2) > 64 * cds_items(nb)) return 67;
+                if (hi >= lo && ((hi + 1) * k.Q + 3) / 4 * 4 > k.PQ) return 68;
+            }
+            return 0;
+        };
         if (stride == 1) {
             const ConvDxPlan pl = conv_dx_plan(a, i8 != 0);
-            if (pl.ok) { const int e = check_dx(pl.args, pl.nb, pl.lds_bytes, pl.grid); if (e) return e; }
+            if (pl.ok) {
+                const int e = pl.waves ? check_split(pl.args, pl.nb, pl.waves, pl.lds_bytes, pl.grid) : check_dx(pl.args, pl.nb, pl.lds_bytes, pl.grid);
+                if (e) return e;
+            }
         } else {
             const ConvDxStridedPlan sp = conv_dx_strided_plan(a, i8 != 0);
             if (sp.ok) {
                 if (sp.multi.n < 0 || sp.multi.n > CDX_MAX_CLASSES || sp.taps > 64) return 27;
                 for (int i = 0; i < sp.multi.n; ++i) {
-                    const int e = check_dx(sp.multi.cls[i], sp.nb, sp.lds_bytes, (int64_t)sp.multi.first[i + 1] - sp.multi.first[i]);
+                    const int64_t grid = (int64_t)sp.multi.first[i + 1] - sp.multi.first[i];
+                    const int e = sp.waves ? check_split(sp.multi.cls[i], sp.nb, sp.waves, sp.lds_bytes, grid) : check_dx(sp.multi.cls[i], sp.nb, sp.lds_bytes, grid);
                     if (e) return e;
                     if (sp.tap_base[i] + sp.multi.cls[i].R * sp.multi.cls[i].S > sp.taps) return 28;
                 }
@@ -1552,6 +1702,17 @@ extern "C" int dbp_plan_check_conv2d(int64_t N, int64_t C, int64_t H, int64_t Wd
     if (N <= 0 || C <= 0 || H <= 0 || Wd <= 0 || K <= 0 || R <= 0 || S <= 0 || stride <= 0 || pad < 0 || H + 2 * pad < R || Wd + 2 * pad < S) return -1;
     if (N > 65535 || C > 65535 || K > 65535 || H > 65535 || Wd > 65535 || R > 255 || S > 255 || pad > 255 || stride > 255) return -1;
     return dbp::check_conv_plans(N, C, H, Wd, K, R, S, stride, pad);
+}
+
+extern "C" int dbp_plan_conv2d_dx(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t stride, int64_t pad, int int8_w)
+{
+    if (dbp_plan_check_conv2d(N, C, H, Wd, K, R, S, stride, pad) != 0) return -1;
+    dbp::ConvArgs a{};
+    a.N = N; a.C = C; a.H = H; a.Wd = Wd; a.K = K; a.R = R; a.S = S; a.pad = pad; a.stride = stride;
+    const dbp::ConvDxPlan pl = dbp::conv_dx_plan(a, int8_w != 0);
+    const dbp::ConvDxStridedPlan sp = dbp::conv_dx_strided_plan(a, int8_w != 0);
+    const int nb = pl.ok ? pl.nb : sp.nb, waves = pl.ok ? pl.waves : sp.waves;
+    return !pl.ok && !sp.ok ? 0 : waves ? 16 * waves + nb : 1;
 }
 
 extern "C" int dbp_plan_conv2d_dw(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t stride, int64_t pad,

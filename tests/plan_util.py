@@ -19,3 +19,11 @@ def conv_dw_kernel(N, C_, H, Wd, K, R, S, stride, pad, i8=0, dense=0, two=0):
     f = dbp.lib().dbp_plan_conv2d_dw
     f.argtypes, f.restype = [C.c_int64] * 9 + [C.c_int] * 3, C.c_int
     return f(N, C_, H, Wd, K, R, S, stride, pad, i8, dense, two)
+
+
+def conv_dx_kernel(N, C_, H, Wd, K, R, S, stride, pad, q8=0):
+    """0: generic, 1: channels and pixels divided, else (wavefronts, pixel blocks) of the kernel that divides the reduction."""
+    f = dbp.lib().dbp_plan_conv2d_dx
+    f.argtypes, f.restype = [C.c_int64] * 9 + [C.c_int], C.c_int
+    r = f(N, C_, H, Wd, K, R, S, stride, pad, q8)
+    return divmod(r, 16) if r > 1 else r

@@ -314,6 +314,26 @@ STRIDED = [  # N, C, H, Wd, K, R, S, pad, stride  (the strided layers of a ResNe
 ]
 
 
+# dX with the reduction divided between wavefronts: every tile form, several images a tile with a last group that is not full, planes copied
+# to whole dwords, K that ends inside a pair of channel groups and pairs that do not divide by the wavefronts, a partial block of
+# input channels, rows that one lane's items just hold, classes of strides 2 and 3, padding 0
+SPLIT_DX = [((5, 33, 7, 7, 200, 3, 3, 1, 1), (8, 2)), ((5, 33, 4, 4, 70, 3, 3, 1, 1), (4, 2)), ((90, 70, 9, 9, 70, 3, 3, 1, 1), (4, 4)),
+            ((90, 130, 13, 13, 70, 3, 3, 1, 1), (4, 7)), ((90, 33, 9, 9, 520, 3, 3, 1, 1), (8, 4)), ((90, 33, 13, 13, 520, 3, 3, 1, 1), (8, 7)),
+            ((90, 33, 14, 14, 520, 1, 1, 1, 0), (8, 7)), ((90, 70, 10, 10, 133, 3, 3, 2, 1), (8, 4)), ((90, 250, 10, 10, 70, 3, 3, 2, 1), (4, 7)),
+            ((3, 40, 20, 20, 264, 3, 3, 3, 1), (8, 2)), ((7, 16, 5, 6, 530, 3, 3, 1, 0), (8, 2)), ((17, 64, 12, 12, 256, 2, 3, 1, 1), (8, 2)),
+            ((1, 48, 100, 100, 70, 5, 5, 1, 2), (4, 2)), ((2, 24, 40, 40, 133, 5, 5, 1, 2), (8, 2))]
+
+
+@pytest.mark.parametrize("case,form", SPLIT_DX)
+def test_conv_dx_with_the_reduction_divided(case, form):
+    from gpu_util import run_conv
+    from plan_util import conv_dx_kernel
+    assert conv_dx_kernel(*case) == form
+    N, C, H, Wd, K, R, S, stride, pad = case
+    p = _problem(N, C, H, Wd, K, R, S, pad, stride=stride)
+    _check(p, run_conv(p, want_dw=False))
+
+
 @pytest.mark.parametrize("case", STRIDED)
 def test_conv_strided_matches_oracle(case):
     from gpu_util import run_conv
