@@ -11,9 +11,11 @@
 //     wavefront are executed in order, so one buffer is enough; the next pair's codes are on their way as global loads.
 //   * At the end the wavefronts add up through LDS by recursive halving, in a fixed order: in every round a wavefront hands half of
 //     its rows to its partner and keeps the other half, so that all of them store.
+//   * A workgroup lives for a few pairs only, so its beginning counts: the first weights and codes are asked for before the indices of the LDS
+//     cells are worked out, and these take no integer division (kernel, us: 14x14 49.0 -> 45.6, 7x7 48.2 -> 42.6).
 // What bounds it: matrix instructions and their operands, at about 45 % of the matrix rate in the multiply loop; every workgroup stages its
 // pixels' codes for 32 channels only, so layers of many channels AND many pixels stay on conv_dx_kernel (conv_dx_workgroup_us).
-// Measured, preparation and kernel (us), conv_dx_kernel / here: 256->256 14x14 N=64 65.6 / 51.1, 512->512 7x7 N=64 82.2 / 57.9,
+// Measured, preparation and kernel (us), conv_dx_kernel / here: 256->256 14x14 N=64 65.6 / 48, 512->512 7x7 N=64 82.2 / 53,
 // 16->537 8x8 N=119 69.7 / 22.0, 40->840 3x3/2 8x8 N=83 80.9 / 27.4, 332->37 5x5 16x16 N=52 63.9 / 49.0; 64->64 32x32 N=128 39.0 / 49.6.
 #pragma once
 #include "conv_dx_kernel.h"
@@ -51,34 +53,46 @@ __device__ __forceinline__ void conv_dx_split_body(const ConvDxArgs &a, int b)
     const int p_a = max(p_lo, 0), p_b = min(h_last + a.pad, a.P - 1);
     const int kg_cells = a.patch_cells;                          // of one k-group: NI images
     uint4 *mine = cdx_lds + wave * a.wave_cells;                 // 2 * kg_cells and one that nobody reads
-    for (int i = lane; i < a.wave_cells; i += 64) mine[i] = uint4{0u, 0u, 0u, 0u};
+
+    // ---- weights: a step is a tap of a pair; a cursor walks the wavefront's steps ahead of them and stays on the last one
+    const int RS = T9 ? 9 : a.R * a.S;
+    const int64_t tap_stride = (int64_t)PL * a.Cp * a.KG;        // cells
+    const uint32_t wl = (uint32_t)(lhalf * PL * a.Cp + cb * 32 + lcol);
+    const int last_pair = wave + (a.pairs - 1 - wave) / waves * waves;           // (wave < pairs)
+    int l_pair = wave, l_tap = 0;
+    auto next_load = [&](u32x4 (&dst)[PL]) {
+        const uint4 *row = a.wp + (l_tap * tap_stride + (int64_t)l_pair * (2 * PL) * a.Cp);     // uniform
+#pragma unroll
+        for (int pl = 0; pl < PL; ++pl) { const uint4 t = row[wl + (uint32_t)(pl * a.Cp)]; dst[pl] = u32x4{t.x, t.y, t.z, t.w}; }
+        if (++l_tap == RS) {
+            if (l_pair < last_pair) { l_tap = 0; l_pair += waves; }
+            else l_tap = RS - 1;
+        }
+    };
+    u32x4 f0[PL], f1[PL], f2[PL];
+    const bool active = wave < a.pairs;                          // uniform; (the plan leaves no wavefront without a pair)
+    if (active) {
+        next_load(f0);
+        if constexpr (T9) next_load(f1);
+    }
 
     // ---- patch-fill items of this lane; places outside the patch go to the cell that nobody reads
     const int f_a = (p_a * a.Q) & ~3;
     const int n_dw = p_b >= p_a ? ((p_b + 1) * a.Q - f_a + 3) >> 2 : 0;
     const int n_items = 2 * ni * n_dw;
+    const float r_dw = cdx_rcp(n_dw), r_all = cdx_rcp(ni * n_dw), r_q = cdx_rcp(a.Q), r_w = cdx_rcp(a.Wd), r_pi = cdx_rcp(a.PI);
     uint32_t item_goff[ITEMS], item_cell[ITEMS][2];
-    int item_k[ITEMS];
+    int item_k[ITEMS], item_cell0[ITEMS], item_rel[ITEMS];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const int it = lane + 64 * i;
-        const uint32_t none = (uint32_t)(2 * kg_cells);
-        item_goff[i] = 0u; item_k[i] = 0;
-        item_cell[i][0] = item_cell[i][1] = none | none << 16;
+        item_goff[i] = 0u; item_k[i] = 0; item_cell0[i] = 0; item_rel[i] = -4;     // none: before the patch
         if (it < n_items) {
-            const int kgl = it / (ni * n_dw), rest = it - kgl * (ni * n_dw), im = rest / n_dw, f = rest - im * n_dw;
-            const int pix0 = f_a + 4 * f;
+            const int kgl = cdx_div(it, r_all), rest = it - kgl * (ni * n_dw), im = cdx_div(rest, r_dw), f = rest - im * n_dw;
             item_k[i] = kgl * G;
-            item_goff[i] = (uint32_t)(im * (int)a.code_img + pix0);
-            uint32_t cells[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int pix = pix0 + e, p = pix / a.Q, q = pix - p * a.Q;
-                const bool need = p >= p_a && p <= p_b && q >= q_lo && q - q_lo < a.pw;
-                cells[e] = need ? (uint32_t)(kgl * kg_cells + im * a.img_cells + (p - p_lo) * a.pw + (q - q_lo)) : none;
-            }
-            item_cell[i][0] = cells[0] | (cells[1] << 16);
-            item_cell[i][1] = cells[2] | (cells[3] << 16);
+            item_goff[i] = (uint32_t)(im * (int)a.code_img + f_a + 4 * f);
+            item_cell0[i] = kgl * kg_cells + im * a.img_cells;
+            item_rel[i] = f_a + 4 * f - p_a * a.Q;
         }
     }
     uint32_t raw[ITEMS][G];
@@ -98,6 +112,21 @@ __device__ __forceinline__ void conv_dx_split_body(const ConvDxArgs &a, int b)
             }
         }
     };
+    if (active) fetch(wave);
+    for (int i = lane; i < a.wave_cells; i += 64) mine[i] = uint4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        if (64 * i >= n_items) break;                                             // uniform
+        uint32_t cells[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int rel = item_rel[i] + e, p = p_a + cdx_div(rel, r_q), q = rel - (p - p_a) * a.Q;
+            const bool need = rel >= 0 && p <= p_b && q >= q_lo && q - q_lo < a.pw;
+            cells[e] = need ? (uint32_t)(item_cell0[i] + (p - p_lo) * a.pw + (q - q_lo)) : (uint32_t)(2 * kg_cells);
+        }
+        item_cell[i][0] = cells[0] | (cells[1] << 16);
+        item_cell[i][1] = cells[2] | (cells[3] << 16);
+    }
     auto store = [&]() {
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
@@ -130,10 +159,10 @@ __device__ __forceinline__ void conv_dx_split_body(const ConvDxArgs &a, int b)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         int j = min(j0 + 32 * nb + lcol, j_end - 1);            // tail lanes compute a valid pixel again; not stored
-        const int im = a.NI > 1 ? j / a.PI : 0;
-        j -= im * a.PI;
-        const int h = j / a.Wd, w = j - h * a.Wd;
-        lane_cell[nb] = im * a.img_cells + (h - h_first) * a.pw + w + lhalf * kg_cells;
+        const int im = a.NI > 1 ? cdx_div(j, r_pi) : 0;
+        j -= im * a.PI + h_first * a.Wd;
+        const int h = cdx_div(j, r_w), w = j - h * a.Wd;
+        lane_cell[nb] = im * a.img_cells + h * a.pw + w + lhalf * kg_cells;
     }
 
     Acc acc[NB];
@@ -142,21 +171,6 @@ __device__ __forceinline__ void conv_dx_split_body(const ConvDxArgs &a, int b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[nb][v] = 0;
 
-    // ---- weights: a step is a tap of a pair; a cursor walks the wavefront's steps ahead of them and stays on the last one
-    const int RS = T9 ? 9 : a.R * a.S;
-    const int64_t tap_stride = (int64_t)PL * a.Cp * a.KG;        // cells
-    const uint32_t wl = (uint32_t)(lhalf * PL * a.Cp + cb * 32 + lcol);
-    const int last_pair = wave + (a.pairs - 1 - wave) / waves * waves;      // (wave < pairs)
-    int l_pair = wave, l_tap = 0;
-    auto next_load = [&](u32x4 (&dst)[PL]) {
-        const uint4 *row = a.wp + (l_tap * tap_stride + (int64_t)l_pair * (2 * PL) * a.Cp);     // uniform
-#pragma unroll
-        for (int pl = 0; pl < PL; ++pl) { const uint4 t = row[wl + (uint32_t)(pl * a.Cp)]; dst[pl] = u32x4{t.x, t.y, t.z, t.w}; }
-        if (++l_tap == RS) {
-            if (l_pair < last_pair) { l_tap = 0; l_pair += waves; }
-            else l_tap = RS - 1;
-        }
-    };
     // Code fragments in two groups of blocks: a group is read from LDS behind the other group's matrix instructions.
     u32x4 bA[NB0], bB[NB1];
     auto read_a = [&](int off) {
@@ -181,11 +195,7 @@ __device__ __forceinline__ void conv_dx_split_body(const ConvDxArgs &a, int b)
             for (int nb = 0; nb < NB1; ++nb) Mma<MODE>::run(cur[pl], bB[nb], acc[NB0 + nb]);
     };
 
-    if (wave < a.pairs) {
-        u32x4 f0[PL], f1[PL], f2[PL];
-        fetch(wave);
-        next_load(f0);
-        if constexpr (T9) next_load(f1);
+    if (active) {
         for (int pair = wave; pair < a.pairs; pair += waves) {
             // The lanes of a wavefront exchange codes through its LDS: in order for the hardware, fenced for the compiler.
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -226,21 +236,39 @@ __device__ __forceinline__ void conv_dx_split_body(const ConvDxArgs &a, int b)
         constexpr int V2 = decltype(vc)::value / 2;
         const bool upper = (wave & h) != 0;                      // uniform
         __syncthreads();
-        uint32_t *dst = fold + wave * (NB * V2 * 64) + lane;
-        const uint32_t *src = fold + (wave ^ h) * (NB * V2 * 64) + lane;
+        constexpr int U = V2 < 4 ? V2 : 4;                       // elements an LDS access takes
+        typedef uint32_t Piece __attribute__((ext_vector_type(U)));
+        Piece *dst = (Piece *)fold + wave * (NB * V2 / U * 64) + lane;
+        const Piece *src = (const Piece *)fold + (wave ^ h) * (NB * V2 / U * 64) + lane;
+        auto give = [&](int first) {
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+            for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int v = 0; v < V2; ++v) {
-                const E lo = acc[nb][v], hi = acc[nb][V2 + v];
-                dst[(nb * V2 + v) * 64] = __builtin_bit_cast(uint32_t, upper ? lo : hi);
-                acc[nb][v] = upper ? hi : lo;
-            }
+                for (int v = 0; v < V2; v += U) {
+                    Piece t;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) t[u] = __builtin_bit_cast(uint32_t, (E)acc[nb][first + v + u]);
+                    dst[(nb * V2 + v) / U * 64] = t;
+                }
+        };
+        if (upper) {
+            give(0);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int v = 0; v < V2; ++v) acc[nb][v] = acc[nb][V2 + v];
+        } else {
+            give(V2);
+        }
         __syncthreads();
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int v = 0; v < V2; ++v) acc[nb][v] += __builtin_bit_cast(E, src[(nb * V2 + v) * 64]);
+            for (int v = 0; v < V2; v += U) {
+                const Piece t = src[(nb * V2 + v) / U * 64];
+#pragma unroll
+                for (int u = 0; u < U; ++u) { const uint32_t x = t[u]; acc[nb][v + u] += __builtin_bit_cast(E, x); }
+            }
         v_first += upper ? V2 : 0;
     };
     const bool eight = waves == 8;
@@ -257,10 +285,10 @@ __device__ __forceinline__ void conv_dx_split_body(const ConvDxArgs &a, int b)
     for (int nb = 0; nb < NB; ++nb) {
         int j = j0 + 32 * nb + lcol;
         if (j >= j_end) continue;
-        const int im = a.NI > 1 ? j / a.PI : 0;
+        const int im = a.NI > 1 ? cdx_div(j, r_pi) : 0;
         j -= im * a.PI;
         int px = j;
-        if constexpr (STRIDED) { const int h = j / a.Wd, w = j - h * a.Wd; px = (a.ost * h + a.oh0) * a.oW + a.ost * w + a.ow0; }
+        if constexpr (STRIDED) { const int h = h_first + cdx_div(j - h_first * a.Wd, r_w), w = j - h * a.Wd; px = (a.ost * h + a.oh0) * a.oW + a.ost * w + a.ow0; }
         const int off = im * (int)a.dx_img + c0 * opi + px;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
