@@ -233,8 +233,7 @@ static const struct { int nb, waves; } kDxSplitForms[6] = {{7, 4}, {4, 4}, {2, 4
 
 ConvDxPlan conv_dx_plan(const ConvArgs &a, bool i8 = false)
 {
-    ConvDxPlan pl;
-    pl.ok = false;
+    ConvDxPlan pl{};
     ConvDxArgs &k = pl.args;
     if (a.stride != 1) return pl;                                // strided layers: conv_dx_strided_plan
     k.N = (int)a.N; k.C = (int)a.C; k.H = (int)a.H; k.Wd = (int)a.Wd; k.K = (int)a.K; k.R = (int)a.R; k.S = (int)a.S;
@@ -260,14 +259,13 @@ struct ConvDxStridedPlan { bool ok, zero_fill; int nb; ConvDxMulti multi; CdxTap
 
 ConvDxStridedPlan conv_dx_strided_plan(const ConvArgs &a, bool i8)
 {
-    ConvDxStridedPlan sp;
-    sp.ok = false; sp.zero_fill = false; sp.taps = 0; sp.lds_bytes = 0; sp.grid = 0;
+    ConvDxStridedPlan sp{};
     const int st = (int)a.stride, R = (int)a.R, S = (int)a.S, pad = (int)a.pad, H = (int)a.H, Wd = (int)a.Wd;
     if (st < 2 || st * st > CDX_MAX_CLASSES || R * S > 64) return sp;
     const int P = (H + 2 * pad - R) / st + 1, Q = (Wd + 2 * pad - S) / st + 1;
     // One pixel-block count for all classes (one launch): conv_dx_kernel's with the least rounds x work per workgroup, and then the faster
     // kernel (conv_dx_workgroup_us).
-    ConvDxStridedPlan best;
+    ConvDxStridedPlan best{};
     double best_cost = -1.0;
     float best_us = 3.0e38f;
     const int cand[3] = {7, 4, 2};
@@ -287,7 +285,7 @@ ConvDxStridedPlan conv_dx_strided_plan(const ConvArgs &a, bool i8)
                 const int r0 = (ph + pad) % st, s0 = (pw + pad) % st;
                 const int Rv = r0 < R ? (R - r0 + st - 1) / st : 0, Sv = s0 < S ? (S - s0 + st - 1) / st : 0;
                 if (Rv == 0 || Sv == 0) { sp.zero_fill = true; continue; }
-                ConvDxPlan pl;
+                ConvDxPlan pl{};
                 ConvDxArgs &k = pl.args;
                 k.N = (int)a.N; k.C = (int)a.C; k.H = Hv; k.Wd = Wv; k.K = (int)a.K; k.R = Rv; k.S = Sv;
                 k.pad = (ph + pad - r0) / st; k.pad_w = (pw + pad - s0) / st;
@@ -1711,8 +1709,9 @@ extern "C" int dbp_plan_conv2d_dx(int64_t N, int64_t C, int64_t H, int64_t Wd, i
     a.N = N; a.C = C; a.H = H; a.Wd = Wd; a.K = K; a.R = R; a.S = S; a.pad = pad; a.stride = stride;
     const dbp::ConvDxPlan pl = dbp::conv_dx_plan(a, int8_w != 0);
     const dbp::ConvDxStridedPlan sp = dbp::conv_dx_strided_plan(a, int8_w != 0);
+    if (!pl.ok && !sp.ok) return 0;
     const int nb = pl.ok ? pl.nb : sp.nb, waves = pl.ok ? pl.waves : sp.waves;
-    return !pl.ok && !sp.ok ? 0 : waves ? 16 * waves + nb : 1;
+    return waves ? 16 * waves + nb : 1;
 }
 
 extern "C" int dbp_plan_conv2d_dw(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t stride, int64_t pad,

@@ -7,7 +7,7 @@ import itertools
 import pytest
 
 import paper_2004_04729_amd as dbp
-from plan_util import DIRECT, GENERAL, GENERIC, GENERIC_FC, ONE, STAGED, THREE, conv_dw_kernel as _dw, fc_kernels as _fc
+from plan_util import DIRECT, GENERAL, GENERIC, GENERIC_FC, ONE, STAGED, THREE, conv_dw_kernel as _dw, conv_dx_kernel as _dx, fc_kernels as _fc
 
 
 def _lib():
@@ -113,6 +113,13 @@ def test_conv_dw_kernels_are_the_faster_ones():
         assert _dw(*case, i8=1) == ONE, case
     assert _dw(1, 1, 12, 12, 64, 5, 5, 2, 0, i8=1) == GENERIC
     assert _dw(128, 64, 4, 4, 64, 3, 3, 1, 1, i8=1) == THREE and _dw(128, 512, 4, 4, 512, 3, 3, 1, 1, i8=1) == GENERAL      # 18 (29); 46 (77)
+
+
+def test_conv_dx_of_layers_that_fit_no_tile_is_generic():
+    """Stride 4 has no class plan; 3x3 rows of 700 codes exceed a workgroup's patch in every form of both kernels."""
+    for q8 in (0, 1):
+        for case in [(2, 8, 19, 19, 64, 3, 3, 4, 1), (2, 64, 700, 700, 128, 3, 3, 1, 1), (2, 64, 1400, 1400, 128, 3, 3, 2, 1)]:
+            assert _dx(*case, q8=q8) == 0, case
 
 
 def test_conv_gather_plans_stay_in_bounds():
