@@ -1589,6 +1589,8 @@ static int check_conv_plans(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t
                 if (hi >= lo && 2 * k.NI * (((hi + 1) * k.Q - (lo * k.Q & ~3) + 3) >> 2) > 64 * cds_items(nb)) return 67;
                 if (hi >= lo && ((hi + 1) * k.Q + 3) / 4 * 4 > k.PQ) return 68;
             }
+            // 32-bit offsets over all images of a tile (the extents are upper bounds of the launch's)
+            if ((int64_t)k.NI * k.code_img >= ((int64_t)1 << 31) || (int64_t)k.NI * (k.dx_img + (int64_t)32 * k.oPI) >= ((int64_t)1 << 31)) return 69;
             return 0;
         };
         if (stride == 1) {

@@ -115,6 +115,13 @@ def test_conv_dw_kernels_are_the_faster_ones():
     assert _dw(128, 64, 4, 4, 64, 3, 3, 1, 1, i8=1) == THREE and _dw(128, 512, 4, 4, 512, 3, 3, 1, 1, i8=1) == GENERAL      # 18 (29); 46 (77)
 
 
+def test_conv_dx_tile_of_few_images_where_offsets_would_pass_31_bits():
+    """One pixel an image under a padding of 100: 20000 planes of 201x201 codes, 0.8e9 codes an image.  Three images fit a lane's items and
+    would pass 2^31 (dbp_plan_check_conv2d answers 69 for such a tile); two do not."""
+    case = (600, 8, 1, 1, 20000, 1, 1, 1, 100)
+    assert _lib().dbp_plan_check_conv2d(*case) == 0 and _dx(*case) == (8, 2)
+
+
 def test_conv_dx_of_layers_that_fit_no_tile_is_generic():
     """Stride 4 has no class plan; 3x3 rows of 700 codes exceed a workgroup's patch in every form of both kernels."""
     for q8 in (0, 1):
