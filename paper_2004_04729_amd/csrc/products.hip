@@ -133,6 +133,32 @@ static float conv_dx_launch_us(float longest, float sum, int64_t grid, int waves
     return (base + (longest > all ? longest : all)) * (waves ? 1.12f : 1.0f);
 }
 
+// The most patch rows, and dwords of one code plane, that a tile of `tile_px` consecutive pixels reads; false as soon as either is beyond what
+// the caller has room for (large planes are refused at their first tile: a plan is made on the host in every call).  No division per tile:
+// tile t begins in row h, column c (dbp_plan_auto_conv2d of a 3x3 layer, us, with divisions and to the end for every form / this: 112x112 8.6 / 5.8,
+// 512x512 88 / 5.0, 2048x2048 1217 / 4.8).
+static bool conv_dx_patch_extent(const ConvDxArgs &k, int tile_px, int tiles, int max_rows, int max_dw, int &prow, int &n_dw)
+{
+    const int rows = tile_px / k.Wd, cols = tile_px - rows * k.Wd;
+    int h = 0, c = 0;
+    prow = n_dw = 0;
+    for (int t = 0; t < tiles; ++t) {
+        const int end = c + cols - 1;                                // column of the tile's last pixel, counted from row h + rows
+        const int h_last = t == tiles - 1 ? k.H - 1 : h + rows + (end >= k.Wd ? 1 : end < 0 ? -1 : 0);
+        const int p_lo = h + k.pad - (k.R - 1);
+        const int p_a = p_lo > 0 ? p_lo : 0, p_b = h_last + k.pad < k.P - 1 ? h_last + k.pad : k.P - 1;
+        if (h_last - h + k.R > prow) prow = h_last - h + k.R;
+        if (p_b >= p_a) {
+            const int f_a = (p_a * k.Q) & ~3, d = ((p_b + 1) * k.Q - f_a + 3) >> 2;
+            if (d > n_dw) n_dw = d;
+        }
+        if (prow > max_rows || n_dw > max_dw) return false;
+        h += rows; c += cols;
+        if (c >= k.Wd) { c -= k.Wd; ++h; }
+    }
+    return true;
+}
+
 static void conv_dx_plan_core(ConvDxPlan &pl, bool i8, int force_nb)
 {
     ConvDxArgs &k = pl.args;
@@ -154,22 +180,12 @@ static void conv_dx_plan_core(ConvDxPlan &pl, bool i8, int force_nb)
         const int nb = cand[ci], tile_px = k.wpx * 32 * nb;
         if (force_nb && nb != force_nb) continue;
         const int tiles = (k.PI + tile_px - 1) / tile_px;
-        int prow = 0, n_dw = 0;
-        for (int t = 0; t < tiles; ++t) {
-            const int j0 = t * tile_px, j_end = j0 + tile_px < k.PI ? j0 + tile_px : k.PI;
-            const int h_first = j0 / k.Wd, h_last = (j_end - 1) / k.Wd;
-            const int p_lo = h_first + k.pad - (k.R - 1);
-            const int p_a = p_lo > 0 ? p_lo : 0, p_b = h_last + k.pad < k.P - 1 ? h_last + k.pad : k.P - 1;
-            if (h_last - h_first + k.R > prow) prow = h_last - h_first + k.R;
-            if (p_b >= p_a) {
-                const int f_a = (p_a * k.Q) & ~3, d = ((p_b + 1) * k.Q - f_a + 3) >> 2;
-                if (d > n_dw) n_dw = d;
-            }
-        }
+        int prow, n_dw;
+        // both patch buffers in LDS, four k-groups each (and so their cell indices in 16 bits, 0xFFFF meaning "no cell"); the items of a lane
+        static_assert(CDX_MAX_LDS / (2 * 16) < 0xFFFF, "cell indices");
+        if (!conv_dx_patch_extent(k, tile_px, tiles, CDX_MAX_LDS / (2 * CDX_KGC * 16) / k.pw, 256 * CDX_ITMAX / CDX_KGC, prow, n_dw)) continue;
         const int64_t cells = (int64_t)prow * k.pw;
         const size_t lds = (size_t)2 * CDX_KGC * cells * 16;
-        // cell indices travel as 16-bit numbers, 0xFFFF meaning "no cell"
-        if (lds > (size_t)CDX_MAX_LDS || (int64_t)n_dw * CDX_KGC > 256 * CDX_ITMAX || CDX_KGC * cells >= 0xFFFF) continue;
         // time ~ rounds of workgroups over the chip (two resident per CU) x work per workgroup
         const int64_t grid = (int64_t)k.N * tiles * k.cgroups;
         const double cost = (double)nb * (double)((grid + 511) / 512);
@@ -205,23 +221,14 @@ static void conv_dx_split_plan_core(ConvDxPlan &pl, bool i8, int nb, int waves)
     if (k.NI > k.N) k.NI = k.N;
     if (k.NI < 1) k.NI = 1;
     k.tiles = k.NI > 1 ? 1 : (k.PI + tile_px - 1) / tile_px;
-    int prow = 0, n_dw = 0;
-    for (int t = 0; t < k.tiles; ++t) {
-        const int j0 = t * tile_px, j_end = k.NI > 1 || j0 + tile_px > k.PI ? k.PI : j0 + tile_px;
-        const int h_first = j0 / k.Wd, h_last = (j_end - 1) / k.Wd, p_lo = h_first + k.pad - (k.R - 1);
-        const int p_a = p_lo > 0 ? p_lo : 0, p_b = h_last + k.pad < k.P - 1 ? h_last + k.pad : k.P - 1;
-        if (h_last - h_first + k.R > prow) prow = h_last - h_first + k.R;
-        if (p_b >= p_a) {
-            const int f_a = (p_a * k.Q) & ~3, d = ((p_b + 1) * k.Q - f_a + 3) >> 2;
-            if (d > n_dw) n_dw = d;
-        }
-    }
-    if (2 * n_dw > 64 * cds_items(nb)) return;
+    if (k.pairs < waves) return;                                     // a wavefront would have nothing to do
+    int prow, n_dw;
+    if (!conv_dx_patch_extent(k, tile_px, k.tiles, CDS_MAX_LDS / (2 * 16 * waves) / k.pw, 64 * cds_items(nb) / 2, prow, n_dw)) return;
     if (k.NI > 1 && 2 * k.NI * n_dw > 64 * cds_items(nb)) k.NI = 64 * cds_items(nb) / (2 * n_dw);
     while (k.NI > 1 && (k.NI * img_codes >= ((int64_t)1 << 31) || k.NI * img_out >= ((int64_t)1 << 31))) --k.NI;
     k.prow = prow; k.img_cells = prow * k.pw; k.patch_cells = k.NI * k.img_cells; k.wave_cells = 2 * k.patch_cells + 1;
     const int64_t stage = (int64_t)waves * k.wave_cells * 16, fold = (int64_t)waves * nb * 8 * 64 * 4, lds = stage > fold ? stage : fold;
-    if (lds > CDS_MAX_LDS || k.wave_cells >= 0xFFFF || k.pairs < waves) return;
+    if (lds > CDS_MAX_LDS || k.wave_cells >= 0xFFFF) return;
     const int64_t grid = (int64_t)((k.N + k.NI - 1) / k.NI) * k.tiles * k.cgroups;
     if (grid > 0x7FFFFFFF) return;
     pl.ok = true; pl.nb = nb; pl.waves = waves; pl.lds_bytes = (size_t)lds; pl.grid = (int)grid;

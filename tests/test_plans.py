@@ -3,6 +3,7 @@ out every work item exactly once, keep every tile / split / class index in range
 the workspace size the library reports.  This is the arithmetic a GPU fault would come from."""
 import ctypes as C
 import itertools
+import time
 
 import pytest
 
@@ -113,6 +114,27 @@ def test_conv_dw_kernels_are_the_faster_ones():
         assert _dw(*case, i8=1) == ONE, case
     assert _dw(1, 1, 12, 12, 64, 5, 5, 2, 0, i8=1) == GENERIC
     assert _dw(128, 64, 4, 4, 64, 3, 3, 1, 1, i8=1) == THREE and _dw(128, 512, 4, 4, 512, 3, 3, 1, 1, i8=1) == GENERAL      # 18 (29); 46 (77)
+
+
+def test_conv_planning_time_does_not_grow_with_the_plane():
+    """Planning is host time of every call.  A 2048x2048 plane has 1000 times the tiles of a 64x64 one, and no tile of it fits: a
+    planner that walks them all takes over 100 times as long, one that stops at the first no longer than for the small plane."""
+    f = dbp.lib().dbp_plan_auto_conv2d
+    f.argtypes, f.restype = [C.c_int64] * 9 + [C.c_int] * 4 + [C.POINTER(C.c_uint64)] * 2, C.c_int
+    a, b = C.c_uint64(), C.c_uint64()
+
+    def microseconds(*case):
+        best = 1e9
+        for _ in range(9):
+            t = time.perf_counter()
+            for _ in range(10):
+                f(*case, 0, 1, 0, 0, C.byref(a), C.byref(b))
+            best = min(best, (time.perf_counter() - t) * 1e5)
+        return best
+
+    for K in (16, 256):
+        assert microseconds(1, 16, 2048, 2048, K, 3, 3, 1, 1) < 10 * microseconds(1, 16, 64, 64, K, 3, 3, 1, 1)
+    assert microseconds(1, 64, 2048, 2048, 256, 3, 3, 2, 1) < 10 * microseconds(1, 64, 64, 64, 256, 3, 3, 2, 1)
 
 
 def test_conv_dx_tile_of_few_images_where_offsets_would_pass_31_bits():
