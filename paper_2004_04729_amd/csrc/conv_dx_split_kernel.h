@@ -317,4 +317,8 @@ __global__ __launch_bounds__(512, 1) void conv_dx_split_multi_kernel(ConvDxMulti
     conv_dx_split_body<NB, MODE, true, false>(a, (int)blockIdx.x - m.first[ci]);
 }
 
+// conv_dx_split.hip: mode MODE_BF16, MODE_BF16X2 or MODE_I8; nb 2, 4 or 7 pixel blocks a tile
+hipError_t launch_conv_dx_split(int mode, const ConvDxArgs &args, int nb, int grid, int waves, size_t lds, hipStream_t s);
+hipError_t launch_conv_dx_split(int mode, const ConvDxMulti &args, int nb, int grid, int waves, size_t lds, hipStream_t s);
+
 }  // namespace dbp

@@ -1203,41 +1203,6 @@ hipError_t launch_zero_words(void *p, int64_t n_words, hipStream_t s)
 // ------------------------------------------------------------------------------------------------
 // Convolution (fast dX kernel: any stride; fast dW kernels: stride 1; the generic kernel serves the rest).
 // ------------------------------------------------------------------------------------------------
-template <class Args>
-static hipError_t launch_dx_split_as(void (*kernel)(Args), bool &raised, const Args &args, int grid, int waves, size_t lds, hipStream_t s)
-{
-    if (!raised) {                                                   // more than 64 KiB of dynamic LDS: allowed per kernel, once
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, CDS_MAX_LDS);
-        if (e != hipSuccess) return e;
-        raised = true;
-    }
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * waves), lds, s, args);
-    return hipGetLastError();
-}
-
-template <int NB, int MODE>
-static hipError_t launch_dx_split_nb(const ConvDxPlan &pl, hipStream_t s)
-{
-    static bool raised[2] = {false, false};
-    if constexpr (NB < 7 || MODE != MODE_I8) {                       // (unrolled, seven blocks and sixteen raw dwords an item do not fit the registers)
-        if (pl.args.R == 3 && pl.args.S == 3) return launch_dx_split_as(&conv_dx_split_kernel<NB, MODE, true>, raised[1], pl.args, pl.grid, pl.waves, pl.lds_bytes, s);
-    }
-    return launch_dx_split_as(&conv_dx_split_kernel<NB, MODE, false>, raised[0], pl.args, pl.grid, pl.waves, pl.lds_bytes, s);
-}
-
-template <int NB, int MODE>
-static hipError_t launch_dx_split_nb(const ConvDxStridedPlan &sp, hipStream_t s)
-{
-    static bool raised = false;
-    return launch_dx_split_as(&conv_dx_split_multi_kernel<NB, MODE>, raised, sp.multi, sp.grid, sp.waves, sp.lds_bytes, s);
-}
-
-template <int MODE, class Plan>
-static hipError_t launch_conv_dx_split(const Plan &pl, hipStream_t s)
-{
-    return pl.nb == 7 ? launch_dx_split_nb<7, MODE>(pl, s) : pl.nb == 4 ? launch_dx_split_nb<4, MODE>(pl, s) : launch_dx_split_nb<2, MODE>(pl, s);
-}
-
 template <int MODE_G, int MODE_K>
 static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, hipStream_t s)
 {
@@ -1294,7 +1259,7 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
                         k.code_img = (pad_codes ? a.K : a.kt()) * k.PQ; k.dx_img = a.ct() * k.oPI;
                         k.wp = (const uint4 *)a.scratch + (int64_t)sp.tap_base[i] * KG * PL * Cp;
                     }
-                    if (sp.waves) return launch_conv_dx_split<MODE_K>(sp, s);
+                    if (sp.waves) return launch_conv_dx_split(MODE_K, sp.multi, sp.nb, sp.grid, sp.waves, sp.lds_bytes, s);
                     if (sp.nb == 7)      hipLaunchKernelGGL((conv_dx_multi_kernel<7, MODE_K>), dim3(sp.grid), dim3(256), sp.lds_bytes, s, sp.multi);
                     else if (sp.nb == 4) hipLaunchKernelGGL((conv_dx_multi_kernel<4, MODE_K>), dim3(sp.grid), dim3(256), sp.lds_bytes, s, sp.multi);
                     else                 hipLaunchKernelGGL((conv_dx_multi_kernel<2, MODE_K>), dim3(sp.grid), dim3(256), sp.lds_bytes, s, sp.multi);
@@ -1309,7 +1274,7 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
             k.codes = kernel_codes; k.wp = (const uint4 *)a.scratch; k.dX = a.dX; k.scale = scale; k.gate = a.gate;
             k.code_img = (pad_codes ? a.K : a.kt()) * k.PQ; k.dx_img = a.ct() * k.PI;
             prepare(k.R * k.S, k.KG, k.Cp, nullptr);
-            if (pl.waves) return launch_conv_dx_split<MODE_K>(pl, s);
+            if (pl.waves) return launch_conv_dx_split(MODE_K, k, pl.nb, pl.grid, pl.waves, pl.lds_bytes, s);
             // tap counts that are a multiple of 3 (3x3 above all) take the form with three weight fragment sets in flight
             const bool ring3 = (k.R * k.S) % 3 == 0;
             const dim3 grid(pl.grid), block(256);
