@@ -109,28 +109,38 @@ struct ConvDxPlan { bool ok; int nb; ConvDxArgs args; size_t lds_bytes; int grid
 
 // Which of the two dX kernels, and with which tiles: by modelled time.  A workgroup costs its pairs (conv_dx_kernel: chunks) of k-groups,
 // each its taps' matrix instructions and the staging of `items` fill items a lane, and its end; workgroups go over the chip's places
-// in a row (two a CU, of eight wavefronts one), half a workgroup longer where they do not fit at once.  The constants (us) are a fit over 360 layers
-// (7 to 112 wide planes, 16 to 1024 channels, 1x1 to 5x5 taps, strides 1 and 2) with six forms of the new kernel each, 18 % rms.  What the rule
-// chooses takes 1.02 (int8 weights 1.01) of the best form's time over them, conv_dx_kernel alone 1.22 (1.12).  conv_dx_kernel keeps a layer
-// unless the other is modelled 12 % faster; a wavefront without a pair would be idle.
+// in a row (two a CU, of eight wavefronts one), half a workgroup longer where they do not fit at once.  The constants (us) are fits over layers of 4 to
+// 260 wide planes, 16 to 1024 channels, 1x1 to 7x7 taps and strides 1 to 3, with every form timed.  Time of the chosen form over the best form's,
+// conv_dx_kernel alone over it, and how many layers were slower than on conv_dx_kernel (by 1.5 % or more):
+//   fp32 weights            302 layers  1.016  1.59   3 (16 % at most)
+//   two bf16 planes         306 layers  1.016  1.64   1 (15 %): chosen by the times of three planes; with the planes in the model as well 1.015, 1
+//   int8 weights, stride 1  566 layers  1.020  1.81  11 (20 %)
+//   int8 weights, strided   566 layers  1.019  1.41  14 (constants of stride 1, seven blocks allowed: 1.037, 63 layers, 38 %)
+// Where the other kernel's time is `margin` times modelled, conv_dx_kernel keeps the layer; a wavefront without a pair would be idle.
+struct ConvDxTimes { float block, tap, mma, staging, trip, base, spread, margin; };
+static const ConvDxTimes &conv_dx_times(bool split, bool i8, bool strided)
+{
+    static const ConvDxTimes t[3][2] = {{{1.21f, 0.0f, 0.0725f, 0.05f, 0.28f, 7.5f, 1.19f, 1.0f}, {0.93f, 0.0635f, 0.0255f, 0.051f, 0.0f, 9.1f, 1.2f, 1.12f}},
+                                        {{0.84f, 0.0f, 0.116f, 0.094f, 0.69f, 11.1f, 1.6f, 1.0f}, {0.76f, 0.095f, 0.0424f, 0.083f, 1.17f, 10.4f, 0.93f, 1.12f}},
+                                        {{3.41f, 0.0f, 0.17f, 0.0709f, 0.0f, 0.0f, 0.78f, 1.0f}, {0.667f, 0.191f, 0.00534f, 0.0379f, 0.24f, 5.94f, 1.64f, 1.0f}}};
+    return t[i8 ? (strided ? 2 : 1) : 0][split];
+}
+
 static float conv_dx_workgroup_us(const ConvDxArgs &k, int nb, int waves, int items, bool i8)
 {
+    const ConvDxTimes &t = conv_dx_times(waves != 0, i8, k.ost > 1);
     const float taps = (float)(k.R * k.S), mma = (float)(i8 ? nb : 3 * nb), staging = (float)(items * (i8 ? 16 : 8));
-    if (waves == 0)
-        return i8 ? 0.84f * nb + (float)k.n_chunks * (taps * 0.116f * mma + 0.094f * staging + 0.69f)
-                  : 1.21f * nb + (float)k.n_chunks * (taps * 0.0725f * mma + 0.05f * staging + 0.28f);
-    const float trips = (float)((k.pairs + waves - 1) / waves);
-    return i8 ? 0.76f * nb + trips * (taps * (0.095f + 0.0424f * mma) + 0.083f * staging + 1.17f)
-              : 0.93f * nb + trips * (taps * (0.0635f + 0.0255f * mma) + 0.051f * staging);
+    const float trips = (float)(waves ? (k.pairs + waves - 1) / waves : k.n_chunks);
+    return t.block * nb + trips * (taps * (t.tap + t.mma * mma) + t.staging * staging + t.trip);
 }
 
 // `longest`: of one workgroup; `sum`: of all of them.
-static float conv_dx_launch_us(float longest, float sum, int64_t grid, int waves, size_t lds, bool i8)
+static float conv_dx_launch_us(float longest, float sum, int64_t grid, int waves, size_t lds, bool i8, bool strided)
 {
-    const float slots = waves == 8 || lds > CDS_MAX_LDS / 2 ? 256.0f : 512.0f, base = waves == 0 ? (i8 ? 11.1f : 7.5f) : i8 ? 10.4f : 9.1f;
-    const float spread = waves == 0 ? (i8 ? 1.6f : 1.19f) : i8 ? 0.93f : 1.2f;
-    const float all = sum / slots * spread + ((float)grid > slots ? 0.5f * longest : 0.0f);
-    return (base + (longest > all ? longest : all)) * (waves ? 1.12f : 1.0f);
+    const ConvDxTimes &t = conv_dx_times(waves != 0, i8, strided);
+    const float slots = waves == 8 || lds > CDS_MAX_LDS / 2 ? 256.0f : 512.0f;
+    const float all = sum / slots * t.spread + ((float)grid > slots ? 0.5f * longest : 0.0f);
+    return (t.base + (longest > all ? longest : all)) * t.margin;
 }
 
 // The most patch rows, and dwords of one code plane, that a tile of `tile_px` consecutive pixels reads; false as soon as either is beyond what
@@ -249,11 +259,11 @@ ConvDxPlan conv_dx_plan(const ConvArgs &a, bool i8 = false)
     k.P = k.H + 2 * k.pad - k.R + 1; k.Q = k.Wd + 2 * k.pad - k.S + 1;
     k.oW = k.Wd; k.oPI = k.H * k.Wd; k.ost = 1; k.oh0 = 0; k.ow0 = 0;
     conv_dx_plan_core(pl, i8, 0);
-    float best = pl.ok ? conv_dx_launch_us(pl.us, pl.us * (float)pl.grid, pl.grid, 0, pl.lds_bytes, i8) : 3.0e38f;
+    float best = pl.ok ? conv_dx_launch_us(pl.us, pl.us * (float)pl.grid, pl.grid, 0, pl.lds_bytes, i8, false) : 3.0e38f;
     for (const auto &f : kDxSplitForms) {
         ConvDxPlan sp = pl;
         conv_dx_split_plan_core(sp, i8, f.nb, f.waves);
-        const float us = sp.ok ? conv_dx_launch_us(sp.us, sp.us * (float)sp.grid, sp.grid, f.waves, sp.lds_bytes, i8) : 3.0e38f;
+        const float us = sp.ok ? conv_dx_launch_us(sp.us, sp.us * (float)sp.grid, sp.grid, f.waves, sp.lds_bytes, i8, false) : 3.0e38f;
         if (sp.ok && us < best) { best = us; pl = sp; }
     }
     return pl;
@@ -280,6 +290,7 @@ ConvDxStridedPlan conv_dx_strided_plan(const ConvArgs &a, bool i8)
         const bool split = attempt >= 3;
         const int nb = split ? kDxSplitForms[attempt - 3].nb : cand[attempt];
         sp.waves = split ? kDxSplitForms[attempt - 3].waves : 0;
+        if (split && i8 && nb == 7) continue;                    // (conv_dx_split.hip)
         float longest = 0.0f, sum = 0.0f;
         sp.ok = false;
         bool all = true;
@@ -320,7 +331,7 @@ ConvDxStridedPlan conv_dx_strided_plan(const ConvArgs &a, bool i8)
         sp.multi.first[sp.multi.n] = (int)grid;
         sp.ok = true; sp.nb = nb; sp.grid = (int)grid;
         const double cost = (double)nb * (double)((grid + 511) / 512);
-        const float us = conv_dx_launch_us(longest, sum, grid, sp.waves, sp.lds_bytes, i8);
+        const float us = conv_dx_launch_us(longest, sum, grid, sp.waves, sp.lds_bytes, i8, true);
         if (split ? us < best_us : best_cost < 0.0 || cost < best_cost) { best_cost = cost; best_us = us; best = sp; }
     }
     if (best_us > 2.0e38f) { sp.ok = false; return sp; }

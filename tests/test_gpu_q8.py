@@ -176,7 +176,8 @@ def test_conv_q8_is_bit_exact(case):
 # dX with the reduction divided between wavefronts (the fp32 form's edges in test_gpu_conv.py), on int8 matrix cores
 @pytest.mark.parametrize("case,form", [((5, 33, 4, 4, 133, 3, 3, 1, 1), (4, 2)), ((5, 33, 7, 7, 270, 3, 3, 1, 1), (8, 2)), ((90, 33, 9, 9, 260, 1, 1, 1, 0), (8, 4)),
                                        ((90, 70, 9, 9, 260, 2, 2, 1, 0), (8, 7)), ((90, 33, 14, 14, 260, 3, 3, 2, 1), (4, 4)),
-                                       ((61, 130, 10, 10, 260, 3, 3, 2, 1), (8, 7))])
+                                       ((61, 130, 10, 10, 260, 3, 3, 2, 1), (4, 4)), ((5, 33, 10, 10, 270, 3, 3, 2, 1), (8, 2)),
+                                       ((8, 130, 18, 18, 560, 3, 3, 2, 1), (8, 4)), ((5, 33, 10, 10, 133, 3, 3, 2, 1), (4, 2))])
 def test_conv_q8_dx_with_the_reduction_divided(case, form):
     from plan_util import conv_dx_kernel
     assert conv_dx_kernel(*case, q8=1) == form
