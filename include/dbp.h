@@ -441,8 +441,9 @@ enum { DBP_DW_GENERIC = 0, DBP_DW_3X3 = 1, DBP_DW_3X3_I8 = 2, DBP_DW_1X1 = 3, DB
 int dbp_plan_conv2d_dw(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t stride, int64_t pad,
                        int int8_x, int dense, int two_planes);
 
-/* The same for dX: 0 the generic kernel, 1 the kernel whose wavefronts divide channels and pixels, else 16 * wavefronts + pixel blocks
- * of the one whose wavefronts divide the reduction; -1 for invalid dimensions.  int8_w: dithered_conv2d_backward_q8. */
+/* The same for dX: 0 the generic kernel; else the pixel blocks (2, 4 or 7) of a wavefront's tile, and 16 * wavefronts on top of them for
+ * the kernel whose wavefronts divide the reduction (without: channels and pixels); -1 for invalid dimensions.  int8_w:
+ * dithered_conv2d_backward_q8.  The choice does not depend on DBP_PATH_TWO_PLANES. */
 int dbp_plan_conv2d_dx(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t stride, int64_t pad, int int8_w);
 
 /* The same for the products of a fully connected layer: DBP_FC_* of dX, or'ed with that of dW << 4 (0: not asked for); -1 for

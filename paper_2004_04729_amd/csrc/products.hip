@@ -1696,7 +1696,7 @@ extern "C" int dbp_plan_conv2d_dx(int64_t N, int64_t C, int64_t H, int64_t Wd, i
     const dbp::ConvDxStridedPlan sp = dbp::conv_dx_strided_plan(a, int8_w != 0);
     if (!pl.ok && !sp.ok) return 0;
     const int nb = pl.ok ? pl.nb : sp.nb, waves = pl.ok ? pl.waves : sp.waves;
-    return waves ? 16 * waves + nb : 1;
+    return 16 * waves + nb;
 }
 
 extern "C" int dbp_plan_conv2d_dw(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t stride, int64_t pad,

@@ -22,8 +22,8 @@ def conv_dw_kernel(N, C_, H, Wd, K, R, S, stride, pad, i8=0, dense=0, two=0):
 
 
 def conv_dx_kernel(N, C_, H, Wd, K, R, S, stride, pad, q8=0):
-    """0: generic, 1: channels and pixels divided, else (wavefronts, pixel blocks) of the kernel that divides the reduction."""
+    """0: generic, else (wavefronts that divide the reduction, pixel blocks); wavefronts 0: the kernel that divides channels and pixels."""
     f = dbp.lib().dbp_plan_conv2d_dx
     f.argtypes, f.restype = [C.c_int64] * 9 + [C.c_int], C.c_int
     r = f(N, C_, H, Wd, K, R, S, stride, pad, q8)
-    return divmod(r, 16) if r > 1 else r
+    return divmod(r, 16) if r > 0 else r

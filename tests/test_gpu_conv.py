@@ -321,17 +321,38 @@ SPLIT_DX = [((5, 33, 7, 7, 200, 3, 3, 1, 1), (8, 2)), ((5, 33, 4, 4, 70, 3, 3, 1
             ((90, 130, 13, 13, 70, 3, 3, 1, 1), (4, 7)), ((90, 33, 9, 9, 520, 3, 3, 1, 1), (8, 4)), ((90, 33, 13, 13, 520, 3, 3, 1, 1), (8, 7)),
             ((90, 33, 14, 14, 520, 1, 1, 1, 0), (8, 7)), ((90, 70, 10, 10, 133, 3, 3, 2, 1), (8, 4)), ((90, 250, 10, 10, 70, 3, 3, 2, 1), (4, 7)),
             ((3, 40, 20, 20, 264, 3, 3, 3, 1), (8, 2)), ((7, 16, 5, 6, 530, 3, 3, 1, 0), (8, 2)), ((17, 64, 12, 12, 256, 2, 3, 1, 1), (8, 2)),
-            ((1, 48, 100, 100, 70, 5, 5, 1, 2), (4, 2)), ((2, 24, 40, 40, 133, 5, 5, 1, 2), (8, 2))]
+            ((1, 48, 100, 100, 70, 5, 5, 1, 2), (4, 2)), ((2, 24, 40, 40, 133, 5, 5, 1, 2), (8, 2)),
+            ((130, 33, 10, 10, 264, 1, 1, 1, 0), (4, 4)), ((61, 260, 6, 6, 200, 1, 1, 1, 0), (8, 4)), ((130, 130, 9, 9, 70, 2, 2, 1, 0), (4, 7)),
+            ((90, 33, 5, 35, 70, 3, 3, 3, 0), (4, 4)), ((130, 33, 34, 12, 200, 2, 2, 3, 0), (8, 7))]
 
 
 @pytest.mark.parametrize("case,form", SPLIT_DX)
 def test_conv_dx_with_the_reduction_divided(case, form):
+    """Three bf16 planes, and two: each on the kernel and tile that the case is for."""
+    import paper_2004_04729_amd as dbp
     from gpu_util import run_conv
     from plan_util import conv_dx_kernel
     assert conv_dx_kernel(*case) == form
     N, C, H, Wd, K, R, S, stride, pad = case
     p = _problem(N, C, H, Wd, K, R, S, pad, stride=stride)
-    _check(p, run_conv(p, want_dw=False))
+    three = run_conv(p, want_dw=False)
+    _check(p, three)
+    two = run_conv(p, path=dbp.PATH_MFMA | dbp.PATH_TWO_PLANES, want_dw=False)
+    _check(p, two)
+    assert not np.array_equal(two["dX"], three["dX"])          # the flag reached a kernel that has the form
+
+
+# dX with channels and pixels divided, every tile and both weight rings: a second group of 128 channels that ends in a partial block of 32, and
+# more than one chunk of the reduction; classes of strides 2 and 3
+WHOLE_DX = [((1, 130, 7, 9, 40, 3, 3, 1, 1), (0, 2)), ((2, 130, 9, 7, 40, 1, 1, 1, 0), (0, 2)), ((2, 130, 9, 11, 40, 3, 3, 2, 1), (0, 2)),
+            ((70, 130, 14, 14, 40, 3, 3, 1, 1), (0, 4)), ((130, 130, 10, 7, 40, 1, 1, 1, 0), (0, 4)), ((33, 130, 27, 11, 40, 2, 2, 2, 0), (0, 4)),
+            ((61, 130, 28, 28, 40, 3, 3, 1, 1), (0, 7)), ((61, 130, 28, 28, 40, 1, 1, 1, 0), (0, 7)), ((64, 130, 28, 28, 40, 3, 3, 2, 1), (0, 7)),
+            ((3, 70, 31, 29, 45, 3, 3, 3, 1), (0, 2))]
+
+
+@pytest.mark.parametrize("case,form", WHOLE_DX)
+def test_conv_dx_with_channels_and_pixels_divided(case, form):
+    test_conv_dx_with_the_reduction_divided(case, form)
 
 
 @pytest.mark.parametrize("case", STRIDED)

@@ -1,5 +1,5 @@
 """GPU parity of the grouped convolution's backward products against the CPU oracle's grouped convolution: every element,
-on every kernel family a group's problem can land on (the fast stride-1 dX kernel, its strided form, the generic
+on every kernel family a group's problem can land on (both dX kernels, at stride 1 and strided, the generic
 implicit-im2col kernel, the 3x3 dW kernel, the 1x1 dW form, the general dW kernel, the int8 dW kernels, the gather kernels)."""
 import numpy as np
 import pytest
@@ -9,6 +9,7 @@ import paper_2004_04729_amd as dbp
 import workloads
 from gpu_util import check_products
 from oracle import oracle as O
+from plan_util import conv_dx_kernel
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -49,7 +50,7 @@ def _run(N, C, H, Wd, K, R, S, stride, pad, groups, path, i8=False, seed=0, c=4.
 
 CASES = [  # N, C, H, Wd, K, R, S, stride, pad, groups
     (2, 8, 9, 7, 6, 3, 3, 1, 1, 2),             # tiny: generic / fast kernels on ragged tiles
-    (3, 64, 14, 14, 96, 3, 3, 1, 1, 2),         # the two-tower AlexNet pattern: fast dX and 3x3 dW kernels per group
+    (3, 64, 14, 14, 96, 3, 3, 1, 1, 2),         # the two-tower AlexNet pattern
     (2, 128, 28, 28, 128, 3, 3, 1, 1, 4),       # ResNeXt-like block, 32 channels per group
     (2, 96, 12, 12, 192, 1, 1, 1, 0, 3),        # 1x1 layer, images strided by the whole tensor
     (2, 32, 13, 13, 64, 3, 3, 2, 1, 2),         # strided: dX as stride-1 problems per pixel class, dW on the general kernel
@@ -60,7 +61,7 @@ CASES = [  # N, C, H, Wd, K, R, S, stride, pad, groups
     (2, 70, 8, 8, 130, 3, 3, 1, 1, 1),          # one group: the ungrouped layer through this entry point
     # 64 and more channels per group: the groups run one after the other on channel blocks of the tensors (fewer: one
     # ungrouped layer with block-diagonal weights)
-    (3, 128, 14, 14, 192, 3, 3, 1, 1, 2),       # fast dX kernel and 3x3 dW kernel per group
+    (3, 128, 14, 14, 192, 3, 3, 1, 1, 2),       # per group: dX with the reduction divided, 3x3 dW kernel
     (2, 192, 12, 12, 384, 1, 1, 1, 0, 3),       # 1x1, images strided by the whole tensor
     (3, 128, 8, 8, 400, 1, 1, 1, 0, 2),         # 1x1: dW on the batched fully connected form
     (2, 128, 13, 13, 128, 3, 3, 2, 1, 2),       # strided: dX per pixel class, dW on the general kernel
@@ -68,6 +69,20 @@ CASES = [  # N, C, H, Wd, K, R, S, stride, pad, groups
     (4, 128, 7, 7, 256, 3, 3, 1, 1, 2),         # 7x7 planes: codes copied into padded planes, planes strided by the whole tensor
     (2, 130, 9, 11, 70, 5, 3, 1, 2, 2),         # odd sizes: generic kernels
 ]
+
+
+# dX of a group on the kernel and tile it is for: channels and pixels divided, at stride 1 and per pixel class; the reduction divided, with a tile
+# of several whole images whose planes lie Kt and Ct planes apart (the last tile not full), codes used in place and copied into padded planes
+DX_FORMS = [((3, 140, 10, 10, 80, 3, 3, 1, 1, 2), (0, 2)), ((3, 140, 13, 11, 80, 3, 3, 2, 1, 2), (0, 2)),
+            ((11, 140, 4, 4, 140, 3, 3, 1, 1, 2), (4, 2)), ((11, 140, 3, 3, 140, 3, 3, 1, 1, 2), (4, 2)), ((6, 140, 8, 8, 140, 3, 3, 2, 1, 2), (4, 2))]
+
+
+@pytest.mark.parametrize("case,form", DX_FORMS)
+def test_grouped_conv_dx_form(case, form):
+    N, C, H, Wd, K, R, S, stride, pad, groups = case
+    assert conv_dx_kernel(N, C // groups, H, Wd, K // groups, R, S, stride, pad) == form
+    _run(*case, path=dbp.PATH_MFMA)
+    _run(*case, path=dbp.PATH_MFMA | dbp.PATH_TWO_PLANES)
 
 
 @pytest.mark.parametrize("case", CASES)

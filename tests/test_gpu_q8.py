@@ -177,12 +177,24 @@ def test_conv_q8_is_bit_exact(case):
 @pytest.mark.parametrize("case,form", [((5, 33, 4, 4, 133, 3, 3, 1, 1), (4, 2)), ((5, 33, 7, 7, 270, 3, 3, 1, 1), (8, 2)), ((90, 33, 9, 9, 260, 1, 1, 1, 0), (8, 4)),
                                        ((90, 70, 9, 9, 260, 2, 2, 1, 0), (8, 7)), ((90, 33, 14, 14, 260, 3, 3, 2, 1), (4, 4)),
                                        ((61, 130, 10, 10, 260, 3, 3, 2, 1), (4, 4)), ((5, 33, 10, 10, 270, 3, 3, 2, 1), (8, 2)),
-                                       ((8, 130, 18, 18, 560, 3, 3, 2, 1), (8, 4)), ((5, 33, 10, 10, 133, 3, 3, 2, 1), (4, 2))])
+                                       ((8, 130, 18, 18, 560, 3, 3, 2, 1), (8, 4)), ((5, 33, 10, 10, 133, 3, 3, 2, 1), (4, 2)),
+                                       ((130, 33, 6, 6, 260, 3, 3, 1, 0), (8, 4)), ((130, 260, 5, 5, 133, 3, 3, 1, 0), (4, 4)),
+                                       ((130, 33, 24, 4, 260, 1, 1, 1, 0), (4, 4)), ((90, 33, 4, 37, 260, 3, 3, 1, 0), (8, 7)),
+                                       ((3, 33, 9, 9, 270, 2, 2, 1, 0), (8, 2))])
 def test_conv_q8_dx_with_the_reduction_divided(case, form):
     from plan_util import conv_dx_kernel
     assert conv_dx_kernel(*case, q8=1) == form
     N, C, H, Wd, K, R, S, stride, pad = case
     test_conv_q8_is_bit_exact((N, C, H, Wd, K, R, S, pad, stride))
+
+
+# the other dX kernel: a partial block of a second group of 128 channels, more than one chunk
+@pytest.mark.parametrize("case,form", [((1, 130, 7, 9, 90, 3, 3, 1, 1), (0, 2)), ((2, 130, 9, 7, 90, 1, 1, 1, 0), (0, 2)),
+                                       ((2, 130, 9, 11, 90, 3, 3, 2, 1), (0, 2)), ((130, 130, 4, 20, 90, 1, 1, 1, 0), (0, 4)),
+                                       ((130, 130, 14, 5, 90, 3, 3, 1, 0), (0, 4)), ((33, 130, 14, 40, 70, 2, 2, 3, 0), (0, 4)),
+                                       ((61, 130, 28, 28, 90, 1, 1, 1, 0), (0, 7)), ((61, 130, 40, 40, 70, 2, 2, 3, 0), (0, 7))])
+def test_conv_q8_dx_with_channels_and_pixels_divided(case, form):
+    test_conv_q8_dx_with_the_reduction_divided(case, form)
 
 
 def test_conv_q8_config5_full_size_in_full():

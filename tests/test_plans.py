@@ -139,17 +139,17 @@ def test_conv_planning_time_does_not_grow_with_the_plane():
 
 def test_conv_dx_kernels_are_the_faster_ones():
     """The choice between the two dX kernels, and of tile and wavefronts, on layers where the forms were measured (us)."""
-    for case, want in [((3, 88, 147, 147, 432, 2, 2, 2, 1), 1),           # int8 weights, strided: 44, the other kernel's 7 blocks x 4 wavefronts 61
-                       ((8, 49, 197, 197, 499, 2, 2, 2, 1), 1),           # 191, 4x4 248
-                       ((96, 24, 145, 7, 188, 3, 3, 3, 2), 1),            # 30, 7x4 38
-                       ((51, 24, 90, 90, 336, 2, 2, 2, 1), 1),            # 101, 7x4 125
+    for case, want in [((3, 88, 147, 147, 432, 2, 2, 2, 1), (0, 2)),       # int8 weights, strided: 44, the other kernel's 7 blocks x 4 wavefronts 61
+                       ((8, 49, 197, 197, 499, 2, 2, 2, 1), (0, 2)),       # 191, 4x4 248
+                       ((96, 24, 145, 7, 188, 3, 3, 3, 2), (0, 2)),       # 30, 7x4 38
+                       ((51, 24, 90, 90, 336, 2, 2, 2, 1), (0, 2)),       # 101, 7x4 125
                        ((70, 427, 20, 7, 475, 3, 3, 2, 1), (4, 4)),       # 50, 7x8 64; 55
                        ((3, 16, 23, 23, 864, 3, 3, 2, 1), (8, 2)),        # 22; 47
                        ((3, 512, 18, 18, 792, 3, 3, 2, 1), (8, 4))]:      # 26; 52
         assert _dx(*case, q8=1) == want, case
     for case, want in [((64, 256, 14, 14, 256, 3, 3, 1, 1), (4, 7)), ((64, 512, 7, 7, 512, 3, 3, 1, 1), (8, 7)),         # 48; 66.  53; 82
                        ((119, 16, 8, 8, 537, 3, 3, 1, 1), (8, 2)), ((83, 40, 8, 8, 840, 3, 3, 2, 1), (8, 2)),           # 22; 70.  27; 81
-                       ((128, 64, 32, 32, 64, 3, 3, 1, 1), 1), ((64, 1024, 14, 14, 256, 1, 1, 1, 0), 1)]:               # 39; 50.  34
+                       ((128, 64, 32, 32, 64, 3, 3, 1, 1), (0, 4)), ((64, 1024, 14, 14, 256, 1, 1, 1, 0), (0, 7))]:     # 39; 50.  34
         assert _dx(*case) == want, case
 
 
