@@ -185,8 +185,11 @@ __device__ __forceinline__ uint32_t cdx_bf16_pair(uint32_t wa, uint32_t wb, int 
 }
 
 // Quotient of two small numbers (0 <= a < 2^20, 0 < d) from r = the reciprocal of d within 1 ulp: (a + 1/2) * r is nearer to (a + 1/2)/d than the
-// 1/(2d) that this lies from an integer.  A division of integers takes ten times the instructions, and a dX workgroup begins with
-// up to 40 a lane before its first load (kernel, us: 64->64 32x32 N=128 34.9 -> 34.3, 3x3/2 128->256 28x28 N=64 45.8 -> 44.6).
+// 1/(2d) that this lies from an integer.  A negative a is allowed (bytes before the patch, items without work) but its quotient, rounded
+// towards zero, means nothing: such callers look at the sign of a first.  A division of integers takes ten times the instructions, and a
+// dX workgroup has up to 40 of these a lane before its first load (preparation and kernel, cold inputs, us, divisions / this: 64->64 32x32
+// N=128 35.5 / 35.3, 3x3/2 128->256 28x28 N=64 48.2 / 48.0, 1x1 256->64 56x56 N=64 74.4 / 73.6, 1x1 1024->256 14x14 N=64 34.8 / 34.4; of 17
+// layers 1x1 512->128 28x28 alone is slower, 48.6 / 49.0).
 __device__ __forceinline__ float cdx_rcp(int d) { return __builtin_amdgcn_rcpf((float)d); }
 __device__ __forceinline__ int cdx_div(int a, float r) { return (int)(((float)a + 0.5f) * r); }
 

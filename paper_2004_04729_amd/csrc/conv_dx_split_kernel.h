@@ -4,7 +4,7 @@
 //   * A workgroup owns 32 input channels x up to 32*NB pixels, a run of pixels of one image or several whole small images
 //     (7x7 planes: 196 of 224 pixel columns in use, where a tile of one image used 49 of 64).  Every wavefront holds the whole
 //     tile in registers, so a weight fragment (from L2, the scarcer stream) is used for NB pixel blocks.  conv_dx_kernel fills the
-//     chip on such layers only with tiles of two blocks, and waits for weights: 3.5 times the L2 reads here.
+//     chip on such layers only with tiles of two blocks, and waits for weights: 3.7 times the L2 reads here.
 //   * Wavefront w takes the pairs of k-groups (2*G output channels) w, w + waves, ...: it stages the codes of its own pair into
 //     LDS of its own, as cells [k-group][patch pixel][G channels], and nobody else reads them.  No barrier before the end: the
 //     wavefronts of a SIMD drift apart and one's staging runs beside the other's matrix instructions.  LDS operations of a
@@ -13,7 +13,8 @@
 //     its rows to its partner and keeps the other half, so that all of them store.
 //   * A workgroup lives for a few pairs only, so its beginning counts: the first weights and codes are asked for before the indices of the LDS
 //     cells are worked out, and these take no integer division (kernel, us: 14x14 49.0 -> 45.6, 7x7 48.2 -> 42.6).
-// What bounds it: matrix instructions and their operands, at about 45 % of the matrix rate in the multiply loop; every workgroup stages its
+// What bounds it: matrix instructions and their operands (256->256 14x14 N=64: matrix cores busy 56 % of the cycles in which a CU has a workgroup,
+// 43 % of the launch; LDS bank conflicts 11 %), and that a CU has nothing to do for a quarter of so short a launch.  Every workgroup stages its
 // pixels' codes for 32 channels only, so layers of many channels AND many pixels stay on conv_dx_kernel (conv_dx_workgroup_us).
 // Measured, preparation and kernel (us), conv_dx_kernel / here: 256->256 14x14 N=64 65.6 / 48, 512->512 7x7 N=64 82.2 / 53,
 // 16->537 8x8 N=119 69.7 / 22.0, 40->840 3x3/2 8x8 N=83 80.9 / 27.4, 332->37 5x5 16x16 N=52 63.9 / 49.0; 64->64 32x32 N=128 39.0 / 49.6.
