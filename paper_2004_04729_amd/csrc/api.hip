@@ -248,8 +248,11 @@ AutoPlan conv_auto_plan(const ConvArgs &call, int64_t P, int64_t Q)
     const double x_elems = (double)(call.N * call.C * call.H * call.Wd);
     const double fixed_us = 15.0 + (call.dX ? x_elems * 4.0 : 0.0) / 2.0e6 + (call.dW ? x_elems * (call.x_dtype == DBP_I8 ? 1.0 : 4.0) : 0.0) / 2.0e6;
     if (fixed_us > 0.5 * mfma_us) return ap;
-    const int products = (call.dX ? 1 : 0) + (call.dW ? 1 : 0);
-    const double per_nnz_us = products * 2.0 * crs / 1.4e6;                          // 1.4 TFLOP/s on nonzeros (LDS read-modify-write bound)
+    // 1.4 TFLOP/s on nonzeros (LDS read-modify-write bound); but dX's workgroups walk an image's entries one after the other, 0.21 us each
+    // whatever the layer (median of 120 layers), which is the longer of the two where the images are few.  180 layers on both sides of
+    // the gate at 0.9 of the threshold, us in all: gather as chosen without the second term 40900, with it 21600, matrix cores 23100.
+    const double flops_us = 2.0 * crs / 1.4e6, walk_us = 0.21 / (double)call.N;
+    const double per_nnz_us = (call.dX ? (flops_us > walk_us ? flops_us : walk_us) : 0.0) + (call.dW ? flops_us : 0.0);
     const double thr = (mfma_us - fixed_us) / per_nnz_us;
     ap.dual = true;
     ap.gather_below = thr >= n_codes ? (uint64_t)n_codes + 1 : (uint64_t)thr;

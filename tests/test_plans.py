@@ -224,6 +224,19 @@ def test_conv_auto_plan_arms_what_the_measurements_say():
     assert L.dbp_plan_auto_conv2d(4, 8, 8, 8, 8, 3, 3, 1, 1, 0, 0, 0, 0, None, None) == -1
 
 
+def test_conv_auto_plan_counts_the_walk_over_an_images_entries():
+    """Few images: dX's gather workgroups walk an image's entries one after the other (0.21 us each).  Layers timed on both sides (us): the
+    threshold lies below the density at which the gather family was the slower one."""
+    f = dbp.lib().dbp_plan_auto_conv2d
+    f.argtypes, f.restype = [C.c_int64] * 9 + [C.c_int] * 4 + [C.POINTER(C.c_uint64)] * 2, C.c_int
+    for case, dw, nonzero in [((10, 80, 6, 153, 936, 3, 3, 1, 1), 0, 0.0008),          # gather 257, matrix cores 112
+                              ((5, 248, 26, 26, 624, 3, 3, 1, 1), 1, 0.0009),          # 171, 112
+                              ((2, 561, 9, 60, 744, 3, 3, 1, 1), 1, 0.0009)]:          # 186, 143
+        g, d = C.c_uint64(), C.c_uint64()
+        N, _, H, Wd, K = case[:5]
+        assert f(*case, 0, 1, dw, 0, C.byref(g), C.byref(d)) == 1 and 0 < g.value < nonzero * N * K * H * Wd, case
+
+
 def test_fc_auto_plan_arms_the_wide_layer_only():
     """Fully connected layers: the gather family's fixed cost (streaming the dense operand, writing dW) is what the matrix
     cores pay too, so the gate is armed only where a layer is wide enough for the nonzero-proportional part to matter:
