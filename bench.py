@@ -160,7 +160,7 @@ def main():
             for _ in range(20):                                            # and the opt-in two-plane form of the same kernel
                 dbp.conv2d_products(b["codes"], None, p5.step, b["W"], b["X"], xd5, N, Cc, H, Wd, K, R, S, p5.stride, p5.pad, b["dX"], None,
                                     b["ws"], dbp.PATH_MFMA | dbp.PATH_TWO_PLANES, stream)
-            what = "20 launches of conv_dx_weight_prep_kernel + conv_dx_kernel on config 5 (90 % zeros), two fp16 planes, then 20 with two bf16 planes"
+            what = "20 launches of conv_dx_weight_prep_kernel + conv_dx_kernel on config 5 (90 % zeros), three planes, then 20 with two planes"
         elif args.probe == "conv_dw":
             b = sets5[0]
             dbp.nsd_quantize(b["d"], N * K, P * Q, p5.step, p5.seed, 0, b["codes"], None, None, stream)
@@ -238,7 +238,7 @@ def main():
     t_dx, t_dw, t_nsd5 = timed(k_dx, it), timed(k_dw, it), timed(k_nsd, it)
     alg_flops = 2.0 * nnz5 * Cc * R * S                                   # the method's work for dX: 2*nnz*C*R*S
     alg_bytes = float(n_codes + 4 * p5.W.size + 4 * p5.X.size)            # codes + W read, dX written (compulsory)
-    exe_flops = 2 * 2.0 * n_codes * Cc * R * S                            # executed: dense product x 2 fp16 planes of W
+    exe_flops = 3 * 2.0 * n_codes * Cc * R * S                            # executed: dense product x 3 exact bf16 planes of W
     t_k = t_dx["mean"]
     t_flop_bound, t_byte_bound = alg_flops / (PEAK_F32_VECTOR_TFLOPS * 1e12), alg_bytes / (PEAK_HBM_GBS * 1e9)
     traffic = None
@@ -248,7 +248,7 @@ def main():
             if line.startswith("traffic_bytes_per_launch:"):
                 traffic = float(line.split(":")[1])
     roofline = {
-        "bound": "alu", "kernel": "conv_dx_kernel<7, fp16x2> (dX of config 5; the event-timed call includes its launches for the weights' ranges and preparation)",
+        "bound": "alu", "kernel": "conv_dx_kernel<7, bf16x3> (dX of config 5; the event-timed call includes its 3-5 us weight preparation launch)",
         "achieved": alg_flops / t_k / 1e12, "peak": PEAK_F32_VECTOR_TFLOPS, "unit": "TFLOP/s",
         "frac": alg_flops / t_k / 1e12 / PEAK_F32_VECTOR_TFLOPS, "traffic": traffic,
         "flops_counted": "the method's work, 2*nnz*C*R*S (Sec. 'Computational complexity'), against the fp32 vector peak",
@@ -256,7 +256,7 @@ def main():
         "binding_bound": "alu" if t_flop_bound > t_byte_bound else "hbm",
         "hbm": {"bytes_compulsory": alg_bytes, "achieved_GBps": alg_bytes / t_k / 1e9, "frac_of_8TBps": alg_bytes / t_k / 1e9 / PEAK_HBM_GBS},
         "executed_mfma": {"flops": exe_flops, "achieved_TFLOPs": exe_flops / t_k / 1e12, "frac_of_2.5PFLOPs_bf16": exe_flops / t_k / 1e12 / PEAK_BF16_TFLOPS,
-                          "note": "what the chosen algorithm executes: dense product x 2 fp16 planes; not the method's work"},
+                          "note": "what the chosen algorithm executes: dense product x 3 bf16 planes; not the method's work"},
         "dense_equiv_tflops": 2.0 * n_codes * Cc * R * S / t_k / 1e12,
     }
     kernels5 = {"nsd_us": t_nsd5["median"] * 1e6, "dX_us": t_dx["median"] * 1e6, "dW_int8_us": t_dw["median"] * 1e6,
@@ -275,7 +275,7 @@ def main():
         "ms_per_step": t_step2 * 1e3, "dense_equiv_tflops": dense_flops5 / t_step2 / 1e12, "dX_us": t_dx2["median"] * 1e6,
         "executed_mfma_frac_of_2.5PFLOPs_bf16": 2 * 2.0 * n_codes * Cc * R * S / t_dx2["mean"] / 1e12 / PEAK_BF16_TFLOPS,
         "note": "opt-in flag DBP_PATH_TWO_PLANES: fp32 W in two bf16 planes rounded to nearest (error <= 2^-16 * sum|q||w| per output, inside the "
-                "1e-4 tolerance); NOT the headline, whose two fp16 planes carry 23 to 24",
+                "1e-4 tolerance); NOT the headline, which multiplies the exact three-plane split",
     }
 
     graphs5 = [captured(lambda st_, b=b: conv_call(b, dims5, xd5, p5, p5.step, on=st_)) for b in sets5]
@@ -285,7 +285,7 @@ def main():
         "metric": "dithered backward dense-equiv TFLOP/s (NSD + dX + dW, one call on config 5: VGG conv3-shaped layer, 8-bit mode)",
         "value": value, "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": t_step * 1e3, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "dX: fp16x2 MFMA (exact int8 codes x fp32 W in two scaled fp16 planes, 23-24 bits), fp32 accumulate; dW: int8 MFMA, exact int32",
+        "dtype": "dX: bf16x3 MFMA (exact int8 codes x 3-plane split of fp32 W), fp32 accumulate; dW: int8 MFMA, exact int32",
         "data": "synthetic",
         "config": {"workload": "configs[4] (config 5): conv 3x3, N=32, 256->256, 56x56, int8 X, fp32 W, Delta for %g %% zeros" % (100 * args.sparsity),
                    "sparsity": 1 - nnz5 / n_codes, "path": "AUTO: " + path5},

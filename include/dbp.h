@@ -84,9 +84,7 @@ typedef enum {
     DBP_PATH_GATHER = 2,
     /* A flag, OR-ed onto one of the three above.  The matrix-core kernels multiply the integer codes with the fp32 operand (W for dX,
      * X for dW) cut into bf16 planes.  By default three planes that add up to the operand exactly, so the only rounding is the fp32
-     * accumulation; dX of 3x3 layers of stride 1 with at least 1024 products a sum takes two scaled fp16 planes instead where every
-     * channel's weights have the range for it (23 to 24 significant bits, error of dX against 64-bit arithmetic no larger on average:
-     * a product less is rounded per term).  With this flag the kernels that support it (the rest ignore it) cut the operand into TWO planes, rounded to
+     * accumulation.  With this flag the kernels that support it (the rest ignore it) cut the operand into TWO planes, rounded to
      * nearest: the operand then carries 16 significant bits, |w - hi - lo| <= 2^-16 |w|, and an output differs from the three-plane
      * one by at most 2^-16 * sum_r |q_r| |w_r| over its own reduction (1.5e-5, against the 1e-4 this library's results are held to;
      * the dither of Eq. (nsd) itself moves every term by up to Delta) for two thirds of the matrix-core work.  The int8 products

@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libdbp_hip.so")
-SOURCES = ["api.hip", "nsd.hip", "products.hip", "conv_dx_split.hip", "conv_dx_planes.hip", "fc_fused.hip", "gather.hip"]
+SOURCES = ["api.hip", "nsd.hip", "products.hip", "conv_dx_split.hip", "conv_dx.hip", "fc_fused.hip", "gather.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-I" + INCLUDE,
          # packed-fp32 VALU forms are disabled on purpose (hipcc's host pass warns it does not know the feature)

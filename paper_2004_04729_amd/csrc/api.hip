@@ -57,7 +57,6 @@ dbp_status format_layout(int64_t rows, int64_t cols, dbp_format_layout *L)
 struct Carve {                      // pieces of a backward workspace
     dbp_format_layout fmt;
     size_t codes_offset, scratch_offset, total;
-    size_t spare_bytes() const { return fmt.tile_nnz_offset; }        // the format's bitmap, first of all: spare where no format is written
 };
 
 Carve carve(int64_t rows, int64_t cols, size_t scratch_bytes)
@@ -75,7 +74,7 @@ Carve carve(int64_t rows, int64_t cols, size_t scratch_bytes)
 dbp_status run_nsd(const float *delta, int64_t rows, int64_t cols, float step, uint64_t seed, uint64_t idx_base,
                    int8_t *codes, char *fmt_base, const dbp_format_layout *L, dbp_stats *stats, hipStream_t s,
                    bool want_format = true, StatsJob *defer = nullptr, const dbp_nsd_extras *ex = nullptr, bool bias_zeroed = false,
-                   const StepTree *tree = nullptr, const uint32_t *topk_thr = nullptr, int64_t topk_vec_rows = 1, const RangeJob &range = RangeJob{})
+                   const StepTree *tree = nullptr, const uint32_t *topk_thr = nullptr, int64_t topk_vec_rows = 1)
 {
     NsdArgs a;
     a.topk_thr = topk_thr; a.topk_vec_rows = topk_vec_rows;
@@ -104,7 +103,7 @@ dbp_status run_nsd(const float *delta, int64_t rows, int64_t cols, float step, u
     }
     const DitherKeys k = make_dither_keys(seed);
     a.k0 = k.k0; a.k1 = k.k1; a.idx_base = idx_base;
-    return launch_nsd(a, s, defer, range) == hipSuccess ? DBP_OK : DBP_ERR_DEVICE;
+    return launch_nsd(a, s, defer) == hipSuccess ? DBP_OK : DBP_ERR_DEVICE;
 }
 
 // The quantiser's part of a fully connected call whose products do it themselves (linear_fused_ok).
@@ -328,7 +327,7 @@ dbp_status conv2d_products(const int8_t *codes, const void *format, float step, 
                                int64_t R, int64_t S, int64_t stride, int64_t pad, float *dX, void *dW,
                                void *workspace, size_t workspace_bytes, dbp_path path, void *stream, const float *step_dev = nullptr,
                                StatsJob job = StatsJob{nullptr, 0, nullptr, nullptr, 0, nullptr, 0.0f, nullptr}, Gate gate = Gate{},
-                               Gate gate_dw = Gate{}, bool rows_gated = false, char *spare = nullptr, size_t spare_bytes = 0, bool range_done = false)
+                               Gate gate_dw = Gate{}, bool rows_gated = false)
 {
     if (!codes || !W || (!dX && !dW) || (dW && !X)) return DBP_ERR_NULL;
     int64_t P, Q;
@@ -365,7 +364,6 @@ dbp_status conv2d_products(const int8_t *codes, const void *format, float step, 
     a.N = N; a.C = C; a.H = H; a.Wd = Wd; a.K = K; a.R = R; a.S = S; a.pad = pad; a.stride = stride;
     a.dX = dX; a.dW = dW; a.scratch = workspace; a.scratch_bytes = workspace_bytes;
     a.stats_job = job; a.pending = nullptr; a.gate = gate; a.gate_dw = gate_dw;
-    a.spare = spare; a.spare_bytes = spare_bytes; a.range_done = range_done;
     a.two_planes = path_two_planes(path);
     return launch_conv_mfma(a, (hipStream_t)stream) == hipSuccess ? DBP_OK : DBP_ERR_DEVICE;
 }
@@ -393,12 +391,11 @@ dbp_status linear_products_dispatch(const AutoPlan &ap, const int8_t *k, char *w
 dbp_status conv2d_products_dispatch(const AutoPlan &ap, const int8_t *k, char *ws, const Carve &c, size_t scratch_bytes, float step,
                                     const float *W, const void *X, dbp_dtype x_dtype, int64_t N, int64_t C, int64_t H, int64_t Wd,
                                     int64_t K, int64_t R, int64_t S, int64_t stride, int64_t pad, float *dX, void *dW, dbp_path path,
-                                    void *stream, StatsJob job, const float *step_dev, bool range_done)
+                                    void *stream, StatsJob job, const float *step_dev)
 {
-    const size_t spare_bytes = ap.dual ? 0 : c.spare_bytes();
     if (!ap.gated())
         return conv2d_products(k, ws, step, W, X, x_dtype, N, C, H, Wd, K, R, S, stride, pad, dX, dW, ws + c.scratch_offset, scratch_bytes,
-                               path, stream, step_dev, job, Gate{}, Gate{}, false, ws, spare_bytes, range_done);
+                               path, stream, step_dev, job);
     // Three states, one flag each (write_density_flags): everything on matrix cores; dX on matrix cores and dW on the gather
     // kernel that scans the code planes; everything on the gather kernels that walk the format's entries.
     int *flag = (int *)(ws + c.fmt.scratch_offset + kNsdFlagOffset);
@@ -413,7 +410,7 @@ dbp_status conv2d_products_dispatch(const AutoPlan &ap, const int8_t *k, char *w
     }
     dbp_status st = conv2d_products(k, ws, step, W, X, x_dtype, N, C, H, Wd, K, R, S, stride, pad, dX, dW, ws + c.scratch_offset,
                                     scratch_bytes, path_with_flags(DBP_PATH_MFMA, path), stream, step_dev, job,
-                                    ap.dual ? Gate{flag, 0} : Gate{}, rows ? Gate{flag + 2, 1} : Gate{}, false, ws, spare_bytes, range_done);
+                                    ap.dual ? Gate{flag, 0} : Gate{}, rows ? Gate{flag + 2, 1} : Gate{});
     if (st != DBP_OK) return st;
     if (ap.dual) {
         st = conv2d_products(k, ws, step, W, X, x_dtype, N, C, H, Wd, K, R, S, stride, pad, dX, dW, ws + c.scratch_offset,
@@ -604,18 +601,17 @@ dbp_status dithered_conv2d_backward(const float *delta, const float *W, const vo
     if (!aligned(delta, 4)) return DBP_ERR_SHAPE;
     char *ws = (char *)workspace;
     int8_t *k = codes ? codes : (int8_t *)(ws + c.codes_offset);
-    ConvArgs call = conv_call(W, X, x_dtype, N, C, H, Wd, K, R, S, stride, pad, dX, dW, k, ws + c.scratch_offset, workspace_bytes - c.scratch_offset,
-                                    path_two_planes(path));
-    const AutoPlan ap = path_family(path) == DBP_PATH_AUTO ? conv_auto_plan(call, P, Q) : AutoPlan{false, 0};
-    if (!ap.dual) { call.spare = ws; call.spare_bytes = c.spare_bytes(); }
-    const RangeJob range = path_family(path) == DBP_PATH_GATHER || ap.dual ? RangeJob{} : conv_dx_range_job(call);
+    const AutoPlan ap = path_family(path) == DBP_PATH_AUTO
+        ? conv_auto_plan(conv_call(W, X, x_dtype, N, C, H, Wd, K, R, S, stride, pad, dX, dW, k, ws + c.scratch_offset,
+                                   workspace_bytes - c.scratch_offset, path_two_planes(path)), P, Q)
+        : AutoPlan{false, 0};
     dbp_stats *st_dev = stats ? stats : ap.gated() ? (dbp_stats *)(ws + c.fmt.scratch_offset + kNsdFlagOffset + 64) : nullptr;
     StatsJob job;
     st = run_nsd(delta, N * K, P * Q, step, seed, idx_base, k, ws, &c.fmt, st_dev, (hipStream_t)stream,
-                 path_family(path) == DBP_PATH_GATHER || ap.dual, &job, nullptr, false, nullptr, nullptr, 1, range);
+                 path_family(path) == DBP_PATH_GATHER || ap.dual, &job);
     if (st != DBP_OK) return st;
     return conv2d_products_dispatch(ap, k, ws, c, workspace_bytes - c.scratch_offset, step, W, X, x_dtype, N, C, H, Wd, K, R, S, stride,
-                                    pad, dX, dW, path, stream, job, nullptr, range.slabs > 0);
+                                    pad, dX, dW, path, stream, job, nullptr);
 }
 
 // ---- grouped convolution: the groups are independent layers on channel blocks of the same tensors, launched one after
@@ -1054,26 +1050,25 @@ dbp_status dithered_conv2d_layer_backward(const float *delta_a, const float *act
     char *ws = (char *)workspace;
     hipStream_t hs = (hipStream_t)stream;
     float *pair = step_out ? step_out : (float *)(ws + lc.step_pair);
-    int8_t *k = codes ? codes : (int8_t *)(ws + c.codes_offset);
-    ConvArgs call = conv_call(W, X, x_dtype, N, C, H, Wd, K, R, S, stride, pad, dX, dW, k, ws + c.scratch_offset, c.total - c.scratch_offset,
-                                    path_two_planes(path));
-    const AutoPlan ap = path_family(path) == DBP_PATH_AUTO && (dX || dW) ? conv_auto_plan(call, P, Q) : AutoPlan{false, 0};
-    if (!ap.dual) { call.spare = ws; call.spare_bytes = c.spare_bytes(); }
-    const RangeJob range = path_family(path) == DBP_PATH_GATHER ? RangeJob{} : conv_dx_range_job(call);
     StepTree tree;
     if (launch_step_size(delta_a, act, N * K * P * Q, s, pair, ws + lc.step_scratch, hs,
-                         db ? (int64_t *)(ws + lc.bias_sums) : nullptr, db ? K : 0, &tree, range) != hipSuccess) return DBP_ERR_DEVICE;
+                         db ? (int64_t *)(ws + lc.bias_sums) : nullptr, db ? K : 0, &tree) != hipSuccess) return DBP_ERR_DEVICE;
     dbp_nsd_extras ex;
     ex.act = act; ex.step_dev = pair; ex.bias_sums = db ? (int64_t *)(ws + lc.bias_sums) : nullptr; ex.bias_grad = db;
     ex.bias_mode = DBP_BIAS_PER_ROW_GROUP; ex.bias_len = K;
+    int8_t *k = codes ? codes : (int8_t *)(ws + c.codes_offset);
     StatsJob job;
+    const AutoPlan ap = path_family(path) == DBP_PATH_AUTO && (dX || dW)
+        ? conv_auto_plan(conv_call(W, X, x_dtype, N, C, H, Wd, K, R, S, stride, pad, dX, dW, k, ws + c.scratch_offset,
+                                   c.total - c.scratch_offset, path_two_planes(path)), P, Q)
+        : AutoPlan{false, 0};
     dbp_stats *st_dev = stats ? stats : ap.gated() ? (dbp_stats *)(ws + c.fmt.scratch_offset + kNsdFlagOffset + 64) : nullptr;
     st = run_nsd(delta_a, N * K, P * Q, 1.0f, seed, idx_base, k, ws, &c.fmt, st_dev, hs, path_family(path) == DBP_PATH_GATHER || ap.dual, &job, &ex,
                  true, &tree);
     if (st != DBP_OK) return st;
     if (!dX && !dW) return launch_stats_job(job, hs) == hipSuccess ? DBP_OK : DBP_ERR_DEVICE;
     return conv2d_products_dispatch(ap, k, ws, c, c.total - c.scratch_offset, 1.0f, W, X, x_dtype, N, C, H, Wd, K, R, S, stride, pad, dX, dW,
-                                    path, stream, job, pair, range.slabs > 0);
+                                    path, stream, job, pair);
 }
 
 // The density dispatch a DBP_PATH_AUTO convolution call would set up, from the host's cost models alone (no GPU call).

@@ -43,18 +43,6 @@ DitherKeys make_dither_keys(uint64_t seed);
 // last levels themselves, in the tree's order, and its first workgroup writes {Delta, 1/Delta}.  count == 0: none.
 struct StepTree { const double *s1, *s2; int count; int64_t n; float s; float *step_out; };
 
-// The range of a convolution's weights [K][C][RS], per channel: bit patterns of the largest |w| and, less one, of the smallest nonzero one
-// (0xFFFFFFFF: all zero), one pair per slab of k_per output channels (conv_dx_weight_prep_kernel combines them).  No slabs: no job.
-struct RangeJob {
-    const float *w = nullptr; uint2 *partial = nullptr;               // partial: [slabs][Cp]
-    int K = 0, C = 0, RS = 0, Cp = 0, slabs = 0, k_per = 0;
-    __host__ __device__ int per_group() const { return RS < 256 ? 256 / RS : 1; }            // channels of a workgroup: a thread per weight of a row
-    __host__ __device__ int groups() const { return (C + per_group() - 1) / per_group(); }
-    __host__ __device__ int workgroups() const { return slabs ? slabs * groups() : 0; }
-};
-
-struct NoJob {};                                                       // a kernel's argument in its place where it takes none
-
 struct NsdArgs {
     const float *delta;
     int8_t      *codes;
@@ -125,8 +113,7 @@ __device__ __forceinline__ int wave_sum(int v)
 // Launches the quantiser.  With `defer` non-null and statistics kept in records, the final sum is not
 // launched: *defer describes it, and the caller either folds it into a later kernel of the same stream
 // or calls launch_stats_job.
-// `range`: taken along in workgroups of its own, in front of the quantiser's (the plain quantiser without format only).
-hipError_t launch_nsd(const NsdArgs &a, hipStream_t s, StatsJob *defer = nullptr, const RangeJob &range = RangeJob{});
+hipError_t launch_nsd(const NsdArgs &a, hipStream_t s, StatsJob *defer = nullptr);
 hipError_t launch_stats_job(const StatsJob &j, hipStream_t s);
 // Top-k sparsifier, first half: thr[v] = bit pattern of the k-th largest magnitude of vector v (n_vec vectors of len
 // consecutive elements, len < 2^31); the quantiser (launch_nsd with NsdArgs::topk_thr) keeps what reaches it.
@@ -141,8 +128,7 @@ size_t     quantize_scratch_bytes(int64_t n);
 hipError_t launch_quantize_int8(const float *x, int64_t n, int8_t *q, float *scale_out, void *scratch, hipStream_t st);
 hipError_t launch_step_size(const float *delta, const float *act, int64_t n, float s, float *step_out, void *scratch, hipStream_t st,
                             int64_t *zero = nullptr, int64_t zero_len = 0,    // also clears zero[0..zero_len)
-                            StepTree *defer = nullptr,    // non-null: small trees are left to the quantiser (defer->count > 0)
-                            const RangeJob &range = RangeJob{});   // taken along in workgroups of its own
+                            StepTree *defer = nullptr);   // non-null: small trees are left to the quantiser (defer->count > 0)
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -208,10 +194,6 @@ struct ConvArgs {
     size_t        scratch_bytes;
     StatsJob      stats_job;   // statistics sum / bias gradient still to be done on this stream (none: n == 0 and bias_len == 0)
     StatsJob     *pending;     // set by launch_conv_mfma: what of stats_job no kernel has taken along yet
-    // room outside the scratch that nobody else uses during the call (0: none), and whether an earlier launch has done conv_dx_range_job(*this)
-    char         *spare = nullptr;
-    size_t        spare_bytes = 0;
-    bool          range_done = false;
     Gate          gate;        // device-side dispatch (the large kernels; the small preparation kernels run regardless)
     Gate          gate_dw;     // matrix-core family: the dW kernels' gate where it differs from the dX kernels' (flag == nullptr: `gate` serves both)
     bool          rows_gated = false;    // gather family: the plane-scanning kernels also behind a gate (else a gated call takes the entry-walking kernels)
@@ -222,7 +204,6 @@ size_t     conv_scratch_bytes(int64_t N, int64_t C, int64_t H, int64_t Wd, int64
 hipError_t launch_linear_mfma(const LinearArgs &a, hipStream_t s);
 bool       linear_fused_ok(const LinearArgs &a);            // the products may quantise themselves (LinearArgs::fused)
 hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t s);
-RangeJob   conv_dx_range_job(const ConvArgs &a);            // what the launch of the quantiser or of the step size may take along for the dX product (no slabs: nothing)
 hipError_t launch_zero_words(void *p, int64_t n_words, hipStream_t s);      // clears n 4-byte words
 // grouped convolution as one ungrouped layer: block-diagonal weights in, diagonal blocks of dW out (products.hip)
 hipError_t launch_group_weights_expand(const float *W, float *full, int64_t K, int64_t C, int64_t groups, int64_t RS, hipStream_t s);

@@ -1,0 +1,48 @@
+// Launches of conv_dx_kernel and conv_dx_multi_kernel; plans: products.hip, the kernel that divides the reduction: conv_dx_split.hip.  A code object of its
+// own: among the dW kernels of products.hip its loops cost calls of those up to 2 % (512->512 7x7 N=64, the call: 126.5 us and 129.4).
+#include <hip/hip_runtime.h>
+#include "conv_dx_kernel.h"
+
+namespace dbp {
+
+template <int MODE>
+static void launch_mode(const ConvDxArgs &args, int nb, int grid, size_t lds, hipStream_t s)
+{
+    // tap counts that are a multiple of 3 (3x3 above all) take the form with three weight fragment sets in flight
+    const bool ring3 = (args.R * args.S) % 3 == 0;
+    auto launch = [&](auto n, auto ring) {
+        hipLaunchKernelGGL((conv_dx_kernel<decltype(n)::value, MODE, decltype(ring)::value>), dim3(grid), dim3(256), lds, s, args);
+    };
+    auto blocks = [&](auto ring) {
+        if (nb == 7)      launch(std::integral_constant<int, 7>{}, ring);
+        else if (nb == 4) launch(std::integral_constant<int, 4>{}, ring);
+        else              launch(std::integral_constant<int, 2>{}, ring);
+    };
+    if (ring3) blocks(std::true_type{}); else blocks(std::false_type{});
+}
+
+template <int MODE>
+static void launch_mode(const ConvDxMulti &args, int nb, int grid, size_t lds, hipStream_t s)
+{
+    if (nb == 7)      hipLaunchKernelGGL((conv_dx_multi_kernel<7, MODE>), dim3(grid), dim3(256), lds, s, args);
+    else if (nb == 4) hipLaunchKernelGGL((conv_dx_multi_kernel<4, MODE>), dim3(grid), dim3(256), lds, s, args);
+    else              hipLaunchKernelGGL((conv_dx_multi_kernel<2, MODE>), dim3(grid), dim3(256), lds, s, args);
+}
+
+hipError_t launch_conv_dx(int mode, const ConvDxArgs &args, int nb, int grid, size_t lds, hipStream_t s)
+{
+    if (mode == MODE_I8)          launch_mode<MODE_I8>(args, nb, grid, lds, s);
+    else if (mode == MODE_BF16X2) launch_mode<MODE_BF16X2>(args, nb, grid, lds, s);
+    else                          launch_mode<MODE_BF16>(args, nb, grid, lds, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_conv_dx(int mode, const ConvDxMulti &args, int nb, int grid, size_t lds, hipStream_t s)
+{
+    if (mode == MODE_I8)          launch_mode<MODE_I8>(args, nb, grid, lds, s);
+    else if (mode == MODE_BF16X2) launch_mode<MODE_BF16X2>(args, nb, grid, lds, s);
+    else                          launch_mode<MODE_BF16>(args, nb, grid, lds, s);
+    return hipGetLastError();
+}
+
+}  // namespace dbp

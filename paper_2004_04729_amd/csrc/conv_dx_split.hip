@@ -23,12 +23,10 @@ static hipError_t launch_nb(const ConvDxArgs &args, int grid, int waves, size_t 
 {
     static bool raised[2] = {false, false};
     // Seven blocks and sixteen raw dwords an item do not fit the registers: unrolled not at all, and rolled one is spilled, outside the loops.
-    if constexpr (MODE == MODE_F16) {
-        return args.R == 3 && args.S == 3 ? launch_as(&conv_dx_split_kernel<NB, MODE, true>, raised[1], args, grid, waves, lds, s) : hipErrorInvalidValue;
-    } else if constexpr (NB < 7 || MODE != MODE_I8) {
+    if constexpr (NB < 7 || MODE != MODE_I8) {
         if (args.R == 3 && args.S == 3) return launch_as(&conv_dx_split_kernel<NB, MODE, true>, raised[1], args, grid, waves, lds, s);
     }
-    if constexpr (MODE != MODE_F16) return launch_as(&conv_dx_split_kernel<NB, MODE, false>, raised[0], args, grid, waves, lds, s);
+    return launch_as(&conv_dx_split_kernel<NB, MODE, false>, raised[0], args, grid, waves, lds, s);
 }
 
 template <int NB, int MODE>
@@ -36,11 +34,9 @@ static hipError_t launch_nb(const ConvDxMulti &args, int grid, int waves, size_t
 {
     // (int8 with seven blocks: spilled registers, too, and of 566 strided layers the fastest form for so few that leaving it out of the choice made
     // the choice better: planned never)
-    if constexpr ((NB == 7 && MODE == MODE_I8) || MODE == MODE_F16) return hipErrorInvalidValue;
-    else {
-        static bool raised = false;
-        return launch_as(&conv_dx_split_multi_kernel<NB, MODE>, raised, args, grid, waves, lds, s);
-    }
+    if constexpr (NB == 7 && MODE == MODE_I8) return hipErrorInvalidValue;
+    static bool raised = false;
+    return launch_as(&conv_dx_split_multi_kernel<NB, MODE>, raised, args, grid, waves, lds, s);
 }
 
 template <int MODE, class Args>
@@ -53,7 +49,6 @@ template <class Args>
 static hipError_t launch(int mode, const Args &args, int nb, int grid, int waves, size_t lds, hipStream_t s)
 {
     return mode == MODE_I8 ? launch_mode<MODE_I8>(args, nb, grid, waves, lds, s) :
-           mode == MODE_F16 ? launch_mode<MODE_F16>(args, nb, grid, waves, lds, s) :
            mode == MODE_BF16X2 ? launch_mode<MODE_BF16X2>(args, nb, grid, waves, lds, s) : launch_mode<MODE_BF16>(args, nb, grid, waves, lds, s);
 }
 

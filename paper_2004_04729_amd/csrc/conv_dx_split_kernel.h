@@ -16,8 +16,7 @@
 // What bounds it: matrix instructions and their operands (256->256 14x14 N=64: matrix cores busy 56 % of the cycles in which a CU has a workgroup,
 // 43 % of the launch; LDS bank conflicts 11 %), and that a CU has nothing to do for a quarter of so short a launch.  Every workgroup stages its
 // pixels' codes for 32 channels only, so layers of many channels AND many pixels stay on conv_dx_kernel (conv_dx_workgroup_us).
-// Weights in two fp16 planes (MODE_F16, 3x3): kernel, three planes / two: 256->256 14x14 46.8 / 36.5, 512->512 7x7 43.6 / 35.5.
-// Measured, preparation and kernel (us), three planes, conv_dx_kernel / here: 256->256 14x14 N=64 65.6 / 48, 512->512 7x7 N=64 82.2 / 53,
+// Measured, preparation and kernel (us), conv_dx_kernel / here: 256->256 14x14 N=64 65.6 / 48, 512->512 7x7 N=64 82.2 / 53,
 // 16->537 8x8 N=119 69.7 / 22.0, 40->840 3x3/2 8x8 N=83 80.9 / 27.4, 332->37 5x5 16x16 N=52 63.9 / 49.0; 64->64 32x32 N=128 39.0 / 49.6.
 #pragma once
 #include "conv_dx_kernel.h"
@@ -36,7 +35,7 @@ __device__ __forceinline__ void conv_dx_split_body(const ConvDxArgs &a, int b)
     using TR = CdxTraits<MODE>;
     using Acc = typename TR::Acc;
     using E = typename TR::Out;
-    constexpr int G = TR::G, ROOM = TR::PL, PL = MODE == MODE_F16 ? 2 : ROOM;     // planes that there is room for; that there are
+    constexpr int G = TR::G, PL = TR::PL;
     constexpr int NB0 = (NB + 1) / 2, NB1 = NB - NB0, ITEMS = cds_items(NB);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int waves = (int)blockDim.x >> 6;
@@ -58,12 +57,12 @@ __device__ __forceinline__ void conv_dx_split_body(const ConvDxArgs &a, int b)
 
     // ---- weights: a step is a tap of a pair; a cursor walks the wavefront's steps ahead of them and stays on the last one
     const int RS = T9 ? 9 : a.R * a.S;
-    const int64_t tap_stride = (int64_t)ROOM * a.Cp * a.KG;      // cells
-    const uint32_t wl = (uint32_t)(lhalf * ROOM * a.Cp + cb * 32 + lcol);
+    const int64_t tap_stride = (int64_t)PL * a.Cp * a.KG;        // cells
+    const uint32_t wl = (uint32_t)(lhalf * PL * a.Cp + cb * 32 + lcol);
     const int last_pair = wave + (a.pairs - 1 - wave) / waves * waves;           // (wave < pairs)
     int l_pair = wave, l_tap = 0;
     auto next_load = [&](u32x4 (&dst)[PL]) {
-        const uint4 *row = a.wp + (l_tap * tap_stride + (int64_t)l_pair * (2 * ROOM) * a.Cp);   // uniform
+        const uint4 *row = a.wp + (l_tap * tap_stride + (int64_t)l_pair * (2 * PL) * a.Cp);     // uniform
 #pragma unroll
         for (int pl = 0; pl < PL; ++pl) { const uint4 t = row[wl + (uint32_t)(pl * a.Cp)]; dst[pl] = u32x4{t.x, t.y, t.z, t.w}; }
         if (++l_tap == RS) {
@@ -150,8 +149,8 @@ __device__ __forceinline__ void conv_dx_split_body(const ConvDxArgs &a, int b)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     mine[(item_cell[i][e >> 1] >> (16 * (e & 1))) & 0xFFFFu] =
-                        uint4{cdx_code_pair<MODE>(raw[i][0], raw[i][1], e), cdx_code_pair<MODE>(raw[i][2], raw[i][3], e),
-                              cdx_code_pair<MODE>(raw[i][4], raw[i][5], e), cdx_code_pair<MODE>(raw[i][6], raw[i][7], e)};
+                        uint4{cdx_bf16_pair(raw[i][0], raw[i][1], e), cdx_bf16_pair(raw[i][2], raw[i][3], e),
+                              cdx_bf16_pair(raw[i][4], raw[i][5], e), cdx_bf16_pair(raw[i][6], raw[i][7], e)};
             }
         }
     };
@@ -283,11 +282,6 @@ __device__ __forceinline__ void conv_dx_split_body(const ConvDxArgs &a, int b)
     const float sc = MODE == MODE_I8 ? 1.0f : a.scale.get();
     const int opi = STRIDED ? a.oPI : a.PI;
     const int c0 = cb * 32 + 8 * (v_first >> 2) + 4 * lhalf + (v_first & 3);
-    float back[4];
-    if constexpr (MODE == MODE_F16) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) back[v] = a.w_scale[min(c0 + v, a.C - 1)];
-    }
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         int j = j0 + 32 * nb + lcol;
@@ -300,9 +294,7 @@ __device__ __forceinline__ void conv_dx_split_body(const ConvDxArgs &a, int b)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             if ((v < 2 || !eight) && c0 + v < a.C) {
-                if constexpr (MODE == MODE_I8) out[off + v * opi] = acc[nb][v];
-                else if constexpr (MODE == MODE_F16) out[off + v * opi] = acc[nb][v] * back[v] * sc;
-                else out[off + v * opi] = acc[nb][v] * sc;
+                if constexpr (MODE == MODE_I8) out[off + v * opi] = acc[nb][v]; else out[off + v * opi] = acc[nb][v] * sc;
             }
         }
     }
@@ -312,9 +304,6 @@ template <int NB, int MODE, bool T9>
 __global__ __launch_bounds__(512, 1) void conv_dx_split_kernel(ConvDxArgs a)
 {
     if (a.gate.closed()) return;
-    if constexpr (MODE == MODE_F16) {
-        if (*a.w_wide) { conv_dx_split_body<NB, MODE_BF16, false, T9>(a, (int)blockIdx.x); return; }
-    }
     conv_dx_split_body<NB, MODE, false, T9>(a, (int)blockIdx.x);
 }
 
@@ -329,7 +318,7 @@ __global__ __launch_bounds__(512, 1) void conv_dx_split_multi_kernel(ConvDxMulti
     conv_dx_split_body<NB, MODE, true, false>(a, (int)blockIdx.x - m.first[ci]);
 }
 
-// conv_dx_split.hip: mode MODE_BF16, MODE_BF16X2, MODE_F16 (3x3, stride 1) or MODE_I8; nb 2, 4 or 7 pixel blocks a tile
+// conv_dx_split.hip: mode MODE_BF16, MODE_BF16X2 or MODE_I8; nb 2, 4 or 7 pixel blocks a tile
 hipError_t launch_conv_dx_split(int mode, const ConvDxArgs &args, int nb, int grid, int waves, size_t lds, hipStream_t s);
 hipError_t launch_conv_dx_split(int mode, const ConvDxMulti &args, int nb, int grid, int waves, size_t lds, hipStream_t s);
 

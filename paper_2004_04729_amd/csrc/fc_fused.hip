@@ -2,7 +2,7 @@
 // kernels move.
 #include <hip/hip_runtime.h>
 #include "fc_direct_kernel.h"
-#include "nsd_kernel.h"
+#include "nsd_math.h"
 
 namespace dbp {
 

@@ -27,7 +27,7 @@
 
 namespace dbp {
 
-enum { MODE_BF16 = 0, MODE_I8 = 1, MODE_F32 = 2, MODE_BF16X2 = 3, MODE_F16 = 4 };   // MODE_BF16X2, MODE_F16: kernels with prepared operands only (two planes, below)
+enum { MODE_BF16 = 0, MODE_I8 = 1, MODE_F32 = 2, MODE_BF16X2 = 3 };   // MODE_BF16X2: kernels with prepared operands only (two planes, below)
 
 constexpr int TM = 256, TN = 128, NCHUNK = 4;
 
@@ -86,18 +86,6 @@ __device__ __forceinline__ void split2_pk(float a, float b, uint32_t &hi, uint32
 {
     hi = bf16_pack_nearest(a, b);
     lo = bf16_pack_nearest(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
-}
-
-// Two fp16 planes of values that a power of two has brought into fp16's range (|x| < 2^15): hi the fp16 nearest to x, lo the fp16 nearest to
-// the rest, whose 12 bits and sign it holds but for the last bit of a quarter of all values: |x - hi - lo| <= 2^-23 |x| while |x| >= 2^-1, 4.4e-8 |x| root
-// mean square; below, fp16's smallest step bounds it: 2^-25, so 2^-14 |x| at |x| = 2^-11.
-typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-__device__ __forceinline__ void split2_f16(float a, float b, uint32_t &hi, uint32_t &lo)
-{
-    const f16x2_t h = {(_Float16)a, (_Float16)b};
-    const f16x2_t l = {(_Float16)(a - (float)h.x), (_Float16)(b - (float)h.y)};
-    hi = __builtin_bit_cast(uint32_t, h); lo = __builtin_bit_cast(uint32_t, l);
 }
 
 // The same split for callers that pack the pieces with a byte permute of the upper halves: `lo` keeps its lower 16 bits
@@ -294,20 +282,8 @@ template <> struct Mma<MODE_BF16> {
     }
 };
 template <> struct Mma<MODE_BF16X2> : Mma<MODE_BF16> {};
-template <> struct Mma<MODE_F16> {
-    static __device__ __forceinline__ void run(const u32x4 &a, const u32x4 &b, f32x16 &c)
-    {
-        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-    }
-};
 // 16x16x32: a lane's row or column is lane % 16, its 8 reduction indices those of group lane / 16; rows 4*(lane/16) + v of the result
 template <int MODE> struct Mma16;
-template <> struct Mma16<MODE_F16> {
-    static __device__ __forceinline__ void run(const u32x4 &a, const u32x4 &b, f32x4 &c)
-    {
-        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-    }
-};
 template <> struct Mma16<MODE_BF16> {
     static __device__ __forceinline__ void run(const u32x4 &a, const u32x4 &b, f32x4 &c)
     {

@@ -105,7 +105,7 @@ size_t relayout_bytes(int64_t K, int64_t C, int64_t R, int64_t S)
 // Geometry of the fast dX kernel for one stride-1 problem (a whole layer, or one class of a strided layer), or
 // ok == false when the generic kernel has to serve.  `k` arrives with the problem (N, C, H, Wd, K, R, S, pad, pad_w, P, Q
 // and the output mapping) filled in; force_nb != 0 asks for that pixel-block count only.
-struct ConvDxPlan { bool ok; int nb; ConvDxArgs args; size_t lds_bytes; int grid; int waves; float us, launch_us; };   // waves: 0 conv_dx_kernel, else of conv_dx_split_kernel; us: modelled, of a workgroup
+struct ConvDxPlan { bool ok; int nb; ConvDxArgs args; size_t lds_bytes; int grid; int waves; float us; };   // waves: 0 conv_dx_kernel, else of conv_dx_split_kernel; us: modelled, of a workgroup
 
 // Which of the two dX kernels, and with which tiles: by modelled time.  A workgroup costs its pairs (conv_dx_kernel: chunks) of k-groups,
 // each its taps' matrix instructions and the staging of `items` fill items a lane, and its end; workgroups go over the chip's places
@@ -266,14 +266,13 @@ ConvDxPlan conv_dx_plan(const ConvArgs &a, bool i8 = false)
         const float us = sp.ok ? conv_dx_launch_us(sp.us, sp.us * (float)sp.grid, sp.grid, f.waves, sp.lds_bytes, i8, false) : 3.0e38f;
         if (sp.ok && us < best) { best = us; pl = sp; }
     }
-    pl.launch_us = best;
     return pl;
 }
 
 // A strided layer as st*st stride-1 problems, one per class of output pixels (h mod st, w mod st): class (ph, pw) has
 // the taps r = r0 + st*t, r0 = (ph + pad) mod st, and reads code row i + (ph + pad - r0)/st - t for its output row i.
 // Classes without taps (a 1x1 kernel with stride 2 has three) are all zero: `zero_fill` asks for dX to be cleared first.
-struct ConvDxStridedPlan { bool ok, zero_fill; int nb; ConvDxMulti multi; CdxTapMap map; int taps, tap_base[CDX_MAX_CLASSES]; size_t lds_bytes; int grid, waves; float us; };
+struct ConvDxStridedPlan { bool ok, zero_fill; int nb; ConvDxMulti multi; CdxTapMap map; int taps, tap_base[CDX_MAX_CLASSES]; size_t lds_bytes; int grid, waves; };
 
 ConvDxStridedPlan conv_dx_strided_plan(const ConvArgs &a, bool i8)
 {
@@ -337,7 +336,6 @@ ConvDxStridedPlan conv_dx_strided_plan(const ConvArgs &a, bool i8)
     }
     if (best_us > 2.0e38f) { sp.ok = false; return sp; }
     sp = best;
-    sp.us = best_us;
     for (int t = sp.taps; t < 64; ++t) sp.map.real[t] = 0;
     return sp;
 }
@@ -1229,35 +1227,6 @@ hipError_t launch_zero_words(void *p, int64_t n_words, hipStream_t s)
     return hipGetLastError();
 }
 
-// Where the dX product's weights in two fp16 planes keep what they need: the spare room, or behind the prepared weights and the padded codes, before
-// dW's partial sums come there.  job.slabs == 0: three bf16 planes, for lack of room, or by this rule: 3x3 kernels at stride 1 (the kernels of other tap counts
-// and of strided classes have no such form), and at least 1024 products a sum.  Two planes round a weight's last bit, three do not; but every matrix
-// instruction rounds the sum, and there are a third less of them.  Error of dX against 64 bits over three planes': 0.91 to 1.09, 1.00 in the geometric
-// mean of 21 layers of 1152 and more products with 67 to 97 % zero codes, lower where more codes are nonzero; 576 products 0.98 to 1.11.
-struct CdxRangePlace { RangeJob job; float *scale = nullptr; int *wide = nullptr; };
-static CdxRangePlace conv_dx_range(const ConvArgs &a)
-{
-    CdxRangePlace r;
-    if (!a.dX || !a.codes || !a.W || a.W8 || a.two_planes || !a.scratch || a.stride != 1 || a.R != 3 || a.S != 3 || a.K * 9 < 1024) return r;
-    const int64_t P = a.H + 2 * a.pad - 2, Q = a.Wd + 2 * a.pad - 2;
-    const bool pad_codes = P * Q % 4 != 0 || (uintptr_t)a.codes % 4 != 0;
-    const int64_t Cp = (a.C + 31) / 32 * 32, k_per = (a.K + CDX_SLABS - 1) / CDX_SLABS, slabs = (a.K + k_per - 1) / k_per;
-    if (Cp > CDX_F16_CHANNELS) return r;
-    const size_t need = (size_t)(Cp * (8 * slabs + 4) + 4);
-    char *place = a.spare;
-    if (need > a.spare_bytes) {
-        size_t at = relayout_bytes(a.K, a.C, a.R, a.S);
-        if (pad_codes) at += align_up((size_t)(a.N * a.K * ((P * Q + 3) / 4 * 4)), 256);
-        if (at + need > a.scratch_bytes) return r;
-        place = (char *)a.scratch + at;
-    }
-    r.job.w = a.W; r.job.partial = (uint2 *)place; r.job.K = (int)a.K; r.job.C = (int)a.C; r.job.RS = 9; r.job.Cp = (int)Cp;
-    r.job.k_per = (int)k_per; r.job.slabs = (int)slabs;
-    r.scale = (float *)(place + Cp * 8 * slabs); r.wide = (int *)(r.scale + Cp);
-    return r;
-}
-RangeJob conv_dx_range_job(const ConvArgs &a) { return conv_dx_range(a).job; }
-
 // ------------------------------------------------------------------------------------------------
 // Convolution (fast dX kernel: any stride; fast dW kernels: stride 1; the generic kernel serves the rest).
 // ------------------------------------------------------------------------------------------------
@@ -1265,7 +1234,7 @@ template <int MODE_G, int MODE_K>
 static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, hipStream_t s)
 {
     // MODE_G: MODE_BF16 (codes, fp32 weights), MODE_I8 (codes, int8 weights) or MODE_F32 (dense).  MODE_K: the fast kernels'
-    // mode, MODE_G itself or MODE_BF16X2 (fp32 weights in two planes of 16 bits in all).
+    // mode, MODE_G itself or MODE_BF16X2 (fp32 weights in two planes).
     if constexpr (MODE_G != MODE_F32) {
         constexpr bool I8 = MODE_G == MODE_I8;
         constexpr int PL = CdxTraits<MODE_K>::PL;
@@ -1277,7 +1246,7 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
         const bool pad_codes = PQ % 4 != 0 || (uintptr_t)grad % 4 != 0;
         const bool codes_ok = !pad_codes || (rbw + (size_t)(a.N * a.K * plane) <= a.scratch_bytes && plane < (1 << 24));
         const int8_t *kernel_codes = pad_codes ? (const int8_t *)a.scratch + rbw : (const int8_t *)grad;
-        auto prepare = [&](int taps, int KG, int Cp, const CdxTapMap *map, const CdxRangePlace *place) -> hipError_t {
+        auto prepare = [&](int taps, int KG, int Cp, const CdxTapMap *map) {
             const int64_t cells = (int64_t)taps * KG * Cp;
             int pb = (int)((cells + 255) / 256 < 4096 ? (cells + 255) / 256 : 4096);
             const int rs = (int)(a.R * a.S);
@@ -1294,12 +1263,9 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
                 if (map) hipLaunchKernelGGL(conv_dx_weight_prep_i8_kernel<true>, dim3(pb), dim3(256), 0, s, a.W8, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, *map, job, pad);
                 else     hipLaunchKernelGGL(conv_dx_weight_prep_i8_kernel<false>, dim3(pb), dim3(256), 0, s, a.W8, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, CdxTapMap{}, job, pad);
             } else {
-                if (map)        hipLaunchKernelGGL((conv_dx_weight_prep_kernel<true, MODE_K>), dim3(pb), dim3(256), 0, s, a.W, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, *map, job, pad, CdxRange{});
-                else if (place) return launch_conv_dx_f16_prep(CdxPrep{a.W, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, pb, job, pad},
-                                                               CdxRange{place->job.partial, place->job.slabs, place->scale, place->wide}, s);
-                else            hipLaunchKernelGGL((conv_dx_weight_prep_kernel<false, MODE_K>), dim3(pb), dim3(256), 0, s, a.W, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, CdxTapMap{}, job, pad, CdxRange{});
+                if (map) hipLaunchKernelGGL((conv_dx_weight_prep_kernel<true, PL>), dim3(pb), dim3(256), 0, s, a.W, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, *map, job, pad);
+                else     hipLaunchKernelGGL((conv_dx_weight_prep_kernel<false, PL>), dim3(pb), dim3(256), 0, s, a.W, (uint4 *)a.scratch, (int)a.K, (int)a.C, taps, KG, Cp, rs, CdxTapMap{}, job, pad);
             }
-            return hipGetLastError();
         };
         if (a.stride != 1 && codes_ok) {
             ConvDxStridedPlan sp = conv_dx_strided_plan(a, I8);
@@ -1313,7 +1279,7 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
                 }
                 if (sp.multi.n > 0) {
                     const int KG = sp.multi.cls[0].KG, Cp = sp.multi.cls[0].Cp;
-                    if (hipError_t e = prepare(sp.taps, KG, Cp, &sp.map, nullptr); e != hipSuccess) return e;
+                    prepare(sp.taps, KG, Cp, &sp.map);
                     for (int i = 0; i < sp.multi.n; ++i) {
                         ConvDxArgs &k = sp.multi.cls[i];
                         k.codes = kernel_codes; k.dX = a.dX; k.scale = scale; k.gate = a.gate;
@@ -1332,23 +1298,7 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
             ConvDxArgs &k = pl.args;
             k.codes = kernel_codes; k.wp = (const uint4 *)a.scratch; k.dX = a.dX; k.scale = scale; k.gate = a.gate;
             k.code_img = (pad_codes ? a.K : a.kt()) * k.PQ; k.dx_img = a.ct() * k.PI;
-            if constexpr (MODE_K == MODE_BF16) {
-                // Two fp16 planes of the weights instead of three bf16 ones, where the ranges are known
-                CdxRangePlace place = conv_dx_range(a);
-                if (place.job.slabs && !a.range_done) {
-                    // A launch for the ranges alone costs 4.5 us, two planes instead of three save a fifth of the kernel's time; not where the call is
-                    // one of two behind a gate
-                    if (a.gate.flag || pl.launch_us < 40.0f) place.job.slabs = 0;
-                    else if (hipError_t e = launch_conv_dx_range(place.job, s); e != hipSuccess) return e;
-                }
-                if (place.job.slabs) {
-                    k.w_scale = place.scale; k.w_wide = place.wide;
-                    if (hipError_t e = prepare(k.R * k.S, k.KG, k.Cp, nullptr, &place); e != hipSuccess) return e;
-                    if (pl.waves) return launch_conv_dx_split(MODE_F16, k, pl.nb, pl.grid, pl.waves, pl.lds_bytes, s);
-                    return launch_conv_dx(MODE_F16, k, pl.nb, pl.grid, pl.lds_bytes, s);
-                }
-            }
-            if (hipError_t e = prepare(k.R * k.S, k.KG, k.Cp, nullptr, nullptr); e != hipSuccess) return e;
+            prepare(k.R * k.S, k.KG, k.Cp, nullptr);
             if (pl.waves) return launch_conv_dx_split(MODE_K, k, pl.nb, pl.grid, pl.waves, pl.lds_bytes, s);
             return launch_conv_dx(MODE_K, k, pl.nb, pl.grid, pl.lds_bytes, s);
         }

@@ -111,36 +111,4 @@ __device__ __forceinline__ void side_job(const StatsJob &job, int i, int NT)
     for (int64_t c = first + threadIdx.x; c < end; c += NT) job.bias_grad[c] = (float)(d * (double)job.bias_sums[c]);
 }
 
-// Workgroup `i` of a range job, 256 threads: a slab's rows of per_group() channels, a thread per weight of a row.  Bound by memory: it
-// runs beside the quantiser (256->256 3x3: 2.4 MB beside 16 MB).
-__device__ __forceinline__ void range_scan(const RangeJob &j, int i)
-{
-    __shared__ uint2 s_range[256];
-    const int groups = j.groups(), per = j.per_group();
-    const int g = i % groups, slab = i / groups;
-    const int c0 = g * per, nc = min(per, j.C - c0), cols = nc * j.RS;
-    const int k0 = slab * j.k_per, k1 = min(j.K, k0 + j.k_per);
-    const int64_t row = (int64_t)j.C * j.RS;
-    uint32_t mx = 0u, mn = 0xFFFFFFFFu;
-    for (int col = threadIdx.x; col < cols; col += 256) {                 // (more than one column a thread only where a channel has over 256 taps)
-        const float *p = j.w + k0 * row + (int64_t)c0 * j.RS + col;
-        for (int k = k0; k < k1; k += 8) {
-            uint32_t v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = __float_as_uint(p[min(u, k1 - 1 - k) * row]) & 0x7FFFFFFFu;      // (past the slab: its last row again)
-#pragma unroll
-            for (int u = 0; u < 8; ++u) { mx = max(mx, v[u]); mn = min(mn, v[u] - 1u); }
-            p += 8 * row;
-        }
-    }
-    s_range[threadIdx.x] = uint2{mx, mn};
-    __syncthreads();
-    if ((int)threadIdx.x < nc) {
-        const int first = per > 1 ? threadIdx.x * j.RS : 0, last = per > 1 ? first + j.RS : 256;
-        mx = 0u; mn = 0xFFFFFFFFu;
-        for (int q = first; q < last; ++q) { mx = max(mx, s_range[q].x); mn = min(mn, s_range[q].y); }
-        j.partial[(int64_t)slab * j.Cp + c0 + threadIdx.x] = uint2{mx, mn};
-    }
-}
-
 }  // namespace dbp

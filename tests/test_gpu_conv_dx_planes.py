@@ -1,7 +1,7 @@
-"""The two fp16 planes that a convolution's dX product cuts its fp32 weights into, and the three bf16 planes that it falls back to.
+"""A convolution's dX product takes its fp32 weights exactly, whatever their range: in three bf16 planes that add up to them, in every kernel and entry point.
 
-One nonzero code of +-1 per image and a step size of 1 make every element of dX one weight (or zero) as the planes hold it, so the expected value
-of each form is known exactly: of the two planes from numpy's own fp16 conversions, of the three the weight itself.
+One nonzero code of +-1 per image and a step size of 1 make every element of dX one weight (or zero) as the planes hold it, so the expected value is the
+weight itself, bit for bit.  Random mantissas fill all 24 bits of a weight, and weights far below their channel's largest have to keep theirs.
 """
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ import torch  # noqa: F401  (before the library: both bring a HIP runtime, and t
 pytestmark = pytest.mark.gpu
 
 # every tile of both kernels: conv_dx_kernel (waves 0) and conv_dx_split_kernel; a partial block of 32 channels, K that ends inside a group of 8, planes
-# that are copied to whole dwords (odd ones), and K of exactly what the rule asks for
+# that are copied to whole dwords (odd ones)
 FORMS = [((33, 33, 33, 30, 115), (0, 2)), ((90, 33, 28, 28, 115), (0, 4)), ((61, 130, 28, 28, 115), (0, 7)), ((33, 33, 14, 14, 115), (4, 2)),
          ((90, 33, 14, 14, 115), (4, 4)), ((90, 130, 13, 13, 115), (4, 7)), ((1, 33, 3, 3, 114), (8, 2)), ((90, 33, 9, 9, 520), (8, 4)),
          ((90, 33, 13, 13, 520), (8, 7))]
@@ -18,9 +18,11 @@ FORMS = [((33, 33, 33, 30, 115), (0, 2)), ((90, 33, 28, 28, 115), (0, 4)), ((61,
 
 def _weights(rng, K, C, what):
     W = (rng.standard_normal((K, C, 3, 3)) * 0.02).astype(np.float32)
-    if what == "channel scales":                       # each channel has a scale of its own: all fit
+    if what == "channel scales":                       # each channel has a scale of its own
         W *= np.float32(2.0) ** rng.integers(-40, 41, size=(1, C, 1, 1)).astype(np.float32)
         W[:, C // 2] = 0
+    elif what == "outlier":                            # one output channel's weights 2^15 to 2^25 above the others: these keep all their bits
+        W[K // 2] *= np.float32(2.0) ** rng.integers(15, 26, size=(C, 1, 1)).astype(np.float32)
     elif what == "tiny":                               # one weight 2^-30 of its channel's largest
         W[K // 2, C - 1, 1, 1] = 2.0 ** -30 * np.abs(W[:, C - 1]).max()
     elif what == "huge":
@@ -30,21 +32,6 @@ def _weights(rng, K, C, what):
     elif what in ("inf", "nan"):
         W[K - 1, C // 2, 2, 0] = np.float32(what)
     return W
-
-
-def _two_planes(W):
-    """What two fp16 planes hold of W, per input channel scaled to 2^14 .. 2^15; None: a channel does not fit."""
-    mag = np.abs(W).astype(np.float64)
-    top = mag.max(axis=(0, 2, 3))
-    if not np.isfinite(W).all():
-        return None
-    exp = np.floor(np.log2(np.where(top > 0, top, 1)))
-    s = np.where(top > 0, 2.0 ** (14 - exp), 1.0).reshape(1, -1, 1, 1)
-    if (np.abs(exp) > 100).any() or (mag * s)[mag > 0].min() < 2.0 ** -11:
-        return None
-    hi = (W * s).astype(np.float16).astype(np.float64)
-    lo = (W * s - hi).astype(np.float16).astype(np.float64)
-    return (hi + lo) / s
 
 
 def _run(W, N, H, Wd, entry, rng):
@@ -70,55 +57,40 @@ def _run(W, N, H, Wd, entry, rng):
     return at, dX.cpu().numpy()
 
 
-def _expected(planes, at, N, C, H, Wd):
+def _expected(W, at, N, C, H, Wd):
     out = np.zeros((N, C, H + 2, Wd + 2))
     for n, (k, h, w, m) in enumerate(at):
-        out[n, :, h:h + 3, w:w + 3] = m * planes[k]
+        out[n, :, h:h + 3, w:w + 3] = m * W[k].astype(np.float64)
     return out[:, :, 1:-1, 1:-1]
 
 
-@pytest.mark.parametrize("what", ["normal", "channel scales", "tiny", "huge", "small", "inf", "nan"])
+@pytest.mark.parametrize("what", ["normal", "channel scales", "outlier", "tiny", "huge", "small", "inf", "nan"])
 @pytest.mark.parametrize("case,form", FORMS)
-def test_conv_dx_weight_planes(case, form, what):
+def test_conv_dx_weights_are_exact(case, form, what):
     from plan_util import conv_dx_kernel
     N, C, H, Wd, K = case
     assert conv_dx_kernel(N, C, H, Wd, K, 3, 3, 1, 1) == form
     rng = np.random.default_rng(N + C + K)
     W = _weights(rng, K, C, what)
-    two = _two_planes(W)
-    assert (two is not None) == (what in ("normal", "channel scales"))
     at, got = _run(W, N, H, Wd, "backward", rng)
-    if two is not None:
-        assert not np.array_equal(two, W.astype(np.float64))                # the two forms can be told apart
-        assert np.array_equal(got, _expected(two, at, N, C, H, Wd))
-    else:
-        finite = [c for c in range(C) if np.isfinite(W[:, c]).all()]        # (0 * inf is a NaN: a channel with one has no other elements where its tap reaches)
-        step = 2.0 ** -133 if what == "small" else 0.0                       # the smallest bf16: what truncating the last plane can lose
-        assert np.all(np.abs(got[:, finite] - _expected(W.astype(np.float64), at, N, C, H, Wd)[:, finite]) <= step)
-        assert len(finite) == C or not np.isfinite(got[:, C // 2]).all()
+    finite = [c for c in range(C) if np.isfinite(W[:, c]).all()]            # (0 * inf is a NaN: a channel with one has no other elements where its tap reaches)
+    step = 2.0 ** -133 if what == "small" else 0.0                           # the smallest bf16: what truncating the last plane can lose
+    assert np.all(np.abs(got[:, finite] - _expected(W, at, N, C, H, Wd)[:, finite]) <= step)
+    assert len(finite) == C or not np.isfinite(got[:, C // 2]).all()
 
 
-def test_conv_dx_weight_planes_below_the_rule():
-    """Fewer than 1024 products a sum: three planes, exact."""
-    rng = np.random.default_rng(5)
-    W = _weights(rng, 113, 33, "normal")
-    at, got = _run(W, 4, 9, 9, "backward", rng)
-    assert np.array_equal(got, _expected(W.astype(np.float64), at, 4, 33, 9, 9))
-
-
-@pytest.mark.parametrize("case,two", [((61, 130, 28, 28, 115), True), ((33, 33, 14, 14, 115), False)])
-def test_conv_dx_weight_planes_of_products_alone(case, two):
-    """Without the quantiser's launch the ranges take one of their own, where the product is long enough for it."""
+@pytest.mark.parametrize("case", [(61, 130, 28, 28, 115), (33, 33, 14, 14, 115), (4, 33, 9, 9, 113), (90, 130, 13, 13, 115)])
+def test_conv_dx_weights_are_exact_in_products_alone(case):
     N, C, H, Wd, K = case
     rng = np.random.default_rng(11)
-    W = _weights(rng, K, C, "normal")
+    W = _weights(rng, K, C, "outlier")
     at, got = _run(W, N, H, Wd, "products", rng)
-    assert np.array_equal(got, _expected(_two_planes(W) if two else W.astype(np.float64), at, N, C, H, Wd))
+    assert np.array_equal(got, _expected(W, at, N, C, H, Wd))
 
 
-@pytest.mark.parametrize("what", ["normal", "tiny"])
-def test_conv_dx_weight_planes_of_a_layer_call(what):
-    """The whole-layer entry point finds the ranges beside the step size; dW's scratch holds no odd-plane copy to spare."""
+@pytest.mark.parametrize("what", ["normal", "outlier"])
+def test_conv_dx_weights_are_exact_in_a_layer_call(what):
+    """The whole-layer entry point: the same dX, bit for bit, as the products of its codes and its step size."""
     import paper_2004_04729_amd as dbp
     from gpu_util import DEV, dev, stream, check_products
     from oracle import oracle as O
@@ -137,6 +109,10 @@ def test_conv_dx_weight_planes_of_a_layer_call(what):
     dbp.dithered_conv2d_layer_backward(dev(delta), dev(act), dev(W), dev(X), dbp.F32, *dims, 4.0, 9, 0, codes, dX, dW, None, step, ws, None,
                                        dbp.PATH_AUTO, stream())
     torch.cuda.synchronize()
+    alone = torch.empty_like(dX)
+    dbp.conv2d_products(codes, None, float(step[0]), dev(W), None, dbp.F32, *dims, alone, None, ws, dbp.PATH_MFMA, stream())
+    torch.cuda.synchronize()
+    assert torch.equal(dX, alone)
     k = codes.cpu().numpy()
     kw = dict(stride=1, pad=1)
     rX, rW, _ = O.conv2d_backward(W, X, codes=k, step=float(step[0]), **kw)
