@@ -7,9 +7,11 @@ import torch
 pytestmark = pytest.mark.gpu
 
 # n = B * out: one gradient, a full level of the step size's tree and one more, the most that a fused call takes (and one call beyond it), rows
-# shorter than a window of the reduction, widths that no vector divides, a reduction split over workgroups (partial sums in a second launch)
+# shorter than a window of the reduction, widths that no vector divides, a reduction split over workgroups (partial sums in a second launch), bias columns
+# that many threads share, that threads do not divide, and more of them than threads
 SIZES = [(1, 5, 2), (2, 64, 1), (16, 100, 1), (17, 100, 1), (64, 100, 10), (16, 33, 16), (257, 70, 1), (27, 2592, 8), (3, 130, 85), (31, 515, 132), (4096, 64, 1),
-         (512, 4096, 8), (16, 4100, 256), (64, 784, 64), (241, 77, 17), (64, 300, 128), (32, 72, 256), (2731, 70, 3), (8192, 64, 1)]
+         (512, 4096, 8), (16, 4100, 256), (64, 784, 64), (241, 77, 17), (64, 300, 128), (32, 72, 256), (2731, 70, 3), (8192, 64, 1),
+         (2730, 70, 3), (4096, 64, 2), (1365, 40, 6), (24, 64, 341), (13, 64, 630), (2, 64, 513), (1, 70, 8192)]
 
 
 def _delta(rng, B, out, odd):
