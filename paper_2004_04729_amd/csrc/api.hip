@@ -124,7 +124,7 @@ bool overlap(const void *a, size_t na, const void *b, size_t nb)
 }
 bool fused_ok(const LinearArgs &a, const float *delta, const float *act, const float *db, const void *pair)
 {
-    if (!linear_fused_ok(a)) return false;
+    if (!linear_fused_ok(a, pair != nullptr)) return false;
     const size_t n = (size_t)(a.B * a.out);
     for (const float *in : {delta, act})
         if (overlap(in, 4 * n, a.dX, (size_t)(a.B * a.in) * 4) || overlap(in, 4 * n, a.dW, (size_t)(a.out * a.in) * 4) || overlap(in, 4 * n, db, (size_t)a.out * 4) ||

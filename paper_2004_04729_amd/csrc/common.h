@@ -202,7 +202,7 @@ struct ConvArgs {
 size_t     linear_scratch_bytes(int64_t B, int64_t in, int64_t out);
 size_t     conv_scratch_bytes(int64_t N, int64_t C, int64_t H, int64_t Wd, int64_t K, int64_t R, int64_t S, int64_t pad, int64_t stride = 1);
 hipError_t launch_linear_mfma(const LinearArgs &a, hipStream_t s);
-bool       linear_fused_ok(const LinearArgs &a);            // the products may quantise themselves (LinearArgs::fused)
+bool       linear_fused_ok(const LinearArgs &a, bool layer);   // the products may quantise themselves (LinearArgs::fused); layer: with the step size, too
 hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t s);
 hipError_t launch_zero_words(void *p, int64_t n_words, hipStream_t s);      // clears n 4-byte words
 // grouped convolution as one ungrouped layer: block-diagonal weights in, diagonal blocks of dW out (products.hip)

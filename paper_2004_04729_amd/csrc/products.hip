@@ -1049,11 +1049,39 @@ static FcChoice linear_choose(const LinearArgs &a)
 // more workgroup writes what the quantiser leaves.  8192 gradients are sixteen a thread.  Launches of their own / one launch (us): 8192 gradients 64x784x128 12.1 / 9.1,
 // 16x8192x512 15.1 / 13.5, with the step size 64x784x128 17.4 / 14.8; of 16384 and more (forty a thread allowed) 64x784x256 12.3 / 11.4, with the step
 // size 17.9 / 18.2, 16x1024x1000 14.5 / 14.8, 64x784x300 12.4 / 12.6, 40x4096x500 14.5 / 21.5.
-bool linear_fused_ok(const LinearArgs &a)
+// Workgroups beyond the first round over the chip quantise once more behind the others, and what a launch less saves is soon gone, the sooner the more
+// gradients there are and the more a workgroup does with them.  The lines below, with the workgroups of the products, launches of their own / one launch (us):
+//   with the step size  52x8069x106 254 18.1 / 14.2, 16x8192x500 256 21.5 / 26.2, 64x16384x96 256 21.5 / 24.1, 512x16384x16 384 32.1 / 36.0, 512x262144x16 4608 291 / 419
+//   ... to 4096         128x65536x32 384 32.0 / 27.6, 128x131072x32 768 46.9 / 44.0, 5x83989x367 1151 52.9 / 55.1
+//   int8 weights        64x65536x96 320 17.0 / 16.9, 378x30130x20 472 23.4 / 22.9, 64x131072x96 640 24.2 / 26.2; to 4096: 183x89604x21 614 28.9 / 25.5, 9x56482x389 830 26.8 / 27.6
+//   neither             16x65536x500 1152 59.1 / 55.3, 3x19865x2486 1673 120.9 / 119.5, 16x131072x500 2304 145 / 149; int8 activations 64x146865x123 861 41.8 / 43.4;
+//                       to 6144: 64x262144x96 1536 98.1 / 89.7
+static int64_t fcd_workgroups(const LinearArgs &a)                    // of both products, as launch_fc_direct plans them
 {
-    if (!a.codes || a.B * a.out > kFusedMax || (!a.dX && !a.dW) || a.gate.flag) return false;
+    const int room = a.dX && a.dW ? 128 : 256;
+    size_t left = a.scratch_bytes & ~(size_t)255;
+    int64_t n = 0;
+    if (a.dX) {
+        const FcdPlan pl = fcd_plan(a.B, a.in, a.out, a.W8 != nullptr, room, left);
+        const size_t used = align_up(pl.partial_bytes, 256);
+        left = left > used ? left - used : 0;
+        n += (int64_t)pl.groups * pl.n_split;
+    }
+    if (a.dW) {
+        const FcdPlan pl = fcd_plan(a.out, a.in, a.B, a.x_dtype == DBP_I8, room, left);
+        n += (int64_t)pl.groups * pl.n_split;
+    }
+    return n;
+}
+
+bool linear_fused_ok(const LinearArgs &a, bool layer)
+{
+    const int64_t n = a.B * a.out;
+    if (!a.codes || n > kFusedMax || (!a.dX && !a.dW) || a.gate.flag) return false;
     const FcChoice c = linear_choose(a);
-    return (!a.dX || c.dx_direct) && (!a.dW || c.dw_direct);
+    if ((a.dX && !c.dx_direct) || (a.dW && !c.dw_direct)) return false;
+    const int64_t most = layer ? (n > 4096 ? 255 : 1024) : a.W8 ? (n > 4096 ? 512 : 768) : n > 6144 ? (a.x_dtype == DBP_I8 ? 768 : 2000) : 8192;
+    return fcd_workgroups(a) <= most;
 }
 
 // ------------------------------------------------------------------------------------------------

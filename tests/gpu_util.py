@@ -134,3 +134,23 @@ def run_conv(p, path=dbp.PATH_MFMA, want_dx=True, want_dw=True):
     torch.cuda.synchronize()
     return {"codes": codes.cpu().numpy(), "dX": None if dX is None else dX.cpu().numpy(),
             "dW": None if dW is None else dW.cpu().numpy(), "stats": dbp.Stats.from_tensor(st)}
+
+
+def graph_nodes(call):
+    """Launches (nodes of a captured graph) of one call(stream)."""
+    import ctypes as C
+    path = next(ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln)       # the runtime that serves this process
+    hip = C.CDLL(path)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    call(s.cuda_stream)                                         # eager first: one-time function attributes are set outside the capture
+    s.synchronize()
+    graph, n = C.c_void_p(), C.c_size_t()
+    assert hip.hipStreamBeginCapture(C.c_void_p(s.cuda_stream), 2) == 0           # relaxed
+    try:
+        call(s.cuda_stream)
+    finally:
+        assert hip.hipStreamEndCapture(C.c_void_p(s.cuda_stream), C.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, C.byref(n)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return n.value

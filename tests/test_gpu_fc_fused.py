@@ -105,3 +105,34 @@ def test_results_in_the_place_of_the_gradients():
         torch.cuda.synchronize()
         out.append((codes, dX, dW))
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+# One launch or launches of their own: the most gradients, kernels other than the direct one (a single output), and, by mode, the most workgroups of the
+# products beside the one that writes what the quantiser leaves (in brackets)
+@pytest.mark.parametrize("B,in_,out,mode,fused", [
+    (64, 100, 10, "plain", True), (64, 100, 10, "layer", True), (64, 100, 10, "q8", True),
+    (64, 64, 128, "plain", True), (64, 64, 128, "layer", True), (64, 64, 128, "q8", True),
+    (64, 64, 129, "plain", False), (2731, 70, 3, "layer", False), (64, 64, 129, "q8", False), (16, 100, 1, "layer", False),
+    (52, 8069, 106, "layer", True), (16, 8192, 500, "layer", False), (16, 8192, 500, "plain", True),         # [254], [256]
+    (128, 65536, 32, "layer", True), (5, 83989, 367, "layer", False),                                        # 4096 gradients and fewer: [384], [1151]
+    (64, 32768, 96, "q8", True), (64, 131072, 96, "q8", False), (183, 89604, 21, "q8", True), (9, 56482, 389, "q8", False),   # [160], [640], [614], [830]
+    (64, 146865, 123, "int8 activations", False), (16, 65536, 500, "plain", True), (16, 131072, 500, "plain", False)])        # [861], [1152], [2304]
+def test_one_launch_where_it_is_the_faster(B, in_, out, mode, fused):
+    import paper_2004_04729_amd as dbp
+    from gpu_util import DEV, graph_nodes
+    layer, q8 = mode == "layer", mode == "q8"
+    xd = dbp.I8 if q8 or mode == "int8 activations" else dbp.F32
+    buf = lambda shape, dt: torch.zeros(shape, dtype=dt, device=DEV)
+    d, W, X = buf((B, out), torch.float32), buf((out, in_), torch.int8 if q8 else torch.float32), buf((B, in_), torch.int8 if xd == dbp.I8 else torch.float32)
+    codes, dX, dW = buf((B, out), torch.int8), buf((B, in_), torch.float32), buf((out, in_), torch.float32)
+    pair, db = buf(2, torch.float32), buf(out, torch.float32)
+    ws = buf(max(dbp.linear_layer_workspace_bytes(B, in_, out, xd), dbp.linear_workspace_bytes(B, in_, out, xd)), torch.uint8)
+
+    def call(s):
+        if layer:
+            dbp.dithered_linear_layer_backward(d, d, W, X, xd, B, in_, out, 3.0, 7, 0, codes, dX, dW, db, pair, ws, None, dbp.PATH_AUTO, s)
+        elif q8:
+            dbp.dithered_linear_backward_q8(d, W, X, B, in_, out, 5e-3, 7, 0, codes, dX, dW, ws, None, s)
+        else:
+            dbp.dithered_linear_backward(d, W, X, xd, B, in_, out, 5e-3, 7, 0, codes, dX, dW, ws, None, dbp.PATH_AUTO, s)
+    assert (graph_nodes(call) == 1) == fused
