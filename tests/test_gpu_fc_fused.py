@@ -136,3 +136,54 @@ def test_one_launch_where_it_is_the_faster(B, in_, out, mode, fused):
         else:
             dbp.dithered_linear_backward(d, W, X, xd, B, in_, out, 5e-3, 7, 0, codes, dX, dW, ws, None, dbp.PATH_AUTO, s)
     assert (graph_nodes(call) == 1) == fused
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("B,in_,out", [(64, 100, 10), (64, 64, 128), (27, 2592, 8)])
+def test_layer_call_with_a_gradient_that_is_no_number(B, in_, out, masked, bad):
+    """No step size: zero codes, products and bias gradient, and the statistics count it; behind the rectifier's mask it is nothing at all."""
+    import paper_2004_04729_amd as dbp
+    from gpu_util import DEV, dev, stream
+    rng = np.random.default_rng(3)
+    d, act = _delta(rng, B, out, False), rng.standard_normal((B, out)).astype(np.float32)
+    d[B // 2, out // 2], act[B // 2, out // 2] = bad, -1.0 if masked else 1.0
+    d, act, W, X = dev(d), dev(act), dev(rng.standard_normal((out, in_)).astype(np.float32)), dev(rng.standard_normal((B, in_)).astype(np.float32))
+    codes, st = torch.full((B, out), 99, dtype=torch.int8, device=DEV), torch.full((32,), 0xEE, dtype=torch.uint8, device=DEV)
+    dX, dW, db = (torch.full(s, -7.0, dtype=torch.float32, device=DEV) for s in ((B, in_), (out, in_), (out,)))
+    pair, ref_pair = torch.empty(2, dtype=torch.float32, device=DEV), torch.empty(2, dtype=torch.float32, device=DEV)
+    ws = torch.empty(dbp.linear_layer_workspace_bytes(B, in_, out), dtype=torch.uint8, device=DEV)
+    dbp.dithered_linear_layer_backward(d, act, W, X, dbp.F32, B, in_, out, 3.0, 7, 5, codes, dX, dW, db, pair, ws, st, dbp.PATH_AUTO, stream())
+    dbp.step_size(d, act, B * out, 3.0, ref_pair, torch.empty(dbp.step_size_workspace_bytes(B * out), dtype=torch.uint8, device=DEV), stream())
+    ref_codes, ref_st = torch.empty_like(codes), torch.zeros_like(st)
+    fmt = torch.empty(dbp.format_layout(B, out)["total_bytes"], dtype=torch.uint8, device=DEV)
+    dbp.nsd_quantize_ex(d, B, out, 1.0, 7, 5, ref_codes, fmt, ref_st, act=act, step_dev=ref_pair, stream=stream())
+    torch.cuda.synchronize()
+    assert torch.equal(pair, ref_pair) and torch.equal(codes, ref_codes) and torch.equal(st, ref_st)
+    assert (float(pair[0]) > 0.0) == masked and bool(codes.any()) == masked
+    assert dbp.Stats.from_tensor(st).n_nonfinite == (0 if masked else 1)
+    if not masked:
+        assert not pair.any() and not dX.any() and not dW.any() and not db.any()
+
+
+@pytest.mark.parametrize("what,over", [("dX", "delta"), ("dX", "act"), ("dW", "delta"), ("dW", "act"), ("db", "delta"), ("db", "act")])
+def test_layer_results_in_the_place_of_gradients_or_activations(what, over):
+    import paper_2004_04729_amd as dbp
+    from gpu_util import DEV, dev, stream
+    rng = np.random.default_rng(4)
+    n = 64
+    d, act = rng.laplace(0, 1e-3, (n, n)).astype(np.float32), rng.standard_normal((n, n)).astype(np.float32)
+    W, X = dev(rng.standard_normal((n, n)).astype(np.float32)), dev(rng.standard_normal((n, n)).astype(np.float32))
+    ws = torch.empty(dbp.linear_layer_workspace_bytes(n, n, n), dtype=torch.uint8, device=DEV)
+    out = []
+    for place in (False, True):
+        t = {"delta": dev(d), "act": dev(act)}
+        r = {"dX": torch.empty((n, n), device=DEV), "dW": torch.empty((n, n), device=DEV), "db": torch.empty(n, device=DEV)}
+        if place:
+            r[what] = t[over].view(-1)[:r[what].numel()].view(r[what].shape)
+        codes, pair = torch.empty((n, n), dtype=torch.int8, device=DEV), torch.empty(2, device=DEV)
+        dbp.dithered_linear_layer_backward(t["delta"], t["act"], W, X, dbp.F32, n, n, n, 3.0, 3, 0, codes, r["dX"], r["dW"], r["db"], pair, ws, None, dbp.PATH_AUTO,
+                                           stream())
+        torch.cuda.synchronize()
+        out.append((codes, pair, r["dX"], r["dW"], r["db"]))
+    assert all(torch.equal(a, b) for a, b in zip(*out))
