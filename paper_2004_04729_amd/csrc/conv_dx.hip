@@ -8,17 +8,18 @@ namespace dbp {
 template <int MODE>
 static void launch_mode(const ConvDxArgs &args, int nb, int grid, size_t lds, hipStream_t s)
 {
-    // tap counts that are a multiple of 3 (3x3 above all) take the form with three weight fragment sets in flight
-    const bool ring3 = (args.R * args.S) % 3 == 0;
-    auto launch = [&](auto n, auto ring) {
-        hipLaunchKernelGGL((conv_dx_kernel<decltype(n)::value, MODE, decltype(ring)::value>), dim3(grid), dim3(256), lds, s, args);
+    const int taps = args.R * args.S;
+    auto launch = [&](auto n, auto form) {
+        hipLaunchKernelGGL((conv_dx_kernel<decltype(n)::value, MODE, decltype(form)::value>), dim3(grid), dim3(256), lds, s, args);
     };
-    auto blocks = [&](auto ring) {
-        if (nb == 7)      launch(std::integral_constant<int, 7>{}, ring);
-        else if (nb == 4) launch(std::integral_constant<int, 4>{}, ring);
-        else              launch(std::integral_constant<int, 2>{}, ring);
+    auto blocks = [&](auto form) {
+        if (nb == 7)      launch(std::integral_constant<int, 7>{}, form);
+        else if (nb == 4) launch(std::integral_constant<int, 4>{}, form);
+        else              launch(std::integral_constant<int, 2>{}, form);
     };
-    if (ring3) blocks(std::true_type{}); else blocks(std::false_type{});
+    if (taps == 1)          blocks(std::integral_constant<int, 1>{});
+    else if (taps % 3 == 0) blocks(std::integral_constant<int, 3>{});
+    else                    blocks(std::integral_constant<int, 0>{});
 }
 
 template <int MODE>

@@ -342,12 +342,14 @@ def test_conv_dx_with_the_reduction_divided(case, form):
     assert not np.array_equal(two["dX"], three["dX"])          # the flag reached a kernel that has the form
 
 
-# dX with channels and pixels divided, every tile and both weight rings: a second group of 128 channels that ends in a partial block of 32, and
-# more than one chunk of the reduction; classes of strides 2 and 3
+# dX with channels and pixels divided, every tile and weight ring: a second group of 128 channels that ends in a partial block of 32, and
+# more than one chunk of the reduction (one tap: also one and three); classes of strides 2 and 3
 WHOLE_DX = [((1, 130, 7, 9, 40, 3, 3, 1, 1), (0, 2)), ((2, 130, 9, 7, 40, 1, 1, 1, 0), (0, 2)), ((2, 130, 9, 11, 40, 3, 3, 2, 1), (0, 2)),
             ((70, 130, 14, 14, 40, 3, 3, 1, 1), (0, 4)), ((130, 130, 10, 7, 40, 1, 1, 1, 0), (0, 4)), ((33, 130, 27, 11, 40, 2, 2, 2, 0), (0, 4)),
             ((61, 130, 28, 28, 40, 3, 3, 1, 1), (0, 7)), ((61, 130, 28, 28, 40, 1, 1, 1, 0), (0, 7)), ((64, 130, 28, 28, 40, 3, 3, 2, 1), (0, 7)),
-            ((3, 70, 31, 29, 45, 3, 3, 3, 1), (0, 2))]
+            ((3, 70, 31, 29, 45, 3, 3, 3, 1), (0, 2)),
+            ((2, 130, 9, 7, 20, 1, 1, 1, 0), (0, 2)), ((2, 130, 9, 7, 70, 1, 1, 1, 0), (0, 2)), ((130, 130, 10, 7, 20, 1, 1, 1, 0), (0, 4)),
+            ((130, 130, 10, 7, 70, 1, 1, 1, 0), (0, 4)), ((61, 130, 28, 28, 20, 1, 1, 1, 0), (0, 7)), ((61, 130, 28, 28, 70, 1, 1, 1, 0), (0, 7))]
 
 
 @pytest.mark.parametrize("case,form", WHOLE_DX)

@@ -188,11 +188,13 @@ def test_conv_q8_dx_with_the_reduction_divided(case, form):
     test_conv_q8_is_bit_exact((N, C, H, Wd, K, R, S, pad, stride))
 
 
-# the other dX kernel: a partial block of a second group of 128 channels, more than one chunk
+# the other dX kernel: a partial block of a second group of 128 channels, more than one chunk; one tap: one and three chunks, whole blocks stored by rows
 @pytest.mark.parametrize("case,form", [((1, 130, 7, 9, 90, 3, 3, 1, 1), (0, 2)), ((2, 130, 9, 7, 90, 1, 1, 1, 0), (0, 2)),
                                        ((2, 130, 9, 11, 90, 3, 3, 2, 1), (0, 2)), ((130, 130, 4, 20, 90, 1, 1, 1, 0), (0, 4)),
                                        ((130, 130, 14, 5, 90, 3, 3, 1, 0), (0, 4)), ((33, 130, 14, 40, 70, 2, 2, 3, 0), (0, 4)),
-                                       ((61, 130, 28, 28, 90, 1, 1, 1, 0), (0, 7)), ((61, 130, 40, 40, 70, 2, 2, 3, 0), (0, 7))])
+                                       ((61, 130, 28, 28, 90, 1, 1, 1, 0), (0, 7)), ((61, 130, 40, 40, 70, 2, 2, 3, 0), (0, 7)),
+                                       ((2, 130, 9, 7, 40, 1, 1, 1, 0), (0, 2)), ((130, 130, 4, 20, 190, 1, 1, 1, 0), (0, 4)),
+                                       ((61, 160, 28, 28, 40, 1, 1, 1, 0), (0, 7)), ((61, 160, 28, 28, 190, 1, 1, 1, 0), (0, 7))])
 def test_conv_q8_dx_with_channels_and_pixels_divided(case, form):
     test_conv_q8_dx_with_the_reduction_divided(case, form)
 
