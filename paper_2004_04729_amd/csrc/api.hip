@@ -122,13 +122,13 @@ bool overlap(const void *a, size_t na, const void *b, size_t nb)
 {
     return a && b && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
 }
-bool fused_ok(const LinearArgs &a, const float *delta, const float *act, const float *db, const void *pair)
+bool fused_ok(const LinearArgs &a, const float *delta, const float *act, const float *db, const void *pair, const dbp_stats *stats)
 {
     if (!linear_fused_ok(a, pair != nullptr)) return false;
     const size_t n = (size_t)(a.B * a.out);
     for (const float *in : {delta, act})
         if (overlap(in, 4 * n, a.dX, (size_t)(a.B * a.in) * 4) || overlap(in, 4 * n, a.dW, (size_t)(a.out * a.in) * 4) || overlap(in, 4 * n, db, (size_t)a.out * 4) ||
-            overlap(in, 4 * n, pair, 8) || overlap(in, 4 * n, a.codes, n)) return false;
+            overlap(in, 4 * n, pair, 8) || overlap(in, 4 * n, a.codes, n) || overlap(in, 4 * n, stats, sizeof(dbp_stats))) return false;
     return true;
 }
 
@@ -558,7 +558,7 @@ dbp_status dithered_linear_backward(const float *delta, const float *W, const vo
     // products' launch, or, with both families behind the density gate, by the kernel that writes the gate's flag
     LinearArgs call = linear_call(W, X, x_dtype, B, in, out, dX, dW, k, ws + c.scratch_offset, workspace_bytes - c.scratch_offset, path_two_planes(path));
     const AutoPlan ap = path_family(path) == DBP_PATH_AUTO ? linear_auto_plan(call, true) : AutoPlan{false, 0};
-    if (path_family(path) != DBP_PATH_GATHER && !ap.gated() && fused_ok(call, delta, nullptr, nullptr, nullptr)) {
+    if (path_family(path) != DBP_PATH_GATHER && !ap.gated() && fused_ok(call, delta, nullptr, nullptr, nullptr, stats)) {
         const FusedQuant q = fused_quant(delta, B, out, step, seed, idx_base, k, stats);
         call.step = step; call.fused = &q;
         return launch_linear_mfma(call, (hipStream_t)stream) == hipSuccess ? DBP_OK : DBP_ERR_DEVICE;
@@ -849,7 +849,7 @@ dbp_status dithered_linear_backward_q8(const float *delta, const int8_t *W8, con
     a.x_dtype = DBP_I8; a.B = B; a.in = in; a.out = out; a.dX = (float *)dX32; a.dW = dW32;
     a.scratch = ws + c.scratch_offset; a.scratch_bytes = workspace_bytes - c.scratch_offset;
     a.stats_job = StatsJob{nullptr, 0, nullptr, nullptr, 0, nullptr, 0.0f, nullptr};
-    if (fused_ok(a, delta, nullptr, nullptr, nullptr)) {
+    if (fused_ok(a, delta, nullptr, nullptr, nullptr, stats)) {
         const FusedQuant q = fused_quant(delta, B, out, step, seed, idx_base, k, stats);
         a.fused = &q;
         return launch_linear_mfma(a, (hipStream_t)stream) == hipSuccess ? DBP_OK : DBP_ERR_DEVICE;
@@ -1007,7 +1007,7 @@ dbp_status dithered_linear_layer_backward(const float *delta_a, const float *act
     int8_t *k = codes ? codes : (int8_t *)(ws + c.codes_offset);
     LinearArgs call = linear_call(W, X, x_dtype, B, in, out, dX, dW, k, ws + c.scratch_offset, c.total - c.scratch_offset, path_two_planes(path));
     const AutoPlan ap = path_family(path) == DBP_PATH_AUTO && (dX || dW) ? linear_auto_plan(call, true) : AutoPlan{false, 0};
-    if (path_family(path) != DBP_PATH_GATHER && !ap.gated() && fused_ok(call, delta_a, act, db, pair)) {
+    if (path_family(path) != DBP_PATH_GATHER && !ap.gated() && fused_ok(call, delta_a, act, db, pair, stats)) {
         FusedQuant q = fused_quant(delta_a, B, out, 1.0f, seed, idx_base, k, stats);
         q.act = act; q.s = s; q.bias_grad = db; q.step_out = pair;
         call.step_dev = pair; call.fused = &q;

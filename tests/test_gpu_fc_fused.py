@@ -166,7 +166,7 @@ def test_layer_call_with_a_gradient_that_is_no_number(B, in_, out, masked, bad):
         assert not pair.any() and not dX.any() and not dW.any() and not db.any()
 
 
-@pytest.mark.parametrize("what,over", [("dX", "delta"), ("dX", "act"), ("dW", "delta"), ("dW", "act"), ("db", "delta"), ("db", "act")])
+@pytest.mark.parametrize("what,over", [("dX", "delta"), ("dX", "act"), ("dW", "delta"), ("dW", "act"), ("db", "delta"), ("db", "act"), ("stats", "delta"), ("stats", "act")])
 def test_layer_results_in_the_place_of_gradients_or_activations(what, over):
     import paper_2004_04729_amd as dbp
     from gpu_util import DEV, dev, stream
@@ -178,12 +178,12 @@ def test_layer_results_in_the_place_of_gradients_or_activations(what, over):
     out = []
     for place in (False, True):
         t = {"delta": dev(d), "act": dev(act)}
-        r = {"dX": torch.empty((n, n), device=DEV), "dW": torch.empty((n, n), device=DEV), "db": torch.empty(n, device=DEV)}
+        r = {"dX": torch.empty((n, n), device=DEV), "dW": torch.empty((n, n), device=DEV), "db": torch.empty(n, device=DEV), "stats": torch.empty(8, device=DEV)}
         if place:
             r[what] = t[over].view(-1)[:r[what].numel()].view(r[what].shape)
         codes, pair = torch.empty((n, n), dtype=torch.int8, device=DEV), torch.empty(2, device=DEV)
-        dbp.dithered_linear_layer_backward(t["delta"], t["act"], W, X, dbp.F32, n, n, n, 3.0, 3, 0, codes, r["dX"], r["dW"], r["db"], pair, ws, None, dbp.PATH_AUTO,
+        dbp.dithered_linear_layer_backward(t["delta"], t["act"], W, X, dbp.F32, n, n, n, 3.0, 3, 0, codes, r["dX"], r["dW"], r["db"], pair, ws, r["stats"], dbp.PATH_AUTO,
                                            stream())
         torch.cuda.synchronize()
-        out.append((codes, pair, r["dX"], r["dW"], r["db"]))
+        out.append((codes, pair, r["dX"], r["dW"], r["db"], r["stats"].view(torch.uint8)))
     assert all(torch.equal(a, b) for a, b in zip(*out))
