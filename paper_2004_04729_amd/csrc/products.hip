@@ -1287,7 +1287,7 @@ static hipError_t conv_dx_run(const ConvArgs &a, const void *grad, Scale scale, 
             if (a.pending && (a.pending->n > 0 || a.pending->bias_len > 0)) { job = *a.pending; *a.pending = StatsJob{}; pb += (int)job.workgroups(); }
             CdxPad pad{};
             if (pad_codes) {
-                const int64_t wgs = (a.N * a.K * (plane / 4) + 256 * CDX_PAD_UNROLL - 1) / (256 * CDX_PAD_UNROLL);
+                const int64_t dwords = a.N * a.K * (plane / 4), per = dwords < CDX_PAD_TWO ? 256 : 512, wgs = (dwords + per - 1) / per;
                 pad = CdxPad{(const int8_t *)grad, (uint32_t *)((char *)a.scratch + rbw), a.N * a.K, (int)PQ, (int)plane, (int)a.K, (int)a.kt(), (int)(wgs < 4096 ? wgs : 4096)};
                 pb += pad.workgroups;
             }
