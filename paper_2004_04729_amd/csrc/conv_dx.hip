@@ -25,9 +25,17 @@ static void launch_mode(const ConvDxArgs &args, int nb, int grid, size_t lds, hi
 template <int MODE>
 static void launch_mode(const ConvDxMulti &args, int nb, int grid, size_t lds, hipStream_t s)
 {
-    if (nb == 7)      hipLaunchKernelGGL((conv_dx_multi_kernel<7, MODE>), dim3(grid), dim3(256), lds, s, args);
-    else if (nb == 4) hipLaunchKernelGGL((conv_dx_multi_kernel<4, MODE>), dim3(grid), dim3(256), lds, s, args);
-    else              hipLaunchKernelGGL((conv_dx_multi_kernel<2, MODE>), dim3(grid), dim3(256), lds, s, args);
+    auto launch = [&](auto n, auto form) {
+        hipLaunchKernelGGL((conv_dx_multi_kernel<decltype(n)::value, MODE, decltype(form)::value>), dim3(grid), dim3(256), lds, s, args);
+    };
+    auto blocks = [&](auto form) {
+        if (nb == 7)      launch(std::integral_constant<int, 7>{}, form);
+        else if (nb == 4) launch(std::integral_constant<int, 4>{}, form);
+        else              launch(std::integral_constant<int, 2>{}, form);
+    };
+    // (a 1x1 kernel: the one class that has a tap)
+    if (MODE != MODE_I8 && args.n == 1 && args.cls[0].R * args.cls[0].S == 1) blocks(std::integral_constant<int, MODE == MODE_I8 ? 0 : 1>{});
+    else                                                                      blocks(std::integral_constant<int, 0>{});
 }
 
 hipError_t launch_conv_dx(int mode, const ConvDxArgs &args, int nb, int grid, size_t lds, hipStream_t s)

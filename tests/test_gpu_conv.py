@@ -349,7 +349,9 @@ WHOLE_DX = [((1, 130, 7, 9, 40, 3, 3, 1, 1), (0, 2)), ((2, 130, 9, 7, 40, 1, 1, 
             ((61, 130, 28, 28, 40, 3, 3, 1, 1), (0, 7)), ((61, 130, 28, 28, 40, 1, 1, 1, 0), (0, 7)), ((64, 130, 28, 28, 40, 3, 3, 2, 1), (0, 7)),
             ((3, 70, 31, 29, 45, 3, 3, 3, 1), (0, 2)),
             ((2, 130, 9, 7, 20, 1, 1, 1, 0), (0, 2)), ((2, 130, 9, 7, 70, 1, 1, 1, 0), (0, 2)), ((130, 130, 10, 7, 20, 1, 1, 1, 0), (0, 4)),
-            ((130, 130, 10, 7, 70, 1, 1, 1, 0), (0, 4)), ((61, 130, 28, 28, 20, 1, 1, 1, 0), (0, 7)), ((61, 130, 28, 28, 70, 1, 1, 1, 0), (0, 7))]
+            ((130, 130, 10, 7, 70, 1, 1, 1, 0), (0, 4)), ((61, 130, 28, 28, 20, 1, 1, 1, 0), (0, 7)), ((61, 130, 28, 28, 70, 1, 1, 1, 0), (0, 7)),
+            ((2, 130, 15, 11, 70, 1, 1, 2, 0), (0, 2)), ((130, 130, 19, 13, 20, 1, 1, 2, 0), (0, 4)), ((130, 130, 21, 13, 70, 1, 1, 2, 0), (0, 4)),
+            ((64, 130, 55, 55, 20, 1, 1, 2, 0), (0, 7)), ((61, 130, 57, 55, 70, 1, 1, 2, 0), (0, 7))]
 
 
 @pytest.mark.parametrize("case,form", WHOLE_DX)
