@@ -16,7 +16,7 @@
 // What bounds it: matrix instructions and their operands (256->256 14x14 N=64: matrix cores busy 56 % of the cycles in which a CU has a workgroup,
 // 43 % of the launch; LDS bank conflicts 11 %), and that a CU has nothing to do for a quarter of so short a launch.  Every workgroup stages its
 // pixels' codes for 32 channels only, so layers of many channels AND many pixels stay on conv_dx_kernel (conv_dx_workgroup_us).
-// Measured, preparation and kernel (us), conv_dx_kernel / here: 256->256 14x14 N=64 65.6 / 48, 512->512 7x7 N=64 82.2 / 53,
+// Measured, preparation and kernel (us), conv_dx_kernel (with 32x32x16 matrix instructions) / here: 256->256 14x14 N=64 65.6 / 48, 512->512 7x7 N=64 82.2 / 53,
 // 16->537 8x8 N=119 69.7 / 22.0, 40->840 3x3/2 8x8 N=83 80.9 / 27.4, 332->37 5x5 16x16 N=52 63.9 / 49.0; 64->64 32x32 N=128 39.0 / 49.6.
 #pragma once
 #include "conv_dx_kernel.h"

@@ -116,6 +116,8 @@ struct ConvDxPlan { bool ok; int nb; ConvDxArgs args; size_t lds_bytes; int grid
 //   two bf16 planes         306 layers  1.016  1.64   1 (15 %): chosen by the times of three planes; with the planes in the model as well 1.015, 1
 //   int8 weights, stride 1  566 layers  1.020  1.81  11 (20 %)
 //   int8 weights, strided   566 layers  1.019  1.41  14 (constants of stride 1, seven blocks allowed: 1.037, 63 layers, 38 %)
+// (Fits and table are of conv_dx_kernel with 32x32x16 matrix instructions; with 16x16x32 it is up to a fifth faster, so that a layer near the line may be the
+// other kernel's although conv_dx_kernel would now be the faster one; none is slower for it than it was.)
 // Where the other kernel's time is `margin` times modelled, conv_dx_kernel keeps the layer; a wavefront without a pair would be idle.
 struct ConvDxTimes { float block, tap, mma, staging, trip, base, spread, margin; };
 static const ConvDxTimes &conv_dx_times(bool split, bool i8, bool strided)
